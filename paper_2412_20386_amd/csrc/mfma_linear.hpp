@@ -465,5 +465,9 @@ int launch_stream_smallk(const LinearArgs &a, bool quantize, hipStream_t stream,
 // in_proj of the Vim-S / Vim-B stacks), defined in gemm_wreg.hip.  Same return convention.
 int launch_wreg(const LinearArgs &a, hipStream_t stream);
 
+// Tile kernels (gemm_tile.hip): any shape, pitch and alignment.
+template <class Path>
+int launch_tiles(const LinearArgs &a, hipStream_t stream);
+
 }  // namespace mfma
 }  // namespace ptq4vm

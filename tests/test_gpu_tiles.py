@@ -1,0 +1,92 @@
+"""The tile kernels of the linears (csrc/gemm_tile.hpp) at the edges of their tiles, on every operand type, against a
+64-bit product (exact for the integer paths)."""
+import pytest
+import torch
+
+import paper_2412_20386_amd as ptq
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+SHAPES = [  # M, K, N (int8 reductions; every operand type picks its own tile from the same rule), pitch of y beyond N
+    (1, 64, 1, 0), (33, 192, 17, 1), (255, 1536, 80, 0),           # split reduction over 16 x 16 blocks: one element, ragged, long
+    (65, 128, 2049, 0), (197, 1088, 769, 3),                       # 32 x 64 tiles; K ends in half a slab; odd rows of y
+    (785, 192, 1601, 0), (1001, 960, 832, 8),                      # 64 x 64 tiles, three ring stages
+    (1999, 320, 1216, 0),                                          # 64 x 64 tiles, two ring stages
+    (3137, 448, 1153, 0),                                          # 64 x 128 tiles
+    (6209, 192, 1025, 5), (49217, 1536, 80, 0),                    # 128 x 128 tiles, and with a column tile mostly padding
+    (13057, 192, 2048, 0),                                         # 128 x 256 tiles
+    (50, 13, 7, 0), (301, 100, 130, 0), (17, 1001, 333, 1),        # any alignment: 16 x 16 blocks
+    (1111, 514, 402, 0),                                           # 32 x 32 blocks
+    (401, 72, 899, 2), (1279, 200, 645, 0), (2049, 722, 643, 0),   # 32 x 64, 64 x 64 with short and long slabs
+    (6401, 30, 1029, 0), (12345, 334, 2179, 1),                    # 64 x 128, 128 x 128
+]
+
+
+def _close(y, y64, magnitude):
+    """One fp16 rounding (half an ulp, 2^-11 of the value; a whole ulp where fp32 rounding tips it) plus the fp32 roundings."""
+    y = y.double()
+    tol = 2.0 ** -10 * y64.abs() + 2.0 ** -21 * magnitude + 2.0 ** -24
+    return bool(((y - y64).abs() <= tol).all())
+
+
+def _output(M, N, pad):
+    buf = torch.full((M, N + pad), 777.0, dtype=torch.float16, device=DEV)
+    return buf, buf[:, :N]
+
+
+@pytest.mark.parametrize("M,K,N,pad", SHAPES)
+def test_tile_kernels_all_operand_types(M, K, N, pad):
+    print(f"tiles M={M} K={K} N={N} pad={pad}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K + N)
+    B, L = (M // 7, 7) if M % 7 == 0 else (1, M)
+    ints = lambda lo, hi, *s: torch.randint(lo, hi, s, generator=g, device=DEV)
+    xq, wq = ints(-127, 128, M, K).to(torch.int8), ints(-127, 128, N, K).to(torch.int8)
+    s_tok = torch.rand(L, generator=g, device=DEV) * 0.01 + 0.001
+    s_w = torch.rand(N, generator=g, device=DEV) * 0.01 + 0.001
+    bias = torch.randn(N, generator=g, device=DEV).half()
+    scale = s_tok.double().repeat(B)[:, None] * s_w.double()[None, :]
+
+    def check(y, buf, acc64, sc, b):
+        p = acc64 * sc
+        assert _close(y, p + b.double(), p.abs() + b.double().abs())
+        assert bool((buf[:, N:] == 777.0).all())
+
+    # int8
+    acc64 = xq.double() @ wq.double().t()
+    acc = torch.full((M, N), -1, dtype=torch.int32, device=DEV)
+    buf, y = _output(M, N, pad)
+    ptq.w8a8_linear(xq, wq, s_tok, s_w, bias, B, L, y=y)
+    check(y, buf, acc64, scale, bias)
+    y2 = ptq.w8a8_linear(xq, wq, s_tok, s_w, bias, B, L, acc_out=acc)
+    assert torch.equal(acc.double(), acc64) and torch.equal(y2, y)
+
+    # zero offset
+    z = ints(-128, 128, L).to(torch.int32)
+    rowsum = ptq.weight_rowsum(wq)
+    buf, y = _output(M, N, pad)
+    ptq.w8a8_linear_offset(xq, wq, s_tok, z, rowsum, s_w, bias, B, L, y=y)
+    check(y, buf, acc64 - z.double().repeat(B)[:, None] * rowsum.double()[None, :], scale, bias)
+
+    # packed 4-bit codes
+    K2 = K - K % 2
+    if K2:
+        x4, w4 = ints(-7, 8, M, K2), ints(-7, 8, N, K2)
+        pack = lambda c: ((c[:, 0::2] & 15) | ((c[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous()
+        acc4 = x4.double() @ w4.double().t()
+        buf, y = _output(M, N, pad)
+        ptq.w4a4_linear(pack(x4), pack(w4), s_tok, s_w, bias, B, L, y=y, acc_out=acc)
+        check(y, buf, acc4, scale, bias)
+        assert torch.equal(acc.double(), acc4)
+
+    # fp16, without and with bias: fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|
+    x, w = torch.randn(M, K, generator=g, device=DEV).half(), torch.randn(N, K, generator=g, device=DEV).half()
+    mag = x.double().abs() @ w.double().abs().t()
+    for b in (None, bias):
+        y64 = x.double() @ w.double().t() + (0 if b is None else b.double())
+        buf, y = _output(M, N, pad)
+        ptq.f16_linear(x, w, b, y=y)
+        err = (y.double() - y64).abs()
+        assert bool((err <= (K + 2) * 2.0 ** -24 * (mag + 4.0) + 2.0 ** -10 * y64.abs() + 2.0 ** -24).all())
+        assert bool((buf[:, N:] == 777.0).all())
