@@ -1,9 +1,13 @@
-"""Thin ctypes binding of libptq4vm.so: argument marshalling only.
+"""Thin binding of libptq4vm.so: argument marshalling only.
 
 Every function takes torch CUDA tensors (used purely as device buffers), passes raw device
 pointers, sizes and the current HIP stream to the C ABI declared in include/ptq4vm.h, and
 returns the output tensors.  No arithmetic happens here and there is no fallback: if the
 library has not been built, loading raises.
+
+The launches of the hot path (quantizers and linears) are callables of the extension module
+_calls (host/calls.cc), which does the same checks natively; the offline preparation of weights
+and the validator go through ctypes here.
 """
 from __future__ import annotations
 
@@ -16,6 +20,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # PTQ4VM_LIB: another build of the same sources (the sanitized host build of the test suite)
 LIB_PATH = os.environ.get("PTQ4VM_LIB") or os.path.join(_HERE, "libptq4vm.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 
 EXPORTS = (
     "ptq4vm_fold_smoothing",
@@ -111,6 +116,38 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+# ---------------------------------------------------------------------------------- launches of the hot path
+HOT_CALLS = ("quantize_pts", "quantize_dynamic", "quantize_pts_offset", "quantize_pts_a4", "quantize_pts_a4_e2m3",
+             "w8a8_linear", "w8a8_linear_offset", "w4a4_linear", "w4a4_linear_e2m3", "w8a8_linear_fused",
+             "w8a8_linear_offset_fused", "w4a4_linear_fused", "f16_linear")
+
+
+def _load_entries() -> None:
+    """Hand the library's entry points to _calls (its callables ask for this on their first call)."""
+    lib = load()
+    _calls.bind({name: ctypes.cast(getattr(lib, "ptq4vm_" + name), ctypes.c_void_p).value for name in HOT_CALLS})
+
+
+def _bind_calls() -> None:
+    if not os.path.exists(CALLS_PATH):
+        raise FileNotFoundError(f"{CALLS_PATH} not found: build it with `python -m paper_2412_20386_amd.build` "
+                                "(there is no CPU or PyTorch fallback)")
+    from . import _calls
+
+    globals()["_calls"] = _calls
+    _calls.setup(_load_entries, check)
+    for name in HOT_CALLS:
+        globals()[name] = getattr(_calls, name)
+
+
+def _bind_late(name: str):
+    """Stands in for a callable of an extension that was not there when the package was imported (the package builds it)."""
+    def call(*args, **kwargs):
+        _bind_calls()
+        return globals()[name](*args, **kwargs)
+    return call
+
+
 def status_string(status: int) -> str:
     return load().ptq4vm_status_string(int(status)).decode()
 
@@ -160,105 +197,12 @@ def fold_smoothing(w: torch.Tensor, m: torch.Tensor, wq: Optional[torch.Tensor] 
     return wq, s_w, inv_m
 
 
-def quantize_pts(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, B: int, L: int,
-                 xq: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_quantize_pts: xq int8 [B*L, K]."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    if M != B * L:
-        raise ValueError("x must have B*L rows")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    if xq is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    _, _, ldxq = _matrix(xq, torch.int8, "xq")
-    check(load().ptq4vm_quantize_pts(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(xq), B, L, K, ldx, ldxq, _stream()))
-    return xq
-
-
-def quantize_dynamic(x: torch.Tensor, inv_m: Optional[torch.Tensor], xq: Optional[torch.Tensor] = None,
-                     s_row: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
-    """ptq4vm_quantize_dynamic: (xq int8 [M, K], s_row f32 [M])."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    if xq is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    _, _, ldxq = _matrix(xq, torch.int8, "xq")
-    if s_row is None:
-        s_row = torch.empty(M, dtype=torch.float32, device=x.device)
-    _vector(s_row, torch.float32, M, "s_row")
-    check(load().ptq4vm_quantize_dynamic(_ptr(x), _ptr(inv_m), _ptr(xq), _ptr(s_row), M, K, ldx, ldxq, _stream()))
-    return xq, s_row
-
-
-def w8a8_linear(xq: torch.Tensor, wq: torch.Tensor, s_tok: torch.Tensor, s_w: torch.Tensor,
-                bias: Optional[torch.Tensor], B: int, L: int, y: Optional[torch.Tensor] = None,
-                acc_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w8a8_linear: y fp16 [B*L, N]; acc_out (int32 [B*L, N], dense) is filled if given."""
-    M, K, ldxq = _matrix(xq, torch.int8, "xq")
-    N, K2, ldwq = _matrix(wq, torch.int8, "wq")
-    if K != K2 or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=xq.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    check(load().ptq4vm_w8a8_linear(_ptr(xq), _ptr(wq), _ptr(s_tok), _ptr(s_w), _ptr(bias), _ptr(y),
-                                    _ptr(acc_out), B, L, K, N, ldxq, ldwq, ldy, _stream()))
-    return y
-
-
-def quantize_pts_offset(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, z_tok: torch.Tensor,
-                        B: int, L: int, xq: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_quantize_pts_offset: xq int8 [B*L, K] with the per-token zero offset z_tok (int32 [L])."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    if M != B * L:
-        raise ValueError("x must have B*L rows")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(z_tok, torch.int32, L, "z_tok")
-    if xq is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    _, _, ldxq = _matrix(xq, torch.int8, "xq")
-    check(load().ptq4vm_quantize_pts_offset(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(z_tok), _ptr(xq), B, L, K, ldx,
-                                            ldxq, _stream()))
-    return xq
-
-
 def weight_rowsum(wq: torch.Tensor) -> torch.Tensor:
     """ptq4vm_weight_rowsum: int32 [N] = sum_k wq[o, k]."""
     N, K, ldwq = _matrix(wq, torch.int8, "wq")
     out = torch.empty(N, dtype=torch.int32, device=wq.device)
     check(load().ptq4vm_weight_rowsum(_ptr(wq), _ptr(out), N, K, ldwq, _stream()))
     return out
-
-
-def w8a8_linear_offset(xq: torch.Tensor, wq: torch.Tensor, s_tok: torch.Tensor, z_tok: torch.Tensor,
-                       rowsum: torch.Tensor, s_w: torch.Tensor, bias: Optional[torch.Tensor], B: int, L: int,
-                       y: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w8a8_linear_offset: y fp16 [B*L, N] with the zero-offset correction in the epilogue."""
-    M, K, ldxq = _matrix(xq, torch.int8, "xq")
-    N, K2, ldwq = _matrix(wq, torch.int8, "wq")
-    if K != K2 or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(z_tok, torch.int32, L, "z_tok")
-    _vector(rowsum, torch.int32, N, "rowsum")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=xq.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    check(load().ptq4vm_w8a8_linear_offset(_ptr(xq), _ptr(wq), _ptr(s_tok), _ptr(z_tok), _ptr(rowsum), _ptr(s_w),
-                                           _ptr(bias), _ptr(y), _ptr(acc_out), B, L, K, N, ldxq, ldwq, ldy, _stream()))
-    return y
 
 
 def fold_smoothing_w4(w: torch.Tensor, m: torch.Tensor, wq4: Optional[torch.Tensor] = None):
@@ -273,43 +217,6 @@ def fold_smoothing_w4(w: torch.Tensor, m: torch.Tensor, wq4: Optional[torch.Tens
     check(load().ptq4vm_fold_smoothing_w4(_ptr(w), _ptr(m), _ptr(wq4), _ptr(s_w), _ptr(inv_m), N, K, ldw, ldwq,
                                           _stream()))
     return wq4, s_w, inv_m
-
-
-def quantize_pts_a4(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, B: int, L: int,
-                    xq4: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_quantize_pts_a4: xq4 uint8 [B*L, K/2], two 4-bit codes per byte."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    if M != B * L:
-        raise ValueError("x must have B*L rows")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    if xq4 is None:
-        xq4 = torch.empty((M, K // 2), dtype=torch.uint8, device=x.device)
-    _, _, ldxq = _matrix(xq4, torch.uint8, "xq4")
-    check(load().ptq4vm_quantize_pts_a4(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(xq4), B, L, K, ldx, ldxq, _stream()))
-    return xq4
-
-
-def w4a4_linear(xq4: torch.Tensor, wq4: torch.Tensor, s_tok: torch.Tensor, s_w: torch.Tensor,
-                bias: Optional[torch.Tensor], B: int, L: int, y: Optional[torch.Tensor] = None,
-                acc_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w4a4_linear: y fp16 [B*L, N] from packed 4-bit operands."""
-    M, K2, ldxq = _matrix(xq4, torch.uint8, "xq4")
-    N, K2w, ldwq = _matrix(wq4, torch.uint8, "wq4")
-    if K2 != K2w or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=xq4.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    check(load().ptq4vm_w4a4_linear(_ptr(xq4), _ptr(wq4), _ptr(s_tok), _ptr(s_w), _ptr(bias), _ptr(y), _ptr(acc_out),
-                                    B, L, 2 * K2, N, ldxq, ldwq, ldy, _stream()))
-    return y
 
 
 def e2m3_blocks(K: int) -> int:
@@ -338,152 +245,6 @@ def fold_smoothing_w4_e2m3(w: torch.Tensor, m: torch.Tensor, wq6: Optional[torch
     check(load().ptq4vm_fold_smoothing_w4_e2m3(_ptr(w), _ptr(m), _ptr(wq6), _ptr(s_w), _ptr(inv_m), N, K, ldw, ldwq,
                                                _stream()))
     return wq6, s_w, inv_m
-
-
-def quantize_pts_a4_e2m3(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, B: int, L: int,
-                         xq6: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_quantize_pts_a4_e2m3: xq6 uint8 [e2m3_blocks(K), B*L, 96], 4-bit codes as E2M3 patterns, block-major."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    if M != B * L:
-        raise ValueError("x must have B*L rows")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    if xq6 is None:
-        xq6 = torch.empty((e2m3_blocks(K), M, 96), dtype=torch.uint8, device=x.device)
-    ldxq = _e2m3_container(xq6, M, K, "xq6")
-    check(load().ptq4vm_quantize_pts_a4_e2m3(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(xq6), B, L, K, ldx, ldxq,
-                                             _stream()))
-    return xq6
-
-
-def w4a4_linear_e2m3(xq6: torch.Tensor, wq6: torch.Tensor, s_tok: torch.Tensor, s_w: torch.Tensor,
-                     bias: Optional[torch.Tensor], B: int, L: int, K: int, y: Optional[torch.Tensor] = None,
-                     acc_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w4a4_linear_e2m3: y fp16 [B*L, N] from operands in the block-major E2M3 container (K codes per row)."""
-    M = B * L
-    ldxq = _e2m3_container(xq6, M, K, "xq6")
-    if not isinstance(wq6, torch.Tensor) or wq6.dim() != 3:
-        raise TypeError("wq6: expected a CUDA uint8 tensor [blocks, N, 96]")
-    N = wq6.shape[1]
-    ldwq = _e2m3_container(wq6, N, K, "wq6")
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=xq6.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    check(load().ptq4vm_w4a4_linear_e2m3(_ptr(xq6), _ptr(wq6), _ptr(s_tok), _ptr(s_w), _ptr(bias), _ptr(y),
-                                         _ptr(acc_out), B, L, K, N, ldxq, ldwq, ldy, _stream()))
-    return y
-
-
-def w8a8_linear_fused(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, wq: torch.Tensor,
-                      s_w: torch.Tensor, bias: Optional[torch.Tensor], B: int, L: int,
-                      y: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None,
-                      xq_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w8a8_linear_fused: y fp16 [B*L, N] from fp16 activations; acc_out / xq_out are filled if given."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    N, K2, ldwq = _matrix(wq, torch.int8, "wq")
-    if K != K2 or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    ldxq = 0
-    if xq_out is not None:
-        Mq, Kq, ldxq = _matrix(xq_out, torch.int8, "xq_out")
-        if (Mq, Kq) != (M, K):
-            raise ValueError("xq_out must be [B*L, K]")
-    check(load().ptq4vm_w8a8_linear_fused(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(wq), _ptr(s_w), _ptr(bias), _ptr(y),
-                                          _ptr(acc_out), _ptr(xq_out), B, L, K, N, ldx, ldwq, ldy, ldxq, _stream()))
-    return y
-
-
-def w8a8_linear_offset_fused(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, z_tok: torch.Tensor,
-                             wq: torch.Tensor, rowsum: torch.Tensor, s_w: torch.Tensor, bias: Optional[torch.Tensor],
-                             B: int, L: int, y: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None,
-                             xq_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w8a8_linear_offset_fused: y fp16 [B*L, N] from fp16 activations, per-token steps and zero offsets;
-    acc_out (raw accumulators) / xq_out (codes with the offset in them) are filled if given."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    N, K2, ldwq = _matrix(wq, torch.int8, "wq")
-    if K != K2 or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(z_tok, torch.int32, L, "z_tok")
-    _vector(rowsum, torch.int32, N, "rowsum")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    ldxq = 0
-    if xq_out is not None:
-        Mq, Kq, ldxq = _matrix(xq_out, torch.int8, "xq_out")
-        if (Mq, Kq) != (M, K):
-            raise ValueError("xq_out must be [B*L, K]")
-    check(load().ptq4vm_w8a8_linear_offset_fused(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(z_tok), _ptr(wq), _ptr(rowsum),
-                                                 _ptr(s_w), _ptr(bias), _ptr(y), _ptr(acc_out), _ptr(xq_out), B, L, K, N,
-                                                 ldx, ldwq, ldy, ldxq, _stream()))
-    return y
-
-
-def w4a4_linear_fused(x: torch.Tensor, inv_m: Optional[torch.Tensor], s_tok: torch.Tensor, wq4: torch.Tensor,
-                      s_w: torch.Tensor, bias: Optional[torch.Tensor], B: int, L: int,
-                      y: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None,
-                      xq_out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_w4a4_linear_fused: y fp16 [B*L, N] from fp16 activations and a packed 4-bit weight [N, K/2];
-    acc_out / xq_out (int8, one 4-bit code per byte) are filled if given."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    N, K2, ldwq = _matrix(wq4, torch.uint8, "wq4")
-    if K != 2 * K2 or M != B * L:
-        raise ValueError("shape mismatch")
-    _vector(inv_m, torch.float32, K, "inv_m", optional=True)
-    _vector(s_tok, torch.float32, L, "s_tok")
-    _vector(s_w, torch.float32, N, "s_w")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    if acc_out is not None and (acc_out.dtype != torch.int32 or tuple(acc_out.shape) != (M, N)
-                                or not acc_out.is_contiguous() or not acc_out.is_cuda):
-        raise TypeError("acc_out: expected a dense CUDA int32 [M, N] tensor")
-    ldxq = 0
-    if xq_out is not None:
-        Mq, Kq, ldxq = _matrix(xq_out, torch.int8, "xq_out")
-        if (Mq, Kq) != (M, K):
-            raise ValueError("xq_out must be [B*L, K]")
-    check(load().ptq4vm_w4a4_linear_fused(_ptr(x), _ptr(inv_m), _ptr(s_tok), _ptr(wq4), _ptr(s_w), _ptr(bias), _ptr(y),
-                                          _ptr(acc_out), _ptr(xq_out), B, L, K, N, ldx, ldwq, ldy, ldxq, _stream()))
-    return y
-
-def f16_linear(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor],
-               y: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """ptq4vm_f16_linear: y fp16 [M, N]."""
-    M, K, ldx = _matrix(x, torch.float16, "x")
-    N, K2, ldw = _matrix(w, torch.float16, "w")
-    if K != K2:
-        raise ValueError("shape mismatch")
-    _vector(bias, torch.float16, N, "bias", optional=True)
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    _, _, ldy = _matrix(y, torch.float16, "y")
-    check(load().ptq4vm_f16_linear(_ptr(x), _ptr(w), _ptr(bias), _ptr(y), M, K, N, ldx, ldw, ldy, _stream()))
-    return y
 
 
 VALIDATE_BLOCK = 4096  # PTQ4VM_VALIDATE_BLOCK
@@ -525,3 +286,9 @@ def validate_scales_static(s_tok: Optional[torch.Tensor], m: Optional[torch.Tens
     _vector(counts, torch.int32, 3, "counts")
     check(load().ptq4vm_validate_scales_static(_ptr(s_tok), sizes[0], _ptr(m), sizes[1], _ptr(s_w), sizes[2],
                                                _ptr(counts), _stream()))
+
+
+if os.path.exists(CALLS_PATH):
+    _bind_calls()
+else:
+    globals().update({_name: _bind_late(_name) for _name in HOT_CALLS})

@@ -1,4 +1,4 @@
-"""Builds libptq4vm.so (HIP kernels + C ABI) for gfx950, in-tree next to this file."""
+"""Builds libptq4vm.so (HIP kernels + C ABI) for gfx950 and _calls.so (its Python callables), in-tree next to this file."""
 from __future__ import annotations
 
 import concurrent.futures
@@ -7,6 +7,7 @@ import hashlib
 import os
 import shutil
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
@@ -70,14 +71,41 @@ def _compile_one(src: str, force: bool, extra=()):
     return obj, res.stdout + res.stderr
 
 
+CALLS_SRC = os.path.join(_HERE, "host", "calls.cc")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
+
+
+def build_calls(force: bool = True) -> str:
+    """_calls.so: the hot path's Python callables, a host-only extension on torch's C++ API."""
+    import torch
+
+    deps = [CALLS_SRC, os.path.join(_HERE, "..", "include", "ptq4vm.h")]
+    if not force and os.path.exists(CALLS_PATH) and os.path.getmtime(CALLS_PATH) >= max(map(os.path.getmtime, deps)):
+        return CALLS_PATH
+    root = os.path.dirname(torch.__file__)
+    tmp = CALLS_PATH + f".tmp{os.getpid()}"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-I{d}" for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"])),
+           CALLS_SRC, "-o", tmp, f"-L{os.path.join(root, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on " + CALLS_SRC + ":\n" + res.stdout + res.stderr)
+    os.replace(tmp, CALLS_PATH)
+    return CALLS_PATH
+
+
 def build(verbose: bool = False, force: bool = True) -> str:
-    """Compile every source under csrc/ (one hipcc process per file, in parallel) and link
-    libptq4vm.so.  force=True recompiles everything; force=False reuses an object file whose source,
+    """Compile every source under csrc/ (one hipcc process per file, in parallel), link
+    libptq4vm.so and build _calls.so.  force=True recompiles everything; force=False reuses an object file whose source,
     headers and flags are unchanged (a convenience while iterating on one kernel)."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as pool:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as pool:
+        calls = pool.submit(build_calls, force)
         results = list(pool.map(lambda s: _compile_one(s, force), srcs))
+        calls.result()
     keep = {obj for obj, _ in results}
     for stale in glob.glob(os.path.join(OBJ_DIR, "*.o")):
         if stale not in keep:
