@@ -5,6 +5,8 @@
 //   linear_mfma_splitk  a few hundred tiles or fewer: the wavefronts of a workgroup share one small tile
 //                       and split the reduction, operands go from memory straight into registers
 #pragma once
+#include <type_traits>
+
 #include "mfma_linear.hpp"
 
 namespace ptq4vm {
@@ -22,7 +24,10 @@ __device__ __forceinline__ v2f finish_four(const typename Path::Acc16 acc, float
     float a[4], s[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-        if constexpr (Path::kElemBytes == 1) {
+        if constexpr (Path::kElemBytes == 1 && std::is_same_v<typename Path::Acc16, v4f>) {  // integers carried in fp32 (E2M3)
+            a[c] = acc[c];
+            s[c] = rs * cs[c];
+        } else if constexpr (Path::kElemBytes == 1) {
             int v = acc[c];
             if constexpr (Path::kPacked4) v >>= 8;              // operands were codes times 16: exact
             if constexpr (Path::kOffset) v -= __mul24(rz, cz[c]);  // |z| < 2^8, |rowsum| < 2^23
@@ -62,13 +67,13 @@ __device__ __forceinline__ void mfma_step(typename Path::Acc16 (&acc)[FO][FR], c
 }
 
 // Eight fp16 results of a row, n_valid of them inside the matrix; rows may start at any even address.
-// NT: non-temporal, for the tiles that large outputs use: written back through the caches, they cost the kernels around
-// them more than they save (one Vim-S block over 64 x 785 rows 156.5 -> 148.2 us, the offset block of Vim-B over 64 x 197
-// rows 141.5 -> 136.8 us with 64 x 128 and larger tiles non-temporal).
-template <bool NT>
-__device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid) {
+// NT: non-temporal.  Large outputs whose row segments are whole 128-byte lines leave that way: written back through the
+// caches they cost the kernels around them more than they save (one Vim-S block over 64 x 785 rows 156.5 -> 148.2 us, the
+// offset block of Vim-B over 64 x 197 rows 141.5 -> 136.8 us).  Partial lines must merge in the L2 instead (15614 x 128 ->
+// 2310, 4620-byte rows: 29 - 48 us non-temporal, 22 us through the L2).
+__device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid, bool nt) {
     if (n_valid >= 8) {
-        if constexpr (NT)
+        if (nt)
             __builtin_nontemporal_store(data, reinterpret_cast<v4f_unaligned *>(dst));
         else
             *reinterpret_cast<v4f_unaligned *>(dst) = data;
@@ -105,6 +110,126 @@ __device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_b
     return out;
 }
 
+// The step, bias and offset vectors of a BR x BO tile, in LDS behind the ring.  fetch() loads one element per thread
+// (before the first operand copies, so that it returns ahead of them), park() writes them to LDS.  Channels and rows
+// beyond the matrix are clamped; they are never stored.
+template <class Path, int BR, int BO, int THREADS>
+struct TileVectors {
+    static_assert(BO <= THREADS && BR <= THREADS, "one thread per channel and per row");
+    static constexpr bool kInt8 = Path::kElemBytes == 1;
+    float *cs;     // s_w of the tile's channels
+    int *cz;       // their weight row sums
+    float *rs;     // s_tok of the tile's rows
+    int *rz;       // their zero offsets
+    uint16_t *cb;  // bias of the channels, raw fp16
+    float col_s = 1.0f, row_s = 1.0f;
+    int col_z = 0, row_z = 0;
+    uint16_t col_b = 0;
+
+    __device__ __forceinline__ explicit TileVectors(char *lds)
+        : cs(reinterpret_cast<float *>(lds)), cz(reinterpret_cast<int *>(cs + BO)), rs(reinterpret_cast<float *>(cz + BO)),
+          rz(reinterpret_cast<int *>(rs + BR)), cb(reinterpret_cast<uint16_t *>(rz + BR)) {}
+    __device__ __forceinline__ void fetch(const LinearArgs &p, int tid, int64_t r0, int64_t o0, int rows_valid, int cols_valid) {
+        if (tid < BO) {
+            const int64_t o = o0 + min(tid, cols_valid - 1);
+            if constexpr (kInt8) col_s = p.s_w[o];
+            if constexpr (Path::kOffset) col_z = p.rowsum[o];
+            if (p.bias) col_b = reinterpret_cast<const uint16_t *>(p.bias)[o];
+        }
+        if constexpr (kInt8) {
+            if (tid < BR) {
+                const uint32_t t = ((uint32_t)(r0 % p.L) + (uint32_t)min(tid, rows_valid - 1)) % (uint32_t)p.L;
+                row_s = p.s_tok[t];
+                if constexpr (Path::kOffset) row_z = p.z_tok[t];
+            }
+        }
+    }
+    __device__ __forceinline__ void park(int tid) {
+        if (tid < BO) {
+            cs[tid] = col_s;
+            cb[tid] = col_b;
+            if constexpr (Path::kOffset) cz[tid] = col_z;
+        }
+        if (tid < BR) {
+            rs[tid] = row_s;
+            if constexpr (Path::kOffset) rz[tid] = row_z;
+        }
+    }
+};
+template <int BR, int BO>
+constexpr int tile_vector_bytes() {
+    return BO * (4 + 2 + 4) + BR * (4 + 4);
+}
+
+// Epilogue of a workgroup: every wavefront dequantizes its (BR / WR) x (BO / WO) accumulators, transposes them through
+// its own patch of the ring (RING_BYTES, free by now) and stores whole row segments.
+template <class Path, int BR, int BO, int WR, int WO, int RING_BYTES, int FO, int FR, class Vectors>
+__device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO][FR], const LinearArgs &p, char *ring, const Vectors &vec,
+                                           int64_t r0, int64_t o0, int rows_valid, int cols_valid) {
+    constexpr bool kInt8 = Path::kElemBytes == 1;
+    constexpr int NW = WR * WO, WAVE_R = BR / WR, WAVE_O = BO / WO;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
+    const int l16 = lane & 15, lq = lane >> 4;
+
+    // Accumulator register v of block (i, j): token row 16 j + l16, channel 16 i + 4 lq + v.
+    if constexpr (kInt8) {
+        if (p.acc_out) {
+#pragma unroll
+            for (int i = 0; i < FO; i++)
+#pragma unroll
+                for (int j = 0; j < FR; j++)
+#pragma unroll
+                    for (int c = 0; c < 4; c++) {
+                        const int r = wave_r + j * 16 + l16, o = wave_o + i * 16 + lq * 4 + c;
+                        if (r < rows_valid && o < cols_valid)
+                            p.acc_out[(r0 + r) * p.N + o0 + o] = Path::kPacked4 ? (int)acc[i][j][c] >> 8 : (int)acc[i][j][c];
+                    }
+        }
+    }
+
+    constexpr int CPR = WAVE_O / 8, RPS = 64 / CPR;  // 16-byte chunks per patch row, rows per store instruction
+    constexpr int FIT = RING_BYTES / NW / (16 * WAVE_O * 2);
+    constexpr int JB = FIT >= FR ? FR : (FIT >= 2 && FR % 2 == 0 ? 2 : 1);  // 16-row blocks per round
+    static_assert(FIT >= 1 && RPS <= 16 * JB, "patches fit the ring");
+    char *const patch = ring + wave * (JB * 16 * WAVE_O * 2);
+    auto patch_chunk = [&](int row, int chunk) {
+        const int sw = CPR >= 8 ? (row & 7) : ((row / (8 / CPR)) & (CPR - 1));
+        return row * (WAVE_O * 2) + ((chunk ^ sw) << 4);
+    };
+    char *const y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
+    const bool nt = BR * BO >= 64 * 128 && p.ldy % 64 == 0 && (reinterpret_cast<uintptr_t>(p.y) & 127) == 0;
+#pragma unroll
+    for (int jb = 0; jb < FR; jb += JB) {
+#pragma unroll
+        for (int jj = 0; jj < JB; jj++) {
+            const int j = jb + jj;
+            const float rs = vec.rs[wave_r + j * 16 + l16];
+            const int rz = Path::kOffset ? vec.rz[wave_r + j * 16 + l16] : 0;
+#pragma unroll
+            for (int i = 0; i < FO; i++) {
+                const int col = wave_o + i * 16 + lq * 4;
+                const v4f cs = *reinterpret_cast<const v4f *>(vec.cs + col);
+                const v2f cb = *reinterpret_cast<const v2f *>(vec.cb + col);
+                v4i cz = {0, 0, 0, 0};
+                if constexpr (Path::kOffset) cz = *reinterpret_cast<const v4i *>(vec.cz + col);
+                *reinterpret_cast<v2f *>(patch + patch_chunk(jj * 16 + l16, 2 * i + (lq >> 1)) + (lq & 1) * 8) =
+                    finish_four<Path>(acc[i][j], rs, rz, cs, cz, cb);
+            }
+        }
+        asm volatile("" ::: "memory");  // wavefront-private patch: LDS runs a wavefront's accesses in order
+#pragma unroll
+        for (int s = 0; s < JB * 16 / RPS; s++) {
+            const int prow = s * RPS + lane / CPR, chunk = lane % CPR;
+            const v4f data = *reinterpret_cast<const v4f *>(patch + patch_chunk(prow, chunk));
+            const int r = wave_r + jb * 16 + prow, o = wave_o + chunk * 8;
+            if (r < rows_valid && o < cols_valid)
+                store_eight(y_tile + (int64_t)r * p.ldy * 2 + o * 2, data, cols_valid - o, nt);
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // One BR x BO tile per workgroup.  K is walked in slabs of SLAB bytes per row through a ring of STAGES LDS stages; what
 // bounds a workgroup is the latency of its copies and of its stores, so the shape of the kernel is small: few registers
@@ -118,7 +243,7 @@ __device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_b
 // ------------------------------------------------------------------------------------------
 template <int BR, int BO, int SLAB, int STAGES>
 constexpr int tile_lds_bytes() {
-    return STAGES * (BR + BO) * SLAB + BO * (4 + 2 + 4) + BR * (4 + 4);
+    return STAGES * (BR + BO) * SLAB + tile_vector_bytes<BR, BO>();
 }
 
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool ALIGNED>
@@ -132,7 +257,6 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
     static_assert(ALIGNED || STAGES == 2, "the register-staged form is double buffered");
     static_assert((BR + BO) % (ROWS_PER_COPY * NW) == 0 && BR % ROWS_PER_COPY == 0, "every wavefront issues the same number of copies");
     static_assert(STAGES >= 2 && (STAGES - 2) * COPIES <= 63, "vmcnt is a 6-bit counter");
-    constexpr bool kInt8 = Path::kElemBytes == 1;
     using Acc = typename Path::Acc16;
 
     int tile_r, tile_o;
@@ -145,31 +269,8 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
     auto chunk_of = [&](int row, int chunk) { return chunk ^ (SLAB == 64 ? swizzle(row) : (row & 7)); };
 
     char *const ring = lds_dyn;
-    float *const cs_lds = reinterpret_cast<float *>(lds_dyn + STAGES * STAGE_BYTES);  // s_w of the tile's channels
-    int *const cz_lds = reinterpret_cast<int *>(cs_lds + BO);                         // their weight row sums
-    float *const rs_lds = reinterpret_cast<float *>(cz_lds + BO);                     // s_tok of the tile's rows
-    int *const rz_lds = reinterpret_cast<int *>(rs_lds + BR);                         // their zero offsets
-    uint16_t *const cb_lds = reinterpret_cast<uint16_t *>(rz_lds + BR);               // bias of the channels, raw fp16
-
-    // Scale vectors first: their loads return before the copies below, and they are parked in LDS while the
-    // copies are in flight.  Channels and rows beyond the matrix are clamped; they are never stored.
-    float col_s = 1.0f, row_s = 1.0f;
-    int col_z = 0, row_z = 0;
-    uint16_t col_b = 0;
-    static_assert(BO <= THREADS && BR <= THREADS, "one thread per channel and per row");
-    if (tid < BO) {
-        const int64_t o = o0 + min(tid, cols_valid - 1);
-        if constexpr (kInt8) col_s = p.s_w[o];
-        if constexpr (Path::kOffset) col_z = p.rowsum[o];
-        if (p.bias) col_b = reinterpret_cast<const uint16_t *>(p.bias)[o];
-    }
-    if constexpr (kInt8) {
-        if (tid < BR) {
-            const uint32_t t = ((uint32_t)(r0 % p.L) + (uint32_t)min(tid, rows_valid - 1)) % (uint32_t)p.L;
-            row_s = p.s_tok[t];
-            if constexpr (Path::kOffset) row_z = p.z_tok[t];
-        }
-    }
+    TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + STAGES * STAGE_BYTES);
+    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
 
     // Copies: 1 KiB per wavefront and instruction, linear on the LDS side, so the swizzle is applied by choosing
     // which global chunk a lane fetches.  Copy c covers LDS rows ROWS_PER_COPY c ..: activation rows, then weights.
@@ -220,16 +321,7 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
 #pragma unroll
     for (int s = 0; s < STAGES - 1; s++)
         if (s < n_slabs) issue(s, s);
-    if (tid < BO) {
-        cs_lds[tid] = col_s;
-        cb_lds[tid] = col_b;
-        if constexpr (Path::kOffset) cz_lds[tid] = col_z;
-    }
-    if (tid < BR) {
-        rs_lds[tid] = row_s;
-        if constexpr (Path::kOffset) rz_lds[tid] = row_z;
-    }
-
+    vec.park(tid);
     if constexpr (!ALIGNED) commit(0);
 
     int stage = 0;
@@ -272,120 +364,17 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
     }
     __syncthreads();  // the ring becomes the wavefronts' transposition patches
 
-    // Accumulator register v of block (i, j): token row 16 j + l16, channel 16 i + 4 lq + v.
-    if constexpr (kInt8) {
-        if (p.acc_out) {
-#pragma unroll
-            for (int i = 0; i < FO; i++)
-#pragma unroll
-                for (int j = 0; j < FR; j++)
-#pragma unroll
-                    for (int c = 0; c < 4; c++) {
-                        const int r = wave_r + j * 16 + l16, o = wave_o + i * 16 + lq * 4 + c;
-                        if (r < rows_valid && o < cols_valid)
-                            p.acc_out[(r0 + r) * p.N + o0 + o] = Path::kPacked4 ? (int)acc[i][j][c] >> 8 : (int)acc[i][j][c];
-                    }
-        }
-    }
-
-    constexpr int CPR = WAVE_O / 8, RPS = 64 / CPR;  // 16-byte chunks per patch row, rows per store instruction
-    constexpr int FIT = STAGES * STAGE_BYTES / NW / (16 * WAVE_O * 2);
-    constexpr int JB = FIT >= FR ? FR : (FIT >= 2 && FR % 2 == 0 ? 2 : 1);  // 16-row blocks per round
-    static_assert(FIT >= 1 && RPS <= 16 * JB, "patches fit the ring");
-    char *const patch = ring + wave * (JB * 16 * WAVE_O * 2);
-    auto patch_chunk = [&](int row, int chunk) {
-        const int sw = CPR >= 8 ? (row & 7) : ((row / (8 / CPR)) & (CPR - 1));
-        return row * (WAVE_O * 2) + ((chunk ^ sw) << 4);
-    };
-    char *const y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
-#pragma unroll
-    for (int jb = 0; jb < FR; jb += JB) {
-#pragma unroll
-        for (int jj = 0; jj < JB; jj++) {
-            const int j = jb + jj;
-            const float rs = rs_lds[wave_r + j * 16 + l16];
-            const int rz = Path::kOffset ? rz_lds[wave_r + j * 16 + l16] : 0;
-#pragma unroll
-            for (int i = 0; i < FO; i++) {
-                const int col = wave_o + i * 16 + lq * 4;
-                const v4f cs = *reinterpret_cast<const v4f *>(cs_lds + col);
-                const v2f cb = *reinterpret_cast<const v2f *>(cb_lds + col);
-                v4i cz = {0, 0, 0, 0};
-                if constexpr (Path::kOffset) cz = *reinterpret_cast<const v4i *>(cz_lds + col);
-                *reinterpret_cast<v2f *>(patch + patch_chunk(jj * 16 + l16, 2 * i + (lq >> 1)) + (lq & 1) * 8) =
-                    finish_four<Path>(acc[i][j], rs, rz, cs, cz, cb);
-            }
-        }
-        asm volatile("" ::: "memory");  // wavefront-private patch: LDS runs a wavefront's accesses in order
-#pragma unroll
-        for (int s = 0; s < JB * 16 / RPS; s++) {
-            const int prow = s * RPS + lane / CPR, chunk = lane % CPR;
-            const v4f data = *reinterpret_cast<const v4f *>(patch + patch_chunk(prow, chunk));
-            const int r = wave_r + jb * 16 + prow, o = wave_o + chunk * 8;
-            if (r < rows_valid && o < cols_valid)
-                store_eight<(BR * BO >= 64 * 128)>(y_tile + (int64_t)r * p.ldy * 2 + o * 2, data, cols_valid - o);
-        }
-        asm volatile("" ::: "memory");
-    }
+    store_tile<Path, BR, BO, WR, WO, STAGES * STAGE_BYTES>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
 }
 
-// ------------------------------------------------------------------------------------------
-// Split reduction, for problems of so few tiles that one wavefront's chain of loads is the whole run time.  A workgroup
-// of SK wavefronts owns one tile of 16 FR rows x 16 FO channels; wavefront w takes
-// the MFMA steps w, w + SK, ... (64 bytes of K each, so that neighbouring wavefronts read neighbouring bytes),
-// with U steps of operands in flight in registers, then the partial sums meet in LDS and wavefront b finishes
-// block b.  ALIGNED: 16-byte aligned bases and pitches and k_bytes a multiple of 64; otherwise any pitch,
-// alignment and K: loads of 16 bytes wherever they fall, bytes beyond K zeroed.
-// ------------------------------------------------------------------------------------------
-template <class Path, int FR, int FO, int SK, int U, bool ALIGNED>
-__global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p) {
+// The partial sums of a workgroup's SK wavefronts meet in LDS (SK FR FO KiB) and wavefront b finishes block b.
+template <class Path, int FR, int FO, int SK>
+__device__ __forceinline__ void finish_split(const typename Path::Acc16 (&acc)[FO][FR], const LinearArgs &p, char *partial, int64_t r0, int64_t o0) {
     constexpr bool kInt8 = Path::kElemBytes == 1;
-    constexpr int BR = 16 * FR, BO = 16 * FO, NB = FR * FO;
+    constexpr int NB = FR * FO;
     using Acc = typename Path::Acc16;
-    __shared__ __attribute__((aligned(16))) char partial[SK * NB * 1024];
-
-    int tile_r, tile_o;
-    if (!tile_of_block(p, tile_r, tile_o)) return;
-    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
-    const char *xrow[FR], *wrow[FO];
-#pragma unroll
-    for (int j = 0; j < FR; j++) xrow[j] = p.x + min(r0 + j * 16 + l16, p.M - 1) * p.ldx_bytes + lq * 16;
-#pragma unroll
-    for (int i = 0; i < FO; i++) wrow[i] = p.w + min(o0 + i * 16 + l16, p.N - 1) * p.ldw_bytes + lq * 16;
-    const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + p.k_bytes), *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + p.k_bytes);
-
-    Acc acc[FO][FR];
-#pragma unroll
-    for (int i = 0; i < FO; i++)
-#pragma unroll
-        for (int j = 0; j < FR; j++)
-#pragma unroll
-            for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
-
-    const int n_steps = (int)((p.k_bytes + 63) / 64);
-    for (int s0 = wave; s0 < n_steps; s0 += SK * U) {
-        v4i fw[U][FO], fx[U][FR];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int s = s0 + u * SK;
-            if (s < n_steps) {
-#pragma unroll
-                for (int i = 0; i < FO; i++)
-                    fw[u][i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + (int64_t)s * 64)
-                                       : load_any(wrow[i] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, w_end);
-#pragma unroll
-                for (int j = 0; j < FR; j++)
-                    fx[u][j] = ALIGNED ? *reinterpret_cast<const v4i *>(xrow[j] + (int64_t)s * 64)
-                                       : load_any(xrow[j] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, x_end);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++)
-            if (s0 + u * SK < n_steps) mfma_step<Path, FO, FR>(acc, fw[u], fx[u]);
-    }
-
     // Partial sums: [wavefront][block][lane] 16-byte pieces.
 #pragma unroll
     for (int i = 0; i < FO; i++)
@@ -436,6 +425,65 @@ __global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p
                     reinterpret_cast<uint16_t *>(dst)[c] = (uint16_t)(__builtin_bit_cast(uint32_t, w[c >> 1]) >> (16 * (c & 1)));
         }
     }
+}
+
+// ------------------------------------------------------------------------------------------
+// Split reduction, for problems of so few tiles that one wavefront's chain of loads is the whole run time.  A workgroup
+// of SK wavefronts owns one tile of 16 FR rows x 16 FO channels; wavefront w takes
+// the MFMA steps w, w + SK, ... (64 bytes of K each, so that neighbouring wavefronts read neighbouring bytes),
+// with U steps of operands in flight in registers, then the partial sums meet in LDS and wavefront b finishes
+// block b.  ALIGNED: 16-byte aligned bases and pitches and k_bytes a multiple of 64; otherwise any pitch,
+// alignment and K: loads of 16 bytes wherever they fall, bytes beyond K zeroed.
+// ------------------------------------------------------------------------------------------
+template <class Path, int FR, int FO, int SK, int U, bool ALIGNED>
+__global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p) {
+    constexpr int BR = 16 * FR, BO = 16 * FO;
+    using Acc = typename Path::Acc16;
+    __shared__ __attribute__((aligned(16))) char partial[SK * FR * FO * 1024];
+
+    int tile_r, tile_o;
+    if (!tile_of_block(p, tile_r, tile_o)) return;
+    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const char *xrow[FR], *wrow[FO];
+#pragma unroll
+    for (int j = 0; j < FR; j++) xrow[j] = p.x + min(r0 + j * 16 + l16, p.M - 1) * p.ldx_bytes + lq * 16;
+#pragma unroll
+    for (int i = 0; i < FO; i++) wrow[i] = p.w + min(o0 + i * 16 + l16, p.N - 1) * p.ldw_bytes + lq * 16;
+    const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + p.k_bytes), *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + p.k_bytes);
+
+    Acc acc[FO][FR];
+#pragma unroll
+    for (int i = 0; i < FO; i++)
+#pragma unroll
+        for (int j = 0; j < FR; j++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
+
+    const int n_steps = (int)((p.k_bytes + 63) / 64);
+    for (int s0 = wave; s0 < n_steps; s0 += SK * U) {
+        v4i fw[U][FO], fx[U][FR];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int s = s0 + u * SK;
+            if (s < n_steps) {
+#pragma unroll
+                for (int i = 0; i < FO; i++)
+                    fw[u][i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + (int64_t)s * 64)
+                                       : load_any(wrow[i] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, w_end);
+#pragma unroll
+                for (int j = 0; j < FR; j++)
+                    fx[u][j] = ALIGNED ? *reinterpret_cast<const v4i *>(xrow[j] + (int64_t)s * 64)
+                                       : load_any(xrow[j] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, x_end);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (s0 + u * SK < n_steps) mfma_step<Path, FO, FR>(acc, fw[u], fx[u]);
+    }
+
+    finish_split<Path, FR, FO, SK>(acc, p, partial, r0, o0);
 }
 
 }  // namespace mfma
