@@ -9,12 +9,13 @@
 // accumulator register v of lane l is (first-operand row 4 (l / 16) + v) x (second-operand row l mod 16).
 // The weight is the first operand: a lane's four results are four consecutive channels of one token row.
 //
-// Two kernels:
+// Kernels:
 //   linear_e2m3_persistent  one workgroup of 8 wavefronts per CU walks 256 x 256 tiles (wave tile 128 token rows x
 //                           64 channels); a ring of 3 stages, each one 128-code block of the tile's 256 + 256
 //                           rows, is filled by direct global -> LDS copies that run two stages ahead.
-//   linear_e2m3_generic     64 x 64 tiles staged through registers, any shape and alignment of y.
-#include "mfma_linear.hpp"
+//   linear_e2m3_tile        one tile of 32 x 64 .. 128 x 128 per workgroup, every other shape and any alignment of y
+//   linear_e2m3_splitk      a few hundred blocks of 16 x 16 or fewer: the wavefronts of a workgroup split the reduction
+#include "gemm_tile.hpp"
 
 // Timing experiments only (results are wrong when any bit is set): 1 no output stores, 2 no epilogue at all,
 // 4 no global -> LDS copies of the operands, 8 no MFMAs.
@@ -39,71 +40,164 @@ __device__ __forceinline__ v8i make_fragment(const v4i &lo, const v2i &hi) {
     return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], 0, 0};
 }
 
+// What the shared pieces of gemm_tile.hpp need to know: 4-bit codes, sums carried exactly in fp32.
+struct E2m3Path {
+    static constexpr int kElemBytes = 1;
+    static constexpr bool kOffset = false;
+    static constexpr bool kPacked4 = false;
+    using Acc16 = v4f;
+};
+
 // ------------------------------------------------------------------------------------------
-// Small tiled kernel: 4 wavefronts, 64 token rows x 64 channels per workgroup, wavefront w owns rows
-// 16 w .. 16 w + 15 against the 64 channels.  One 128-code block per trip, staged through registers.
+// One BR x BO tile per workgroup, the structure of linear_mfma_tile (gemm_tile.hpp): a ring of STAGES stages, each one
+// 128-code block of the tile's rows, filled by direct global -> LDS copies; several small workgroups per CU overlap each
+// other's copies, MFMAs and stores.  A block of the tile's rows is one contiguous span of the container; a stage row
+// is the 96-byte block as in memory, except that rows whose bit 3 is set keep their two high-part chunks swapped (bank
+// conflicts, see the persistent kernel).  3152 x 384 -> 1536 takes 6.1 us = 620
+// TOP/s (18.4 us with the register-staged 64 x 64 kernel before), 25216 x 1536 -> 768 28.6 us = 2.1 POP/s.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void linear_e2m3_generic(const LinearArgs p) {
-    __shared__ __attribute__((aligned(16))) char xs[64 * kBlockBytes];
-    __shared__ __attribute__((aligned(16))) char ws[64 * kBlockBytes];
+template <int BR, int BO, int STAGES>
+constexpr int e2m3_tile_lds_bytes() {
+    return STAGES * (BR + BO) * kBlockBytes + tile_vector_bytes<BR, BO>();
+}
+
+template <int BR, int BO, int WR, int WO, int STAGES>
+__global__ __launch_bounds__(64 * WR * WO) void linear_e2m3_tile(const LinearArgs p) {
+    constexpr int NW = WR * WO, THREADS = 64 * NW;
+    constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
+    constexpr int STAGE_BYTES = (BR + BO) * kBlockBytes;
+    constexpr int X_COPIES = BR * kBlockBytes / 1024, ALL_COPIES = STAGE_BYTES / 1024, COPIES = (ALL_COPIES + NW - 1) / NW;
+    static_assert(BR % 32 == 0 && BO % 32 == 0, "whole 1 KiB copies");
+    static_assert((STAGES - 2) * COPIES <= 63, "vmcnt is a 6-bit counter");
+
     int tile_r, tile_o;
     if (!tile_of_block(p, tile_r, tile_o)) return;
-    const int64_t r0 = (int64_t)tile_r * 64, o0 = (int64_t)tile_o * 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
     const int l16 = lane & 15, lq = lane >> 4;
+    const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
 
-    v4f acc[4];
+    char *const ring = lds_dyn;
+    TileVectors<E2m3Path, BR, BO, THREADS> vec(lds_dyn + STAGES * STAGE_BYTES);
+    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
+
+    // Every wavefront issues the same number of copies: those beyond the last repeat it.  Rows beyond the matrix fetch
+    // its last 16 bytes; they are never stored.
+    uint32_t off[COPIES];
 #pragma unroll
-    for (int i = 0; i < 4; i++) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < COPIES; i++) {
+        const int c = min(wave + NW * i, ALL_COPIES - 1);
+        const bool is_x = c < X_COPIES;
+        const int piece = (is_x ? c : c - X_COPIES) * 64 + lane;  // 16-byte pieces, 6 a row
+        const int row = piece / 6, chunk = piece - row * 6;
+        const int src = row * 6 + (chunk >= 4 && (row & 8) ? 9 - chunk : chunk);
+        off[i] = (uint32_t)min(src, (is_x ? rows_valid : cols_valid) * 6 - 1) * 16;
+    }
+    const char *const gx = p.x + r0 * kBlockBytes, *const gw = p.w + o0 * kBlockBytes;
+    auto issue = [&](int block, int stage) {
+#pragma unroll
+        for (int i = 0; i < COPIES; i++) {
+            const int c = min(wave + NW * i, ALL_COPIES - 1);  // scalar
+            const char *src = c < X_COPIES ? gx + block * p.ldx_bytes : gw + block * p.ldw_bytes;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off[i]),
+                                             (__attribute__((address_space(3))) void *)(ring + stage * STAGE_BYTES + c * 1024), 16, 0, 0);
+        }
+    };
+
+    v4f acc[FO][FR];
+#pragma unroll
+    for (int i = 0; i < FO; i++)
+#pragma unroll
+        for (int j = 0; j < FR; j++) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int n_blocks = (int)(p.k_bytes / kBlockBytes);
-    for (int kb = 0; kb < n_blocks; kb++) {
-        for (int q = tid; q < 64 * 6; q += kThreads) {  // 16-byte chunks of the two 64-row tiles
-            const int row = q / 6, c = q - row * 6;
-            v4i vx = {0, 0, 0, 0}, vw = {0, 0, 0, 0};
-            if (r0 + row < p.M) vx = *reinterpret_cast<const v4i *>(p.x + kb * p.ldx_bytes + (r0 + row) * kBlockBytes + c * 16);
-            if (o0 + row < p.N) vw = *reinterpret_cast<const v4i *>(p.w + kb * p.ldw_bytes + (o0 + row) * kBlockBytes + c * 16);
-            *reinterpret_cast<v4i *>(xs + q * 16) = vx;
-            *reinterpret_cast<v4i *>(ws + q * 16) = vw;
-        }
-        __syncthreads();
-        const char *xrow = xs + (wave * 16 + l16) * kBlockBytes;
-        const v8i fx = make_fragment(*reinterpret_cast<const v4i *>(xrow + lq * 16), *reinterpret_cast<const v2i *>(xrow + 64 + lq * 8));
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const char *wrow = ws + (i * 16 + l16) * kBlockBytes;
-            const v8i fw = make_fragment(*reinterpret_cast<const v4i *>(wrow + lq * 16), *reinterpret_cast<const v2i *>(wrow + 64 + lq * 8));
-            acc[i] = mfma_e2m3(fw, fx, acc[i]);
-        }
-        __syncthreads();
-    }
+    for (int s = 0; s < STAGES - 1; s++)
+        if (s < n_blocks) issue(s, s);
+    vec.park(tid);
 
-    const int64_t r = r0 + wave * 16 + l16;
-    if (r >= p.M) return;
-    const float rs = p.s_tok[r % p.L];
-    uint16_t *yrow = reinterpret_cast<uint16_t *>(p.y) + r * p.ldy;
+    int stage = 0;
+    for (int it = 0; it < n_blocks; it++) {
+        constexpr int KEEP = (STAGES - 2) * COPIES;  // younger blocks that may stay in flight
+        if (it + STAGES - 2 < n_blocks)
+            wait_vmcnt_at_most<KEEP>();
+        else
+            wait_vmcnt_at_most<0>();
+        if (it == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the scale vectors are in LDS
+        __builtin_amdgcn_s_barrier();  // everyone's copies of block `it` are visible; block it-1 is fully consumed
+        int refill = stage + STAGES - 1;
+        if (refill >= STAGES) refill -= STAGES;
+        if (it + STAGES - 1 < n_blocks) issue(it + STAGES - 1, refill);
+        const char *sx = ring + stage * STAGE_BYTES + wave_r * kBlockBytes;
+        const char *sw = ring + stage * STAGE_BYTES + (BR + wave_o) * kBlockBytes;
+        auto fragment = [&](const char *rows, int row) {
+            const char *r = rows + row * kBlockBytes;  // (wave rows start at multiples of 16: bit 3 is that of the tile's row)
+            return make_fragment(*reinterpret_cast<const v4i *>(r + lq * 16),
+                                 *reinterpret_cast<const v2i *>(r + 64 + ((lq * 8) ^ ((row & 8) << 1))));
+        };
+        v8i fw[FO];
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+        for (int i = 0; i < FO; i++) fw[i] = fragment(sw, i * 16 + l16);
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int64_t o = o0 + i * 16 + lq * 4 + 2 * h;
-            const bool ok0 = o < p.N, ok1 = o + 1 < p.N;
-            const float a0 = acc[i][2 * h], a1 = acc[i][2 * h + 1];
-            if (p.acc_out) {
-                if (ok0) p.acc_out[r * p.N + o] = (int)a0;
-                if (ok1) p.acc_out[r * p.N + o + 1] = (int)a1;
-            }
-            const float cs0 = ok0 ? p.s_w[o] : 0.0f, cs1 = ok1 ? p.s_w[o + 1] : 0.0f;
-            uint32_t bias_word = 0;
-            if (p.bias) {
-                const uint16_t *b = reinterpret_cast<const uint16_t *>(p.bias);
-                bias_word = (ok0 ? (uint32_t)b[o] : 0u) | (ok1 ? (uint32_t)b[o + 1] << 16 : 0u);
-            }
-            const uint32_t out = __builtin_bit_cast(
-                uint32_t, dequantize_pair_f16(a0, rs * cs0, a1, rs * cs1, __builtin_bit_cast(float, bias_word)));
-            if (ok0) yrow[o] = (uint16_t)out;
-            if (ok1) yrow[o + 1] = (uint16_t)(out >> 16);
+        for (int j = 0; j < FR; j++) {
+            const v8i fx = fragment(sx, j * 16 + l16);
+#pragma unroll
+            for (int i = 0; i < FO; i++) acc[i][j] = mfma_e2m3(fw[i], fx, acc[i][j]);
         }
+        if (++stage == STAGES) stage = 0;
+    }
+    __syncthreads();  // the ring becomes the wavefronts' transposition patches
+    store_tile<E2m3Path, BR, BO, WR, WO, STAGES * STAGE_BYTES>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+}
+
+// Split reduction (see linear_mfma_splitk): wavefront w takes the 128-code blocks w, w + SK, ... with U blocks of operands
+// in flight in registers.
+template <int FR, int FO, int SK, int U>
+__global__ __launch_bounds__(64 * SK) void linear_e2m3_splitk(const LinearArgs p) {
+    __shared__ __attribute__((aligned(16))) char partial[SK * FR * FO * 1024];
+    int tile_r, tile_o;
+    if (!tile_of_block(p, tile_r, tile_o)) return;
+    const int64_t r0 = (int64_t)tile_r * 16 * FR, o0 = (int64_t)tile_o * 16 * FO;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const char *xrow[FR], *wrow[FO];
+#pragma unroll
+    for (int j = 0; j < FR; j++) xrow[j] = p.x + min(r0 + j * 16 + l16, p.M - 1) * kBlockBytes;
+#pragma unroll
+    for (int i = 0; i < FO; i++) wrow[i] = p.w + min(o0 + i * 16 + l16, p.N - 1) * kBlockBytes;
+    auto fragment = [&](const char *row) {
+        return make_fragment(*reinterpret_cast<const v4i *>(row + lq * 16), *reinterpret_cast<const v2i *>(row + 64 + lq * 8));
+    };
+
+    v4f acc[FO][FR];
+#pragma unroll
+    for (int i = 0; i < FO; i++)
+#pragma unroll
+        for (int j = 0; j < FR; j++) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    const int n_blocks = (int)(p.k_bytes / kBlockBytes);
+    for (int b0 = wave; b0 < n_blocks; b0 += SK * U) {
+        v8i fw[U][FO], fx[U][FR];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t b = b0 + u * SK;
+            if (b < n_blocks) {
+#pragma unroll
+                for (int i = 0; i < FO; i++) fw[u][i] = fragment(wrow[i] + b * p.ldw_bytes);
+#pragma unroll
+                for (int j = 0; j < FR; j++) fx[u][j] = fragment(xrow[j] + b * p.ldx_bytes);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (b0 + u * SK < n_blocks) {
+#pragma unroll
+                for (int i = 0; i < FO; i++)
+#pragma unroll
+                    for (int j = 0; j < FR; j++) acc[i][j] = mfma_e2m3(fw[u][i], fx[u][j], acc[i][j]);
+            }
+    }
+    finish_split<E2m3Path, FR, FO, SK>(acc, p, partial, r0, o0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -425,13 +519,26 @@ int launch_persistent(LinearArgs a, hipStream_t stream) {
     return ptq4vm::check_launch("linear_e2m3_persistent");
 }
 
-int launch_generic(LinearArgs a, hipStream_t stream) {
+template <int BR, int BO, int WR, int WO, int STAGES>
+int launch_tile(LinearArgs a, hipStream_t stream) {
     dim3 grid;
-    if (!set_grid<64, 64>(a, grid)) return PTQ4VM_ERR_SHAPE;
-    linear_e2m3_generic<<<grid, dim3(kThreads), 0, stream>>>(a);
-    return ptq4vm::check_launch("linear_e2m3_generic");
+    if (!set_grid<BR, BO>(a, grid)) return PTQ4VM_ERR_SHAPE;
+    constexpr int lds_bytes = e2m3_tile_lds_bytes<BR, BO, STAGES>();
+    auto kernel = linear_e2m3_tile<BR, BO, WR, WO, STAGES>;
+    if constexpr (lds_bytes > 64 * 1024) {
+        if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_e2m3_tile)")) return rc;
+    }
+    kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(a);
+    return ptq4vm::check_launch("linear_e2m3_tile");
 }
 
+template <int FR, int FO, int SK, int U>
+int launch_splitk(LinearArgs a, hipStream_t stream) {
+    dim3 grid;
+    if (!set_grid<16 * FR, 16 * FO>(a, grid)) return PTQ4VM_ERR_SHAPE;
+    linear_e2m3_splitk<FR, FO, SK, U><<<grid, dim3(64 * SK), 0, stream>>>(a);
+    return ptq4vm::check_launch("linear_e2m3_splitk");
+}
 }  // namespace
 }  // namespace mfma
 }  // namespace ptq4vm
@@ -469,10 +576,26 @@ extern "C" int ptq4vm_w4a4_linear_e2m3(const uint8_t *xq6, const uint8_t *wq6, c
     a.ldy = ldy;
     a.L = L;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    const int64_t tiles = ptq4vm::ceil_div(M, 256) * ptq4vm::ceil_div(N, kTile);
+    // 256 x 256 tiles from two rounds of them (50432 x 384 -> 1536 [1182 tiles] 43.8 us against 54.0 on 128 x 256 tiles,
+    // 50432 x 1536 -> 768 [591] 56.2 / 60.0, 12608 x 768 -> 3072 [600] 35.4 / 34.8, but 25216 x 1536 -> 768 [297] 35.0 / 28.6),
+    // unless they pad the channels by more than a quarter (40000 x 768 -> 520: 29.3 / 24.3).
+    const int64_t big_tiles = ptq4vm::ceil_div(M, 256) * ptq4vm::ceil_div(N, kTile);
     const bool persistent_ok = K % 128 == 0 && K >= 256 && N % 8 == 0 && ptq4vm::aligned_to(y_f16, 16) && ldy % 8 == 0 &&
-                               ptq4vm::aligned_to(bias_f16, 4) &&
-                               ldy * 2 * kTile < (1LL << 31) && L < (1LL << 31) && tiles >= 128 && tiles <= 0x3fffffffLL;
+                               ptq4vm::aligned_to(bias_f16, 4) && ptq4vm::ceil_div(N, kTile) * kTile * 4 <= N * 5 &&
+                               ldy * 2 * kTile < (1LL << 31) && L < (1LL << 31) && big_tiles >= 512 && big_tiles <= 0x3fffffffLL;
     if (persistent_ok) return launch_persistent(a, stream);
-    return launch_generic(a, stream);
+    // The largest tile that leaves the CUs a few workgroups each, as in gemm_tile.hip; measured (us, tiles in brackets):
+    //   split reduction / 32 x 64:  197 x 1536 -> 80 [65 blocks] 3.2 / 4.9, 392 x 1152 -> 200 [325] 3.5 / 4.5, 60 x 384 -> 2281 [572] 3.4 / 3.2
+    //   32 x 64 / 64 x 64:          788 x 1536 -> 768 [156] 5.9 / 6.3, 197 x 768 -> 3072 [192] 5.0 / 4.3
+    //   64 x 64 / 64 x 128:         6304 x 768 -> 384 [297] 6.1 / 6.4, 3192 x 896 -> 1047 [450] 8.1 / 7.6
+    //   64 x 128 / 128 x 128:       3152 x 384 -> 1536 [300] 6.1 / 6.4, 6304 x 384 -> 1536 [600] 9.5 / 8.1
+    //   128 x 128 / 128 x 256:      25216 x 768 -> 384 [394] 11.6 / 12.3, 12608 x 768 -> 3072 [1188] 36.3 / 32.9
+    auto tiles = [&](int br, int bo) { return ptq4vm::ceil_div(M, br) * ptq4vm::ceil_div(N, bo); };
+    if (L >= (1LL << 31) || tiles(16, 16) <= (K >= 896 ? 600 : 256)) return launch_splitk<1, 1, 4, 3>(a, stream);
+    const int64_t most = tiles(32, 64) * 32 * 64 * 4 / 3;  // padded size that a tile may have
+    if (tiles(128, 256) >= 800 && tiles(128, 256) * 128 * 256 <= most) return launch_tile<128, 256, 2, 4, 2>(a, stream);
+    if (tiles(128, 128) >= 500 && tiles(128, 128) * 128 * 128 <= most) return launch_tile<128, 128, 2, 4, 2>(a, stream);
+    if (tiles(64, 128) >= 400 && tiles(64, 128) * 64 * 128 <= most) return launch_tile<64, 128, 2, 2, 2>(a, stream);
+    if (tiles(64, 64) >= 190) return launch_tile<64, 64, 2, 2, 2>(a, stream);
+    return launch_tile<32, 64, 2, 2, 3>(a, stream);
 }

@@ -1,4 +1,4 @@
-"""The tile kernels of the linears (csrc/gemm_tile.hpp) at the edges of their tiles, on every operand type, against a
+"""The tile kernels of the linears (csrc/gemm_tile.hpp, csrc/gemm_e2m3.hip) at the edges of their tiles, on every operand type, against a
 64-bit product (exact for the integer paths)."""
 import pytest
 import torch
@@ -79,6 +79,20 @@ def test_tile_kernels_all_operand_types(M, K, N, pad):
         ptq.w4a4_linear(pack(x4), pack(w4), s_tok, s_w, bias, B, L, y=y, acc_out=acc)
         check(y, buf, acc4, scale, bias)
         assert torch.equal(acc.double(), acc4)
+
+    # 4-bit codes in the E2M3 container: integer activations at step 1 are their own codes; an integer weight row whose
+    # largest entry is 7 folds to step 1
+    x4, w4 = ints(-7, 8, M, K), ints(-7, 8, N, K)
+    w4[:, 0] = 7
+    one = torch.ones(max(K, L), device=DEV)
+    xq6 = ptq.quantize_pts_a4_e2m3(x4.half(), None, one[:L], B, L)
+    wq6, step, _ = ptq.fold_smoothing_w4_e2m3(w4.half(), one[:K])
+    assert bool((step == 1).all())
+    acc4 = x4.double() @ w4.double().t()
+    buf, y = _output(M, N, pad)
+    ptq.w4a4_linear_e2m3(xq6, wq6, s_tok, s_w, bias, B, L, K, y=y, acc_out=acc)
+    check(y, buf, acc4, scale, bias)
+    assert torch.equal(acc.double(), acc4)
 
     # fp16, without and with bias: fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|
     x, w = torch.randn(M, K, generator=g, device=DEV).half(), torch.randn(N, K, generator=g, device=DEV).half()
