@@ -12,6 +12,11 @@
 namespace ptq4vm {
 namespace mfma {
 
+// Token position of row r (a 64-bit remainder is some 150 instructions; hardly any problem needs it).
+__device__ __forceinline__ uint32_t token_of(const LinearArgs &p, int64_t r) {
+    return p.M <= 0x7fffffffLL ? (uint32_t)r % (uint32_t)p.L : (uint32_t)(r % p.L);
+}
+
 // 16-byte accesses at any byte address and 8- / 16-byte ones at any even address: gfx950 takes unaligned vector accesses
 typedef int v4i_unaligned __attribute__((ext_vector_type(4), aligned(1)));
 typedef float v4f_unaligned __attribute__((ext_vector_type(4), aligned(2)));
@@ -399,7 +404,7 @@ __device__ __forceinline__ void finish_split(const typename Path::Acc16 (&acc)[F
         v4i cz = {0, 0, 0, 0};
         uint32_t bias_word[2] = {0, 0};
         if constexpr (kInt8) {
-            const uint32_t t = (uint32_t)(r % p.L);
+            const uint32_t t = token_of(p, r);
             rs = p.s_tok[t];
             if constexpr (Path::kOffset) rz = p.z_tok[t];
         }

@@ -11,12 +11,13 @@
 // quantizer is cheaper.  Kernels:
 //   pts_linear_wres     N <= 128 over many rows (x_proj): weight resident in LDS, every fp16
 //                       activation read once from HBM in whole 128-byte lines, quantized once.
+//   pts_linear_split    the same over up to 20 000 rows, and few rows of any width: the reduction spread over a
+//                       workgroup's wavefronts (pts_linear_split.hpp).
 //   pts_linear_generic  every other shape: the register-staged tiled kernel with the quantizer in
 //                       its loader (correct everywhere, re-quantizes per tile column).
 #include <type_traits>
 
-#include "mfma_linear.hpp"
-#include "quant_device.hpp"
+#include "pts_linear_split.hpp"
 
 namespace {
 
@@ -25,17 +26,6 @@ using ptq4vm::pack4;
 
 using namespace ptq4vm::mfma;
 
-// One PTS code (Sec. 5.1): smoothing multiply, step multiply, round half to even, clip.  Two
-// separate fp32 multiplies in this order: the codes must equal the stand-alone quantizer's.
-// BITS4: clip to +-7 (Sec. 2.3 with b = 4) instead of +-127.
-// OFFSET: per-token zero offset z (Sec. 5.1; the quantizer of Sec. 2.3 with its code range shifted into int8):
-// clip(q + z, -128, 127), formed as clip(q, -128 - z, 127 - z) + z so that a saturated q cannot overflow.
-template <bool BITS4, bool OFFSET>
-__device__ __forceinline__ int clip_code(int q, int z) {
-    if constexpr (OFFSET) return min(max(q, -128 - z), 127 - z) + z;
-    return BITS4 ? min(max(q, -7), 7) : min(max(q, -127), 127);
-}
-
 template <bool BITS4 = false, bool OFFSET = false>
 __device__ __forceinline__ int quantize_one(float x, float inv_m, float inv_s, int z = 0) {
     float v = x * inv_m;
@@ -43,54 +33,12 @@ __device__ __forceinline__ int quantize_one(float x, float inv_m, float inv_s, i
     return clip_code<BITS4, OFFSET>(cvt_i32_f32(__builtin_rintf(v)), z);
 }
 
-// Four int8 bytes holding 4-bit codes -> the same codes times 16 (what the int8 MFMA is fed on the 4-bit path:
-// the accumulator is then 256 times the sum, undone exactly in the channel steps).
-__device__ __forceinline__ uint32_t times16(uint32_t packed_codes) { return (packed_codes << 4) & 0xF0F0F0F0u; }
-
 // 32 packed 4-bit codes (16 bytes, even index in the low nibble) -> 32 int8 bytes, codes times 16, in index order.
 __device__ __forceinline__ void expand_nibbles_in_order(const v4i &packed, v4i &first16, v4i &last16) {
-    uint32_t out[8];
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        const uint32_t p = (uint32_t)packed[e];
-        const uint32_t even = (p << 4) & 0xF0F0F0F0u, odd = p & 0xF0F0F0F0u;  // codes 0, 2, 4, 6 / 1, 3, 5, 7 of this dword, times 16
-        out[2 * e] = __builtin_amdgcn_perm(odd, even, 0x05010400u);      // even.b0, odd.b0, even.b1, odd.b1
-        out[2 * e + 1] = __builtin_amdgcn_perm(odd, even, 0x07030602u);  // even.b2, odd.b2, even.b3, odd.b3
-    }
-    first16 = v4i{(int)out[0], (int)out[1], (int)out[2], (int)out[3]};
-    last16 = v4i{(int)out[4], (int)out[5], (int)out[6], (int)out[7]};
-}
-
-// f32(fp16 half of `pair`) * m in one instruction: v_fma_mix_f32 converts the selected half exactly,
-// multiplies and rounds once to fp32 - the same value as a conversion followed by v_mul_f32.
-template <bool HIGH>
-__device__ __forceinline__ float half_times(int pair, float m) {
-    float d;
-    if constexpr (HIGH)
-        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(m));
-    else
-        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(m));
-    return d;
-}
-
-template <bool BITS4, bool OFFSET>
-__device__ __forceinline__ int code_of_smoothed(float v, float inv_s, int z) {
-    return clip_code<BITS4, OFFSET>(cvt_i32_f32(__builtin_rintf(v * inv_s)), z);
-}
-
-// Eight fp16 values (one 16-byte load) -> eight int8 codes (BITS4: 4-bit codes times 16).
-template <bool BITS4, bool OFFSET>
-__device__ __forceinline__ u32x2 quantize_8(v4i raw, const float (&im)[8], float inv_s, int z) {
-    int q[8];
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        const int word = raw[e];  // (a bit_cast applied directly to a vector element reads element 0 with this compiler)
-        q[2 * e] = code_of_smoothed<BITS4, OFFSET>(half_times<false>(word, im[2 * e]), inv_s, z);
-        q[2 * e + 1] = code_of_smoothed<BITS4, OFFSET>(half_times<true>(word, im[2 * e + 1]), inv_s, z);
-    }
-    u32x2 out = {pack4(q[0], q[1], q[2], q[3]), pack4(q[4], q[5], q[6], q[7])};
-    if constexpr (BITS4) out = u32x2{times16(out[0]), times16(out[1])};
-    return out;
+    const u32x2 a = ptq4vm::mfma::expand_nibbles_in_order((uint32_t)packed[0]), b = ptq4vm::mfma::expand_nibbles_in_order((uint32_t)packed[1]);
+    const u32x2 c = ptq4vm::mfma::expand_nibbles_in_order((uint32_t)packed[2]), d = ptq4vm::mfma::expand_nibbles_in_order((uint32_t)packed[3]);
+    first16 = v4i{(int)a[0], (int)a[1], (int)b[0], (int)b[1]};
+    last16 = v4i{(int)c[0], (int)c[1], (int)d[0], (int)d[1]};
 }
 
 // ------------------------------------------------------------------------------------------
@@ -880,8 +828,35 @@ int launch_stream_aligned(const LinearArgs &a, int xa, int wa, const StreamLayou
     return ptq4vm::check_launch("linear_stream_smallk");
 }
 
-// Form of a fused launch: 8-bit codes, 4-bit codes (packed weight), or 8-bit codes with a per-token zero offset.
-enum class Form { kInt8 = 0, kBits4 = 1, kOffset = 2 };
+template <Form FORM, int RB, int W, bool ALIGNED>
+int launch_split(LinearArgs a, hipStream_t stream) {
+    using Kernel = void (*)(const LinearArgs);
+    static const Kernel kernels[8] = {  // by the number of 16-channel blocks of a tile
+        pts_linear_split<FORM, 1, RB, W, ALIGNED>, pts_linear_split<FORM, 2, RB, W, ALIGNED>, pts_linear_split<FORM, 3, RB, W, ALIGNED>,
+        pts_linear_split<FORM, 4, RB, W, ALIGNED>, pts_linear_split<FORM, 5, RB, W, ALIGNED>, pts_linear_split<FORM, 6, RB, W, ALIGNED>,
+        pts_linear_split<FORM, 7, RB, W, ALIGNED>, pts_linear_split<FORM, 8, RB, W, ALIGNED>};
+    const int64_t nb = a.N >= 128 ? 8 : ptq4vm::ceil_div(a.N, 16);
+    const int64_t tiles_r = ptq4vm::ceil_div(a.M, 16 * RB), tiles_o = ptq4vm::ceil_div(a.N, 16 * nb);
+    if (tiles_r * tiles_o > 0x3fffffffLL) return PTQ4VM_ERR_SHAPE;
+    a.tiles_r = (int)tiles_r;
+    a.tiles_o = (int)tiles_o;
+    kernels[nb - 1]<<<dim3((unsigned)(ptq4vm::ceil_div(tiles_r * tiles_o, kXcds) * kXcds)), dim3(64 * W), 0, stream>>>(a);
+    return ptq4vm::check_launch("pts_linear_split");
+}
+// Eight wavefronts on 16 rows while that gives every CU at most one workgroup, four on 32 rows beyond (us, 8 x 16 / 4 x 32
+// rows: 2364 x 768 -> 56 5.6 / 8.3, 4137 x 1536 -> 80 13.5 / 12.9, 12608 x 768 -> 56 13.3 / 10.8).
+template <Form FORM, bool ALIGNED>
+int launch_split_rows(const LinearArgs &a, hipStream_t stream) {
+    return ptq4vm::ceil_div(a.M, 16) * ptq4vm::ceil_div(a.N, 128) <= 256 ? launch_split<FORM, 1, 8, ALIGNED>(a, stream)
+                                                                         : launch_split<FORM, 2, 4, ALIGNED>(a, stream);
+}
+int launch_split_form(const LinearArgs &a, hipStream_t stream, Form form) {
+    switch (form) {
+        case Form::kInt8: return launch_split_rows<Form::kInt8, true>(a, stream);
+        case Form::kBits4: return launch_split_rows<Form::kBits4, true>(a, stream);
+        default: return launch_split_rows<Form::kOffset, true>(a, stream);
+    }
+}
 
 int launch_wres(const LinearArgs &a, hipStream_t stream, Form form) {
     const FusedLayout lay = fused_layout((int)a.N, (int)a.k_bytes, (int)a.L, form == Form::kOffset);
@@ -954,14 +929,20 @@ int dispatch(LinearArgs a, hipStream_t stream, Form form = Form::kInt8) {
                          a.M >= kFusedMinRows && a.L <= 65536 &&
                          (!a.xq_out || (ptq4vm::aligned_to(a.xq_out, 8) && a.ldxq_out % 8 == 0)) &&
                          fused_layout((int)a.N, (int)a.k_bytes, (int)a.L, form == Form::kOffset).total <= kLdsBytes;
-    if (wres_ok) return launch_wres(a, stream, form);
+    // up to about 20 000 rows a unit per wavefront leaves most of the chip idle: the reduction is split instead
+    // (us, split / resident: 12608 x 1536 -> 80 19.3 / 27.7, 25216 x 768 -> 56 19.1 / 17.7)
+    if (wres_ok) return a.M < 20480 ? launch_split_form(a, stream, form) : launch_wres(a, stream, form);
     if (a.k_bytes <= 128) {
         const int rc = launch_stream_smallk(a, true, stream, form == Form::kBits4, form == Form::kOffset);
         if (rc <= 0) return rc;
     }
     if (form != Form::kInt8) return PTQ4VM_ERR_SHAPE;
-    if (a.N > 64) return launch_generic<256, 128, 2, 2>(a, xa, wa, stream);
-    return launch_generic<256, 64, 4, 1>(a, xa, wa, stream);
+    // Narrow outputs, or so few rows that the tiled kernel below has no more than a few workgroups a CU
+    // (us, split / tiled: 19031 x 1000 -> 80 24 / 144, 4137 x 333 -> 128 14 / 123, 197 x 1536 -> 80 8 / 164).
+    if (a.N <= 128 || a.M <= 2048)
+        return small && xa == 16 && wa == 16 && a.k_bytes % 64 == 0 ? launch_split_rows<Form::kInt8, true>(a, stream)
+                                                           : launch_split_rows<Form::kInt8, false>(a, stream);
+    return launch_generic<256, 128, 2, 2>(a, xa, wa, stream);
 }
 
 }  // namespace
