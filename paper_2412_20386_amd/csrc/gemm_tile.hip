@@ -40,6 +40,9 @@ int launch_splitk(LinearArgs a, hipStream_t stream) {
 //   64 x 128 against 64 x 64, 384 tiles:     3152 x 384 -> 1536 [600] 7.2 / 7.9;       1576 x 384 -> 1536 [300] 5.5 / 5.0
 //   64 x 64 against 32 x 64, 190 tiles:      197 x 768 -> 3072 [192] 4.8 / 5.9;        197 x 1536 -> 768 [48] 5.5 / 5.0
 //   split reduction, 256 blocks of 16 x 16:  197 x 1536 -> 80 [65] 3.8 / 4.8 (32 x 64); 659 x 256 -> 232 [630] 3.3 / 2.9
+// 128 x 128 tiles: three 64-byte stages are 48 KiB, a third workgroup per CU, and waste no half slab; over a long reduction
+// twice the barriers cost more (12608 x 192 -> 768 9.0 / 10.8, 6304 x 384 -> 1536 11.2 / 11.8, 50240 x 768 -> 384 32.0 / 33.4,
+// but 12608 x 1536 -> 768 25.0 / 24.6).
 // A tile that pads the matrix by a third more than the best one is passed over.  Two or three ring stages of 64 x 64
 // tiles: three hold more of a long reduction in flight while few tiles are resident anyway (6304 x 1536 -> 80 [198]
 // 6.2 / 8.0), two leave room for a fourth workgroup per CU (788 x 768 -> 3072 [624] 7.3 / 7.9).
@@ -56,7 +59,8 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         auto padded = [&](int br, int bo) { return tiles(a, br, bo) * br * bo; };
         const int64_t most = padded(32, 64) * 4 / 3;
         if (tiles(a, 128, 256) >= 800 && padded(128, 256) <= most) return launch<Path, 128, 256, 2, 4, 64, 3, true>(a, stream);
-        if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most) return launch<Path, 128, 128, 2, 4, 128, 2, true>(a, stream);
+        if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most)
+            return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 4, 64, 3, true>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, true>(a, stream);
         if (tiles(a, 64, 128) >= 384 && padded(64, 128) <= most) return launch<Path, 64, 128, 2, 2, 128, 2, true>(a, stream);
         if (tiles(a, 64, 64) > 512) return launch<Path, 64, 64, 2, 2, 128, 2, true>(a, stream);
         if (tiles(a, 64, 64) >= 190) return launch<Path, 64, 64, 2, 2, 128, 3, true>(a, stream);
