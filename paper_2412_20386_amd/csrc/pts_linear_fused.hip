@@ -11,7 +11,7 @@
 // quantizer is cheaper.  Kernels:
 //   pts_linear_wres     N <= 128 over many rows (x_proj): weight resident in LDS, every fp16
 //                       activation read once from HBM in whole 128-byte lines, quantized once.
-//   pts_linear_split    the same over up to 20 000 rows, and few rows of any width: the reduction spread over a
+//   pts_linear_split    the same below 4096 rows or at any alignment, and few rows of any width: the reduction spread over a
 //                       workgroup's wavefronts (pts_linear_split.hpp).
 //   pts_linear_generic  every other shape: the register-staged tiled kernel with the quantizer in
 //                       its loader (correct everywhere, re-quantizes per tile column).
@@ -65,6 +65,7 @@ constexpr int kFusedWaves = 16 / kFusedRB;
 constexpr int kFusedPatchRows = 8 * kFusedRB;   // result rows staged per pass of the epilogue
 constexpr int kFusedMaxBlocks = 8;   // 16-channel blocks: N <= 128
 constexpr int kLdsBytes = 160 * 1024;
+constexpr int64_t kFusedMinRowsResident = 4096;  // from here the weight-resident kernel, below it the split reduction
 constexpr int64_t kFusedMinRows = 2048;   // below this the one-off table copies per workgroup do not pay (4 k rows: 11 us against 48 us for the tiled fused kernel at 384 -> 44)
 
 struct FusedLayout {
@@ -164,18 +165,18 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
     int unit_rows = 0, next_rows = 0;
     bool have = item(0, unit_r0, unit_rows);
 
-    v4i raw[D][NL];
+    v4i raw[D * NL];  // load i of the k-step d ahead of the one at hand: slot d * (loads per k-step) + i
     const char *xrow[NL];
     uint32_t tok[NL];
     // 8-row groups (load instructions per k-step) of the unit being loaded: all NL, or half of them for a short
     // unit, whose further groups are neither loaded nor quantized.  The k loop is compiled once for either count
     // (branches inside it would cost the counted waits on the loads).
+    // A short unit keeps twice the k-steps in flight in the same registers, where K has a whole number of such rounds: below
+    // 32 000 rows all units are short and the chain of loads is the run time (12608 x 1536 -> 80 15.0 -> 13.1 us,
+    // 4137 x 1536 -> 80 14.1 -> 12.2 us at 48 rows a workgroup).
     int groups = 0;
-    auto load_x = [&](int d, int ks) {  // outside the k loop only
-#pragma unroll
-        for (int i = 0; i < NL; i++)
-            if (i < groups) raw[d][i] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + ks * 128));
-    };
+    constexpr int DS = 2 * D;  // k-steps in flight of a short unit
+    const bool deep = n_ksteps % DS == 0;
     auto start_unit = [&](int64_t r0, int nrows) {  // first D k-steps of the unit's rows
         groups = nrows > 8 * (NL / 2) ? NL : NL / 2;
 #pragma unroll
@@ -184,8 +185,21 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
             xrow[i] = p.x + r * p.ldx_bytes + pc * 16;
             tok[i] = (uint32_t)r % (uint32_t)L;
         }
+        auto fetch = [&](int d, int i, int slot) {
+            raw[slot] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + d * 128));
+        };
+        if (groups == NL) {
 #pragma unroll
-        for (int d = 0; d < D; d++) load_x(d, d);
+            for (int d = 0; d < D; d++)
+#pragma unroll
+                for (int i = 0; i < NL; i++) fetch(d, i, d * NL + i);
+        } else {
+#pragma unroll
+            for (int d = 0; d < DS; d++)
+#pragma unroll
+                for (int i = 0; i < NL / 2; i++)
+                    if (d < D || deep) fetch(d, i, d * (NL / 2) + i);
+        }
     };
     if (have) start_unit(unit_r0, unit_rows);
 
@@ -260,12 +274,12 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
         const int64_t r_end = min(p.M, unit_r0 + unit_rows);  // rows at or beyond it are not this unit's
         const int unit_groups = groups;                        // (`groups` moves on to the next unit before the epilogue)
 
-        auto k_loop = [&](auto g_tag) {
-            constexpr int G = decltype(g_tag)::value;
+        auto k_loop = [&](auto g_tag, auto depth_tag) {
+            constexpr int G = decltype(g_tag)::value, DEPTH = decltype(depth_tag)::value;
             auto load_g = [&](int d, int ks) {
 #pragma unroll
                 for (int i = 0; i < G; i++)
-                    raw[d][i] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + ks * 128));
+                    raw[d * G + i] = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + ks * 128));
             };
             auto compute = [&](int d, int ks) {
                 float im[8];
@@ -275,7 +289,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
                 for (int e = 0; e < 4; e++) im[e] = im_lo[e], im[4 + e] = im_hi[e];
 #pragma unroll
                 for (int i = 0; i < G; i++) {  // tile rows of further groups keep stale codes: results of rows nobody stores
-                    const u32x2 codes = quantize_8<BITS4, OFFSET>(raw[d][i], im, inv_s[i], zq[i]);
+                    const u32x2 codes = quantize_8<BITS4, OFFSET>(raw[d * G + i], im, inv_s[i], zq[i]);
                     *reinterpret_cast<u32x2 *>(tile + tile_wr[i]) = codes;
                     if (DUMP && p.xq_out) {  // parity aid: the codes that the MFMA will see (4-bit path: divided by 16 again)
                         const int64_t r = r_unit + i * 8 + rr;
@@ -309,24 +323,26 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
             // left alone the scheduler sinks all loads of a group to its end and the wavefront then
             // waits for the whole group before every pass.
             int ks0 = 0;
-            for (; ks0 + D < n_ksteps; ks0 += D) {  // every register slot is refilled (K is a multiple of 64 D)
+            for (; ks0 + DEPTH < n_ksteps; ks0 += DEPTH) {  // every register slot is refilled (K is a multiple of 64 DEPTH)
 #pragma unroll
-                for (int d = 0; d < D; d++) {
+                for (int d = 0; d < DEPTH; d++) {
                     compute(d, ks0 + d);
-                    load_g(d, ks0 + d + D);
+                    load_g(d, ks0 + d + DEPTH);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
 #pragma unroll
-            for (int d = 0; d < D; d++) {  // last group: drain
+            for (int d = 0; d < DEPTH; d++) {  // last group: drain
                 compute(d, ks0 + d);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         if (unit_groups == NL)
-            k_loop(std::integral_constant<int, NL>{});
+            k_loop(std::integral_constant<int, NL>{}, std::integral_constant<int, D>{});
+        else if (deep)
+            k_loop(std::integral_constant<int, NL / 2>{}, std::integral_constant<int, DS>{});
         else
-            k_loop(std::integral_constant<int, NL / 2>{});
+            k_loop(std::integral_constant<int, NL / 2>{}, std::integral_constant<int, D>{});
 
         // Accumulator register v of block (j, i): token row 16 j + (lane mod 16), channel 16 i + 4 (lane / 16) + v.
         float rs[RB];
@@ -850,11 +866,12 @@ int launch_split_rows(const LinearArgs &a, hipStream_t stream) {
     return ptq4vm::ceil_div(a.M, 16) * ptq4vm::ceil_div(a.N, 128) <= 256 ? launch_split<FORM, 1, 8, ALIGNED>(a, stream)
                                                                          : launch_split<FORM, 2, 4, ALIGNED>(a, stream);
 }
+// The shapes of the resident kernel below its rows (N <= 128, fewer than 4096 rows): 16 rows a workgroup always.
 int launch_split_form(const LinearArgs &a, hipStream_t stream, Form form) {
     switch (form) {
-        case Form::kInt8: return launch_split_rows<Form::kInt8, true>(a, stream);
-        case Form::kBits4: return launch_split_rows<Form::kBits4, true>(a, stream);
-        default: return launch_split_rows<Form::kOffset, true>(a, stream);
+        case Form::kInt8: return launch_split<Form::kInt8, 1, 8, true>(a, stream);
+        case Form::kBits4: return launch_split<Form::kBits4, 1, 8, true>(a, stream);
+        default: return launch_split<Form::kOffset, 1, 8, true>(a, stream);
     }
 }
 
@@ -865,8 +882,13 @@ int launch_wres(const LinearArgs &a, hipStream_t stream, Form form) {
     if (err == hipSuccess) err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (err != hipSuccess) return ptq4vm::record_hip_error(err, "hipDeviceGetAttribute(multiprocessor count)");
     if (cus < 1) cus = 1;
-    const int64_t units = ptq4vm::ceil_div(a.M, 16 * kFusedRB);
-    int64_t wgs = ptq4vm::ceil_div(units, kFusedWaves);
+    // Rows a workgroup takes at least.  Below some 20 000 rows the run time is a wavefront's serial chain over the reduction,
+    // and spreading the rows over all CUs costs nothing but the tables once more (us, 256 / 64 / 32 rows: 4137 x 1536 -> 80
+    // 26.9 / 12.3 / 10.3, 12608 x 1536 -> 80 27.3 / 13.3 / 13.0).  Where the activations keep the memory busy fewer, fuller
+    // workgroups do as well and load fewer tables (a Vim-S block over 25216 rows, 256 / 128 / 32 rows: 92.3 / 88.7 / 91.4 us;
+    // a Vim-B block over 50432 rows: 317.6 / 319.1 / 319.0).
+    const int64_t min_rows = a.M < 20480 ? 32 : (a.M < 40960 ? 128 : 256);
+    int64_t wgs = ptq4vm::ceil_div(a.M, min_rows);
     if (wgs > cus) wgs = cus;  // one workgroup per CU: the resident tables take most of its LDS
     using Kernel = void (*)(const LinearArgs);
     // four k-steps in flight need too many registers next to the accumulators of 7 or 8 channel blocks
@@ -929,9 +951,10 @@ int dispatch(LinearArgs a, hipStream_t stream, Form form = Form::kInt8) {
                          a.M >= kFusedMinRows && a.L <= 65536 &&
                          (!a.xq_out || (ptq4vm::aligned_to(a.xq_out, 8) && a.ldxq_out % 8 == 0)) &&
                          fused_layout((int)a.N, (int)a.k_bytes, (int)a.L, form == Form::kOffset).total <= kLdsBytes;
-    // up to about 20 000 rows a unit per wavefront leaves most of the chip idle: the reduction is split instead
-    // (us, split / resident: 12608 x 1536 -> 80 19.3 / 27.7, 25216 x 768 -> 56 19.1 / 17.7)
-    if (wres_ok) return a.M < 20480 ? launch_split_form(a, stream, form) : launch_wres(a, stream, form);
+    // with fewer rows the resident kernel leaves CUs idle and the reduction is split over a workgroup instead
+    // (us, split / resident: 4137 x 384 -> 44 6.3 / 5.8, 4137 x 1536 -> 80 14.1 / 10.3, 12608 x 1536 -> 80 19.7 / 13.0,
+    // 25216 x 768 -> 56 19.4 / 12.4)
+    if (wres_ok) return a.M < kFusedMinRowsResident ? launch_split_form(a, stream, form) : launch_wres(a, stream, form);
     if (a.k_bytes <= 128) {
         const int rc = launch_stream_smallk(a, true, stream, form == Form::kBits4, form == Form::kOffset);
         if (rc <= 0) return rc;

@@ -86,8 +86,8 @@ struct FusedPath<Form::kOffset> {
 // end.  No barrier before that: where the weight-resident kernel gives a wavefront the whole reduction of its rows, this
 // one spreads it over the workgroup, so that a few thousand rows fill the chip.  The price is the weight read once per
 // 16 RB rows (from L2, through the CU's one 64-byte-per-clock load path, which is what bounds long reductions) instead of
-// once per CU.  Measured (us, this / weight-resident): 4137 x 384 -> 44 5.0 / 10.4, 6304 x 768 -> 56 7.2 / 16.2,
-// 12608 x 1536 -> 80 19.3 / 27.7, 25216 x 1536 -> 80 34.0 / 30.5, 50432 x 768 -> 56 29.9 / 19.1.
+// once per CU (us, this / weight-resident: 4137 x 1536 -> 80 14.1 / 10.3, 25216 x 768 -> 56 19.4 / 12.4), so it serves what
+// that kernel cannot: fewer rows than fill its CUs, any alignment, tables beyond the LDS.
 // ALIGNED: K % 64 == 0, 16-byte aligned rows of x and of the weight.  Otherwise any K and pitch: weight bytes beyond K
 // read as zero, so the codes there do not matter.
 // ------------------------------------------------------------------------------------------

@@ -1,5 +1,5 @@
 """The fused quantizer + linear on both sides of its kernels' lines (split reduction on 16 or 32 rows a workgroup, weight
-resident from 20 480 rows), in the three forms: the same bits as the two-launch form, whose kernels have their own tests."""
+resident from 4096 rows), in the three forms: the same bits as the two-launch form, whose kernels have their own tests."""
 import pytest
 import torch
 
@@ -13,7 +13,9 @@ bits = lambda t: t.view(torch.int16)
 
 @pytest.mark.parametrize("B,L,K,N,pad", [
     (21, 98, 64, 1, 0), (13, 163, 448, 128, 3), (16, 255, 1536, 80, 0),   # at most one workgroup of 16 rows per CU
-    (17, 241, 320, 97, 0), (101, 197, 768, 56, 8),                       # 32 rows
+    (17, 241, 320, 97, 0), (101, 197, 768, 56, 8),                       # few resident rows a CU
+    (21, 195, 256, 72, 0), (32, 128, 256, 72, 4),                        # the line between split and resident
+    (83, 57, 384, 128, 0), (61, 89, 1024, 40, 0), (42, 197, 576, 64, 0),  # 8-row units: 2, 4 and 1 k-steps in flight
     (104, 197, 320, 80, 0), (104, 199, 192, 33, 1), (211, 98, 1088, 16, 0),  # resident: odd step counts, ragged rows
 ])
 def test_fused_forms_aligned(B, L, K, N, pad):
