@@ -104,3 +104,21 @@ def test_tile_kernels_all_operand_types(M, K, N, pad):
         err = (y.double() - y64).abs()
         assert bool((err <= (K + 2) * 2.0 ** -24 * (mag + 4.0) + 2.0 ** -10 * y64.abs() + 2.0 ** -24).all())
         assert bool((buf[:, N:] == 777.0).all())
+
+
+@pytest.mark.parametrize("K,N,B,L", [(384, 3072, 124, 199), (768, 3072, 128, 197), (768, 1536, 190, 260)])
+def test_weights_in_registers_against_smaller_launches(K, N, B, L):
+    """Around nine 128 x 256 units a CU the weight-in-registers kernel takes over: the same bits as two launches of half the
+    images, which stay on the persistent or tile kernels (ragged and whole units)."""
+    print(f"wreg line B={B} L={L} K={K} N={N}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(77 + K + N)
+    M = B * L
+    x = torch.randint(-127, 128, (M, K), dtype=torch.int8, device=DEV, generator=g)
+    w = torch.randint(-127, 128, (N, K), dtype=torch.int8, device=DEV, generator=g)
+    s_tok = torch.rand(L, device=DEV, generator=g) * 0.02 + 0.001
+    s_w = torch.rand(N, device=DEV, generator=g) * 0.002 + 0.0001
+    for bias in (None, torch.randn(N, device=DEV, generator=g).half()):
+        y = ptq.w8a8_linear(x, w, s_tok, s_w, bias, B, L)
+        half = M // 2
+        parts = [ptq.w8a8_linear(p, w, s_tok, s_w, bias, B // 2, L) for p in (x[:half], x[half:])]
+        assert torch.equal(torch.cat(parts).view(torch.int16), y.view(torch.int16))
