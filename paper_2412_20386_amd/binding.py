@@ -174,6 +174,15 @@ def _matrix(t: torch.Tensor, dtype, name: str) -> Tuple[int, int, int]:
     return t.shape[0], t.shape[1], (t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1]))
 
 
+def _written(t: torch.Tensor, dtype, rows: int, cols: int, name: str) -> int:
+    """Pitch of a matrix that the library writes rows x cols elements of.  A larger one is taken too; the C boundary sees a
+    pointer and a pitch only, so a smaller one has to be refused here."""
+    r, c, ld = _matrix(t, dtype, name)
+    if r < rows or c < cols:
+        raise ValueError(f"{name}: expected at least {rows} x {cols} elements, got {r} x {c}")
+    return ld
+
+
 def _vector(t: Optional[torch.Tensor], dtype, n: int, name: str, optional=False):
     if t is None:
         if optional:
@@ -189,7 +198,7 @@ def fold_smoothing(w: torch.Tensor, m: torch.Tensor, wq: Optional[torch.Tensor] 
     _vector(m, torch.float32, K, "m")
     if wq is None:
         wq = torch.empty((N, K), dtype=torch.int8, device=w.device)
-    _, _, ldwq = _matrix(wq, torch.int8, "wq")
+    ldwq = _written(wq, torch.int8, N, K, "wq")
     s_w = torch.empty(N, dtype=torch.float32, device=w.device)
     inv_m = torch.empty(K, dtype=torch.float32, device=w.device)
     check(load().ptq4vm_fold_smoothing(_ptr(w), _ptr(m), _ptr(wq), _ptr(s_w), _ptr(inv_m), N, K, ldw, ldwq,
@@ -211,7 +220,7 @@ def fold_smoothing_w4(w: torch.Tensor, m: torch.Tensor, wq4: Optional[torch.Tens
     _vector(m, torch.float32, K, "m")
     if wq4 is None:
         wq4 = torch.empty((N, K // 2), dtype=torch.uint8, device=w.device)
-    _, _, ldwq = _matrix(wq4, torch.uint8, "wq4")
+    ldwq = _written(wq4, torch.uint8, N, K // 2, "wq4")
     s_w = torch.empty(N, dtype=torch.float32, device=w.device)
     inv_m = torch.empty(K, dtype=torch.float32, device=w.device)
     check(load().ptq4vm_fold_smoothing_w4(_ptr(w), _ptr(m), _ptr(wq4), _ptr(s_w), _ptr(inv_m), N, K, ldw, ldwq,

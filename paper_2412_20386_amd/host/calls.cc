@@ -90,6 +90,16 @@ Matrix matrix(PyObject *o, at::ScalarType dtype, const char *name) {
     return {rows, cols, rows > 1 ? pitch : std::max(pitch, cols), t->data_ptr()};
 }
 
+// A matrix that the kernels write rows x cols elements of.  A larger one (a buffer of the largest batch) is taken too; the
+// C boundary sees a pointer and a pitch only, so a smaller one has to be refused here.
+Matrix written(PyObject *o, at::ScalarType dtype, int64_t rows, int64_t cols, const char *name) {
+    const Matrix m = matrix(o, dtype, name);
+    if (m.rows < rows || m.cols < cols)
+        raise(PyExc_ValueError, std::string(name) + ": expected at least " + std::to_string(rows) + " x " + std::to_string(cols) + " elements, got " +
+                                    std::to_string(m.rows) + " x " + std::to_string(m.cols));
+    return m;
+}
+
 void *vector(PyObject *o, at::ScalarType dtype, int64_t n, const char *name, bool optional = false) {
     if (!given(o)) {
         if (optional) return nullptr;
@@ -183,7 +193,7 @@ PyObject *quantize_pts(Args a) {  // x inv_m s_tok B L xq
     same_rows(x.rows, B, L);
     void *inv_m = vector(a[1], at::kFloat, x.cols, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok");
     Owned out(output(a[5], {x.rows, x.cols}, at::kChar, a[0]));
-    const Matrix xq = matrix(out.o, at::kChar, "xq");
+    const Matrix xq = written(out.o, at::kChar, x.rows, x.cols, "xq");
     launch([&](void *s) { return entry.quantize_pts(x.data, floats(inv_m), floats(s_tok), static_cast<int8_t *>(xq.data), B, L, x.cols, x.ld, xq.ld, s); });
     return out.release();
 }
@@ -195,7 +205,7 @@ PyObject *quantize_pts_offset(Args a) {  // x inv_m s_tok z_tok B L xq
     void *inv_m = vector(a[1], at::kFloat, x.cols, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *z_tok = vector(a[3], at::kInt, L, "z_tok");
     Owned out(output(a[6], {x.rows, x.cols}, at::kChar, a[0]));
-    const Matrix xq = matrix(out.o, at::kChar, "xq");
+    const Matrix xq = written(out.o, at::kChar, x.rows, x.cols, "xq");
     launch([&](void *s) { return entry.quantize_pts_offset(x.data, floats(inv_m), floats(s_tok), ints(z_tok), static_cast<int8_t *>(xq.data), B, L, x.cols,
                                     x.ld, xq.ld, s); });
     return out.release();
@@ -207,7 +217,7 @@ PyObject *quantize_pts_a4(Args a) {  // x inv_m s_tok B L xq4
     same_rows(x.rows, B, L);
     void *inv_m = vector(a[1], at::kFloat, x.cols, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok");
     Owned out(output(a[5], {x.rows, x.cols / 2}, at::kByte, a[0]));
-    const Matrix xq = matrix(out.o, at::kByte, "xq4");
+    const Matrix xq = written(out.o, at::kByte, x.rows, x.cols / 2, "xq4");
     launch([&](void *s) { return entry.quantize_pts_a4(x.data, floats(inv_m), floats(s_tok), static_cast<uint8_t *>(xq.data), B, L, x.cols, x.ld, xq.ld, s); });
     return out.release();
 }
@@ -228,7 +238,7 @@ PyObject *quantize_dynamic(Args a) {  // x inv_m xq s_row
     const Matrix x = matrix(a[0], at::kHalf, "x");
     void *inv_m = vector(a[1], at::kFloat, x.cols, "inv_m", true);
     Owned out(output(a[2], {x.rows, x.cols}, at::kChar, a[0]));
-    const Matrix xq = matrix(out.o, at::kChar, "xq");
+    const Matrix xq = written(out.o, at::kChar, x.rows, x.cols, "xq");
     Owned steps(output(a[3], {x.rows}, at::kFloat, a[0]));
     void *s_row = vector(steps.o, at::kFloat, x.rows, "s_row");
     launch([&](void *s) { return entry.quantize_dynamic(x.data, floats(inv_m), static_cast<int8_t *>(xq.data), static_cast<float *>(s_row), x.rows, x.cols, x.ld,
@@ -244,7 +254,7 @@ PyObject *w8a8_linear(Args a) {  // xq wq s_tok s_w bias B L y acc_out
     same_shape(xq.cols == wq.cols && M == B * L);
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *s_w = vector(a[3], at::kFloat, N, "s_w"), *bias = vector(a[4], at::kHalf, N, "bias", true);
     Owned out(output(a[7], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[8], M, N);
     launch([&](void *s) { return entry.w8a8_linear(codes(xq), codes(wq), floats(s_tok), floats(s_w), bias, y.data, static_cast<int32_t *>(acc), B, L, xq.cols, N,
                             xq.ld, wq.ld, y.ld, s); });
@@ -259,7 +269,7 @@ PyObject *w8a8_linear_offset(Args a) {  // xq wq s_tok z_tok rowsum s_w bias B L
          *rowsum = vector(a[4], at::kInt, N, "rowsum"), *s_w = vector(a[5], at::kFloat, N, "s_w"),
          *bias = vector(a[6], at::kHalf, N, "bias", true);
     Owned out(output(a[9], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[10], M, N);
     launch([&](void *s) { return entry.w8a8_linear_offset(codes(xq), codes(wq), floats(s_tok), ints(z_tok), ints(rowsum), floats(s_w), bias, y.data,
                                    static_cast<int32_t *>(acc), B, L, xq.cols, N, xq.ld, wq.ld, y.ld, s); });
@@ -272,7 +282,7 @@ PyObject *w4a4_linear(Args a) {  // xq4 wq4 s_tok s_w bias B L y acc_out
     same_shape(xq.cols == wq.cols && M == B * L);
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *s_w = vector(a[3], at::kFloat, N, "s_w"), *bias = vector(a[4], at::kHalf, N, "bias", true);
     Owned out(output(a[7], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[8], M, N);
     launch([&](void *s) { return entry.w4a4_linear(bytes(xq.data), bytes(wq.data), floats(s_tok), floats(s_w), bias, y.data, static_cast<int32_t *>(acc), B, L,
                             2 * xq.cols, N, xq.ld, wq.ld, y.ld, s); });
@@ -288,7 +298,7 @@ PyObject *w4a4_linear_e2m3(Args a) {  // xq6 wq6 s_tok s_w bias B L K y acc_out
     const Container wq = container(a[1], N, K, "wq6");
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *s_w = vector(a[3], at::kFloat, N, "s_w"), *bias = vector(a[4], at::kHalf, N, "bias", true);
     Owned out(output(a[8], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[9], M, N);
     launch([&](void *s) { return entry.w4a4_linear_e2m3(bytes(xq.data), bytes(wq.data), floats(s_tok), floats(s_w), bias, y.data, static_cast<int32_t *>(acc), B, L,
                                  K, N, xq.pitch, wq.pitch, y.ld, s); });
@@ -313,7 +323,7 @@ PyObject *w8a8_linear_fused(Args a) {  // x inv_m s_tok wq s_w bias B L y acc_ou
     void *inv_m = vector(a[1], at::kFloat, K, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *s_w = vector(a[4], at::kFloat, N, "s_w"), *bias = vector(a[5], at::kHalf, N, "bias", true);
     Owned out(output(a[8], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[9], M, N);
     const CodesOut xq = codes_out(a[10], M, K);
     launch([&](void *s) { return entry.w8a8_linear_fused(x.data, floats(inv_m), floats(s_tok), codes(wq), floats(s_w), bias, y.data, static_cast<int32_t *>(acc),
@@ -329,7 +339,7 @@ PyObject *w8a8_linear_offset_fused(Args a) {  // x inv_m s_tok z_tok wq rowsum s
          *z_tok = vector(a[3], at::kInt, L, "z_tok"), *rowsum = vector(a[5], at::kInt, N, "rowsum"),
          *s_w = vector(a[6], at::kFloat, N, "s_w"), *bias = vector(a[7], at::kHalf, N, "bias", true);
     Owned out(output(a[10], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[11], M, N);
     const CodesOut xq = codes_out(a[12], M, K);
     launch([&](void *s) { return entry.w8a8_linear_offset_fused(x.data, floats(inv_m), floats(s_tok), ints(z_tok), codes(wq), ints(rowsum), floats(s_w), bias, y.data,
@@ -344,7 +354,7 @@ PyObject *w4a4_linear_fused(Args a) {  // x inv_m s_tok wq4 s_w bias B L y acc_o
     void *inv_m = vector(a[1], at::kFloat, K, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *s_w = vector(a[4], at::kFloat, N, "s_w"), *bias = vector(a[5], at::kHalf, N, "bias", true);
     Owned out(output(a[8], {M, N}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, M, N, "y");
     void *acc = accumulators(a[9], M, N);
     const CodesOut xq = codes_out(a[10], M, K);
     launch([&](void *s) { return entry.w4a4_linear_fused(x.data, floats(inv_m), floats(s_tok), bytes(wq.data), floats(s_w), bias, y.data, static_cast<int32_t *>(acc),
@@ -357,7 +367,7 @@ PyObject *f16_linear(Args a) {  // x w bias y
     same_shape(x.cols == w.cols);
     void *bias = vector(a[2], at::kHalf, w.rows, "bias", true);
     Owned out(output(a[3], {x.rows, w.rows}, at::kHalf, a[0]));
-    const Matrix y = matrix(out.o, at::kHalf, "y");
+    const Matrix y = written(out.o, at::kHalf, x.rows, w.rows, "y");
     launch([&](void *s) { return entry.f16_linear(x.data, w.data, bias, y.data, x.rows, x.cols, w.rows, x.ld, w.ld, y.ld, s); });
     return out.release();
 }
