@@ -8,6 +8,7 @@
 #include <ATen/ATen.h>
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string>
@@ -412,6 +413,7 @@ void parse(const Signature &sig, Args args, Py_ssize_t nargs, PyObject *kwnames,
 
 template <PyObject *(*CALL)(Args), Signature *SIG>
 PyObject *call(PyObject *, Args args, Py_ssize_t nargs, PyObject *kwnames) {
+    HANDLE_TH_ERRORS
     try {
         PyObject *a[kMaxParams];
         parse(*SIG, args, nargs, kwnames, a);
@@ -419,10 +421,8 @@ PyObject *call(PyObject *, Args args, Py_ssize_t nargs, PyObject *kwnames) {
         return CALL(a);
     } catch (const Raised &) {
         return nullptr;
-    } catch (const std::exception &e) {  // an allocation that failed
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
     }
+    END_HANDLE_TH_ERRORS  // an output that could not be allocated keeps torch's exception (torch.OutOfMemoryError)
 }
 
 #define SIG(name, required, total, ...) Signature sig_##name = {#name, required, total, {__VA_ARGS__}, {}};

@@ -3,6 +3,7 @@ CUDA device, a shape and no storage), so a call whose arguments pass gets as far
 import pytest
 import torch
 from torch._subclasses.fake_tensor import FakeTensorMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 import paper_2412_20386_amd as ptq
 from paper_2412_20386_amd import build as hip_build
@@ -84,3 +85,26 @@ def test_wrong_types_and_arguments_are_refused(name):
         call(*args[:-1])
     with pytest.raises(TypeError):
         call(args[0].float(), *args[1:])
+
+
+class _NoMemory(TorchDispatchMode):
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        if func is torch.ops.aten.empty.memory_format:
+            raise torch.OutOfMemoryError("no room")
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("name", [n for n in calls() if not n.startswith("fold")])
+def test_an_output_that_does_not_fit_raises_torchs_exception(name):
+    args, _ = calls()[name]
+    with _NoMemory(), pytest.raises(torch.OutOfMemoryError, match="no room"):
+        getattr(ptq, name)(*args)
+
+
+@pytest.mark.gpu
+def test_an_output_larger_than_the_device():
+    x = torch.zeros((1 << 21, 8), dtype=torch.float16, device="cuda:0")
+    with pytest.raises(torch.OutOfMemoryError):  # 8 TiB of y
+        ptq.f16_linear(x, x, None)
+    with pytest.raises(torch.OutOfMemoryError):
+        ptq.w8a8_linear(x.char(), x.char(), torch.ones(1 << 21, device="cuda:0"), torch.ones(1 << 21, device="cuda:0"), None, 1, 1 << 21)
