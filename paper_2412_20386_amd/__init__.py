@@ -1,7 +1,9 @@
 """MI355X-native PTQ4VM quantized-linear path (arXiv 2412.20386).
 
 `binding` exposes the C ABI of libptq4vm.so (hand-written HIP for gfx950); `synth` draws the
-seeded Vim-shaped inputs; `build` compiles the library.  Nothing is loaded at import time.
+seeded Vim-shaped inputs; `build` compiles the library.  Importing the package loads the extension
+with the Python callables if it is there and fits (libptq4vm.so itself is loaded by the first call);
+if not, the import succeeds all the same and the first call says what is missing.
 """
 from . import binding, synth  # noqa: F401
 from .binding import (  # noqa: F401

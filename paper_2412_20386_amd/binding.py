@@ -12,7 +12,10 @@ and the validator go through ctypes here.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import sys
+import sysconfig
 from typing import Optional, Tuple
 
 import torch
@@ -20,7 +23,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # PTQ4VM_LIB: another build of the same sources (the sanitized host build of the test suite)
 LIB_PATH = os.environ.get("PTQ4VM_LIB") or os.path.join(_HERE, "libptq4vm.so")
-CALLS_PATH = os.path.join(_HERE, "_calls.so")
+CALLS_PATH = os.path.join(_HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 EXPORTS = (
     "ptq4vm_fold_smoothing",
@@ -63,8 +66,7 @@ def load() -> ctypes.CDLL:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise FileNotFoundError(
-            f"{LIB_PATH} not found: build it with `python -m paper_2412_20386_amd.build` "
-            "(there is no CPU or PyTorch fallback)")
+            f"{LIB_PATH} not found: " + _BUILD_HINT)
     lib = ctypes.CDLL(LIB_PATH)
     i64, vp, ci = ctypes.c_int64, ctypes.c_void_p, ctypes.c_int
     lib.ptq4vm_fold_smoothing.restype = ci
@@ -128,24 +130,38 @@ def _load_entries() -> None:
     _calls.bind({name: ctypes.cast(getattr(lib, "ptq4vm_" + name), ctypes.c_void_p).value for name in HOT_CALLS})
 
 
+_BUILD_HINT = "build it with `python -m paper_2412_20386_amd.build` (there is no CPU or PyTorch fallback)"
+
+
 def _bind_calls() -> None:
+    """Import the extension and put its callables in the place of the stand-ins, here and in the package."""
     if not os.path.exists(CALLS_PATH):
-        raise FileNotFoundError(f"{CALLS_PATH} not found: build it with `python -m paper_2412_20386_amd.build` "
-                                "(there is no CPU or PyTorch fallback)")
-    from . import _calls
+        raise FileNotFoundError(f"{CALLS_PATH} not found: " + _BUILD_HINT)
+    importlib.invalidate_caches()  # (it may have been built a moment ago)
+    try:
+        from . import _calls as extension
 
-    globals()["_calls"] = _calls
-    _calls.setup(_load_entries, check)
-    for name in HOT_CALLS:
-        globals()[name] = getattr(_calls, name)
+        callables = {name: getattr(extension, name) for name in HOT_CALLS}
+    except (ImportError, AttributeError) as err:  # built for another torch or Python, or from other sources
+        raise ImportError(f"{CALLS_PATH} does not fit this package ({err}): " + _BUILD_HINT) from err
+    extension.setup(_load_entries, check)
+    globals()["_calls"] = extension
+    for namespace in (globals(), vars(sys.modules[__package__])):
+        namespace.update({name: call for name, call in callables.items() if namespace.get(name, _stand_ins[name]) is _stand_ins[name]})
 
 
-def _bind_late(name: str):
-    """Stands in for a callable of an extension that was not there when the package was imported (the package builds it)."""
+def _stand_in(name: str):
+    """A callable that binds the extension when it is first called: importing the package needs no built extension, and the
+    package builds it."""
     def call(*args, **kwargs):
-        _bind_calls()
+        if globals()[name] is call:
+            _bind_calls()
         return globals()[name](*args, **kwargs)
+    call.__name__ = name
     return call
+
+
+_stand_ins = {_name: _stand_in(_name) for _name in HOT_CALLS}
 
 
 def status_string(status: int) -> str:
@@ -297,7 +313,8 @@ def validate_scales_static(s_tok: Optional[torch.Tensor], m: Optional[torch.Tens
                                                _ptr(counts), _stream()))
 
 
-if os.path.exists(CALLS_PATH):
+globals().update(_stand_ins)
+try:
     _bind_calls()
-else:
-    globals().update({_name: _bind_late(_name) for _name in HOT_CALLS})
+except (FileNotFoundError, ImportError):
+    pass  # raised again, with the reason, by the first call

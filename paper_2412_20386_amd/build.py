@@ -1,4 +1,4 @@
-"""Builds libptq4vm.so (HIP kernels + C ABI) for gfx950 and _calls.so (its Python callables), in-tree next to this file."""
+"""Builds libptq4vm.so (HIP kernels + C ABI) for gfx950 and _calls (its Python callables), in-tree next to this file."""
 from __future__ import annotations
 
 import concurrent.futures
@@ -7,6 +7,7 @@ import hashlib
 import os
 import shutil
 import subprocess
+import sys
 import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -72,33 +73,44 @@ def _compile_one(src: str, force: bool, extra=()):
 
 
 CALLS_SRC = os.path.join(_HERE, "host", "calls.cc")
-CALLS_PATH = os.path.join(_HERE, "_calls.so")
+CALLS_PATH = os.path.join(_HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def build_calls(force: bool = True) -> str:
-    """_calls.so: the hot path's Python callables, a host-only extension on torch's C++ API."""
+    """_calls: the hot path's Python callables, a host-only extension on torch's C++ API.  Built for one Python (the file
+    name says which) and one torch; force=False reuses a build of the same sources, flags, torch and Python."""
     import torch
 
-    deps = [CALLS_SRC, os.path.join(_HERE, "..", "include", "ptq4vm.h")]
-    if not force and os.path.exists(CALLS_PATH) and os.path.getmtime(CALLS_PATH) >= max(map(os.path.getmtime, deps)):
-        return CALLS_PATH
     root = os.path.dirname(torch.__file__)
+    flags = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+             *(f"-I{d}" for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                                  os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"])),
+             f"-L{os.path.join(root, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    h = hashlib.sha1(" ".join([torch.__version__, sys.version, *flags]).encode())
+    for path in (CALLS_SRC, os.path.join(_HERE, "..", "include", "ptq4vm.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    os.makedirs(OBJ_DIR, exist_ok=True)
+    built = os.path.join(OBJ_DIR, f"_calls.{h.hexdigest()[:16]}.so")
+    if force or not os.path.exists(built):
+        tmp = built + f".tmp{os.getpid()}"
+        res = subprocess.run(["g++", CALLS_SRC, *flags, "-o", tmp], capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed on " + CALLS_SRC + ":\n" + res.stdout + res.stderr)
+        os.replace(tmp, built)
+    for stale in glob.glob(os.path.join(OBJ_DIR, "_calls.*.so")):
+        if stale != built:
+            os.remove(stale)
     tmp = CALLS_PATH + f".tmp{os.getpid()}"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           *(f"-I{d}" for d in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"])),
-           CALLS_SRC, "-o", tmp, f"-L{os.path.join(root, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("g++ failed on " + CALLS_SRC + ":\n" + res.stdout + res.stderr)
+    shutil.copy(built, tmp)
     os.replace(tmp, CALLS_PATH)
     return CALLS_PATH
 
 
 def build(verbose: bool = False, force: bool = True) -> str:
     """Compile every source under csrc/ (one hipcc process per file, in parallel), link
-    libptq4vm.so and build _calls.so.  force=True recompiles everything; force=False reuses an object file whose source,
+    libptq4vm.so and build _calls.  force=True recompiles everything; force=False reuses an object file whose source,
     headers and flags are unchanged (a convenience while iterating on one kernel)."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
@@ -147,8 +159,6 @@ def sanitizer_runtime() -> str:
 
 
 if __name__ == "__main__":
-    import sys
-
     if "--sanitize" in sys.argv:
         print(build_sanitized())
     else:
