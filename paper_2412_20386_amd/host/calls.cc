@@ -178,8 +178,13 @@ const int8_t *codes(const Matrix &m) { return static_cast<const int8_t *>(m.data
 const uint8_t *bytes(void *p) { return static_cast<const uint8_t *>(p); }
 const int32_t *ints(void *p) { return static_cast<const int32_t *>(p); }
 
+// M == B * L, in exact arithmetic
+bool is_product(int64_t M, int64_t B, int64_t L) {
+    int64_t p;
+    return !__builtin_mul_overflow(B, L, &p) && p == M;
+}
 void same_rows(int64_t M, int64_t B, int64_t L) {
-    if (M != B * L) raise(PyExc_ValueError, "x must have B*L rows");
+    if (!is_product(M, B, L)) raise(PyExc_ValueError, "x must have B*L rows");
 }
 void same_shape(bool ok) {
     if (!ok) raise(PyExc_ValueError, "shape mismatch");
@@ -252,7 +257,7 @@ PyObject *quantize_dynamic(Args a) {  // x inv_m xq s_row
 PyObject *w8a8_linear(Args a) {  // xq wq s_tok s_w bias B L y acc_out
     const Matrix xq = matrix(a[0], at::kChar, "xq"), wq = matrix(a[1], at::kChar, "wq");
     const int64_t B = integer(a[5]), L = integer(a[6]), M = xq.rows, N = wq.rows;
-    same_shape(xq.cols == wq.cols && M == B * L);
+    same_shape(xq.cols == wq.cols && is_product(M, B, L));
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *s_w = vector(a[3], at::kFloat, N, "s_w"), *bias = vector(a[4], at::kHalf, N, "bias", true);
     Owned out(output(a[7], {M, N}, at::kHalf, a[0]));
     const Matrix y = written(out.o, at::kHalf, M, N, "y");
@@ -265,7 +270,7 @@ PyObject *w8a8_linear(Args a) {  // xq wq s_tok s_w bias B L y acc_out
 PyObject *w8a8_linear_offset(Args a) {  // xq wq s_tok z_tok rowsum s_w bias B L y acc_out
     const Matrix xq = matrix(a[0], at::kChar, "xq"), wq = matrix(a[1], at::kChar, "wq");
     const int64_t B = integer(a[7]), L = integer(a[8]), M = xq.rows, N = wq.rows;
-    same_shape(xq.cols == wq.cols && M == B * L);
+    same_shape(xq.cols == wq.cols && is_product(M, B, L));
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *z_tok = vector(a[3], at::kInt, L, "z_tok"),
          *rowsum = vector(a[4], at::kInt, N, "rowsum"), *s_w = vector(a[5], at::kFloat, N, "s_w"),
          *bias = vector(a[6], at::kHalf, N, "bias", true);
@@ -280,7 +285,7 @@ PyObject *w8a8_linear_offset(Args a) {  // xq wq s_tok z_tok rowsum s_w bias B L
 PyObject *w4a4_linear(Args a) {  // xq4 wq4 s_tok s_w bias B L y acc_out
     const Matrix xq = matrix(a[0], at::kByte, "xq4"), wq = matrix(a[1], at::kByte, "wq4");
     const int64_t B = integer(a[5]), L = integer(a[6]), M = xq.rows, N = wq.rows;
-    same_shape(xq.cols == wq.cols && M == B * L);
+    same_shape(xq.cols == wq.cols && is_product(M, B, L));
     void *s_tok = vector(a[2], at::kFloat, L, "s_tok"), *s_w = vector(a[3], at::kFloat, N, "s_w"), *bias = vector(a[4], at::kHalf, N, "bias", true);
     Owned out(output(a[7], {M, N}, at::kHalf, a[0]));
     const Matrix y = written(out.o, at::kHalf, M, N, "y");
@@ -291,7 +296,9 @@ PyObject *w4a4_linear(Args a) {  // xq4 wq4 s_tok s_w bias B L y acc_out
 }
 
 PyObject *w4a4_linear_e2m3(Args a) {  // xq6 wq6 s_tok s_w bias B L K y acc_out
-    const int64_t B = integer(a[5]), L = integer(a[6]), K = integer(a[7]), M = B * L;
+    const int64_t B = integer(a[5]), L = integer(a[6]), K = integer(a[7]);
+    int64_t M;
+    if (__builtin_mul_overflow(B, L, &M)) raise(PyExc_ValueError, "xq6: B*L is out of range");
     const Container xq = container(a[0], M, K, "xq6");
     const at::Tensor *w = tensor(a[1]);
     if (!w || w->dim() != 3) raise(PyExc_TypeError, "wq6: expected a CUDA uint8 tensor [blocks, N, 96]");
@@ -320,7 +327,7 @@ CodesOut codes_out(PyObject *o, int64_t M, int64_t K) {
 PyObject *w8a8_linear_fused(Args a) {  // x inv_m s_tok wq s_w bias B L y acc_out xq_out
     const Matrix x = matrix(a[0], at::kHalf, "x"), wq = matrix(a[3], at::kChar, "wq");
     const int64_t B = integer(a[6]), L = integer(a[7]), M = x.rows, K = x.cols, N = wq.rows;
-    same_shape(K == wq.cols && M == B * L);
+    same_shape(K == wq.cols && is_product(M, B, L));
     void *inv_m = vector(a[1], at::kFloat, K, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *s_w = vector(a[4], at::kFloat, N, "s_w"), *bias = vector(a[5], at::kHalf, N, "bias", true);
     Owned out(output(a[8], {M, N}, at::kHalf, a[0]));
@@ -335,7 +342,7 @@ PyObject *w8a8_linear_fused(Args a) {  // x inv_m s_tok wq s_w bias B L y acc_ou
 PyObject *w8a8_linear_offset_fused(Args a) {  // x inv_m s_tok z_tok wq rowsum s_w bias B L y acc_out xq_out
     const Matrix x = matrix(a[0], at::kHalf, "x"), wq = matrix(a[4], at::kChar, "wq");
     const int64_t B = integer(a[8]), L = integer(a[9]), M = x.rows, K = x.cols, N = wq.rows;
-    same_shape(K == wq.cols && M == B * L);
+    same_shape(K == wq.cols && is_product(M, B, L));
     void *inv_m = vector(a[1], at::kFloat, K, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *z_tok = vector(a[3], at::kInt, L, "z_tok"), *rowsum = vector(a[5], at::kInt, N, "rowsum"),
          *s_w = vector(a[6], at::kFloat, N, "s_w"), *bias = vector(a[7], at::kHalf, N, "bias", true);
@@ -351,7 +358,7 @@ PyObject *w8a8_linear_offset_fused(Args a) {  // x inv_m s_tok z_tok wq rowsum s
 PyObject *w4a4_linear_fused(Args a) {  // x inv_m s_tok wq4 s_w bias B L y acc_out xq_out
     const Matrix x = matrix(a[0], at::kHalf, "x"), wq = matrix(a[3], at::kByte, "wq4");
     const int64_t B = integer(a[6]), L = integer(a[7]), M = x.rows, K = x.cols, N = wq.rows;
-    same_shape(K == 2 * wq.cols && M == B * L);
+    same_shape(K == 2 * wq.cols && is_product(M, B, L));
     void *inv_m = vector(a[1], at::kFloat, K, "inv_m", true), *s_tok = vector(a[2], at::kFloat, L, "s_tok"),
          *s_w = vector(a[4], at::kFloat, N, "s_w"), *bias = vector(a[5], at::kHalf, N, "bias", true);
     Owned out(output(a[8], {M, N}, at::kHalf, a[0]));

@@ -87,6 +87,22 @@ def test_wrong_types_and_arguments_are_refused(name):
         call(args[0].float(), *args[1:])
 
 
+@pytest.mark.parametrize("name", [n for n in calls() if not n.startswith("fold") and n not in ("quantize_dynamic", "f16_linear")])
+@pytest.mark.parametrize("b,l", [(B + 1, L), (1 << 62, 4), ((1 << 62) + B, L), (-(1 << 62), 8)])
+def test_batch_times_tokens_is_exact(name, b, l):
+    """B * L has to be the number of rows, also where the product leaves 64 bits."""
+    args, _ = calls()[name]
+    at = next(i for i, a in enumerate(args) if isinstance(a, int))
+    args = list(args)
+    args[at:at + 2] = [b, l]
+    if l != L:  # the token vectors have l entries, and the activations as many rows as the wrapped product
+        rows = (b * l + (1 << 63)) % (1 << 64) - (1 << 63)
+        args = [fake(a.dtype, l) if isinstance(a, torch.Tensor) and tuple(a.shape) == (L,) else a for a in args]
+        args[0] = fake(args[0].dtype, *(rows if d == M else d for d in args[0].shape))
+    with pytest.raises(ValueError):
+        getattr(ptq, name)(*args)
+
+
 class _NoMemory(TorchDispatchMode):
     def __torch_dispatch__(self, func, types, args=(), kwargs=None):
         if func is torch.ops.aten.empty.memory_format:
