@@ -105,13 +105,23 @@ extern __shared__ __attribute__((aligned(16))) char lds_dyn[];
 
 __device__ __forceinline__ int swizzle(int row) { return ((row >> 1) ^ (row >> 2)) & 3; }
 
+// A launch holds fewer than 2^32 threads per grid dimension (its packet counts work items in 32 bits), which small tiles
+// reach at some 2^29 rows; from 2^22 workgroups on the grid has rows of that many.  (Workgroups start in the order of x
+// first, and a row is a multiple of the XCDs, so the round robin over them goes on from row to row.)
+constexpr int kGridRowLog2 = 22;
+inline dim3 grid_of_tiles(int64_t tiles) {
+    const int64_t blocks = ptq4vm::ceil_div(tiles, kXcds) * kXcds, row = 1LL << kGridRowLog2;
+    return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)ptq4vm::ceil_div(blocks, row));
+}
+
 // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give each XCD a
 // contiguous range of tiles, output-channel tiles fastest (they share the activation strip).
 __device__ __forceinline__ bool tile_of_block(const LinearArgs &p, int &tile_r, int &tile_o) {
     const int total_tiles = p.tiles_o * p.tiles_r;
     const int per_xcd = (total_tiles + kXcds - 1) / kXcds;
-    const int tile = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
-    if (tile >= total_tiles) return false;
+    const int block = (int)(blockIdx.x + (blockIdx.y << kGridRowLog2));  // (grid_of_tiles)
+    const int tile = (block % kXcds) * per_xcd + block / kXcds;
+    if (block >= per_xcd * kXcds || tile >= total_tiles) return false;
     tile_o = tile % p.tiles_o;
     tile_r = tile / p.tiles_o;
     return true;
@@ -333,7 +343,7 @@ inline bool set_grid(LinearArgs &a, dim3 &grid) {
     if (tiles_r * tiles_o > 0x3fffffffLL) return false;
     a.tiles_r = (int)tiles_r;
     a.tiles_o = (int)tiles_o;
-    grid = dim3((unsigned)(ptq4vm::ceil_div(tiles_r * tiles_o, kXcds) * kXcds));
+    grid = grid_of_tiles(tiles_r * tiles_o);
     return true;
 }
 

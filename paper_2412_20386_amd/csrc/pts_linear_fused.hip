@@ -856,7 +856,7 @@ int launch_split(LinearArgs a, hipStream_t stream) {
     if (tiles_r * tiles_o > 0x3fffffffLL) return PTQ4VM_ERR_SHAPE;
     a.tiles_r = (int)tiles_r;
     a.tiles_o = (int)tiles_o;
-    kernels[nb - 1]<<<dim3((unsigned)(ptq4vm::ceil_div(tiles_r * tiles_o, kXcds) * kXcds)), dim3(64 * W), 0, stream>>>(a);
+    kernels[nb - 1]<<<grid_of_tiles(tiles_r * tiles_o), dim3(64 * W), 0, stream>>>(a);
     return ptq4vm::check_launch("pts_linear_split");
 }
 // Eight wavefronts on 16 rows while that gives every CU at most one workgroup, four on 32 rows beyond (us, 8 x 16 / 4 x 32
