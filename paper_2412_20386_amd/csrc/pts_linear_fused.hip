@@ -95,7 +95,10 @@ __host__ __device__ __forceinline__ FusedLayout fused_layout(int N, int K, int L
 // BITS4: the weight arrives as packed 4-bit codes ([N, K / 2] bytes) and is expanded once into LDS (codes times 16, in
 // index order); activations are clipped to +-7 and also fed times 16; the factor 256 is undone in the channel steps.
 // OFFSET: the zero-offset form (8 bits): codes carry z_tok[t], the epilogue takes z_tok[t] * rowsum[o] off the accumulator.
-template <int NB, int D, bool DUMP, bool BITS4 = false, bool OFFSET = false>
+// DEEP: short units keep 2 D k-steps in flight.  Not from six channel blocks on: the second k loop takes the registers over
+// the 128 that 16 wavefronts leave (spills of 7 .. 29 registers instead of 0 .. 22), which the long units pay for (us, with /
+// without: 43245 x 256 -> 100 14.5 / 13.3, 47432 x 960 -> 113 31.3 / 28.0, 4-bit 50184 x 384 -> 103 19.7 / 18.5).
+template <int NB, int D, bool DUMP, bool BITS4 = false, bool OFFSET = false, bool DEEP = (NB <= 5)>
 __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const LinearArgs p) {
     static_assert(!(BITS4 && OFFSET), "the zero-offset form is 8-bit");
     using Acc = v4i;
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
     // 4137 x 1536 -> 80 14.1 -> 12.2 us at 48 rows a workgroup).
     int groups = 0;
     constexpr int DS = 2 * D;  // k-steps in flight of a short unit
-    const bool deep = n_ksteps % DS == 0;
+    const bool deep = DEEP && n_ksteps % DS == 0;
     auto start_unit = [&](int64_t r0, int nrows) {  // first D k-steps of the unit's rows
         groups = nrows > 8 * (NL / 2) ? NL : NL / 2;
 #pragma unroll
@@ -910,7 +913,15 @@ int launch_wres(const LinearArgs &a, hipStream_t stream, Form form) {
 #undef PTQ4VM_WRES_ROW
     const int n_ksteps = (int)(a.k_bytes / 64);
     const int depth_row = (PTQ4VM_FUSED_MAXD >= 4 && n_ksteps % 4 == 0 && lay.nb <= 6) ? 0 : (n_ksteps % 2 == 0 ? 1 : 2);
-    const Kernel kernel = kernels[(int)form][(a.xq_out || a.acc_out) ? 1 : 0][depth_row][lay.nb - 1];
+    const bool dump = a.xq_out || a.acc_out;
+    Kernel kernel = kernels[(int)form][dump ? 1 : 0][depth_row][lay.nb - 1];
+    // Six channel blocks, few rows and a long reduction: all units are short and the chain of loads is the run time, so the
+    // deep loop is worth its spills (us, with / without: 5576 x 1280 -> 92 10.3 / 12.3, offset 5772 x 1024 -> 84 10.2 / 11.0, but
+    // 8764 x 1280 -> 83 13.0 / 13.1, 8576 x 256 -> 86 7.0 / 6.5; seven and eight blocks gain nothing).
+    static const Kernel six_deep[3][2] = {{pts_linear_wres<6, 2, false, false, false, true>, pts_linear_wres<6, 1, false, false, false, true>},
+                                          {pts_linear_wres<6, 2, false, true, false, true>, pts_linear_wres<6, 1, false, true, false, true>},
+                                          {pts_linear_wres<6, 2, false, false, true, true>, pts_linear_wres<6, 1, false, false, true, true>}};
+    if (lay.nb == 6 && a.M < 7168 && a.k_bytes >= 768 && !dump) kernel = six_deep[(int)form][n_ksteps % 2 == 0 ? 0 : 1];
     if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), kLdsBytes, "hipFuncSetAttribute(pts_linear_wres)")) return rc;
     kernel<<<dim3((unsigned)wgs), dim3(kFusedWaves * 64), lay.total, stream>>>(a);
     return ptq4vm::check_launch("pts_linear_wres");
