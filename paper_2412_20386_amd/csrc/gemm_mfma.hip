@@ -663,9 +663,18 @@ int dispatch(LinearArgs a, hipStream_t stream) {
               : ((a.ldy % 4 == 0 && ptq4vm::aligned_to(a.y, 8)) ? 4 : 1);
     if constexpr (Path::kElemBytes == 1) {
         // Very short reductions over many rows: whole rows of y streamed out by one wavefront each.  (us, streamed / tiles:
-        // 50432 x 48 -> 1536 36.3 / 44.7, 25216 x 24 -> 768 11.6 / 13.5, but 12608 x 48 -> 1536 18.0 / 12.4 and, with two MFMA
-        // steps of K, 25216 x 128 -> 1536 33.2 / 19.4.)
-        if (a.k_bytes <= (Path::kPacked4 ? 32 : 64)) {
+        // 50432 x 48 -> 1536 36.3 / 44.7, 25216 x 24 -> 768 11.6 / 13.5, but 12608 x 48 -> 1536 18.0 / 12.4.)
+        // Two MFMA steps of K (65 .. 128 codes): where the streamed segments of 64 channels leave whole half lines of y (45408 x
+        // 68 -> 192 9.3 / 13.9, 29120 x 112 -> 512 10.0 / 13.3, 46726 x 96 -> 896 21.6 / 27.1, 47424 x 128 -> 832 19.8 / 30.2; at 128
+        // codes, which the tiles copy directly, from 30 000 rows: 29376 x 128 -> 128 6.2 / 5.6), or where 128-channel tiles
+        // would be half padding (47736 x 108 -> 176 11.4 / 14.7, 44040 x 96 -> 96 6.3 / 7.8, but 21111 x 112 -> 160 7.1 / 6.4).  Other
+        // channel counts merge their segments in the L2, which tiles do better (46648 x 80 -> 664: 1.4 times slower streamed), and
+        // operands of any alignment would be loaded byte by byte (2 to 3 times slower).
+        const int64_t codes = Path::kPacked4 ? 2 * a.k_bytes : a.k_bytes;
+        const bool direct = a.k_bytes % 64 == 0;
+        const bool half_lines = a.N % 32 == 0 && a.N >= 96 && (a.N > 128 || a.M >= (a.N == 128 ? 28000 : 40000)) && (!direct || a.M >= 30000 || a.N >= 448);
+        const bool half_padding = a.N > 128 && a.N <= 192 && a.N % 4 == 0 && a.M >= 36000 && !direct;
+        if (codes <= 64 || (codes <= 128 && la >= 4 && (half_lines || half_padding))) {
             const int rc = launch_stream_smallk(a, false, stream, Path::kPacked4, Path::kOffset);
             if (rc <= 0) return rc;
         }

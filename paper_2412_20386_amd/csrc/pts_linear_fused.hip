@@ -992,7 +992,6 @@ int ptq4vm::mfma::launch_stream_smallk(const LinearArgs &a, bool quantize, hipSt
     const int64_t k_codes = (packed4 && !quantize) ? 2 * a.k_bytes : a.k_bytes;
     if (k_codes > 128 || (offset && packed4) || a.M < (quantize ? kStreamMinRowsFused : kStreamMinRows) || a.M >= (1LL << 31) || a.L >= (1LL << 31) || a.N > 8192) return 1;
     const int ksteps = k_codes <= 64 ? 1 : 2;
-    if (ksteps == 2 && !quantize) return 1;
     const StreamLayout lay = stream_layout((int)a.N, ksteps);
     if (lay.total > kLdsBytes) return 1;
     int device = 0, cus = 0;
@@ -1012,10 +1011,14 @@ int ptq4vm::mfma::launch_stream_smallk(const LinearArgs &a, bool quantize, hipSt
     if (quantize)
         return ksteps == 1 ? launch_stream_aligned<1, true>(a, xa, wa, lay, (unsigned)wgs, stream)
                            : launch_stream_aligned<2, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    // codes already quantized: one MFMA step of K (longer reductions run faster on the tile kernels)
-    if (offset) return launch_stream_aligned<1, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    if (packed4) return launch_stream_aligned<1, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    return launch_stream_aligned<1, false>(a, xa, wa, lay, (unsigned)wgs, stream);
+    if (offset)
+        return ksteps == 1 ? launch_stream_aligned<1, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream)
+                           : launch_stream_aligned<2, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
+    if (packed4)
+        return ksteps == 1 ? launch_stream_aligned<1, false, true>(a, xa, wa, lay, (unsigned)wgs, stream)
+                           : launch_stream_aligned<2, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
+    return ksteps == 1 ? launch_stream_aligned<1, false>(a, xa, wa, lay, (unsigned)wgs, stream)
+                       : launch_stream_aligned<2, false>(a, xa, wa, lay, (unsigned)wgs, stream);
 }
 
 extern "C" int ptq4vm_w4a4_linear_fused(const void *x_f16, const float *inv_m, const float *s_tok, const uint8_t *wq4,
