@@ -7,17 +7,23 @@ using namespace ptq4vm::mfma;
 
 int64_t tiles(const LinearArgs &a, int br, int bo) { return ptq4vm::ceil_div(a.M, br) * ptq4vm::ceil_div(a.N, bo); }
 
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool ALIGNED>
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY>
 int launch(LinearArgs a, hipStream_t stream) {
     dim3 grid;
     if (!set_grid<BR, BO>(a, grid)) return PTQ4VM_ERR_SHAPE;
     constexpr int lds_bytes = tile_lds_bytes<BR, BO, SLAB, STAGES>();
-    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, ALIGNED>;
+    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, COPY>;
     if constexpr (lds_bytes > 64 * 1024) {
         if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_mfma_tile)")) return rc;
     }
     kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(a);
     return ptq4vm::check_launch("linear_mfma_tile");
+}
+
+// Slabs through registers (any pitch, alignment and K).
+template <class Path, int BR, int BO, int WR, int WO, int SLAB>
+int launch_staged(const LinearArgs &a, hipStream_t stream) {
+    return a.k_bytes <= SLAB ? launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kOneSlab>(a, stream) : launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kRegisters>(a, stream);
 }
 
 template <class Path, int FR, int FO, int SK, int U, bool ALIGNED>
@@ -58,25 +64,29 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         if (tiles(a, 16, 16) <= 256) return launch_splitk<Path, 1, 1, 4, 4, true>(a, stream);
         auto padded = [&](int br, int bo) { return tiles(a, br, bo) * br * bo; };
         const int64_t most = padded(32, 64) * 4 / 3;
-        if (tiles(a, 128, 256) >= 800 && padded(128, 256) <= most) return launch<Path, 128, 256, 2, 4, 64, 3, true>(a, stream);
+        if (tiles(a, 128, 256) >= 800 && padded(128, 256) <= most) return launch<Path, 128, 256, 2, 4, 64, 3, Copy::kDirect>(a, stream);
         if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most)
-            return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 4, 64, 3, true>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, true>(a, stream);
-        if (tiles(a, 64, 128) >= 384 && padded(64, 128) <= most) return launch<Path, 64, 128, 2, 2, 128, 2, true>(a, stream);
-        if (tiles(a, 64, 64) > 512) return launch<Path, 64, 64, 2, 2, 128, 2, true>(a, stream);
-        if (tiles(a, 64, 64) >= 190) return launch<Path, 64, 64, 2, 2, 128, 3, true>(a, stream);
-        return launch<Path, 32, 64, 2, 2, 128, 3, true>(a, stream);
+            return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 4, 64, 3, Copy::kDirect>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 128) >= 384 && padded(64, 128) <= most) return launch<Path, 64, 128, 2, 2, 128, 2, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 64) > 512) return launch<Path, 64, 64, 2, 2, 128, 2, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 64) >= 190) return launch<Path, 64, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
+        return launch<Path, 32, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
     }
     // Any pitch, alignment and K.  Loads go through registers, so the small tiles hide less of their latency and the
-    // split reduction, with all of its loads in flight, holds out longer (1707 x 1528 -> 424 [756 blocks of 32 x 32] 9.5 us
-    // against 12.5); the element-wise loads and stores used before took 86 us there, 396 us for 24104 x 830 -> 760 (now 44)
-    // and 79 us for 3184 x 1000 -> 500 (12.5).
+    // split reduction, with all of its loads in flight, holds out longer (1707 x 1528 -> 424 [756 blocks of 32 x 32] 9.6 us
+    // against 12.5); the element-wise loads and stores used before took 86 us there, 396 us for 24104 x 830 -> 760 (now 36)
+    // and 79 us for 3184 x 1000 -> 500 (10.3).  128 x 128 tiles from 300 of them unless they pad the matrix by a third more than
+    // 64 x 64 ones (against 64 x 128 tiles, over 300 shapes: 0.7 .. 0.85 of the time from 1024 bytes of K, there with 128-byte
+    // slabs, 0.85 .. 0.95 below; half-padded ones, 46670 x 1968 -> 61, 1.4 times); with one or two slabs their larger epilogue
+    // counts more (11938 x 32 -> 745 [564 tiles] 10.4 / 9.0) and they start at 1600.
     if (tiles(a, 16, 16) <= 600) return launch_splitk<Path, 1, 1, 4, 4, false>(a, stream);
     if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= 1000)) return launch_splitk<Path, 2, 2, 4, 3, false>(a, stream);
-    if (tiles(a, 128, 128) >= 1600) return launch<Path, 128, 128, 2, 4, 64, 2, false>(a, stream);
-    if (tiles(a, 64, 128) >= 800) return launch<Path, 64, 128, 2, 2, 64, 2, false>(a, stream);
+    if (tiles(a, 128, 128) >= (a.k_bytes > 128 ? 300 : 1600) && 3 * tiles(a, 128, 128) * 128 * 128 <= 4 * tiles(a, 64, 64) * 64 * 64)
+        return a.k_bytes < 1024 ? launch_staged<Path, 128, 128, 2, 4, 64>(a, stream) : launch_staged<Path, 128, 128, 2, 4, 128>(a, stream);
+    if (tiles(a, 64, 128) >= 800) return launch_staged<Path, 64, 128, 2, 2, 64>(a, stream);
     if (tiles(a, 64, 64) >= 150)
-        return a.k_bytes <= 320 ? launch<Path, 64, 64, 2, 2, 64, 2, false>(a, stream) : launch<Path, 64, 64, 2, 2, 128, 2, false>(a, stream);
-    return launch<Path, 32, 64, 2, 2, 128, 2, false>(a, stream);
+        return a.k_bytes <= 320 ? launch_staged<Path, 64, 64, 2, 2, 64>(a, stream) : launch_staged<Path, 64, 64, 2, 2, 128>(a, stream);
+    return launch_staged<Path, 32, 64, 2, 2, 128>(a, stream);
 }
 
 template int ptq4vm::mfma::launch_tiles<ptq4vm::mfma::Int8Path>(const LinearArgs &, hipStream_t);

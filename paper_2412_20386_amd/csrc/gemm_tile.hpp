@@ -242,8 +242,11 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
 // pipelining inside the workgroup.  The step, bias and offset vectors are fetched before the first copy and wait in
 // LDS, and results cross a wavefront-private patch into 16-byte stores of whole row segments (25216 x 768 -> 384: 15.6 us
 // = 2.5 TB/s, 22.3 us with the tile kernel before, whose epilogue loaded each scale where it was used).
-// ALIGNED: 16-byte aligned bases and pitches, k_bytes % 64 == 0; slabs are copied global -> LDS directly.  Otherwise any
-// pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).
+// COPY kDirect: 16-byte aligned bases and pitches, k_bytes % 64 == 0; slabs are copied global -> LDS directly.  Otherwise any
+// pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).  Only the last
+// slab reaches beyond K; the loads of the others carry no tests (16236 x 1584 -> 760 fp16 106.7 -> 62.8 us, 24104 x 830 -> 760
+// 45.7 -> 36.1, 3184 x 1000 -> 500 12.3 -> 10.3, each with the larger tiles that this pays for; 69.1, 43.4 and 12.3 with the
+// tiles alone).  A reduction of one slab keeps the tested loads alone (kOneSlab): the second form costs it 2 %.
 // Requirements (host-checked): L < 2^31, BR * ldx_bytes and BO * ldw_bytes below 2^31.
 // ------------------------------------------------------------------------------------------
 template <int BR, int BO, int SLAB, int STAGES>
@@ -251,8 +254,11 @@ constexpr int tile_lds_bytes() {
     return STAGES * (BR + BO) * SLAB + tile_vector_bytes<BR, BO>();
 }
 
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool ALIGNED>
+enum class Copy { kDirect, kRegisters, kOneSlab };
+
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY>
 __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArgs p) {
+    constexpr bool ALIGNED = COPY == Copy::kDirect;
     constexpr int NW = WR * WO, THREADS = 64 * NW;
     constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
     constexpr int CHUNKS = SLAB / 16, ROWS_PER_COPY = 64 / CHUNKS, COPIES = (BR + BO) / ROWS_PER_COPY / NW;
@@ -303,6 +309,10 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
                                                  (__attribute__((address_space(3))) void *)(ring + stage * STAGE_BYTES + c * 1024), 16, 0, 0);
             } else {
                 const int chunk = chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS);
+                if (COPY == Copy::kRegisters && (int64_t)(slab + 1) * SLAB <= p.k_bytes) {  // a slab inside the rows
+                    staged[i] = *reinterpret_cast<const v4i_unaligned *>(src + off[i] + (int64_t)slab * SLAB + chunk * 16);
+                    continue;
+                }
                 const char *end = c * ROWS_PER_COPY < BR ? p.x + ((p.M - 1) * p.ldx_bytes + p.k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + p.k_bytes);
                 staged[i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, p.k_bytes, end);
             }
