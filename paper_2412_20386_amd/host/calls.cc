@@ -418,9 +418,16 @@ void parse(const Signature &sig, Args args, Py_ssize_t nargs, PyObject *kwnames,
         if (!out[i]) raise(PyExc_TypeError, std::string(sig.function) + "() missing required argument: '" + sig.names[i] + "'");
 }
 
+// Inside a catch block: the exception as torch raises it (torch.OutOfMemoryError).  Apart from the call itself, because
+// torch's macros set up a warning handler on the way in, 0.2 us a call.
+PyObject *raise_as_torch() {
+    HANDLE_TH_ERRORS
+    throw;
+    END_HANDLE_TH_ERRORS
+}
+
 template <PyObject *(*CALL)(Args), Signature *SIG>
 PyObject *call(PyObject *, Args args, Py_ssize_t nargs, PyObject *kwnames) {
-    HANDLE_TH_ERRORS
     try {
         PyObject *a[kMaxParams];
         parse(*SIG, args, nargs, kwnames, a);
@@ -428,8 +435,9 @@ PyObject *call(PyObject *, Args args, Py_ssize_t nargs, PyObject *kwnames) {
         return CALL(a);
     } catch (const Raised &) {
         return nullptr;
+    } catch (...) {  // an output that could not be allocated
+        return raise_as_torch();
     }
-    END_HANDLE_TH_ERRORS  // an output that could not be allocated keeps torch's exception (torch.OutOfMemoryError)
 }
 
 #define SIG(name, required, total, ...) Signature sig_##name = {#name, required, total, {__VA_ARGS__}, {}};
