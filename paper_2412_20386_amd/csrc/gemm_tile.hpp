@@ -71,17 +71,13 @@ __device__ __forceinline__ void mfma_step(typename Path::Acc16 (&acc)[FO][FR], c
     }
 }
 
-// Eight fp16 results of a row, n_valid of them inside the matrix; rows may start at any even address.
-// NT: non-temporal.  Large outputs whose row segments are whole 128-byte lines leave that way: written back through the
-// caches they cost the kernels around them more than they save (one Vim-S block over 64 x 785 rows 156.5 -> 148.2 us, the
-// offset block of Vim-B over 64 x 197 rows 141.5 -> 136.8 us).  Partial lines must merge in the L2 instead (15614 x 128 ->
-// 2310, 4620-byte rows: 29 - 48 us non-temporal, 22 us through the L2).
-__device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid, bool nt) {
+// Eight fp16 results of a row, n_valid of them inside the matrix; rows may start at any even address.  Through the caches:
+// with non-temporal stores instead the blocks of all sizes take the same time (a Vim-S block over 64 x 785 rows 149.8 / 149.3 us,
+// the offset block of Vim-B over 64 x 197 rows 121.1 / 121.4, a fp16 Vim-S block over 128 x 197 rows 101.7 / 101.5), and lines that
+// two stores share have to meet in the L2 (15614 x 128 -> 2310, 4620-byte rows: 29 - 48 us non-temporal, 22 us through it).
+__device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid) {
     if (n_valid >= 8) {
-        if (nt)
-            __builtin_nontemporal_store(data, reinterpret_cast<v4f_unaligned *>(dst));
-        else
-            *reinterpret_cast<v4f_unaligned *>(dst) = data;
+        *reinterpret_cast<v4f_unaligned *>(dst) = data;
         return;
     }
     const float w[4] = {data.x, data.y, data.z, data.w};
@@ -203,7 +199,6 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
         return row * (WAVE_O * 2) + ((chunk ^ sw) << 4);
     };
     char *const y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
-    const bool nt = BR * BO >= 64 * 128 && p.ldy % 64 == 0 && (reinterpret_cast<uintptr_t>(p.y) & 127) == 0;
 #pragma unroll
     for (int jb = 0; jb < FR; jb += JB) {
 #pragma unroll
@@ -229,7 +224,7 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
             const v4f data = *reinterpret_cast<const v4f *>(patch + patch_chunk(prow, chunk));
             const int r = wave_r + jb * 16 + prow, o = wave_o + chunk * 8;
             if (r < rows_valid && o < cols_valid)
-                store_eight(y_tile + (int64_t)r * p.ldy * 2 + o * 2, data, cols_valid - o, nt);
+                store_eight(y_tile + (int64_t)r * p.ldy * 2 + o * 2, data, cols_valid - o);
         }
         asm volatile("" ::: "memory");
     }
