@@ -30,12 +30,12 @@ def _sampled_rows(M, step, L):
     return rows[(rows >= 0) & (rows < M)]
 
 
-E2M3_SHAPES = [  # B, L, K, N: small tiled kernel (few tiles, odd shapes) and persistent kernel (>= 128 tiles of 256 x 256)
+E2M3_SHAPES = [  # B, L, K, N: split reduction and tiles (test_gpu_routes.py has the persistent kernel)
     (3, 197, 384, 192), (2, 197, 192, 768), (2, 197, 384, 44), (3, 197, 12, 384), (2, 50, 768, 56),
     (1, 300, 1536, 80), (1, 1, 64, 32), (1, 257, 100, 130), (2, 33, 14, 5), (1, 129, 1000, 257), (5, 7, 16, 1),
     (2, 140, 128, 300), (1, 70, 33, 9),
-    (33, 197, 256, 1288),   # persistent: 26 x 6 tiles, 2 blocks, ragged last row and channel tiles
-    (40, 211, 384, 776),    # persistent: 33 x 4 tiles, 3 blocks, N = 8 (mod 256)
+    (33, 197, 256, 1288),   # 128 x 128 tiles, 2 blocks, ragged last row and channel tiles
+    (40, 211, 384, 776),    # 64 x 128 tiles, 3 blocks, N = 8 (mod 256)
 ]
 
 

@@ -258,9 +258,9 @@ def test_zero_offset_longest_reduction_24_bit_product():
 
 
 DETERMINISM_SHAPES = [  # B, L, K, N, which kernels the library picks at this shape
-    (4, 197, 768, 384, "tiled 4-wavefront kernel"),
+    (4, 197, 768, 384, "tile kernels"),
     (64, 197, 768, 3072, "persistent 256 x 256 kernel, whole rounds plus a round of half tiles"),
-    (64, 197, 1536, 80, "weight-resident kernels (two-launch and fused)"),
+    (64, 197, 1536, 80, "tile kernel and weight-resident fused kernel"),
     (110, 197, 48, 1536, "row-streaming short-reduction kernel (two-launch and fused)"),
 ]
 
@@ -408,17 +408,14 @@ def test_vim_b_other_layers_sampled(layer, linear):
                                      (41, 251, 768, 1280), (67, 193, 768, 256), (53, 211, 384, 768), (20, 517, 384, 3328),
                                      (129, 199, 512, 376), (105, 251, 256, 264)])
 def test_large_ragged_shapes_sampled(B, L, K, N):
-    """Many 256 x 256 tiles with ragged last tiles in both directions; shapes 4 and 6 have a reduction
-    length the persistent kernel takes (2 and 5 slabs of 128 bytes), with and without a partial last
-    round of tiles that is cut into half tiles.  K = 384 and K = 768 with at least 8192 rows and N a
-    multiple of 256 run on the weights-in-registers kernel: ragged last row tile, a single strip, more
-    workgroups than units in an XCD's last band.  The last two (fewer than 256 tiles of 256 x 256, 256 < N <= 384)
-    run on 256 x 128 tiles of the persistent kernel: ragged rows and a ragged third / nearly empty third column tile."""
+    """Many tiles with ragged last tiles in both directions.  Reductions of 256 codes and more over at least 256 tiles of 256 x
+    256 (channels padded by at most a quarter) run on the persistent kernel, with and without a partial last round of tiles
+    that is cut into half tiles; the others on the tile kernels.  (test_gpu_routes.py holds shapes by the kernel they run on.)"""
     c = synth.random_problem(4242 + N, B, L, K, N, device=DEV)
     _check_case_on_sampled_rows(c, _sampled_rows(B * L, 61, L), "ragged")
 
 
-SKINNY_SHAPES = [  # B, L, K, N, ldy, bias: few output channels over many rows (weight-resident kernel)
+SKINNY_SHAPES = [  # B, L, K, N, ldy, bias: few output channels over many rows
     (83, 199, 192, 44, None, True),     # 3 k-steps; 88-byte dense rows; M mod 32 = 5
     (64, 257, 320, 80, None, False),    # 5 k-steps, fewer than the fragments kept in flight
     (70, 241, 1024, 128, None, True),   # exactly two register groups of k-steps; 8 channel blocks; M mod 32 = 6
@@ -437,14 +434,14 @@ def test_skinny_output_shapes_sampled(B, L, K, N, ldy, bias):
 
 @pytest.mark.parametrize("B,L,K,N,bias", [(43, 197, 768, 512, True), (65, 131, 384, 256, False)])
 def test_weights_in_registers_kernel_whole_result(B, L, K, N, bias):
-    """Every code, accumulator and output of a launch of the weights-in-registers kernel (K = 768 / 384,
-    at least 8192 rows), ragged in rows and channels."""
+    """Every code, accumulator and output at the reductions of the weights-in-registers kernel (K = 768 / 384), ragged in rows,
+    below the nine units a CU from which it takes over (test_gpu_routes.py has those)."""
     c = synth.random_problem(4100 + K + N, B, L, K, N, device=DEV)
     _run_w8a8_case(c, use_bias=bias, what="wreg-whole")
 
 
 def test_skinny_output_whole_result():
-    """Every element of a weight-resident launch, not a sample: 83 * 199 rows, 192 -> 44."""
+    """Every element of a launch with few channels, not a sample: 83 * 199 rows, 192 -> 44."""
     c = synth.random_problem(99, 83, 199, 192, 44, device=DEV)
     _run_w8a8_case(c, what="skinny-whole")
 
@@ -491,7 +488,7 @@ def _run_fused_case(c, use_bias=True, use_m=True, ldy=None, what=""):
     return stats
 
 
-FUSED_SHAPES = [  # B, L, K, N: the tiled kernel with the quantizer in its loader
+FUSED_SHAPES = [  # B, L, K, N: few rows (the split reduction)
     (3, 197, 384, 192),
     (2, 197, 384, 44),
     (3, 197, 12, 384),    # dt_proj (Vim-Ti): 24-byte fp16 rows
@@ -518,22 +515,22 @@ def test_fused_linear_config0_and_options():
     _run_fused_case(c, ldy=c.N + 8, what="fused-ldy")
 
 
-FUSED_SKINNY = [  # B, L, K, N, ldy, bias, m: weight-resident fused kernel (N <= 128, >= 2048 rows)
+FUSED_SKINNY = [  # B, L, K, N, ldy, bias, m: weight-resident fused kernel (N <= 128, >= 4096 rows; the last two: split reduction)
     (83, 199, 128, 44, None, True, True),     # 2 k-steps (depth 2); 88-byte dense rows; M mod 32 = 5
     (64, 257, 320, 80, None, False, True),    # 5 k-steps (depth 1)
     (70, 241, 1024, 128, None, True, True),   # 16 k-steps, 8 channel blocks (depth 2); M mod 32 = 6
-    (83, 199, 768, 50, None, True, False),    # 12 k-steps (depth 4); N not a multiple of 4; no smoothing
+    (83, 199, 768, 50, None, True, False),    # 12 k-steps (depth 2); N not a multiple of 4; no smoothing
     (83, 199, 1536, 72, 80, True, True),      # padded output rows
     (66, 250, 1600, 16, None, True, True),    # 25 k-steps (depth 1); one channel block; M mod 32 = 20
     (330, 199, 128, 44, None, True, True),    # 65670 rows: one full pass of 16-row units, then a tail of 17 groups of 8 rows
-    (11, 191, 256, 80, None, True, True),     # 2101 rows: a grid of 9 workgroups, 29 or 30 groups each (wavefronts with 2 and 1)
-    (13, 163, 192, 33, None, False, True),    # 2119 rows, M mod 8 = 7: the last group is ragged
+    (11, 191, 256, 80, None, True, True),     # 2101 rows: 132 workgroups of 16 rows, the last ragged
+    (13, 163, 192, 33, None, False, True),    # 2119 rows, M mod 8 = 7
 ]
 
 
 @pytest.mark.parametrize("B,L,K,N,ldy,bias,use_m", FUSED_SKINNY)
 def test_fused_linear_skinny_whole_result(B, L, K, N, ldy, bias, use_m):
-    """Every code, accumulator and output of a weight-resident fused launch against the oracle."""
+    """Every code, accumulator and output of a fused launch with few channels against the oracle."""
     c = synth.random_problem(1234 + K + N, B, L, K, N, device=DEV)
     _run_fused_case(c, use_bias=bias, use_m=use_m, ldy=ldy, what="fused-skinny")
 
@@ -692,9 +689,8 @@ def test_zero_offset_vim_b_full_size_sampled(linear):
                                      (110, 197, 24, 776), (105, 197, 100, 520), (107, 199, 48, 1536),
                                      (83, 199, 256, 80), (64, 257, 1536, 44), (70, 241, 704, 121)])
 def test_zero_offset_large_ragged_shapes_sampled(B, L, K, N):
-    """Ragged last tiles in the persistent kernel (first two), the short-reduction kernel (next two), the
-    row-streaming kernel (from 20 480 rows: one and two k-steps, ragged rows and channels) and the weight-resident
-    kernel (N <= 128: 5, 3 and 8 channel blocks, ragged rows and channels)."""
+    """Ragged last tiles in the persistent kernel (first two), short reductions below 20 480 rows (next two: tiles) and
+    above (24 and 48 codes: the row-streaming kernel), and few channels (N <= 128: 5, 3 and 8 blocks of them)."""
     c, x, s_off, z_off = _offset_case(5000 + K + N, B, L, K, N)
     _check_offset_on_sampled_rows(c, x, s_off, z_off, _sampled_rows(B * L, 61, L), "ragged")
 
@@ -710,13 +706,13 @@ def test_zero_offset_quantizer_long_sequence_and_plain_kernels():
 
 
 FUSED_OFFSET_SHAPES = [  # B, L, K, N, ldy, bias
-    # weight-resident kernel (N <= 128, K a multiple of 64, >= 2048 rows)
+    # weight-resident kernel (N <= 128, K a multiple of 64, >= 4096 rows; from 2048 split reduction)
     (83, 199, 128, 44, None, True),      # 2 k-steps; M mod 32 = 5
     (64, 257, 320, 80, None, False),     # 5 k-steps (depth 1)
     (70, 241, 1024, 96, None, True),     # 16 k-steps, 6 channel blocks
     (70, 241, 512, 128, None, True),     # 8 channel blocks
     (83, 199, 1536, 72, 80, True),       # x_proj-like, padded output rows
-    (13, 163, 192, 33, None, False),     # 2119 rows, M mod 8 = 7: the last group is ragged
+    (13, 163, 192, 33, None, False),     # 2119 rows, M mod 8 = 7
     # row-streaming kernel (K <= 128, >= 1024 rows)
     (105, 197, 40, 100, 104, True),      # padded output rows
     (21, 199, 12, 130, None, True),      # 24-byte fp16 rows
@@ -924,9 +920,9 @@ def test_w4a4_full_size_sampled(cfg, linear):
 @pytest.mark.parametrize("B,L,K,N", [(41, 251, 512, 1544), (20, 517, 768, 3400), (300, 65, 24, 776), (250, 33, 100, 520),
                                      (110, 197, 24, 776), (105, 197, 100, 520), (107, 199, 48, 1536), (104, 197, 128, 130)])
 def test_w4a4_large_ragged_shapes_sampled(B, L, K, N):
-    """Ragged last tiles in the persistent kernel (128-row tiles; 2 and 3 slabs of packed bytes), in
-    the short-reduction kernel (12 and 50 packed bytes per row) and, from 20 480 rows, in the row-streaming
-    kernel (12, 50, 24 and 64 packed bytes per row: one and two k-steps once expanded, ragged rows and channels)."""
+    """Ragged last tiles in the persistent kernel (128-row tiles; 2 and 3 slabs of packed bytes), short reductions below
+    20 480 rows (12 and 50 packed bytes per row: tiles) and above (12 and 24: the row-streaming kernel; 50 and 64 with ragged
+    channels: tiles)."""
     c = synth.random_problem(6000 + K + N, B, L, K, N, device=DEV)
     _check_w4a4_on_sampled_rows(c, "ragged")
 
@@ -972,7 +968,7 @@ def _run_fused_w4a4_case(c, use_bias=True, use_m=True, ldy=None, what=""):
 
 
 FUSED_W4A4_SHAPES = [  # B, L, K, N, ldy, bias, m
-    # weight-resident kernel (N <= 128, K a multiple of 64, >= 2048 rows)
+    # weight-resident kernel (N <= 128, K a multiple of 64, >= 4096 rows; from 2048 split reduction)
     (83, 199, 128, 44, None, True, True),     # 2 k-steps; M mod 32 = 5
     (64, 257, 320, 80, None, False, True),    # 5 k-steps (depth 1)
     (70, 241, 1024, 96, None, True, True),    # 16 k-steps, 6 channel blocks
@@ -980,7 +976,7 @@ FUSED_W4A4_SHAPES = [  # B, L, K, N, ldy, bias, m
     (83, 199, 768, 50, None, True, False),    # N not a multiple of 4; no smoothing
     (83, 199, 1536, 72, 80, True, True),      # x_proj-like, padded output rows
     (66, 250, 1600, 16, None, True, True),    # 25 k-steps; one channel block
-    (13, 163, 192, 33, None, False, True),    # 2119 rows, M mod 8 = 7: the last group is ragged
+    (13, 163, 192, 33, None, False, True),    # 2119 rows, M mod 8 = 7
     # row-streaming kernel (K <= 128, >= 1024 rows)
     (105, 197, 40, 100, 104, True, True),     # 20-byte packed weight rows, padded output rows
     (21, 199, 12, 130, None, True, True),     # 6 packed bytes per weight row: element-wise weight loads

@@ -1,0 +1,202 @@
+"""Which kernel a call runs on, by its name in the profiler's record, on both sides of the lines of the dispatch, with the
+result checked against a 64-bit product.  The shapes are the smallest that reach a kernel, ragged in rows and channels."""
+import warnings
+
+import pytest
+import torch
+from torch.profiler import ProfilerActivity, profile
+
+import paper_2412_20386_amd as ptq
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+WREG, PERSISTENT, STREAM, SMALLK = "linear_mfma_wreg<", "linear_mfma_persistent<", "linear_stream_smallk<", "linear_mfma_smallk<"
+TILE, SPLITK, WRES, SPLIT, FUSED_TILE = "linear_mfma_tile<", "linear_mfma_splitk<", "pts_linear_wres<", "pts_linear_split<", "pts_linear_generic<"
+E_PERSISTENT, E_TILE, E_SPLITK = "linear_e2m3_persistent<", "linear_e2m3_tile<", "linear_e2m3_splitk<"
+DIRECT, STAGED, ONE_SLAB = "Copy)0>", "Copy)1>", "Copy)2>"  # how linear_mfma_tile brings its slabs
+
+
+def ran(call):
+    """Names of this library's kernels that the call launched."""
+    call()
+    torch.cuda.synchronize()
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        with profile(activities=[ProfilerActivity.CUDA]) as record:
+            call()
+            torch.cuda.synchronize()
+    return [e.key for e in record.key_averages() if "linear" in e.key and "<" in e.key]
+
+
+def check_kernel(call, *parts):
+    names = ran(call)
+    assert len(names) == 1 and all(p in names[0] for p in parts), (names, parts)
+
+
+def rows_of(L, M):
+    return torch.arange(M, device=DEV) % L
+
+
+def close(y, acc64, scale, bias):
+    """One fp16 rounding plus the fp32 roundings of the epilogue."""
+    p = acc64 * scale
+    y64 = p if bias is None else p + bias.double()
+    tol = 2.0 ** -10 * y64.abs() + 2.0 ** -21 * (p.abs() + (0 if bias is None else bias.double().abs())) + 2.0 ** -24
+    return bool(((y.double() - y64).abs() <= tol).all())
+
+
+class Problem:
+    def __init__(self, M, K, N, L=None, limit=127):
+        g = torch.Generator(device=DEV).manual_seed(M + 3 * K + 7 * N)
+        ints = lambda lo, hi, *s: torch.randint(lo, hi, s, generator=g, device=DEV)
+        self.L = L = L or next(d for d in (11, 7, 5, 3, 2, 1) if M % d == 0)
+        self.M, self.K, self.N, self.B = M, K, N, M // L
+        self.x, self.w = ints(-limit, limit + 1, M, K).to(torch.int8), ints(-limit, limit + 1, N, K).to(torch.int8)
+        self.s_tok, self.s_w = (torch.rand(n, generator=g, device=DEV) * 0.01 + 0.001 for n in (L, N))
+        self.bias = torch.randn(N, generator=g, device=DEV).half()
+        self.z = ints(-128, 128, L).to(torch.int32)
+        self.rowsum = self.w.sum(1, dtype=torch.int32)
+        self.acc64 = self.x.double() @ self.w.double().t()
+        self.scale = self.s_tok.double()[rows_of(L, M)][:, None] * self.s_w.double()[None, :]
+        self.acc = torch.empty((M, N), dtype=torch.int32, device=DEV)
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (128 * 2303 + 5, 384, 256), (128 * 191 + 77, 384, 3072), (128 * 575 + 1, 768, 1024), (128 * 767 + 100, 768, 768),
+])
+def test_weights_in_registers_kernel(M, K, N):
+    """From nine units of 128 rows x 256 channels a CU; ragged last units; one strip and several, an uneven band; with and
+    without bias; with the accumulators.  One row unit less runs on the persistent kernel."""
+    print(f"wreg M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N)
+    for bias in (p.bias, None):
+        run = lambda **kw: ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, bias, p.B, p.L, **kw)
+        check_kernel(run, WREG, f"<{K // 64},")
+        y = run()
+        assert close(y, p.acc64, p.scale, bias)
+        check_kernel(lambda: run(acc_out=p.acc), WREG)
+        p.acc.fill_(-1)
+        y_dump = run(acc_out=p.acc)
+        assert torch.equal(p.acc.double(), p.acc64) and torch.equal(y_dump.view(torch.int16), y.view(torch.int16))
+    M = (M // 128) * 128 - M // 128 // 100  # fewer than nine units a CU
+    x = p.x[:M]
+    check_kernel(lambda: ptq.w8a8_linear(x, p.w, p.s_tok[:1], p.s_w, p.bias, M, 1), PERSISTENT)
+
+
+def _e2m3(p):
+    x6 = ptq.quantize_pts_a4_e2m3(p.x.half(), None, torch.ones(p.L, device=DEV), p.B, p.L)
+    p.w[:, 0] = 7  # every weight row folds to step 1
+    w6, step, _ = ptq.fold_smoothing_w4_e2m3(p.w.half(), torch.ones(p.K, device=DEV))
+    assert bool((step == 1).all())
+    p.acc64 = p.x.double() @ p.w.double().t()
+    return x6, w6
+
+
+@pytest.mark.parametrize("M,K,N,kernel", [
+    (26373, 256, 1032, E_PERSISTENT), (14807, 384, 2056, E_PERSISTENT),      # 520 and 522 tiles, 8 channels in the last; 2 and 3 blocks
+    (26112, 256, 1032, E_TILE),                                               # 510 tiles
+    (12301, 256, 1024, E_PERSISTENT), (12288, 256, 1024, E_TILE),             # 776 and 768 tiles of 128 x 128
+    (13312, 384, 1024, E_TILE), (13312, 1152, 1024, E_PERSISTENT),            # 832: from there long reductions only
+    (17000, 1152, 1032, E_TILE), (26900, 384, 520, E_TILE),                   # more than one round; padding
+])
+def test_e2m3_kernels(M, K, N, kernel):
+    """The persistent kernel down to its shortest reduction (fewer blocks than ring stages), ragged in rows and channels, with
+    and without bias, with the accumulators; and what lies just beyond its lines."""
+    print(f"e2m3 M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N, limit=7)
+    x6, w6 = _e2m3(p)
+    for bias in (p.bias, None):
+        run = lambda **kw: ptq.w4a4_linear_e2m3(x6, w6, p.s_tok, p.s_w, bias, p.B, p.L, p.K, **kw)
+        check_kernel(run, kernel)
+        y = run()
+        assert close(y, p.acc64, p.scale, bias)
+        p.acc.fill_(-1)
+        check_kernel(lambda: run(acc_out=p.acc), kernel)
+        assert torch.equal(p.acc.double(), p.acc64)
+        assert torch.equal(run(acc_out=p.acc).view(torch.int16), y.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,K,N,kernel", [
+    (20480, 66, 160, TILE), (20483, 68, 160, STREAM), (20479, 68, 160, TILE), (20501, 100, 416, STREAM), (20501, 100, 424, TILE),
+    (27999, 72, 128, TILE), (28001, 72, 128, STREAM), (39999, 72, 96, TILE), (40003, 72, 96, STREAM),
+    (36001, 76, 132, STREAM), (36001, 76, 130, TILE), (35999, 76, 132, TILE), (36001, 76, 196, TILE),
+    (29999, 128, 416, TILE), (30001, 128, 416, STREAM), (20483, 128, 448, STREAM), (20483, 128, 2080, TILE),
+])
+def test_streaming_kernel_two_steps_of_k(M, K, N, kernel):
+    """65 to 128 codes, in the three forms (packed 4-bit: the same number of codes, so half the bytes and half the alignment)."""
+    print(f"stream M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N)
+    check_kernel(lambda: ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, p.bias, p.B, p.L), kernel)
+    y = ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, p.bias, p.B, p.L, acc_out=p.acc)
+    assert close(y, p.acc64, p.scale, p.bias) and torch.equal(p.acc.double(), p.acc64)
+    offset = lambda: ptq.w8a8_linear_offset(p.x, p.w, p.s_tok, p.z, p.rowsum, p.s_w, None, p.B, p.L, acc_out=p.acc)
+    check_kernel(offset, kernel)
+    z = p.z.double()[rows_of(p.L, M)][:, None] * p.rowsum.double()[None, :]
+    assert close(offset(), p.acc64 - z, p.scale, None) and torch.equal(p.acc.double(), p.acc64)
+    x4, w4 = p.x.clamp(-7, 7), p.w.clamp(-7, 7)
+    pack = lambda c: ((c[:, 0::2] & 15) | ((c[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous()
+    xp, wp = pack(x4), pack(w4)
+    packed = lambda: ptq.w4a4_linear(xp, wp, p.s_tok, p.s_w, p.bias, p.B, p.L, acc_out=p.acc)
+    check_kernel(packed, TILE if K // 2 % 4 else kernel)
+    acc4 = x4.double() @ w4.double().t()
+    assert close(packed(), acc4, p.scale, p.bias) and torch.equal(p.acc.double(), acc4)
+
+
+@pytest.mark.parametrize("M,K,N,parts", [
+    (16 * 16, 1536, 16 * 16, (SPLITK,)), (16 * 16 + 1, 64, 16 * 16, (TILE, "32, 64", DIRECT)),
+    (1001, 960, 832, (TILE, "64, 64", DIRECT)), (3137, 448, 1153, (TILE, "64, 128", DIRECT)), (6209, 192, 1025, (TILE, "128, 128", DIRECT)),
+    (13057, 192, 2048, (TILE, "128, 256", DIRECT)), (65536, 256, 256, (PERSISTENT,)), (65536, 256, 416, (PERSISTENT,)), (65536, 256, 408, (TILE, "128, 256")), (65281, 256, 264, (TILE,)),
+    # any pitch and K: one slab (63, 64 unaligned rows, 128), two with one byte in the second, more; each tile
+    (12345, 63, 2179, (TILE, "128, 128", ONE_SLAB)), (12345, 65, 2179, (TILE, "128, 128", STAGED)), (6401, 1030, 900, (TILE, "128, 128", "128, 2,", STAGED)),
+    (6401, 63, 1029, (TILE, "64, 128", ONE_SLAB)), (6401, 65, 1029, (TILE, "64, 128", STAGED)), (1279, 33, 645, (TILE, "64, 64", ONE_SLAB)),
+    (1279, 129, 645, (TILE, "64, 64", STAGED)), (2049, 321, 643, (TILE, "64, 64", "128, 2,", STAGED)), (401, 127, 899, (TILE, "32, 64", ONE_SLAB)),
+    (401, 130, 899, (TILE, "32, 64", STAGED)), (46670, 250, 61, (TILE, "64, 64", STAGED)), (401, 1001, 403, (SPLITK, "2, 2")), (50, 13, 7, (SPLITK, "1, 1")),
+])
+def test_int8_tiles(M, K, N, parts):
+    print(f"tiles M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N)
+    run = lambda **kw: ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, p.bias, p.B, p.L, **kw)
+    check_kernel(run, *parts)
+    y = run()
+    assert close(y, p.acc64, p.scale, p.bias)
+    p.acc.fill_(-1)
+    run(acc_out=p.acc)
+    assert torch.equal(p.acc.double(), p.acc64)
+
+
+@pytest.mark.parametrize("M,K,N", [(12345, 31, 2179), (12345, 33, 2179), (5121, 520, 900), (6401, 32, 1028), (6401, 33, 1029), (401, 66, 899), (2049, 200, 643)])
+def test_f16_tiles_any_alignment(M, K, N):
+    """fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|, and one fp16 rounding.  Infinities beyond K (the
+    padding of wider rows) stay out."""
+    print(f"f16 tiles M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    x, w = (torch.full((r, K + 1 + K % 2), float("inf"), dtype=torch.float16, device=DEV)[:, :K] for r in (M, N))  # odd pitch
+    x.copy_(torch.randn(M, K, generator=g, device=DEV))
+    w.copy_(torch.randn(N, K, generator=g, device=DEV))
+    check_kernel(lambda: ptq.f16_linear(x, w, None), TILE)
+    y, y64, mag = ptq.f16_linear(x, w, None), x.double() @ w.double().t(), x.double().abs() @ w.double().abs().t()
+    assert bool(((y.double() - y64).abs() <= (K + 2) * 2.0 ** -24 * mag + 2.0 ** -10 * y64.abs() + 2.0 ** -24).all())
+
+
+@pytest.mark.parametrize("M,K,N,parts", [
+    (2048, 256, 72, (SPLIT, "1, 8")), (4095, 1536, 80, (SPLIT, "1, 8")), (4096, 1536, 80, (WRES, "<5,")), (4099, 192, 33, (WRES, "<3,")),
+    (7167, 1280, 92, (WRES, "<6,", "false, true>")), (7168, 1280, 92, (WRES, "<6,", "false, false>")), (7167, 704, 92, (WRES, "<6,", "false, false>")),
+    (33001, 256, 113, (WRES, "<8,")), (50001, 384, 100, (WRES, "<7,")), (40003, 832, 90, (WRES, "<6,")),
+    (4096, 100, 300, (STREAM,)), (1000, 100, 300, (SPLIT,)), (5000, 200, 128, (SPLIT, "2, 4")), (2048, 200, 130, (SPLIT,)), (2049, 200, 130, (FUSED_TILE,)),
+])
+def test_fused_kernels(M, K, N, parts):
+    """The one-launch form: the codes, accumulators and outputs of the two-launch form."""
+    print(f"fused M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N)
+    x = (torch.randn(M, K, generator=torch.Generator(device=DEV).manual_seed(K), device=DEV) * 0.3).half()
+    inv_m = torch.rand(K, device=DEV) + 0.5
+    run = lambda **kw: ptq.w8a8_linear_fused(x, inv_m, p.s_tok, p.w, p.s_w, p.bias, p.B, p.L, **kw)
+    check_kernel(run, *parts)
+    q = ptq.quantize_pts(x, inv_m, p.s_tok, p.B, p.L)
+    y = ptq.w8a8_linear(q, p.w, p.s_tok, p.s_w, p.bias, p.B, p.L)
+    acc64 = q.double() @ p.w.double().t()
+    assert close(run(), acc64, p.scale, p.bias)
+    codes = torch.empty_like(q)
+    y_dump = run(acc_out=p.acc, xq_out=codes)
+    assert torch.equal(codes, q) and torch.equal(p.acc.double(), acc64)
+    assert torch.equal(run().view(torch.int16), y.view(torch.int16)) and torch.equal(y_dump.view(torch.int16), y.view(torch.int16))
