@@ -1,6 +1,6 @@
 // Shared pieces of the MFMA linear kernels for gfx950: operand/accumulator types of the int8 and
 // fp16 paths, the kernel argument block, the LDS swizzle, the XCD-aware tile order, the MFMA loop over
-// one 64-byte slab, the fused dequantization epilogue and the zero-filling chunk loader.
+// one 64-byte slab and the dequantization epilogue of the tiled fused kernel, the zero-filling chunk loader.
 #pragma once
 #include <hip/hip_fp16.h>
 #include <math.h>
@@ -127,10 +127,9 @@ __device__ __forceinline__ bool tile_of_block(const LinearArgs &p, int &tile_r, 
     return true;
 }
 
-// MFMA work on one 64-byte slab held in LDS: x_rows/w_rows point at the wave's first row.
-template <class Path, int FO, int FR>
-__device__ __forceinline__ void mfma_slab(typename Path::Acc (&acc)[FO][FR], const char *x_rows, const char *w_rows,
-                                          int l32, int lhalf) {
+// MFMA work on one 64-byte slab held in LDS (int8): x_rows/w_rows point at the wave's first row.
+template <int FO, int FR>
+__device__ __forceinline__ void mfma_slab(Int8Path::Acc (&acc)[FO][FR], const char *x_rows, const char *w_rows, int l32, int lhalf) {
 #pragma unroll
     for (int s = 0; s < 2; s++) {
         const int kc = 2 * s + lhalf;
@@ -145,29 +144,14 @@ __device__ __forceinline__ void mfma_slab(typename Path::Acc (&acc)[FO][FR], con
             const int row = j * 32 + l32;
             fx[j] = *reinterpret_cast<const v4i *>(x_rows + row * kSlabBytes + ((kc ^ swizzle(row)) << 4));
         }
-        if constexpr (Path::kPacked4) {
 #pragma unroll
-            for (int half = 0; half < 2; half++) {
-                v4i ew[FO], ex[FR];
+        for (int i = 0; i < FO; i++)
 #pragma unroll
-                for (int i = 0; i < FO; i++) ew[i] = half ? Path::odd_codes(fw[i]) : Path::even_codes(fw[i]);
-#pragma unroll
-                for (int j = 0; j < FR; j++) ex[j] = half ? Path::odd_codes(fx[j]) : Path::even_codes(fx[j]);
-#pragma unroll
-                for (int i = 0; i < FO; i++)
-#pragma unroll
-                    for (int j = 0; j < FR; j++) acc[i][j] = Path::mfma(ew[i], ex[j], acc[i][j]);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < FO; i++)
-#pragma unroll
-                for (int j = 0; j < FR; j++) acc[i][j] = Path::mfma(fw[i], fx[j], acc[i][j]);
-        }
+            for (int j = 0; j < FR; j++) acc[i][j] = Int8Path::mfma(fw[i], fx[j], acc[i][j]);
     }
 }
 
-// Epilogue of one wavefront.  Accumulator register v of a lane in block (i, j):
+// Epilogue of one wavefront (int8).  Accumulator register v of a lane in block (i, j):
 //   token row       r = r_base + 32 j + (lane mod 32)
 //   output channel  o = o_base + 32 i + 8 (v / 4) + 4 (lane / 32) + (v mod 4)
 // A lane therefore owns 8-byte runs scattered over 32 rows.  The wavefront transposes its
@@ -178,9 +162,9 @@ __device__ __forceinline__ void mfma_slab(typename Path::Acc (&acc)[FO][FR], con
 // barrier is needed; the empty asm statements only stop the compiler from reordering LDS
 // accesses.  Column scales and biases are fetched per group of four channels (outer loops) so
 // that they do not have to live in registers next to the accumulators.
-template <class Path, int FO, int FR, int JB>
-__device__ __forceinline__ void epilogue(const typename Path::Acc (&acc)[FO][FR], const LinearArgs &p, char *patch,
-                                         int64_t r_base, int64_t o_base, int lane) {
+template <int FO, int FR, int JB>
+__device__ __forceinline__ void epilogue(const Int8Path::Acc (&acc)[FO][FR], const LinearArgs &p, char *patch, int64_t r_base, int64_t o_base,
+                                         int lane) {
     constexpr int WAVE_O = FO * 32;
     constexpr int CPR = WAVE_O / 8;           // 16-byte chunks per staged row
     constexpr int ROWS_PER_STORE = 64 / CPR;  // rows covered by one store instruction
@@ -195,30 +179,22 @@ __device__ __forceinline__ void epilogue(const typename Path::Acc (&acc)[FO][FR]
 #pragma unroll
     for (int jb = 0; jb < FR; jb += JB) {
         float row_scale[JB];
-        int row_z[JB];
 #pragma unroll
         for (int jj = 0; jj < JB; jj++) {
             const int64_t r = r_base + (jb + jj) * 32 + l32;
-            row_scale[jj] = 1.0f;
-            row_z[jj] = 0;
-            if constexpr (Path::kElemBytes == 1) row_scale[jj] = p.s_tok[(r < p.M ? r : 0) % p.L];
-            if constexpr (Path::kOffset) row_z[jj] = p.z_tok[(r < p.M ? r : 0) % p.L];
+            row_scale[jj] = p.s_tok[(r < p.M ? r : 0) % p.L];
         }
 #pragma unroll
         for (int i = 0; i < FO; i++) {
 #pragma unroll
             for (int g = 0; g < 4; g++) {
                 float col_scale[4], col_bias[4];
-                int col_sum[4];
 #pragma unroll
                 for (int c = 0; c < 4; c++) {
                     const int64_t o = o_base + i * 32 + g * 8 + lhalf * 4 + c;
                     const bool ok = o < p.N;
                     col_bias[c] = (ok && p.bias) ? __half2float(p.bias[o]) : 0.0f;
-                    col_scale[c] = 1.0f;
-                    col_sum[c] = 0;
-                    if constexpr (Path::kElemBytes == 1) col_scale[c] = ok ? p.s_w[o] : 0.0f;
-                    if constexpr (Path::kOffset) col_sum[c] = ok ? p.rowsum[o] : 0;
+                    col_scale[c] = ok ? p.s_w[o] : 0.0f;
                 }
 #pragma unroll
                 for (int jj = 0; jj < JB; jj++) {
@@ -226,21 +202,13 @@ __device__ __forceinline__ void epilogue(const typename Path::Acc (&acc)[FO][FR]
                     float out[4];
 #pragma unroll
                     for (int c = 0; c < 4; c++) {
-                        if constexpr (Path::kElemBytes == 1) {
-                            int a = acc[i][j][g * 4 + c];
-                            if constexpr (Path::kPacked4) a >>= 8;  // operands were codes times 16: exact
-                            if (p.acc_out) {
-                                const int64_t r = r_base + j * 32 + l32;
-                                const int64_t o = o_base + i * 32 + g * 8 + lhalf * 4 + c;
-                                if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = a;
-                            }
-                            int corrected = a;
-                            // 24-bit multiply (full rate): |z| < 2^8 and |rowsum| <= 127 K < 2^23 for every accepted K
-                            if constexpr (Path::kOffset) corrected = a - __mul24(row_z[jj], col_sum[c]);
-                            out[c] = (float)corrected * (row_scale[jj] * col_scale[c]) + col_bias[c];
-                        } else {
-                            out[c] = acc[i][j][g * 4 + c] + col_bias[c];
+                        const int a = acc[i][j][g * 4 + c];
+                        if (p.acc_out) {
+                            const int64_t r = r_base + j * 32 + l32;
+                            const int64_t o = o_base + i * 32 + g * 8 + lhalf * 4 + c;
+                            if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = a;
                         }
+                        out[c] = (float)a * (row_scale[jj] * col_scale[c]) + col_bias[c];
                     }
                     __half2 lo = __floats2half2_rn(out[0], out[1]);
                     __half2 hi = __floats2half2_rn(out[2], out[3]);
@@ -298,8 +266,8 @@ __device__ __forceinline__ uint32_t keep_low_bytes(uint32_t v, int nbytes) {
 
 // One 16-byte chunk of row `row_ptr` at byte offset `kb`; bytes at or beyond k_bytes read as 0.
 // LOAD_ALIGN 16: pitch and base are multiples of 16, so the full chunk is inside the row's pitch.
-// LOAD_ALIGN 4:  same with 4.  LOAD_ALIGN 0: element-wise (ELEM bytes each), any pitch.
-template <int LOAD_ALIGN, int ELEM>
+// LOAD_ALIGN 4:  same with 4.  LOAD_ALIGN 0: byte by byte, any pitch.
+template <int LOAD_ALIGN>
 __device__ __forceinline__ v4i load_chunk(const char *row_ptr, int64_t kb, int64_t k_bytes, bool row_ok) {
     v4i out = {0, 0, 0, 0};
     if (!row_ok || kb >= k_bytes) return out;
@@ -323,14 +291,8 @@ __device__ __forceinline__ v4i load_chunk(const char *row_ptr, int64_t kb, int64
         for (int j = 0; j < 4; j++) {
             uint32_t v = 0;
 #pragma unroll
-            for (int b = 0; b < 4; b += ELEM) {
-                if (4 * j + b < valid) {
-                    if constexpr (ELEM == 1)
-                        v |= (uint32_t) * reinterpret_cast<const uint8_t *>(row_ptr + kb + 4 * j + b) << (8 * b);
-                    else
-                        v |= (uint32_t) * reinterpret_cast<const uint16_t *>(row_ptr + kb + 4 * j + b) << (8 * b);
-                }
-            }
+            for (int b = 0; b < 4; b++)
+                if (4 * j + b < valid) v |= (uint32_t) * reinterpret_cast<const uint8_t *>(row_ptr + kb + 4 * j + b) << (8 * b);
             out[j] = (int)v;
         }
     }
@@ -355,18 +317,6 @@ inline bool set_grid(LinearArgs &a, dim3 &grid) {
 // this compiler reads every element of an integer-vector asm output from its first register.
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)p; }
 
-// eight 16-byte reads at base + STEP n (n = 0..3) and base + JUMP + STEP n
-template <int STEP, int JUMP>
-__device__ __forceinline__ void lds_read_8x_b128(uint32_t base, v4f (&v)[8]) {
-    asm volatile(
-        "ds_read_b128 %0, %8 offset:%9\n ds_read_b128 %1, %8 offset:%10\n ds_read_b128 %2, %8 offset:%11\n"
-        "ds_read_b128 %3, %8 offset:%12\n ds_read_b128 %4, %8 offset:%13\n ds_read_b128 %5, %8 offset:%14\n"
-        "ds_read_b128 %6, %8 offset:%15\n ds_read_b128 %7, %8 offset:%16\n s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(JUMP), "n"(JUMP + STEP), "n"(JUMP + 2 * STEP),
-          "n"(JUMP + 3 * STEP)
-        : "memory");
-}
 // four 16-byte reads at base + STEP n
 template <int STEP>
 __device__ __forceinline__ void lds_read_4x_b128(uint32_t base, v4f (&v)[4]) {
@@ -421,14 +371,6 @@ __device__ __forceinline__ void wait_vmcnt_at_most() {
 
 __device__ __forceinline__ void lds_read_1x_b128(uint32_t addr, v4f &v) {
     asm volatile("ds_read_b128 %0, %1\n s_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(addr) : "memory");
-}
-// two 16-byte reads at base and base + STEP
-template <int STEP>
-__device__ __forceinline__ void lds_read_2x_b128(uint32_t base, v4f (&v)[2]) {
-    asm volatile("ds_read_b128 %0, %2 offset:%3\n ds_read_b128 %1, %2 offset:%4\n s_waitcnt lgkmcnt(0)"
-                 : "=&v"(v[0]), "=&v"(v[1])
-                 : "v"(base), "n"(0), "n"(STEP)
-                 : "memory");
 }
 // Reads that are only ISSUED here (eight 4-byte reads at base + STEP n; three 16-byte reads at base +
 // STEP n): the caller must pass every destination through lds_wait_all before using it.

@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void linear_stream_smallk(const 
             const int packed_bytes = BITS4 ? K / 2 : K;
             for (int idx = tid; idx < lay.rows * (CPR / 2); idx += kStreamWaves * 64) {
                 const int row = idx / (CPR / 2), c = idx - row * (CPR / 2);
-                const v4i v = load_chunk<W_ALIGN, 1>(p.w + (int64_t)min(row, N - 1) * p.ldw_bytes, c * 16, packed_bytes, row < N);
+                const v4i v = load_chunk<W_ALIGN>(p.w + (int64_t)min(row, N - 1) * p.ldw_bytes, c * 16, packed_bytes, row < N);
                 v4i first, second;
                 if constexpr (BITS4) expand_nibbles_in_order(v, first, second);
                 else first = Int4Path::even_codes(v), second = Int4Path::odd_codes(v);
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void linear_stream_smallk(const 
         } else
         for (int idx = tid; idx < lay.rows * CPR; idx += kStreamWaves * 64) {
             const int row = idx / CPR, c = idx - row * CPR;
-            const v4i v = load_chunk<W_ALIGN, 1>(p.w + (int64_t)min(row, N - 1) * p.ldw_bytes, c * 16, K, row < N);
+            const v4i v = load_chunk<W_ALIGN>(p.w + (int64_t)min(row, N - 1) * p.ldw_bytes, c * 16, K, row < N);
             *reinterpret_cast<v4i *>(w_lds + row * lay.pitch + ((c ^ swz(row)) << 4)) = v;
         }
         for (int o = tid; o < lay.rows; o += kStreamWaves * 64) {
@@ -622,10 +622,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void linear_stream_smallk(const 
                     fx[jb][ks] = codes;
                 } else if constexpr (PACKED4) {
                     // int8 chunk 4 ks + lq comes from packed chunk (4 ks + lq) / 2: its even codes, or its odd ones
-                    const v4i packed = load_chunk<X_ALIGN, 1>(xrow, ((4 * ks + lq) >> 1) * 16, K, true);
+                    const v4i packed = load_chunk<X_ALIGN>(xrow, ((4 * ks + lq) >> 1) * 16, K, true);
                     fx[jb][ks] = (lq & 1) ? Int4Path::odd_codes(packed) : Int4Path::even_codes(packed);
                 } else {
-                    fx[jb][ks] = load_chunk<X_ALIGN, 1>(xrow, k0, K, true);
+                    fx[jb][ks] = load_chunk<X_ALIGN>(xrow, k0, K, true);
                 }
             }
         }
@@ -734,7 +734,6 @@ __global__ __launch_bounds__(kStreamWaves * 64) void linear_stream_smallk(const 
 // ------------------------------------------------------------------------------------------
 template <int BR, int BO, int WR, int WO, int X_ALIGN, int W_ALIGN>
 __global__ __launch_bounds__(kThreads, 2) void pts_linear_generic(const LinearArgs p) {
-    using Path = Int8Path;
     static_assert(WR * WO == kWaves, "four wavefronts per workgroup");
     constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO;
     constexpr int FR = WAVE_R / 32, FO = WAVE_O / 32;
@@ -742,7 +741,7 @@ __global__ __launch_bounds__(kThreads, 2) void pts_linear_generic(const LinearAr
     static_assert(BR * 4 % kThreads == 0, "every thread stages the same rows in every slab");
     constexpr int X_CHUNKS = BR * 4 / kThreads;  // 16-code chunks per thread per slab
     constexpr int W_CHUNKS = (BO * 4 + kThreads - 1) / kThreads;
-    using Acc = typename Path::Acc;
+    using Acc = Int8Path::Acc;
 
     __shared__ __attribute__((aligned(16))) char lds_x[2][BR * kSlabBytes];
     __shared__ __attribute__((aligned(16))) char lds_w[2][BO * kSlabBytes];
@@ -794,7 +793,7 @@ __global__ __launch_bounds__(kThreads, 2) void pts_linear_generic(const LinearAr
         for (int i = 0; i < W_CHUNKS; i++) {
             const int cid = tid + kThreads * i, row = cid >> 2, kc = cid & 3;
             const bool ok = (cid < BO * 4) && (o0 + row < p.N);
-            stage_w[i] = load_chunk<W_ALIGN, 1>(p.w + (o0 + row) * p.ldw_bytes, kb0 + kc * 16, p.k_bytes, ok);
+            stage_w[i] = load_chunk<W_ALIGN>(p.w + (o0 + row) * p.ldw_bytes, kb0 + kc * 16, p.k_bytes, ok);
         }
     };
     auto commit = [&](int buf) {
@@ -819,11 +818,11 @@ __global__ __launch_bounds__(kThreads, 2) void pts_linear_generic(const LinearAr
         const int buf = it & 1;
         const bool more = it + 1 < n_slabs;
         if (more) fetch((int64_t)(it + 1) * kSlabBytes);
-        mfma_slab<Path, FO, FR>(acc, &lds_x[buf][wave_r * kSlabBytes], &lds_w[buf][wave_o * kSlabBytes], l32, lhalf);
+        mfma_slab<FO, FR>(acc, &lds_x[buf][wave_r * kSlabBytes], &lds_w[buf][wave_o * kSlabBytes], l32, lhalf);
         if (more) commit(buf ^ 1);
         __syncthreads();
     }
-    epilogue<Path, FO, FR, JB>(acc, p, &lds_x[0][0] + wave * (JB * 32 * WAVE_O * 2), r0 + wave_r, o0 + wave_o, lane);
+    epilogue<FO, FR, JB>(acc, p, &lds_x[0][0] + wave * (JB * 32 * WAVE_O * 2), r0 + wave_r, o0 + wave_o, lane);
 }
 
 // ------------------------------------------------------------------------------------------

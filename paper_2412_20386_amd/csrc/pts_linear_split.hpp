@@ -95,6 +95,7 @@ template <Form FORM, int NB, int RB, int W, bool ALIGNED>
 __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
     using Path = typename FusedPath<FORM>::Path;
     constexpr bool BITS4 = FORM == Form::kBits4, OFFSET = FORM == Form::kOffset;
+    static_assert(ALIGNED || FORM == Form::kInt8, "the other forms exist for the shapes of the resident kernel only");
     constexpr int NL = 2 * RB;  // loads of 8 rows per step
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     constexpr int LDS_BYTES = W * RB * NB * 1024;  // partial sums; before that the wavefronts' code tiles (RB KiB each)
@@ -132,8 +133,7 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
 #pragma unroll
     for (int i = 0; i < NB; i++) wrow[i] = p.w + min(o0 + i * 16 + l16, p.N - 1) * p.ldw_bytes;
     const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + K * 2);
-    const int64_t w_row_bytes = BITS4 ? K / 2 : K;
-    const char *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + w_row_bytes);
+    const char *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + K);
 
     v4i acc[NB][RB];
 #pragma unroll
@@ -168,16 +168,10 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             if constexpr (BITS4) {
-                const int64_t kb = k0 / 2 + lq * 8;
-                if constexpr (ALIGNED) {
-                    f.w4[i] = *reinterpret_cast<const u32x2 *>(wrow[i] + kb);
-                } else {
-                    const v4i sixteen = load_any(wrow[i], kb, w_row_bytes, w_end);
-                    f.w4[i] = u32x2{(uint32_t)sixteen[0], (uint32_t)sixteen[1]};
-                }
+                f.w4[i] = *reinterpret_cast<const u32x2 *>(wrow[i] + k0 / 2 + lq * 8);
             } else {
                 f.w[i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + k0 + lq * 16)
-                                 : load_any(wrow[i], k0 + lq * 16, w_row_bytes, w_end);
+                                 : load_any(wrow[i], k0 + lq * 16, K, w_end);
             }
         }
     };
