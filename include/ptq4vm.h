@@ -132,8 +132,8 @@ int ptq4vm_w8a8_linear(const int8_t *xq, const int8_t *wq, const float *s_tok, c
  * [-128, 127]) and rowsum [N] int32.  acc_out receives the raw accumulators (before the correction).
  * K <= PTQ4VM_MAX_K_OFFSET keeps acc - z * rowsum inside int32 and |rowsum| <= 128 K inside 24 signed
  * bits: the kernels form z * rowsum with a 24-bit multiply, so z_tok outside [-128, 127] or a rowsum
- * that is not the weight's row sum gives undefined results (not checked).  Runs on the same tiled,
- * persistent and short-reduction kernels as ptq4vm_w8a8_linear.
+ * that is not the weight's row sum gives undefined results (not checked).  Runs on the same tile,
+ * persistent and row-streaming kernels as ptq4vm_w8a8_linear.
  */
 #define PTQ4VM_MAX_K_OFFSET 65536
 int ptq4vm_quantize_pts_offset(const void *x_f16, const float *inv_m, const float *s_tok, const int32_t *z_tok,
@@ -154,7 +154,7 @@ int ptq4vm_w8a8_linear_offset(const int8_t *xq, const int8_t *wq, const float *s
  *   ptq4vm_w4a4_linear        as ptq4vm_w8a8_linear on packed operands; acc_out holds sum_k xq wq
  * gfx950 has no int4 MFMA: packed operands are expanded in registers to int8 right before the
  * int8 MFMA, so the gain over W8A8 is in bytes moved, not in MFMA rate.  The linear runs on the
- * tiled, persistent (128-row tiles) and short-reduction kernels of ptq4vm_w8a8_linear.  Errors as
+ * tile, persistent (128-row tiles) and row-streaming kernels of ptq4vm_w8a8_linear.  Errors as
  * for the 8-bit entry points, plus odd K -> PTQ4VM_ERR_SHAPE and K > PTQ4VM_MAX_K_W4 ->
  * PTQ4VM_ERR_SHAPE: the kernels multiply codes scaled by 16, so the int32 accumulator holds 256 times
  * the sum, and with the nibble -8 accepted on input (the quantizers never emit it) |256 acc| can reach
@@ -190,7 +190,8 @@ int ptq4vm_w4a4_linear(const uint8_t *xq4, const uint8_t *wq4, const float *s_to
  * xq6 / wq6 are 16-byte aligned; any K >= 1 (odd K too).  Errors as for the 4-bit entry points, with
  * K > PTQ4VM_MAX_K_E2M3 -> PTQ4VM_ERR_SHAPE and a plane pitch below 96 R or not a multiple of 16 -> PTQ4VM_ERR_STRIDE.
  * The linear runs on a persistent 256 x 256-tile kernel (K a multiple of 128 and >= 256, N a multiple of 8,
- * 16-byte aligned y rows, enough tiles to fill the device) or on smaller tiles (every other shape).
+ * 16-byte aligned y rows, tiles that fill nearly one round of the device or two and more) or on smaller tiles (every
+ * other shape).
  */
 #define PTQ4VM_E2M3_BLOCKS(K) ((((int64_t)(K)) + 127) / 128)
 #define PTQ4VM_MAX_K_E2M3 262144
@@ -208,9 +209,10 @@ int ptq4vm_w4a4_linear_e2m3(const uint8_t *xq6, const uint8_t *wq6, const float 
  * Computes exactly, bit for bit, what ptq4vm_quantize_pts followed by ptq4vm_w8a8_linear
  * compute; the int8 codes stay on chip.  Worth using over many rows when the output is narrow
  * (N <= 128 over >= 4096 rows, e.g. x_proj: every activation element is read and quantized once)
- * or the reduction short (K <= 128 over >= 16384 rows, e.g. dt_proj); for wide outputs a tiled GEMM
- * would re-quantize each element once per tile column and below ~2000 rows only that tiled kernel
- * applies: the two separate calls are faster there, but every shape is accepted.
+ * or the reduction short (K <= 128 over >= 16384 rows, e.g. dt_proj) and the weight small enough for
+ * the chip's local memory: about 1600 channels up to K = 64, 900 up to K = 128.  Other wide outputs
+ * over more than 2048 rows run on a tiled kernel that re-quantizes each element once per tile column:
+ * the two separate calls are several times faster there, but every shape is accepted.
  *   x_f16    [B*L, ldx]  fp16 in
  *   inv_m    [K]         f32  in   may be NULL (no smoothing)
  *   s_tok    [L]         f32  in
@@ -235,8 +237,9 @@ int ptq4vm_w8a8_linear_fused(const void *x_f16, const float *inv_m, const float 
  *   wq4      [N, ldwq]   packed 4-bit codes in (two per byte, even index in the low nibble; ldwq in bytes >= K / 2)
  *   s_tok    [L]         the 4-bit steps
  *   xq_out   [B*L, ldxq] int8 out; may be NULL (parity aid: the 4-bit codes the GEMM consumed, ONE per byte)
- * Runs on the weight-resident kernel (N <= 128, K a multiple of 64, >= 2048 rows, 16-byte aligned rows of x and
- * wq4) and on the row-streaming kernel (K <= 128, >= 1024 rows): the shapes where fusing pays (x_proj, dt_proj).
+ * Exists for N <= 128, K a multiple of 64, >= 2048 rows, 16-byte aligned rows of x and wq4 (from 4096 rows with the
+ * weight resident on chip, below with the reduction split over a workgroup) and for K <= 128, >= 1024 rows as long as
+ * the weight fits the chip's local memory (row-streaming kernel): the shapes where fusing pays (x_proj, dt_proj).
  * Every other shape returns PTQ4VM_ERR_SHAPE - call ptq4vm_quantize_pts_a4 and ptq4vm_w4a4_linear there.
  * Errors otherwise as ptq4vm_w4a4_linear / ptq4vm_w8a8_linear_fused (odd K, K > PTQ4VM_MAX_K_W4 -> PTQ4VM_ERR_SHAPE).
  */
@@ -251,8 +254,9 @@ int ptq4vm_w4a4_linear_fused(const void *x_f16, const float *inv_m, const float 
  * accumulators and outputs as the two calls, bit for bit.  Arguments as ptq4vm_w8a8_linear_fused plus z_tok [L] int32
  * and rowsum [N] int32 as in ptq4vm_w8a8_linear_offset; acc_out receives the raw accumulators (before the correction),
  * xq_out the codes with the offset in them.
- * Runs on the weight-resident kernel (N <= 128, K a multiple of 64, >= 2048 rows, 16-byte aligned rows of x and wq)
- * and on the row-streaming kernel (K <= 128, >= 1024 rows): the shapes where fusing pays (x_proj, dt_proj).  Every
+ * Exists for N <= 128, K a multiple of 64, >= 2048 rows, 16-byte aligned rows of x and wq (from 4096 rows with the
+ * weight resident on chip, below with the reduction split over a workgroup) and for K <= 128, >= 1024 rows as long as
+ * the weight fits the chip's local memory (row-streaming kernel): the shapes where fusing pays (x_proj, dt_proj).  Every
  * other shape returns PTQ4VM_ERR_SHAPE - call the two entry points there.
  * Errors otherwise as ptq4vm_w8a8_linear_fused, with NULL z_tok / rowsum -> PTQ4VM_ERR_NULL and
  * K > PTQ4VM_MAX_K_OFFSET -> PTQ4VM_ERR_SHAPE.

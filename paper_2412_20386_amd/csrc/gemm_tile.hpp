@@ -233,9 +233,9 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
 // ------------------------------------------------------------------------------------------
 // One BR x BO tile per workgroup.  K is walked in slabs of SLAB bytes per row through a ring of STAGES LDS stages; what
 // bounds a workgroup is the latency of its copies and of its stores, so the shape of the kernel is small: few registers
-// and 32 - 74 KiB of LDS let 2 - 5 workgroups share a CU, and one's epilogue runs under the others' MFMAs without any
-// pipelining inside the workgroup.  The step, bias and offset vectors are fetched before the first copy and wait in
-// LDS, and results cross a wavefront-private patch into 16-byte stores of whole row segments (25216 x 768 -> 384: 15.6 us
+// and 33 - 76 KiB of LDS (17 - 66 with the slabs through registers) let 2 - 4 (2 - 8) workgroups share a CU, and one's
+// epilogue runs under the others' MFMAs without any pipelining inside the workgroup.  The step, bias and offset vectors
+// are fetched before the first copy and wait in LDS, and results cross a wavefront-private patch into 16-byte stores of whole row segments (25216 x 768 -> 384: 15.6 us
 // = 2.5 TB/s, 22.3 us with the tile kernel before, whose epilogue loaded each scale where it was used).
 // COPY kDirect: 16-byte aligned bases and pitches, k_bytes % 64 == 0; slabs are copied global -> LDS directly.  Otherwise any
 // pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).  Only the last

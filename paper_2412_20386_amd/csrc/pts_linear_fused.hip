@@ -11,8 +11,10 @@
 // quantizer is cheaper.  Kernels:
 //   pts_linear_wres     N <= 128 over many rows (x_proj): weight resident in LDS, every fp16
 //                       activation read once from HBM in whole 128-byte lines, quantized once.
-//   pts_linear_split    the same below 4096 rows or at any alignment, and few rows of any width: the reduction spread over a
-//                       workgroup's wavefronts (pts_linear_split.hpp).
+//   pts_linear_split    the same below 4096 rows or at any alignment, and up to 2048 rows of any width: the reduction spread
+//                       over a workgroup's wavefronts (pts_linear_split.hpp).
+//   linear_stream_smallk  K <= 128 from 1024 rows, as long as the whole weight fits the LDS (some 900 channels, 1660 up to
+//                       64 codes): y streamed out in whole rows; also the two-launch form's kernel from 20 480 rows.
 //   pts_linear_generic  every other shape: the register-staged tiled kernel with the quantizer in
 //                       its loader (correct everywhere, re-quantizes per tile column).
 #include <type_traits>
@@ -65,8 +67,8 @@ constexpr int kFusedWaves = 16 / kFusedRB;
 constexpr int kFusedPatchRows = 8 * kFusedRB;   // result rows staged per pass of the epilogue
 constexpr int kFusedMaxBlocks = 8;   // 16-channel blocks: N <= 128
 constexpr int kLdsBytes = 160 * 1024;
-constexpr int64_t kFusedMinRowsResident = 4096;  // from here the weight-resident kernel, below it the split reduction
-constexpr int64_t kFusedMinRows = 2048;   // below this the one-off table copies per workgroup do not pay (4 k rows: 11 us against 48 us for the tiled fused kernel at 384 -> 44)
+constexpr int64_t kFusedMinRowsResident = 4096;  // from here the weight-resident kernel, below it the split reduction (dispatch)
+constexpr int64_t kFusedMinRows = 2048;          // from here all three forms exist
 
 struct FusedLayout {
     int nb, n4, pw, w_bytes, inv_m_off, inv_s_off, z_off, scale_off, tile_off, tile_bytes, total;
@@ -862,7 +864,7 @@ int launch_split(LinearArgs a, hipStream_t stream) {
     return ptq4vm::check_launch("pts_linear_split");
 }
 // Eight wavefronts on 16 rows while that gives every CU at most one workgroup, four on 32 rows beyond (us, 8 x 16 / 4 x 32
-// rows: 2364 x 768 -> 56 5.6 / 8.3, 4137 x 1536 -> 80 13.5 / 12.9, 12608 x 768 -> 56 13.3 / 10.8).
+// rows: 2364 x 768 -> 56 5.6 / 8.3, 4137 x 1536 -> 80 13.3 / 12.9, 12608 x 768 -> 56 13.3 / 10.8).
 template <Form FORM, bool ALIGNED>
 int launch_split_rows(const LinearArgs &a, hipStream_t stream) {
     return ptq4vm::ceil_div(a.M, 16) * ptq4vm::ceil_div(a.N, 128) <= 256 ? launch_split<FORM, 1, 8, ALIGNED>(a, stream)
@@ -961,9 +963,11 @@ int dispatch(LinearArgs a, hipStream_t stream, Form form = Form::kInt8) {
                          a.M >= kFusedMinRows && a.L <= 65536 &&
                          (!a.xq_out || (ptq4vm::aligned_to(a.xq_out, 8) && a.ldxq_out % 8 == 0)) &&
                          fused_layout((int)a.N, (int)a.k_bytes, (int)a.L, form == Form::kOffset).total <= kLdsBytes;
-    // with fewer rows the resident kernel leaves CUs idle and the reduction is split over a workgroup instead
-    // (us, split / resident: 4137 x 384 -> 44 6.3 / 5.8, 4137 x 1536 -> 80 14.1 / 10.3, 12608 x 1536 -> 80 19.7 / 13.0,
-    // 25216 x 768 -> 56 19.4 / 12.4)
+    // Up to 4095 rows the split reduction has at most one workgroup of 16 rows a CU and is faster for every width and
+    // length (us, split / resident: 2364 x 1536 -> 80 8.9 / 10.3, 4090 x 384 -> 44 4.7 / 6.2, 4090 x 768 -> 56 6.0 / 7.0, 4090 x
+    // 1536 -> 80 9.1 / 10.2; over 1500 shapes of 2048 .. 4095 rows the resident kernel takes 1.1 to 2.7 times as long).  The
+    // first row of a second round costs it the most where the reduction is long (4137 x 1536 -> 80 13.3 / 10.4, 12608 x 1536
+    // -> 80 19.7 / 13.0, 25216 x 768 -> 56 19.4 / 12.4, but 4137 x 384 -> 44 5.3 / 6.1, 4137 x 768 -> 56 7.0 / 6.9).
     if (wres_ok) return a.M < kFusedMinRowsResident ? launch_split_form(a, stream, form) : launch_wres(a, stream, form);
     if (a.k_bytes <= 128) {
         const int rc = launch_stream_smallk(a, true, stream, form == Form::kBits4, form == Form::kOffset);

@@ -24,10 +24,10 @@ import statistics
 import sys
 
 OURS = ("linear_", "pts_linear", "quantize_", "fold_smoothing", "weight_rowsum", "count_bad_scales", "sum_bad_scales")
-BASES = ("linear_e2m3_persistent", "linear_e2m3_generic", "quantize_pts_a4_e2m3_blocks", "quantize_pts_a4_e2m3_stream",
-         "quantize_pts_a4_e2m3_generic", "fold_smoothing_w4_e2m3_rows", "linear_mfma_wreg", "linear_mfma_persistent", "linear_mfma_smallk", "linear_mfma_dma", "linear_mfma_generic",
-         "linear_mfma_wres", "linear_stream_smallk", "pts_linear_wres", "pts_linear_generic", "quantize_pts_a4_stream",
-         "quantize_pts_stream", "quantize_pts_generic", "quantize_dynamic_rows", "fold_smoothing_w4_rows",
+BASES = ("linear_e2m3_persistent", "linear_e2m3_tile", "linear_e2m3_splitk", "quantize_pts_a4_e2m3_blocks", "quantize_pts_a4_e2m3_stream",
+         "quantize_pts_a4_e2m3_generic", "fold_smoothing_w4_e2m3_rows", "linear_mfma_wreg", "linear_mfma_persistent", "linear_mfma_smallk",
+         "linear_mfma_tile", "linear_mfma_splitk", "linear_stream_smallk", "pts_linear_wres", "pts_linear_split", "pts_linear_generic",
+         "quantize_pts_stream", "quantize_pts_any", "quantize_dynamic_rows", "quantize_dynamic_generic", "fold_smoothing_w4_rows",
          "fold_smoothing_rows", "weight_rowsum_rows", "count_bad_scales", "sum_bad_scales")
 COPY_KIB = 262144.0  # bench.py's calibration copy
 
@@ -56,8 +56,18 @@ def short(name: str) -> str:
         if tag == "<fused int8>":
             tag = "<fused>"
     if base == "pts_linear_wres":  # <channel blocks, depth, parity aids, 4-bit, zero offset>
-        f = flags(r"wresILi\d+ELi\d+ELb[01]ELb([01])ELb([01])E", r"wres<\d+, \d+, (?:true|false), (true|false), (true|false)>") or [False, False]
+        f = flags(r"wresILi\d+ELi\d+ELb[01]ELb([01])ELb([01])E", r"wres<\d+, \d+, (?:true|false), (true|false), (true|false)") or [False, False]
         tag = "<int4>" if f[0] else ("<int8+offset>" if f[1] else "")
+    if base in ("quantize_pts_stream", "quantize_pts_any", "pts_linear_split"):  # the form comes first in the template arguments
+        m = re.search(r"Form\)(\d)|FormE(\d)E", name)
+        if m:
+            forms = ("", "<int4>", "<int8+offset>") if base == "pts_linear_split" else ("", "<int8+offset>", "<int4>")
+            tag = forms[int(m.group(1) or m.group(2))]
+    if base in ("linear_mfma_tile", "linear_e2m3_tile"):  # tile rows x channels
+        m = re.search(r"tile<(?:[\w:]+Path, )?(\d+), (\d+),|tileI(?:NS\d*_\w*?PathE)?Li(\d+)ELi(\d+)E", name)
+        if m:
+            rows, cols = m.group(1) or m.group(3), m.group(2) or m.group(4)
+            tag = f"{tag[:-1]} {rows}x{cols}>" if tag else f"<{rows}x{cols}>"
     if base == "linear_mfma_wreg":
         tag = "<K=768>" if ("ILi12E" in name or "<12," in name) else "<K=384>"
     return base + tag
