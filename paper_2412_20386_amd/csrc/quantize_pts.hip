@@ -95,8 +95,8 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_pts_stream(
     const int chunk8 = (int)(gtid - row32 * (uint32_t)chunks) * 8;
     const int col = ALIGNED ? chunk8 : min(chunk8, K - 8);
     int64_t row = row32;
-    int t = (int)(row32 % (uint32_t)L);
-    const int t_step = (int)(row_step % L);
+    uint32_t t = row32 % (uint32_t)L;  // (unsigned: t + t_step passes 2^31 for the longest sequences)
+    const uint32_t t_step = (uint32_t)(row_step % L);
     const __half *xp = x + row * ldx + col;
     uint8_t *qp = xq + row * ldxq + (FORM == Form::kBits4 ? col / 2 : col);
     const int64_t x_step = row_step * ldx, q_step = row_step * ldxq;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_pts_stream(
             is[u] = TABLE ? inv_s_lds[t] : 1.0f / s_tok[t];
             zs[u] = kOffset ? (TABLE ? z_lds[t] : z_tok[t]) : 0;
             t += t_step;
-            if (t >= L) t -= L;
+            if (t >= (uint32_t)L) t -= (uint32_t)L;
         }
     };
     auto finish = [&]() {

@@ -84,8 +84,8 @@ __global__ __launch_bounds__(kThreads) void quantize_pts_a4_e2m3_stream(const __
         for (; row < M; row += row_step) store_group(xq6, row, group, ldxq, zero);
         return;
     }
-    int t = (int)(row % L);
-    const int t_step = (int)(row_step % L);
+    uint32_t t = (uint32_t)(row % L);  // (unsigned: t + t_step passes 2^31 for the longest sequences)
+    const uint32_t t_step = (uint32_t)(row_step % L);
     float im[kGroupCodes];
 #pragma unroll
     for (int i = 0; i < kGroupCodes; i++) im[i] = HAS_M ? inv_m[group * kGroupCodes + i] : 1.0f;
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void quantize_pts_a4_e2m3_stream(const __
         for (int c = 0; c < 4; c++) in[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(xp) + c);
         const float inv_s = LDS_TABLE ? inv_s_lds[t] : 1.0f / s_tok[t];
         t += t_step;
-        if (t >= L) t -= L;
+        if (t >= (uint32_t)L) t -= (uint32_t)L;
         float v[kGroupCodes];
 #pragma unroll
         for (int c = 0; c < 4; c++)

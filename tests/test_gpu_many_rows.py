@@ -1,5 +1,6 @@
 """Row counts at which one workgroup per small tile would be 2^32 threads or more, the limit of a grid dimension: the tile
-kernels and the split reduction of the fused form.  Steps are powers of two, so outputs are exact."""
+kernels and the split reduction of the fused form; and the longest sequence of the quantizers.  Steps are powers of two, so
+outputs are exact."""
 import pytest
 import torch
 
@@ -50,3 +51,25 @@ def test_w8a8_linears_beyond_two_billion_rows():
     for lo in range(0, M, CHUNK):
         hi = min(M, lo + CHUNK)
         assert torch.equal(y[lo:hi], x[lo:hi] * 3), lo
+
+
+def test_quantizers_longest_sequence():
+    """L = 2^31 - 1: the token position that follows a thread's last row lies beyond 2^31."""
+    L, K = 2 ** 31 - 1, 8
+    print(f"quantizers L={L} K={K}", flush=True)
+    x = torch.empty((L, K), dtype=torch.float16, device=DEV)
+    for lo in range(0, L, CHUNK):
+        hi = min(L, lo + CHUNK)
+        x[lo:hi] = (_rows(lo, hi) % 127 - 63).half()[:, None]
+    s_tok = torch.ones(L, device=DEV)
+    s_tok[1::2] = 0.5
+    for quantize, dtype in ((ptq.quantize_pts, torch.int8), (ptq.quantize_pts_a4, torch.uint8)):
+        q = quantize(x, None, s_tok, 1, L)
+        for lo in range(0, L, CHUNK):
+            hi = min(L, lo + CHUNK)
+            want = (_rows(lo, hi) % 127 - 63) * (1 + _rows(lo, hi) % 2)
+            if dtype is torch.uint8:
+                want = want.clamp(-7, 7) & 15
+                want = want | (want << 4)
+            assert bool((q[lo:hi] == want.to(dtype)[:, None]).all()), lo
+        del q
