@@ -28,7 +28,6 @@ namespace mfma {
 namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v2i __attribute__((ext_vector_type(2)));
 
 constexpr int kBlockBytes = 96;  // one row's 128 codes: 4 x 16 bytes (groups' low parts), 4 x 8 bytes (high parts)
 
@@ -45,110 +44,21 @@ struct E2m3Path {
     static constexpr int kElemBytes = 1;
     static constexpr bool kOffset = false;
     static constexpr bool kPacked4 = false;
+    static constexpr bool kE2m3 = true;
     using Acc16 = v4f;
+    using Frag = v8i;
+    static __device__ __forceinline__ Acc16 mfma16(const Frag &w, const Frag &x, const Acc16 &c) { return mfma_e2m3(w, x, c); }
+    static __device__ __forceinline__ Frag make_fragment(const v4i &lo, const v2i &hi) { return mfma::make_fragment(lo, hi); }
 };
 
 // ------------------------------------------------------------------------------------------
-// One BR x BO tile per workgroup, the structure of linear_mfma_tile (gemm_tile.hpp): a ring of STAGES stages, each one
-// 128-code block of the tile's rows, filled by direct global -> LDS copies; several small workgroups per CU overlap each
-// other's copies, MFMAs and stores.  A block of the tile's rows is one contiguous span of the container; a stage row
-// is the 96-byte block as in memory, except that rows whose bit 3 is set keep their two high-part chunks swapped (bank
-// conflicts, see the persistent kernel).  3152 x 384 -> 1536 takes 6.1 us = 620
-// TOP/s (18.4 us with the register-staged 64 x 64 kernel before), 25216 x 1536 -> 768 28.6 us = 2.1 POP/s.
+// One BR x BO tile per workgroup: direct_tile of gemm_tile.hpp with ring stages of one 128-code block.  A block of the tile's rows is
+// one contiguous span of the container; a stage row is the 96-byte block as in memory, except that rows whose bit 3 is set keep
+// their two high-part chunks swapped (bank conflicts, see the persistent kernel).
 // ------------------------------------------------------------------------------------------
-template <int BR, int BO, int STAGES>
-constexpr int e2m3_tile_lds_bytes() {
-    return STAGES * (BR + BO) * kBlockBytes + tile_vector_bytes<BR, BO>();
-}
-
-template <int BR, int BO, int WR, int WO, int STAGES>
-__global__ __launch_bounds__(64 * WR * WO) void linear_e2m3_tile(const LinearArgs p) {
-    constexpr int NW = WR * WO, THREADS = 64 * NW;
-    constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
-    constexpr int STAGE_BYTES = (BR + BO) * kBlockBytes;
-    constexpr int X_COPIES = BR * kBlockBytes / 1024, ALL_COPIES = STAGE_BYTES / 1024, COPIES = (ALL_COPIES + NW - 1) / NW;
-    static_assert(BR % 32 == 0 && BO % 32 == 0, "whole 1 KiB copies");
-    static_assert((STAGES - 2) * COPIES <= 63, "vmcnt is a 6-bit counter");
-
-    int tile_r, tile_o;
-    if (!tile_of_block(p, tile_r, tile_o)) return;
-    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
-    const int l16 = lane & 15, lq = lane >> 4;
-    const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
-
-    char *const ring = lds_dyn;
-    TileVectors<E2m3Path, BR, BO, THREADS> vec(lds_dyn + STAGES * STAGE_BYTES);
-    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
-
-    // Every wavefront issues the same number of copies: those beyond the last repeat it.  Rows beyond the matrix fetch
-    // its last 16 bytes; they are never stored.
-    uint32_t off[COPIES];
-#pragma unroll
-    for (int i = 0; i < COPIES; i++) {
-        const int c = min(wave + NW * i, ALL_COPIES - 1);
-        const bool is_x = c < X_COPIES;
-        const int piece = (is_x ? c : c - X_COPIES) * 64 + lane;  // 16-byte pieces, 6 a row
-        const int row = piece / 6, chunk = piece - row * 6;
-        const int src = row * 6 + (chunk >= 4 && (row & 8) ? 9 - chunk : chunk);
-        off[i] = (uint32_t)min(src, (is_x ? rows_valid : cols_valid) * 6 - 1) * 16;
-    }
-    const char *const gx = p.x + r0 * kBlockBytes, *const gw = p.w + o0 * kBlockBytes;
-    auto issue = [&](int block, int stage) {
-#pragma unroll
-        for (int i = 0; i < COPIES; i++) {
-            const int c = min(wave + NW * i, ALL_COPIES - 1);  // scalar
-            const char *src = c < X_COPIES ? gx + block * p.ldx_bytes : gw + block * p.ldw_bytes;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off[i]),
-                                             (__attribute__((address_space(3))) void *)(ring + stage * STAGE_BYTES + c * 1024), 16, 0, 0);
-        }
-    };
-
-    v4f acc[FO][FR];
-#pragma unroll
-    for (int i = 0; i < FO; i++)
-#pragma unroll
-        for (int j = 0; j < FR; j++) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-
-    const int n_blocks = (int)(p.k_bytes / kBlockBytes);
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; s++)
-        if (s < n_blocks) issue(s, s);
-    vec.park(tid);
-
-    int stage = 0;
-    for (int it = 0; it < n_blocks; it++) {
-        constexpr int KEEP = (STAGES - 2) * COPIES;  // younger blocks that may stay in flight
-        if (it + STAGES - 2 < n_blocks)
-            wait_vmcnt_at_most<KEEP>();
-        else
-            wait_vmcnt_at_most<0>();
-        if (it == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the scale vectors are in LDS
-        __builtin_amdgcn_s_barrier();  // everyone's copies of block `it` are visible; block it-1 is fully consumed
-        int refill = stage + STAGES - 1;
-        if (refill >= STAGES) refill -= STAGES;
-        if (it + STAGES - 1 < n_blocks) issue(it + STAGES - 1, refill);
-        const char *sx = ring + stage * STAGE_BYTES + wave_r * kBlockBytes;
-        const char *sw = ring + stage * STAGE_BYTES + (BR + wave_o) * kBlockBytes;
-        auto fragment = [&](const char *rows, int row) {
-            const char *r = rows + row * kBlockBytes;  // (wave rows start at multiples of 16: bit 3 is that of the tile's row)
-            return make_fragment(*reinterpret_cast<const v4i *>(r + lq * 16),
-                                 *reinterpret_cast<const v2i *>(r + 64 + ((lq * 8) ^ ((row & 8) << 1))));
-        };
-        v8i fw[FO];
-#pragma unroll
-        for (int i = 0; i < FO; i++) fw[i] = fragment(sw, i * 16 + l16);
-#pragma unroll
-        for (int j = 0; j < FR; j++) {
-            const v8i fx = fragment(sx, j * 16 + l16);
-#pragma unroll
-            for (int i = 0; i < FO; i++) acc[i][j] = mfma_e2m3(fw[i], fx, acc[i][j]);
-        }
-        if (++stage == STAGES) stage = 0;
-    }
-    __syncthreads();  // the ring becomes the wavefronts' transposition patches
-    store_tile<E2m3Path, BR, BO, WR, WO, STAGES * STAGE_BYTES>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+template <int BR, int BO, int WR, int WO, int STAGES, bool DUMP>
+__global__ __launch_bounds__(64 * WR * WO, (tile_waves<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES>())) void linear_e2m3_tile(const TileArgs p) {
+    direct_tile<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES, DUMP, tile_is_tight<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES>()>(p);
 }
 
 // Split reduction (see linear_mfma_splitk): wavefront w takes the 128-code blocks w, w + SK, ... with U blocks of operands
@@ -520,15 +430,16 @@ int launch_persistent(LinearArgs a, hipStream_t stream) {
 }
 
 template <int BR, int BO, int WR, int WO, int STAGES>
-int launch_tile(LinearArgs a, hipStream_t stream) {
+int launch_tile(const LinearArgs &a, hipStream_t stream) {
+    TileArgs t;
     dim3 grid;
-    if (!set_grid<BR, BO>(a, grid)) return PTQ4VM_ERR_SHAPE;
-    constexpr int lds_bytes = e2m3_tile_lds_bytes<BR, BO, STAGES>();
-    auto kernel = linear_e2m3_tile<BR, BO, WR, WO, STAGES>;
+    if (!tile_args<BR, BO>(a, t, grid)) return PTQ4VM_ERR_SHAPE;
+    constexpr int lds_bytes = tile_lds_bytes<BR, BO, kBlockBytes, STAGES>();
+    auto kernel = a.acc_out ? linear_e2m3_tile<BR, BO, WR, WO, STAGES, true> : linear_e2m3_tile<BR, BO, WR, WO, STAGES, false>;
     if constexpr (lds_bytes > 64 * 1024) {
         if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_e2m3_tile)")) return rc;
     }
-    kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(a);
+    kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(t);
     return ptq4vm::check_launch("linear_e2m3_tile");
 }
 

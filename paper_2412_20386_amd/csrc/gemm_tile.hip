@@ -8,15 +8,19 @@ using namespace ptq4vm::mfma;
 int64_t tiles(const LinearArgs &a, int br, int bo) { return ptq4vm::ceil_div(a.M, br) * ptq4vm::ceil_div(a.N, bo); }
 
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY>
-int launch(LinearArgs a, hipStream_t stream) {
+int launch(const LinearArgs &a, hipStream_t stream) {
+    TileArgs t;
     dim3 grid;
-    if (!set_grid<BR, BO>(a, grid)) return PTQ4VM_ERR_SHAPE;
+    if (!tile_args<BR, BO>(a, t, grid)) return PTQ4VM_ERR_SHAPE;
     constexpr int lds_bytes = tile_lds_bytes<BR, BO, SLAB, STAGES>();
-    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, COPY>;
+    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, false, COPY>;
+    if constexpr (Path::kElemBytes == 1) {
+        if (a.acc_out) kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, true, COPY>;
+    }
     if constexpr (lds_bytes > 64 * 1024) {
         if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_mfma_tile)")) return rc;
     }
-    kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(a);
+    kernel<<<grid, dim3(64 * WR * WO), lds_bytes, stream>>>(t);
     return ptq4vm::check_launch("linear_mfma_tile");
 }
 
@@ -38,22 +42,20 @@ int launch_splitk(LinearArgs a, hipStream_t stream) {
 
 // The rule: the largest tile that still leaves the 256 CUs a few workgroups each, because a larger tile moves fewer
 // operand bytes per product, but a CU needs several resident workgroups to overlap one's copies and stores with
-// another's MFMAs.  The thresholds were read off sweeps over 130 random and model shapes (M 50 .. 50 432, K 24 .. 2048,
-// N 16 .. 3072, int8 and fp16): the rule costs 2 % on average against the best tile of each shape.  Around the lines
-// (us, int8 unless said; tiles in brackets):
-//   128 x 256 against 128 x 128, 800 tiles:  12608 x 768 -> 3072 [1188] 46.6 / 52.0;   9485 x 512 -> 1328 [450] 15.0 / 16.0, but 16346 x 384 -> 464 [256] 10.0 / 9.2
-//   128 x 128 against 64 x 128, 384 tiles:   50432 x 1536 -> 80 [394] 17.0 / 22.8;     12608 x 384 -> 192 [198] 5.3 / 5.4, 6304 x 768 -> 384 [150] 6.8 / 6.8
-//   64 x 128 against 64 x 64, 384 tiles:     3152 x 384 -> 1536 [600] 7.2 / 7.9;       1576 x 384 -> 1536 [300] 5.5 / 5.0
-//   64 x 64 against 32 x 64, 190 tiles:      197 x 768 -> 3072 [192] 4.8 / 5.9;        197 x 1536 -> 768 [48] 5.5 / 5.0
-//   split reduction, 256 blocks of 16 x 16:  197 x 1536 -> 80 [65] 3.8 / 4.8 (32 x 64); 659 x 256 -> 232 [630] 3.3 / 2.9
-// 128 x 128 tiles: three 64-byte stages are 48 KiB, a third workgroup per CU, and waste no half slab; over a long reduction
-// twice the barriers cost more (12608 x 192 -> 768 9.0 / 10.8, 6304 x 384 -> 1536 11.2 / 11.8, 50240 x 768 -> 384 32.0 / 33.4,
-// but 12608 x 1536 -> 768 25.0 / 24.6).
-// A tile that pads the matrix by a third more than the best one is passed over.  Two or three ring stages of 64 x 64
-// tiles: three hold more of a long reduction in flight while few tiles are resident anyway (6304 x 1536 -> 80 [198]
-// 6.2 / 8.0), two leave room for a fourth workgroup per CU (788 x 768 -> 3072 [624] 7.3 / 7.9).
-// Before these kernels everything here ran on 256 x 128 tiles: 12.3 .. 24 us for the 197-row shapes (now 2.9 .. 5.5),
-// 17.3 us for 3152 x 768 -> 384 (5.0), 36.0 us for 12608 x 1536 -> 768 (24.4), 72 us for 19231 x 960 -> 1057 (33.4).
+// another's MFMAs; and tiles that take a CU each, where they fill their rounds of 256.  The lines were read off sweeps over 170 random and
+// model shapes (M 49 .. 50 240, K 64 .. 2048, N 16 .. 3072, int8 and fp16).  Around the lines (us, int8; tiles in brackets):
+//   256 x 256, one round:                    9456 x 384 -> 1536 [222] 11.6 / 13.0 (64 x 128); 18912 x 1536 -> 768 [222] 25.6 / 29.9; 18912 x 192 -> 768 [222] 9.6 / 10.6
+//   256 x 192, rounds filled to 70 %:        25216 x 768 -> 384 [198] 12.7 / 14.8 (64 x 128); 6304 x 384 -> 1536 [200] 9.4 / 10.1; 12608 x 1536 -> 768 [200] 19.9 / 22.8;
+//                                            50240 x 768 -> 384 [394] 25.3 / 26.2 (128 x 128), but short K 12608 x 192 -> 768 [200] 7.9 / 7.2, half-filled 18912 x 768 -> 384 [148] 12.0 / 11.7
+//   128 x 256 against 128 x 128, 800 tiles:  25216 x 384 -> 1536 [1182] 28.1 / 29.8; 13057 x 192 -> 2048 [824] 16.8 / 16.2, but 12608 x 192 -> 768 [297] 7.7 / 7.2
+//   128 x 128 against 64 x 128, 384 tiles:   4728 x 384 -> 1536 [444] 7.4 / 7.6;         9456 x 384 -> 192 [148] 5.3 / 5.1, 6304 x 768 -> 384 [150] 6.6 / 6.5
+//   64 x 128 against 64 x 64, 384 tiles:     3152 x 384 -> 1536 [600] 6.1 / 7.2;         6304 x 768 -> 384 [297] 6.5 / 6.3
+//   64 x 64 against 32 x 64, 200 tiles:      3152 x 768 -> 384 [300] 4.8 / 5.0;          197 x 768 -> 3072 [192] 4.6 / 4.3
+//   split reduction, 256 blocks of 16 x 16:  788 x 1536 -> 80 [250] 4.3 / 5.1 (32 x 64); 1576 x 1536 -> 80 [495] 5.6 / 5.1
+// 128 x 128 tiles: three 64-byte stages on four wavefronts let three workgroups share a CU and waste no half slab (25216 x 192 -> 1536 21.6 / 25.3);
+// over a long reduction twice the barriers cost more (12608 x 1536 -> 768 25.6 / 23.3).  64 x 64 tiles: three stages, but two from 768 tiles on, which
+// leave room for a fourth workgroup per CU (6304 x 1536 -> 80 [198] 6.4 / 8.2, 12608 x 384 -> 192 [591] 4.6 / 4.8; 37824 x 768 -> 56 [591] 8.9 / 8.2).
+// A tile that pads the matrix by a third more than the best one is passed over.
 template <class Path>
 int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
     const bool aligned = ptq4vm::aligned_to(a.x, 16) && ptq4vm::aligned_to(a.w, 16) && a.ldx_bytes % 16 == 0 && a.ldw_bytes % 16 == 0 &&
@@ -64,12 +66,20 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         if (tiles(a, 16, 16) <= 256) return launch_splitk<Path, 1, 1, 4, 4, true>(a, stream);
         auto padded = [&](int br, int bo) { return tiles(a, br, bo) * br * bo; };
         const int64_t most = padded(32, 64) * 4 / 3;
+        auto fills = [&](int br, int bo, int percent) {  // whole rounds of 256 workgroups, the last one to `percent`
+            const int64_t n = tiles(a, br, bo);
+            return n * 100 >= ptq4vm::ceil_div(n, 256) * 256 * percent;
+        };
+        if constexpr (!Path::kPacked4) {  // (packed operands are expanded into more registers than these leave)
+            if (tiles(a, 256, 256) <= 256 && fills(256, 256, 80) && padded(256, 256) <= most) return launch<Path, 256, 256, 2, 4, 128, 2, Copy::kDirect>(a, stream);
+            if (a.k_bytes >= 384 && fills(256, 192, 70) && padded(256, 192) <= most) return launch<Path, 256, 192, 4, 3, 128, 2, Copy::kDirect>(a, stream);
+        }
         if (tiles(a, 128, 256) >= 800 && padded(128, 256) <= most) return launch<Path, 128, 256, 2, 4, 64, 3, Copy::kDirect>(a, stream);
         if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most)
-            return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 4, 64, 3, Copy::kDirect>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, Copy::kDirect>(a, stream);
+            return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 2, 64, 3, Copy::kDirect>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, Copy::kDirect>(a, stream);
         if (tiles(a, 64, 128) >= 384 && padded(64, 128) <= most) return launch<Path, 64, 128, 2, 2, 128, 2, Copy::kDirect>(a, stream);
-        if (tiles(a, 64, 64) > 512) return launch<Path, 64, 64, 2, 2, 128, 2, Copy::kDirect>(a, stream);
-        if (tiles(a, 64, 64) >= 190) return launch<Path, 64, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 64) > 768) return launch<Path, 64, 64, 2, 2, 128, 2, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 64) >= 200) return launch<Path, 64, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
         return launch<Path, 32, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
     }
     // Any pitch, alignment and K.  Loads go through registers, so the small tiles hide less of their latency and the

@@ -111,9 +111,87 @@ __device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_b
     return out;
 }
 
-// The step, bias and offset vectors of a BR x BO tile, in LDS behind the ring.  fetch() loads one element per thread
-// (before the first operand copies, so that it returns ahead of them), park() writes them to LDS.  Channels and rows
-// beyond the matrix are clamped; they are never stored.
+// n / d for n < 2^31 and a divisor known on the host, 1 <= d < 2^31: with 2^(shift-1) < d <= 2^shift and mul = floor(2^32 (2^shift -
+// d) / d) + 1, (mulhi(n, mul) + n) >> shift is the quotient (Granlund and Montgomery, division by invariant integers).
+struct FastDiv {
+    uint32_t mul, shift, d;
+};
+inline FastDiv fast_div(uint32_t d) {
+    uint32_t shift = 0;
+    while ((1ULL << shift) < d) shift++;
+    return {(uint32_t)(((1ULL << 32) * ((1ULL << shift) - d)) / d + 1), shift, d};
+}
+__device__ __forceinline__ uint32_t quotient(const FastDiv &f, uint32_t n) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+__device__ __forceinline__ uint32_t remainder_of(const FastDiv &f, uint32_t n) { return n - quotient(f, n) * f.d; }
+
+// What a tile kernel reads of LinearArgs, with the divisions of its set-up prepared on the host: a workgroup's set-up is a serial chain
+// that nothing hides in small problems (64-bit remainders and divisions by tiles_o took 0.35 us of 1.4).
+struct TileArgs {
+    const char *x, *w;
+    int64_t M, N, ldx_bytes, ldw_bytes, k_bytes;
+    uint32_t per_xcd, xcd_extra;  // 8 per_xcd + xcd_extra tiles
+    FastDiv inner, tok;           // tiles along the dimension walked first; L
+    uint32_t rows_first;          // which dimension that is
+    uint32_t stores;              // Stores
+    const float *s_tok, *s_w;
+    const __half *bias;
+    __half *y;
+    int64_t ldy, L;
+    const int32_t *z_tok, *rowsum;
+    int32_t *acc_out;
+};
+// How results leave: kAny any address and channel count; the others whole 16-byte pieces at 16-byte aligned addresses (y, its
+// pitch and N multiples of 8 elements), kThrough at device scope, kPast non-temporal.
+enum Stores : uint32_t { kAny = 0, kThrough = 1, kPast = 2 };
+// Device-scope stores leave no dirty lines in the L2 for the end of the launch to write back, but push the operands of this and the
+// next launches out of the memory-side cache (us, kThrough / kPast / ordinary stores: 12608 x 384 -> 384 6.1 / 6.8 / 7.8, 6304 x 384 -> 1536
+// 9.4 / 10.1 / 11.0, 25216 x 768 -> 384 13.4 / 13.7 / 14.5, 50240 x 768 -> 384 30.0 / 24.7 / 32.4; whole Vim-S blocks over 128 x 197 rows, results of
+// 9.7 M elements, 88.2 / 86.9, and over 64 x 785 rows 155.5 / 152.3).
+constexpr int64_t kThroughElements = 6LL << 20;  // results up to this many are stored kThrough
+
+// Tiles of BR x BO for `a`; false if there are too many.  Neighbouring workgroups of an XCD walk the dimension with the
+// smaller operand behind it first, so that an XCD reads its share of the larger operand once (197 x 768 -> 3072: 4.3 us with the
+// rows first, 4.8 with the channels first; 197 x 1536 -> 768 5.0 / 5.4).
+template <int BR, int BO>
+inline bool tile_args(const LinearArgs &a, TileArgs &t, dim3 &grid) {
+    const int64_t tiles_r = ptq4vm::ceil_div(a.M, BR), tiles_o = ptq4vm::ceil_div(a.N, BO);
+    if (tiles_r * tiles_o > 0x3fffffffLL) return false;
+    t.x = a.x, t.w = a.w, t.s_tok = a.s_tok, t.s_w = a.s_w, t.bias = a.bias, t.y = a.y, t.z_tok = a.z_tok, t.rowsum = a.rowsum, t.acc_out = a.acc_out;
+    t.M = a.M, t.N = a.N, t.ldx_bytes = a.ldx_bytes, t.ldw_bytes = a.ldw_bytes, t.k_bytes = a.k_bytes, t.ldy = a.ldy, t.L = a.L;
+    t.per_xcd = (uint32_t)(tiles_r * tiles_o / kXcds);
+    t.xcd_extra = (uint32_t)(tiles_r * tiles_o % kXcds);
+    t.rows_first = a.M < a.N;
+    t.inner = fast_div((uint32_t)(t.rows_first ? tiles_r : tiles_o));
+    t.tok = fast_div((uint32_t)a.L);
+    const bool wide = a.N % 8 == 0 && a.ldy % 8 == 0 && ptq4vm::aligned_to(a.y, 16) && a.ldy * 2 * BR < (1LL << 31);
+    t.stores = !wide ? kAny : (a.M * a.N > kThroughElements ? kPast : kThrough);
+    grid = grid_of_tiles(tiles_r * tiles_o);
+    return true;
+}
+
+// The workgroup's tile: workgroup ids go round-robin over the 8 XCDs, each XCD gets a contiguous range of tiles.
+__device__ __forceinline__ bool locate_tile(const TileArgs &p, uint32_t &tile_r, uint32_t &tile_o) {
+    // What the set-up needs is wanted here, so that it is loaded with one wait instead of one behind every branch
+    asm volatile("" ::"s"(p.x), "s"(p.w), "s"(p.M), "s"(p.N), "s"(p.ldx_bytes), "s"(p.ldw_bytes), "s"(p.k_bytes), "s"(p.tok.mul), "s"(p.tok.shift),
+                 "s"(p.tok.d), "s"(p.s_tok), "s"(p.s_w), "s"(p.bias));
+    const uint32_t block = blockIdx.x + (blockIdx.y << kGridRowLog2), xcd = block % kXcds;  // (grid_of_tiles)
+    const uint32_t i = block / kXcds;
+    if (i >= p.per_xcd + (xcd < p.xcd_extra)) return false;
+    const uint32_t tile = xcd * p.per_xcd + min(xcd, p.xcd_extra) + i;
+    const uint32_t outer = quotient(p.inner, tile), first = tile - outer * p.inner.d;
+    tile_r = p.rows_first ? first : outer;
+    tile_o = p.rows_first ? outer : first;
+    return true;
+}
+
+// The channel of a 32-channel group that LDS row `row` of the weight (0 .. 31) holds: MFMA block h = row / 16, operand row a = row mod
+// 16 carries channel 8 (a / 4) + 4 h + a mod 4, so that a lane's results of two blocks are eight neighbouring channels.
+__device__ __forceinline__ int channel_of_row(int row) { return (row & ~31) + 8 * ((row >> 2) & 3) + 4 * ((row >> 4) & 1) + (row & 3); }
+
+// The step, bias and offset vectors of a BR x BO tile, in LDS behind the ring.  fetch() loads one element per thread into
+// registers (behind the first operand copies), park() writes them to LDS after the reduction, before a barrier.  Channels and
+// rows beyond the matrix are clamped; they are never stored.  Every thread loads, without a branch: a load that only some
+// paths have issued makes the compiler wait for everything in flight at the next use of a register.
 template <class Path, int BR, int BO, int THREADS>
 struct TileVectors {
     static_assert(BO <= THREADS && BR <= THREADS, "one thread per channel and per row");
@@ -130,25 +208,26 @@ struct TileVectors {
     __device__ __forceinline__ explicit TileVectors(char *lds)
         : cs(reinterpret_cast<float *>(lds)), cz(reinterpret_cast<int *>(cs + BO)), rs(reinterpret_cast<float *>(cz + BO)),
           rz(reinterpret_cast<int *>(rs + BR)), cb(reinterpret_cast<uint16_t *>(rz + BR)) {}
-    __device__ __forceinline__ void fetch(const LinearArgs &p, int tid, int64_t r0, int64_t o0, int rows_valid, int cols_valid) {
-        if (tid < BO) {
-            const int64_t o = o0 + min(tid, cols_valid - 1);
-            if constexpr (kInt8) col_s = p.s_w[o];
-            if constexpr (Path::kOffset) col_z = p.rowsum[o];
-            if (p.bias) col_b = reinterpret_cast<const uint16_t *>(p.bias)[o];
-        }
+    __device__ __forceinline__ void fetch(const TileArgs &p, int tid, int64_t r0, int64_t o0, int rows_valid, int cols_valid) {
+        const int64_t o = o0 + min(tid, cols_valid - 1);
         if constexpr (kInt8) {
-            if (tid < BR) {
-                const uint32_t t = ((uint32_t)(r0 % p.L) + (uint32_t)min(tid, rows_valid - 1)) % (uint32_t)p.L;
-                row_s = p.s_tok[t];
-                if constexpr (Path::kOffset) row_z = p.z_tok[t];
-            }
+            const bool small = p.M <= 0x7fffffffLL;
+            const uint32_t t0 = small ? remainder_of(p.tok, (uint32_t)r0) : (uint32_t)(r0 % p.L);
+            const uint32_t n = t0 + (uint32_t)min(tid, rows_valid - 1);
+            const uint32_t t = small ? remainder_of(p.tok, n) : n % (uint32_t)p.L;
+            row_s = p.s_tok[t];
+            if constexpr (Path::kOffset) row_z = p.z_tok[t];
+            col_s = p.s_w[o];
+            if constexpr (Path::kOffset) col_z = p.rowsum[o];
         }
+        // without a bias any readable address of N elements stands in
+        const uint16_t *bias = reinterpret_cast<const uint16_t *>(p.bias ? static_cast<const void *>(p.bias) : kInt8 ? static_cast<const void *>(p.s_w) : p.w);
+        col_b = bias[o];
     }
-    __device__ __forceinline__ void park(int tid) {
+    __device__ __forceinline__ void park(const TileArgs &p, int tid) {
         if (tid < BO) {
             cs[tid] = col_s;
-            cb[tid] = col_b;
+            cb[tid] = p.bias ? col_b : (uint16_t)0;
             if constexpr (Path::kOffset) cz[tid] = col_z;
         }
         if (tid < BR) {
@@ -163,42 +242,58 @@ constexpr int tile_vector_bytes() {
 }
 
 // Epilogue of a workgroup: every wavefront dequantizes its (BR / WR) x (BO / WO) accumulators, transposes them through
-// its own patch of the ring (RING_BYTES, free by now) and stores whole row segments.
-template <class Path, int BR, int BO, int WR, int WO, int RING_BYTES, int FO, int FR, class Vectors>
-__device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO][FR], const LinearArgs &p, char *ring, const Vectors &vec,
+// its own patch of the ring (RING_BYTES, free by now) and stores whole row segments.  The weight rows lie in LDS in the order
+// of channel_of_row, so a lane's results are 16-byte pieces of its row.  Whole pieces leave as buffer stores, whose range
+// check drops the rows beyond the matrix.
+template <class Path, int BR, int BO, int WR, int WO, int RING_BYTES, bool DUMP, int FO, int FR, class Vectors>
+__device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO][FR], const TileArgs &p, char *ring, const Vectors &vec,
                                            int64_t r0, int64_t o0, int rows_valid, int cols_valid) {
-    constexpr bool kInt8 = Path::kElemBytes == 1;
     constexpr int NW = WR * WO, WAVE_R = BR / WR, WAVE_O = BO / WO;
+    static_assert(FO % 2 == 0, "pairs of MFMA blocks");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
     const int l16 = lane & 15, lq = lane >> 4;
 
-    // Accumulator register v of block (i, j): token row 16 j + l16, channel 16 i + 4 lq + v.
-    if constexpr (kInt8) {
-        if (p.acc_out) {
+    // Accumulator register v of block (i, j): token row 16 j + l16, channel 32 (i / 2) + 8 lq + 4 (i mod 2) + v.
+    if constexpr (DUMP) {
 #pragma unroll
-            for (int i = 0; i < FO; i++)
+        for (int i = 0; i < FO; i++)
 #pragma unroll
-                for (int j = 0; j < FR; j++)
+            for (int j = 0; j < FR; j++)
 #pragma unroll
-                    for (int c = 0; c < 4; c++) {
-                        const int r = wave_r + j * 16 + l16, o = wave_o + i * 16 + lq * 4 + c;
-                        if (r < rows_valid && o < cols_valid)
-                            p.acc_out[(r0 + r) * p.N + o0 + o] = Path::kPacked4 ? (int)acc[i][j][c] >> 8 : (int)acc[i][j][c];
-                    }
-        }
+                for (int c = 0; c < 4; c++) {
+                    const int r = wave_r + j * 16 + l16, o = wave_o + (i >> 1) * 32 + 8 * lq + 4 * (i & 1) + c;
+                    if (r < rows_valid && o < cols_valid)
+                        p.acc_out[(r0 + r) * p.N + o0 + o] = Path::kPacked4 ? (int)acc[i][j][c] >> 8 : (int)acc[i][j][c];
+                }
     }
 
-    constexpr int CPR = WAVE_O / 8, RPS = 64 / CPR;  // 16-byte chunks per patch row, rows per store instruction
-    constexpr int FIT = RING_BYTES / NW / (16 * WAVE_O * 2);
+    // Patch rows of 16 (CPR + 2) bytes: measured in a read loop, 16-byte accesses of 16 rows run at 241 bytes per clock and CU
+    // when the pitch is 2 mod 4 pieces and at 128 when it is odd.
+    constexpr int CPR = WAVE_O / 8, RPS = 64 / CPR, PITCH = CPR * 16 + 32;  // 16-byte chunks per patch row, rows per store instruction
+    constexpr int FIT = RING_BYTES / NW / (16 * PITCH);
     constexpr int JB = FIT >= FR ? FR : (FIT >= 2 && FR % 2 == 0 ? 2 : 1);  // 16-row blocks per round
-    static_assert(FIT >= 1 && RPS <= 16 * JB, "patches fit the ring");
-    char *const patch = ring + wave * (JB * 16 * WAVE_O * 2);
-    auto patch_chunk = [&](int row, int chunk) {
-        const int sw = CPR >= 8 ? (row & 7) : ((row / (8 / CPR)) & (CPR - 1));
-        return row * (WAVE_O * 2) + ((chunk ^ sw) << 4);
-    };
+    static_assert(FIT >= 1 && RPS <= 16 * JB && 64 % CPR == 0, "patches fit the ring");
+    char *const patch = ring + wave * (JB * 16 * PITCH);
+
+    v4f cs[FO / 2][2], cb[FO / 2];
+    v4i cz[FO / 2][2];
+#pragma unroll
+    for (int g = 0; g < FO / 2; g++) {
+        const int col = wave_o + 32 * g + 8 * lq;
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            cs[g][h] = *reinterpret_cast<const v4f *>(vec.cs + col + 4 * h);
+            cz[g][h] = Path::kOffset ? *reinterpret_cast<const v4i *>(vec.cz + col + 4 * h) : v4i{0, 0, 0, 0};
+        }
+        cb[g] = *reinterpret_cast<const v4f *>(vec.cb + col);
+    }
+    const int srow = lane / CPR, schunk = lane % CPR;
+    const int first_row = wave_r + srow, col = wave_o + schunk * 8;
     char *const y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
+    // (the span of a tile; with kAny stores, whose pitch may be anything, the descriptor is not used)
+    const __amdgpu_buffer_rsrc_t y_rows = __builtin_amdgcn_make_buffer_rsrc(y_tile, 0, (int)(((int64_t)(rows_valid - 1) * p.ldy + cols_valid) * 2), 0x00020000);
+    const uint32_t ldy_bytes = (uint32_t)p.ldy * 2, y_off = (uint32_t)first_row * ldy_bytes + (uint32_t)col * 2;
 #pragma unroll
     for (int jb = 0; jb < FR; jb += JB) {
 #pragma unroll
@@ -207,110 +302,291 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
             const float rs = vec.rs[wave_r + j * 16 + l16];
             const int rz = Path::kOffset ? vec.rz[wave_r + j * 16 + l16] : 0;
 #pragma unroll
-            for (int i = 0; i < FO; i++) {
-                const int col = wave_o + i * 16 + lq * 4;
-                const v4f cs = *reinterpret_cast<const v4f *>(vec.cs + col);
-                const v2f cb = *reinterpret_cast<const v2f *>(vec.cb + col);
-                v4i cz = {0, 0, 0, 0};
-                if constexpr (Path::kOffset) cz = *reinterpret_cast<const v4i *>(vec.cz + col);
-                *reinterpret_cast<v2f *>(patch + patch_chunk(jj * 16 + l16, 2 * i + (lq >> 1)) + (lq & 1) * 8) =
-                    finish_four<Path>(acc[i][j], rs, rz, cs, cz, cb);
+            for (int g = 0; g < FO / 2; g++) {
+                const v2f lo = finish_four<Path>(acc[2 * g][j], rs, rz, cs[g][0], cz[g][0], v2f{cb[g].x, cb[g].y});
+                const v2f hi = finish_four<Path>(acc[2 * g + 1][j], rs, rz, cs[g][1], cz[g][1], v2f{cb[g].z, cb[g].w});
+                *reinterpret_cast<v4f *>(patch + (jj * 16 + l16) * PITCH + (4 * g + lq) * 16) = v4f{lo.x, lo.y, hi.x, hi.y};
             }
         }
         asm volatile("" ::: "memory");  // wavefront-private patch: LDS runs a wavefront's accesses in order
+        constexpr int S = JB * 16 / RPS;
+        v4f data[S];
 #pragma unroll
-        for (int s = 0; s < JB * 16 / RPS; s++) {
-            const int prow = s * RPS + lane / CPR, chunk = lane % CPR;
-            const v4f data = *reinterpret_cast<const v4f *>(patch + patch_chunk(prow, chunk));
-            const int r = wave_r + jb * 16 + prow, o = wave_o + chunk * 8;
-            if (r < rows_valid && o < cols_valid)
-                store_eight(y_tile + (int64_t)r * p.ldy * 2 + o * 2, data, cols_valid - o);
+        for (int s = 0; s < S; s++) data[s] = *reinterpret_cast<const v4f *>(patch + (s * RPS + srow) * PITCH + schunk * 16);
+        if (p.stores == kAny) {
+#pragma unroll
+            for (int s = 0; s < S; s++) {
+                const int r = first_row + jb * 16 + s * RPS;
+                if (r < rows_valid && col < cols_valid) store_eight(y_tile + (int64_t)r * p.ldy * 2 + col * 2, data[s], cols_valid - col);
+            }
+        } else if (col < cols_valid) {
+            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+            // cache policy of the store: 16 is sc1 (device scope), 2 is nt
+            if (p.stores == kThrough) {
+#pragma unroll
+                for (int s = 0; s < S; s++)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[s]), y_rows, (int)(y_off + (uint32_t)(jb * 16 + s * RPS) * ldy_bytes), 0, 16);
+            } else {
+#pragma unroll
+                for (int s = 0; s < S; s++)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[s]), y_rows, (int)(y_off + (uint32_t)(jb * 16 + s * RPS) * ldy_bytes), 0, 2);
+            }
         }
         asm volatile("" ::: "memory");
     }
 }
 
-// ------------------------------------------------------------------------------------------
-// One BR x BO tile per workgroup.  K is walked in slabs of SLAB bytes per row through a ring of STAGES LDS stages; what
-// bounds a workgroup is the latency of its copies and of its stores, so the shape of the kernel is small: few registers
-// and 33 - 76 KiB of LDS (17 - 66 with the slabs through registers) let 2 - 4 (2 - 8) workgroups share a CU, and one's
-// epilogue runs under the others' MFMAs without any pipelining inside the workgroup.  The step, bias and offset vectors
-// are fetched before the first copy and wait in LDS, and results cross a wavefront-private patch into 16-byte stores of whole row segments (25216 x 768 -> 384: 15.6 us
-// = 2.5 TB/s, 22.3 us with the tile kernel before, whose epilogue loaded each scale where it was used).
-// COPY kDirect: 16-byte aligned bases and pitches, k_bytes % 64 == 0; slabs are copied global -> LDS directly.  Otherwise any
-// pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).  Only the last
-// slab reaches beyond K; the loads of the others carry no tests (16236 x 1584 -> 760 fp16 106.7 -> 62.8 us, 24104 x 830 -> 760
-// 45.7 -> 36.1, 3184 x 1000 -> 500 12.3 -> 10.3, each with the larger tiles that this pays for; 69.1, 43.4 and 12.3 with the
-// tiles alone).  A reduction of one slab keeps the tested loads alone (kOneSlab): the second form costs it 2 %.
-// Requirements (host-checked): L < 2^31, BR * ldx_bytes and BO * ldw_bytes below 2^31.
-// ------------------------------------------------------------------------------------------
+// How linear_mfma_tile brings its slabs to LDS: copied directly, through registers, through registers with a reduction of one slab.
+enum class Copy { kDirect, kRegisters, kOneSlab };
+
 template <int BR, int BO, int SLAB, int STAGES>
 constexpr int tile_lds_bytes() {
     return STAGES * (BR + BO) * SLAB + tile_vector_bytes<BR, BO>();
 }
 
-enum class Copy { kDirect, kRegisters, kOneSlab };
-
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY>
-__global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArgs p) {
-    constexpr bool ALIGNED = COPY == Copy::kDirect;
+// ------------------------------------------------------------------------------------------
+// One BR x BO tile per workgroup, operands copied global -> LDS directly, K walked in slabs of SLAB bytes per row (SLAB 96: one
+// 128-code block of the E2M3 container) through a ring of STAGES stages.  The fragments of the next MFMA step are fetched from LDS
+// while the present step's MFMAs run, each into the registers that its predecessor has just left (the weight's are doubled).
+// A slab's end - its last fragments in registers, the next slab landed, one barrier, the refill of its stage - stands between the
+// MFMAs of its last step.  What bounds it now (12608 x 1536 -> 768 in 256 x 192 tiles, 18.8 us of which 2 are the launch): MFMAs 8.8 us
+// at the 2.0 GHz that the chip holds, operand reads and copies that do not hide 5, set-up and epilogue 3.  Before, with fragments
+// fetched and used step by step and a set-up that waited for the scale vectors: 23.7 us; 197 x 768 -> 3072 5.8 -> 4.3,
+// 3152 x 384 -> 1536 8.0 -> 5.9, 25216 x 768 -> 384 16.5 -> 12.6.
+// Requirements (host-checked): 16-byte aligned bases and pitches, k_bytes a multiple of 64 (E2M3: of 96), L < 2^31, 256 pitches
+// below 2^31.
+// ------------------------------------------------------------------------------------------
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, bool TIGHT>
+__device__ __forceinline__ void direct_tile(const TileArgs &p) {
     constexpr int NW = WR * WO, THREADS = 64 * NW;
     constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
-    constexpr int CHUNKS = SLAB / 16, ROWS_PER_COPY = 64 / CHUNKS, COPIES = (BR + BO) / ROWS_PER_COPY / NW;
-    constexpr int STAGE_BYTES = (BR + BO) * SLAB;
-    static_assert(SLAB == 64 || SLAB == 128, "LDS rows hold 64 or 128 bytes of K");
-    static_assert(WAVE_R % 16 == 0 && WAVE_O % 16 == 0, "wave tile must be whole MFMA blocks");
-    static_assert(ALIGNED || STAGES == 2, "the register-staged form is double buffered");
-    static_assert((BR + BO) % (ROWS_PER_COPY * NW) == 0 && BR % ROWS_PER_COPY == 0, "every wavefront issues the same number of copies");
-    static_assert(STAGES >= 2 && (STAGES - 2) * COPIES <= 63, "vmcnt is a 6-bit counter");
+    constexpr bool E2M3 = Path::kE2m3;
+    constexpr int KS = E2M3 ? 1 : SLAB / 64;  // MFMA steps per slab
+    constexpr int CHUNKS = SLAB / 16;
+    constexpr int STAGE_BYTES = (BR + BO) * SLAB, X_COPIES = BR * SLAB / 1024, ALL_COPIES = STAGE_BYTES / 1024;
+    constexpr int COPIES = (ALL_COPIES + NW - 1) / NW;     // 1 KiB each; those beyond the last repeat it
+    constexpr int KEEP = (STAGES - 2) * COPIES;            // copies of younger slabs that may stay in flight
+    using Frag = typename Path::Frag;
     using Acc = typename Path::Acc16;
+    static_assert(SLAB == (E2M3 ? 96 : SLAB >= 128 ? 128 : 64), "LDS rows hold 64 or 128 bytes of K or one E2M3 block");
+    static_assert(WAVE_R % 16 == 0 && WAVE_O % 32 == 0 && BR * SLAB % 1024 == 0 && STAGE_BYTES % 1024 == 0, "whole MFMA blocks and copies");
+    static_assert(STAGES >= 2 && KEEP <= 63, "vmcnt is a 6-bit counter");
 
-    int tile_r, tile_o;
-    if (!tile_of_block(p, tile_r, tile_o)) return;
+    uint32_t tile_r, tile_o;
+    if (!locate_tile(p, tile_r, tile_o)) return;
     const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
     const int l16 = lane & 15, lq = lane >> 4;
     const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
-    auto chunk_of = [&](int row, int chunk) { return chunk ^ (SLAB == 64 ? swizzle(row) : (row & 7)); };
-
+    // Which 16-byte chunk of its row lies at position c of LDS row `row` (bank conflicts: 241 bytes per clock and CU in a read loop)
+    auto chunk_at = [](int row, int c) {
+        if constexpr (E2M3) return c < 4 ? c : 4 + ((c - 4) ^ ((row >> 3) & 1));
+        return c ^ (SLAB == 64 ? swizzle(row) : (row & 7));
+    };
     char *const ring = lds_dyn;
-    TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + STAGES * STAGE_BYTES);
-    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
 
-    // Copies: 1 KiB per wavefront and instruction, linear on the LDS side, so the swizzle is applied by choosing
-    // which global chunk a lane fetches.  Copy c covers LDS rows ROWS_PER_COPY c ..: activation rows, then weights.
-    // The register-staged form writes the same LDS places from registers.
+    // Copies: linear on the LDS side, so order of the rows and swizzle are applied by choosing which global chunk a lane fetches.
+    // Rows beyond the matrix repeat its last one.
+    uint32_t off[COPIES];
+#pragma unroll
+    for (int i = 0; i < COPIES; i++) {
+        const int c = min(wave + NW * i, ALL_COPIES - 1);  // scalar
+        const bool is_x = c < X_COPIES;
+        const int piece = (is_x ? c : c - X_COPIES) * 64 + lane, row = piece / CHUNKS;
+        const int src = min(is_x ? row : channel_of_row(row), (is_x ? rows_valid : cols_valid) - 1);
+        off[i] = (uint32_t)src * (uint32_t)(E2M3 ? SLAB : is_x ? p.ldx_bytes : p.ldw_bytes) + chunk_at(row, piece - row * CHUNKS) * 16;
+    }
+    const char *const gx = p.x + r0 * (E2M3 ? SLAB : p.ldx_bytes), *const gw = p.w + o0 * (E2M3 ? SLAB : p.ldw_bytes);
+    const uint32_t k_bytes = (uint32_t)p.k_bytes;
+    auto issue = [&](int slab, int stage) {
+#pragma unroll
+        for (int i = 0; i < COPIES; i++) {
+            const int c = min(wave + NW * i, ALL_COPIES - 1);
+            const bool is_x = c < X_COPIES;
+            const char *src = (is_x ? gx : gw) + (E2M3 ? slab * (is_x ? p.ldx_bytes : p.ldw_bytes) : (int64_t)(uint32_t)slab * SLAB);
+            uint32_t o = off[i];
+            // the last slab of a K that ends in half a slab: the far chunks re-read the near ones, nobody uses them
+            if (SLAB == 128 && (uint32_t)(slab + 1) * SLAB > k_bytes) {
+                const int piece = (is_x ? c : c - X_COPIES) * 64 + lane, row = piece / CHUNKS;
+                o -= chunk_at(row, piece - row * CHUNKS) & 4 ? 64 : 0;
+            }
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + o),
+                                             (__attribute__((address_space(3))) void *)(ring + stage * STAGE_BYTES + c * 1024), 16, 0, 0);
+        }
+    };
+    const int n_slabs = (int)((k_bytes + SLAB - 1) / SLAB);
+    issue(0, 0);
+    TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + STAGES * STAGE_BYTES);
+    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);  // under the first slab's latency
+#pragma unroll
+    for (int s = 1; s < STAGES - 1; s++)
+        if (s < n_slabs) issue(s, s);
+
+    Acc acc[FO][FR];
+#pragma unroll
+    for (int i = 0; i < FO; i++)
+#pragma unroll
+        for (int j = 0; j < FR; j++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
+
+    uint32_t frag[KS];  // where row l16 of a block has the lane's operand
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) frag[ks] = (uint32_t)l16 * SLAB + (E2M3 ? lq * 16 : chunk_at(l16, 4 * ks + lq) << 4);
+    const uint32_t frag_high = (uint32_t)l16 * SLAB + 64 + ((lq * 8) ^ ((l16 & 8) << 1));  // E2M3: high parts, swapped as copied
+    auto fragment = [&](const char *rows, int ks) {
+        if constexpr (E2M3)
+            return Path::make_fragment(*reinterpret_cast<const v4i *>(rows + frag[0]), *reinterpret_cast<const v2i *>(rows + frag_high));
+        else
+            return *reinterpret_cast<const v4i *>(rows + frag[ks]);
+    };
+    // Both operands' fragments are doubled; in a TIGHT kernel the activations' are not: each is fetched again as soon as its MFMAs
+    // have been issued, and the other wavefronts of the SIMD hide what is left of that latency.
+    Frag fw[2][FO], fx[TIGHT ? 1 : 2][FR];
+    auto load_fw = [&](int buf, const char *st, int ks) {
+#pragma unroll
+        for (int i = 0; i < FO; i++) fw[buf][i] = fragment(st + (BR + wave_o + i * 16) * SLAB, ks);
+    };
+    auto load_fx = [&](int buf, int j, const char *st, int ks) { fx[TIGHT ? 0 : buf][j] = fragment(st + (wave_r + j * 16) * SLAB, ks); };
+    // The products of buffer `buf`, `fetch(j)` behind those of row block j
+    auto products = [&](int buf, auto fetch) {
+        Frag we[FO], wo[FO];
+#pragma unroll
+        for (int i = 0; i < FO; i++) {
+            if constexpr (Path::kPacked4)
+                we[i] = Path::even_codes(fw[buf][i]), wo[i] = Path::odd_codes(fw[buf][i]);
+            else
+                we[i] = fw[buf][i];
+        }
+#pragma unroll
+        for (int j = 0; j < FR; j++) {
+            const Frag x = fx[TIGHT ? 0 : buf][j];
+            if constexpr (Path::kPacked4) {
+                const v4i xe = Path::even_codes(x), xo = Path::odd_codes(x);
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(we[i], xe, acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(wo[i], xo, acc[i][j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(we[i], x, acc[i][j]);
+            }
+            fetch(j);
+        }
+    };
+    auto wait_slab = [&](int slab) {  // this wavefront's copies of it have landed
+        if (KEEP == 0 || slab + STAGES - 2 >= n_slabs)
+            wait_vmcnt_at_most<0>();
+        else
+            wait_vmcnt_at_most<KEEP>();
+    };
+    wait_slab(0);
+    __builtin_amdgcn_s_barrier();
+    if (STAGES - 1 < n_slabs) issue(STAGES - 1, STAGES - 1);
+    load_fw(0, ring, 0);
+#pragma unroll
+    for (int j = 0; j < FR; j++) load_fx(0, j, ring, 0);
+
+    // One MFMA step on the fragments of buffer `cur`; the next step's, step `nks` of its slab, are fetched meanwhile.  Where a slab
+    // ends (over) every wavefront holds its last fragments, so one barrier makes the next slab visible and frees this one's stage.
+    // What the very last step fetches nobody uses.
+    int stage = 0;
+    auto step = [&](int cur, int nks, bool over, int slab) {
+        wait_lgkmcnt_0();  // (known to the compiler, so that no MFMA waits for the fetches that follow)
+        if (over) {
+            if (slab + 1 < n_slabs) {
+                wait_slab(slab + 1);
+                __builtin_amdgcn_s_barrier();
+                if (slab + STAGES < n_slabs) issue(slab + STAGES, stage);
+            }
+            if (++stage == STAGES) stage = 0;
+        }
+        const char *const next = ring + stage * STAGE_BYTES;
+        load_fw(cur ^ 1, next, nks);
+        if constexpr (TIGHT) {
+            products(cur, [&](int j) {
+                load_fx(0, j, next, nks);
+                __builtin_amdgcn_sched_barrier(0);  // keep a fetch behind the MFMAs that free its registers
+            });
+        } else {
+#pragma unroll
+            for (int j = 0; j < FR; j++) load_fx(cur ^ 1, j, next, nks);
+            __builtin_amdgcn_sched_barrier(0);  // fetch first, then multiply
+            products(cur, [](int) {});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if constexpr (KS == 2) {
+        const int whole = (int)(k_bytes / SLAB);
+#pragma unroll 1
+        for (int it = 0; it < whole; it++) {
+            step(0, 1, false, it);
+            step(1, 0, true, it);
+        }
+        if (whole < n_slabs) step(0, 0, false, whole);
+    } else {
+#pragma unroll 1
+        for (int it = 0; it + 2 <= n_slabs; it += 2) {
+            step(0, 0, true, it);
+            step(1, 0, true, it + 1);
+        }
+        if (n_slabs & 1) step(0, 0, true, n_slabs - 1);
+    }
+    vec.park(p, tid);
+    __syncthreads();  // the vectors are visible, the ring becomes the wavefronts' transposition patches
+    store_tile<Path, BR, BO, WR, WO, STAGES * STAGE_BYTES, DUMP>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+}
+
+// The same tile for any pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).
+// Only the last slab reaches beyond K; the loads of the others carry no tests (16236 x 1584 -> 760 fp16 106.7 -> 62.8 us, 24104 x 830 -> 760
+// 45.7 -> 36.1, 3184 x 1000 -> 500 12.3 -> 10.3, each with the larger tiles that this pays for; 69.1, 43.4 and 12.3 with the
+// tiles alone).  A reduction of one slab keeps the tested loads alone (ONE): the second form costs it 2 %.
+// Requirements (host-checked): L < 2^31, BR * ldx_bytes and BO * ldw_bytes below 2^31.
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, bool DUMP, bool ONE>
+__device__ __forceinline__ void staged_tile(const TileArgs &p) {
+    constexpr int NW = WR * WO, THREADS = 64 * NW;
+    constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
+    constexpr int CHUNKS = SLAB / 16, ROWS_PER_COPY = 64 / CHUNKS, COPIES = (BR + BO) / ROWS_PER_COPY / NW;
+    constexpr int STAGE_BYTES = (BR + BO) * SLAB;
+    static_assert(SLAB == 64 || SLAB == 128, "LDS rows hold 64 or 128 bytes of K");
+    static_assert(WAVE_R % 16 == 0 && WAVE_O % 32 == 0, "wave tile must be whole MFMA blocks");
+    static_assert((BR + BO) % (ROWS_PER_COPY * NW) == 0 && BR % ROWS_PER_COPY == 0, "every wavefront brings the same number of pieces");
+    using Acc = typename Path::Acc16;
+
+    uint32_t tile_r, tile_o;
+    if (!locate_tile(p, tile_r, tile_o)) return;
+    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
+    auto chunk_of = [](int row, int chunk) { return chunk ^ (SLAB == 64 ? swizzle(row) : (row & 7)); };
+    char *const ring = lds_dyn;
+
     uint32_t off[COPIES];
 #pragma unroll
     for (int i = 0; i < COPIES; i++) {
         const int row = (wave + NW * i) * ROWS_PER_COPY + lane / CHUNKS;
-        const int chunk = chunk_of(row, lane % CHUNKS);  // (BR is a multiple of 16: a weight row swizzles like row - BR)
-        const bool is_x = row < BR;
-        const int src_row = is_x ? min(row, rows_valid - 1) : min(row - BR, cols_valid - 1);
-        off[i] = (uint32_t)src_row * (uint32_t)(is_x ? p.ldx_bytes : p.ldw_bytes) + (ALIGNED ? chunk * 16 : 0);
+        const bool is_x = (wave + NW * i) * ROWS_PER_COPY < BR;
+        const int src_row = is_x ? min(row, rows_valid - 1) : min(channel_of_row(row - BR), cols_valid - 1);
+        off[i] = (uint32_t)src_row * (uint32_t)(is_x ? p.ldx_bytes : p.ldw_bytes);
     }
     const char *gx = p.x + r0 * p.ldx_bytes, *gw = p.w + o0 * p.ldw_bytes;
-    v4i staged[ALIGNED ? 1 : COPIES];
-    auto issue = [&](int slab, int stage) {  // ALIGNED: copy a slab into a ring stage; otherwise fetch it into registers
+    const int64_t k_bytes = p.k_bytes;
+    v4i staged[COPIES];
+    auto fetch = [&](int slab) {
 #pragma unroll
         for (int i = 0; i < COPIES; i++) {
             const int c = wave + NW * i;  // scalar
             const char *src = c * ROWS_PER_COPY < BR ? gx : gw;
-            if constexpr (ALIGNED) {
-                // the last slab of a K that ends in half a slab: the far chunks re-read the near ones, nobody uses them
-                if (SLAB == 128 && (int64_t)(slab + 1) * SLAB > p.k_bytes) src -= chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS) & 4 ? 64 : 0;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (int64_t)slab * SLAB + off[i]),
-                                                 (__attribute__((address_space(3))) void *)(ring + stage * STAGE_BYTES + c * 1024), 16, 0, 0);
-            } else {
-                const int chunk = chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS);
-                if (COPY == Copy::kRegisters && (int64_t)(slab + 1) * SLAB <= p.k_bytes) {  // a slab inside the rows
-                    staged[i] = *reinterpret_cast<const v4i_unaligned *>(src + off[i] + (int64_t)slab * SLAB + chunk * 16);
-                    continue;
-                }
-                const char *end = c * ROWS_PER_COPY < BR ? p.x + ((p.M - 1) * p.ldx_bytes + p.k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + p.k_bytes);
-                staged[i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, p.k_bytes, end);
+            const int chunk = chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS);  // (BR is a multiple of 16: a weight row swizzles like row - BR)
+            if (!ONE && (int64_t)(slab + 1) * SLAB <= k_bytes) {  // a slab inside the rows
+                staged[i] = *reinterpret_cast<const v4i_unaligned *>(src + off[i] + (int64_t)slab * SLAB + chunk * 16);
+                continue;
             }
+            const char *end = c * ROWS_PER_COPY < BR ? p.x + ((p.M - 1) * p.ldx_bytes + k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
+            staged[i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, k_bytes, end);
         }
     };
     auto commit = [&](int stage) {
@@ -327,33 +603,18 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
 #pragma unroll
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
 
-    const int n_slabs = (int)((p.k_bytes + SLAB - 1) / SLAB);
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; s++)
-        if (s < n_slabs) issue(s, s);
-    vec.park(tid);
-    if constexpr (!ALIGNED) commit(0);
-
-    int stage = 0;
+    const int n_slabs = (int)((k_bytes + SLAB - 1) / SLAB);
+    fetch(0);
+    TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * STAGE_BYTES);
+    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
+    commit(0);
     for (int it = 0; it < n_slabs; it++) {
-        constexpr int KEEP = (STAGES - 2) * COPIES;  // younger slabs that may stay in flight
-        if constexpr (!ALIGNED) {
-            __syncthreads();
-        } else {
-            if (it + STAGES - 2 < n_slabs)
-                wait_vmcnt_at_most<KEEP>();
-            else
-                wait_vmcnt_at_most<0>();
-            if (it == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the scale vectors are in LDS
-            __builtin_amdgcn_s_barrier();  // everyone's copies of slab `it` are visible; slab it-1 is fully consumed
-        }
-        int refill = stage + STAGES - 1;
-        if (refill >= STAGES) refill -= STAGES;
-        if (it + STAGES - 1 < n_slabs) issue(it + STAGES - 1, refill);
-        const char *sx = ring + stage * STAGE_BYTES + wave_r * SLAB, *sw = ring + stage * STAGE_BYTES + (BR + wave_o) * SLAB;
+        __syncthreads();
+        if (it + 1 < n_slabs) fetch(it + 1);
+        const char *sx = ring + (it & 1) * STAGE_BYTES + wave_r * SLAB, *sw = ring + (it & 1) * STAGE_BYTES + (BR + wave_o) * SLAB;
 #pragma unroll
         for (int ks = 0; ks < SLAB / 64; ks++) {
-            if (ks > 0 && (int64_t)it * SLAB + ks * 64 >= p.k_bytes) break;
+            if (ks > 0 && (int64_t)it * SLAB + ks * 64 >= k_bytes) break;
             v4i fw[FO], fx[FR];
 #pragma unroll
             for (int i = 0; i < FO; i++) {
@@ -367,14 +628,40 @@ __global__ __launch_bounds__(64 * WR * WO) void linear_mfma_tile(const LinearArg
             }
             mfma_step<Path, FO, FR>(acc, fw, fx);
         }
-        if constexpr (!ALIGNED) {
-            if (it + 1 < n_slabs) commit(refill);
-        }
-        if (++stage == STAGES) stage = 0;
+        if (it + 1 < n_slabs) commit((it + 1) & 1);
     }
-    __syncthreads();  // the ring becomes the wavefronts' transposition patches
+    vec.park(p, tid);
+    __syncthreads();  // the vectors are visible, the ring becomes the wavefronts' transposition patches
+    store_tile<Path, BR, BO, WR, WO, 2 * STAGE_BYTES, DUMP>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+}
 
-    store_tile<Path, BR, BO, WR, WO, STAGES * STAGE_BYTES>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+// Registers of a direct tile: results, the fragments of two steps (TIGHT: those of the activations once), some for everything else.
+template <class Path, int FR, int FO>
+constexpr int tile_registers(bool tight) {
+    constexpr int frag = sizeof(typename Path::Frag) / 4;
+    return FR * FO * 4 + (2 * FO + (tight ? FR : 2 * FR)) * frag + (Path::kPacked4 ? (FO + 2) * frag : 0) + (Path::kE2m3 ? 24 : 16);
+}
+// Wavefronts per SIMD that a direct tile is compiled for: those of as many workgroups as the LDS of a CU holds, as far as the registers
+// go round.  (A bound also keeps results in plain registers; moving them from accumulation registers costs an instruction each.)
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES>
+constexpr int tile_waves() {
+    constexpr int by_lds = 160 * 1024 / tile_lds_bytes<BR, BO, SLAB, STAGES>() * WR * WO / 4;
+    constexpr int by_registers = 512 / tile_registers<Path, BR / WR / 16, BO / WO / 16>(true);
+    constexpr int waves = by_lds < by_registers ? by_lds : by_registers;
+    return waves < 1 ? 1 : (waves > 8 ? 8 : waves);
+}
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES>
+constexpr bool tile_is_tight() {
+    return tile_registers<Path, BR / WR / 16, BO / WO / 16>(false) > 512 / tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() / 8 * 8;
+}
+
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, Copy COPY>
+__global__ __launch_bounds__(64 * WR * WO, (COPY == Copy::kDirect ? tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() : 4)) void linear_mfma_tile(const TileArgs p) {
+    static_assert(COPY == Copy::kDirect || STAGES == 2, "the register-staged form is double buffered");
+    if constexpr (COPY == Copy::kDirect)
+        direct_tile<Path, BR, BO, WR, WO, SLAB, STAGES, DUMP, tile_is_tight<Path, BR, BO, WR, WO, SLAB, STAGES>()>(p);
+    else
+        staged_tile<Path, BR, BO, WR, WO, SLAB, DUMP, COPY == Copy::kOneSlab>(p);
 }
 
 // The partial sums of a workgroup's SK wavefronts meet in LDS (SK FR FO KiB) and wavefront b finishes block b.

@@ -14,6 +14,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -30,7 +31,9 @@ struct Int8Path {
     static constexpr int kElemBytes = 1;
     static constexpr bool kOffset = false;
     static constexpr bool kPacked4 = false;
+    static constexpr bool kE2m3 = false;
     using Acc = v16i;
+    using Frag = v4i;  // an operand of mfma16
     static __device__ __forceinline__ Acc mfma(v4i a, v4i b, Acc c) {
         return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
     }
@@ -64,7 +67,9 @@ struct Half16Path {
     static constexpr int kElemBytes = 2;
     static constexpr bool kOffset = false;
     static constexpr bool kPacked4 = false;
+    static constexpr bool kE2m3 = false;
     using Acc = v16f;
+    using Frag = v4i;
     static __device__ __forceinline__ Acc mfma(v4i a, v4i b, Acc c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0,
                                                       0, 0);
@@ -367,6 +372,12 @@ __device__ __forceinline__ void wait_vmcnt_at_most() {
     // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14
     static_assert(KEEP >= 0 && KEEP <= 63, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt(0x0F70 | (KEEP & 15) | ((KEEP >> 4) << 14));
+}
+
+// Every LDS read and scalar load has returned (a wait that the compiler takes into account, unlike one inside inline asm).
+__device__ __forceinline__ void wait_lgkmcnt_0() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ void lds_read_1x_b128(uint32_t addr, v4f &v) {

@@ -164,6 +164,16 @@ def test_int8_tiles(M, K, N, parts):
     assert torch.equal(p.acc.double(), p.acc64)
 
 
+@pytest.mark.parametrize("M,K,N,parts", [
+    (25009, 448, 380, (TILE, "256, 192", DIRECT)), (25009, 320, 380, (TILE, "128, 128", DIRECT)),  # from 384 bytes of K
+    (22785, 384, 384, (TILE, "256, 192", DIRECT)), (22784, 384, 384, (TILE, "128, 128", DIRECT)),  # 180 and 178 of 256
+    (8705, 320, 1536, (TILE, "256, 256", DIRECT)), (8704, 320, 1536, (TILE, "128, 128", DIRECT)),  # 210 and 204 of 256
+    (4225, 64, 520, (TILE, "64, 64", "128, 3,", DIRECT)), (50001, 192, 56, (TILE, "64, 64", "128, 2,", DIRECT)),  # 603 and 782 tiles
+])
+def test_int8_tiles_of_whole_rounds(M, K, N, parts):
+    test_int8_tiles(M, K, N, parts)
+
+
 @pytest.mark.parametrize("M,K,N", [(12345, 31, 2179), (12345, 33, 2179), (5121, 520, 900), (6401, 32, 1028), (6401, 33, 1029), (401, 66, 899), (2049, 200, 643)])
 def test_f16_tiles_any_alignment(M, K, N):
     """fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|, and one fp16 rounding.  Infinities beyond K (the

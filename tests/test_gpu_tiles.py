@@ -106,6 +106,19 @@ def test_tile_kernels_all_operand_types(M, K, N, pad):
         assert bool((buf[:, N:] == 777.0).all())
 
 
+@pytest.mark.parametrize("M,K,N,pad", [
+    (25009, 448, 380, 3),    # 256 x 192 tiles, K ends in half a slab, odd rows of y
+    (25201, 1152, 376, 8),   # the same, whole slabs and 16-byte stores, the last tile partly empty both ways
+    (9433, 320, 1531, 0),    # 256 x 256 tiles
+    (40009, 128, 640, 0),    # 128 x 256 tiles, results past the caches
+    (12301, 64, 776, 0),     # 128 x 128 tiles of one step
+    (97, 320, 2048, 0),      # more channels than rows: rows walked first
+])
+def test_tiles_of_whole_rounds(M, K, N, pad):
+    """Tiles that take a CU each, the stores of large results, and the tile order of small ones."""
+    test_tile_kernels_all_operand_types(M, K, N, pad)
+
+
 @pytest.mark.parametrize("K,N,B,L", [(384, 3072, 124, 199), (768, 3072, 128, 197), (768, 1536, 190, 260)])
 def test_weights_in_registers_against_smaller_launches(K, N, B, L):
     """Around nine 128 x 256 units a CU the weight-in-registers kernel takes over: the same bits as two launches of half the
