@@ -18,15 +18,7 @@
 // bytes), the row-streaming kernel of pts_linear_fused.hip (very short reductions over many rows), the
 // weights-in-registers kernel of gemm_wreg.hip (wide outputs, short reductions), and the tile kernels of
 // gemm_tile.hip for everything else.
-#include "mfma_linear.hpp"
-
-#ifndef PTQ4VM_PERSISTENT_BO
-#define PTQ4VM_PERSISTENT_BO 256
-#endif
-#ifndef PTQ4VM_PERSISTENT_PHYS_SLAB
-#define PTQ4VM_PERSISTENT_PHYS_SLAB 128  // K bytes per LDS row of a ring stage (64: twice the stages in the same LDS)
-#define PTQ4VM_PERSISTENT_STAGES 2
-#endif
+#include "gemm_tile.hpp"
 
 namespace {
 
@@ -34,394 +26,305 @@ using namespace ptq4vm::mfma;
 
 // ------------------------------------------------------------------------------------------
 // Large-problem path: persistent workgroups, one per CU, 8 wavefronts on a 256 x 256 tile
-// (wave tile 128 token rows x 64 channels), LDS ring fed by direct global -> LDS copies.
-// Compared with the one-tile-per-workgroup kernels of gemm_tile.hpp:
-//   * the 256 x 256 tile halves the L2 -> LDS traffic per MAC of a 256 x 128 tile (which needs more
-//     L2 bandwidth than the chip has once the MFMA pipes are kept busy); with SLAB = 128 every
-//     copied row segment is a whole 128-byte cache line (measured: 64-byte segments cap the
-//     L2 -> LDS path at ~16 TB/s, 128-byte ones reach 22 TB/s and more);
-//   * the slab pipeline never drains: a workgroup walks its tiles in a loop and the copies for
-//     the next tile's first slabs are issued during the current tile's last slabs and epilogue;
-//   * the MFMA is v_mfma_i32_16x16x64_i8 (v_mfma_f32_16x16x32_f16 on the fp16 path): with random
-//     operand bytes it sustains ~18 % more than the 32x32x32 form on this part (3.5 vs 3.0 POP/s in
-//     an isolated LDS-fed loop; the matrix pipes are clock/power limited once operands toggle),
-//     for the same LDS traffic per MAC;
-//   * MFMA fragments are double buffered in registers: the LDS reads of k-step n+1 are issued
-//     before the MFMAs of k-step n, so LDS latency hides behind the matrix pipe even though all
-//     wavefronts of the workgroup run in lock step;
-//   * per-tile scale vectors (s_w, bias, s_tok[r mod L]) are copied into LDS by the same
-//     asynchronous path at the start of a tile (double buffered), so the epilogue issues no
-//     register loads and never forces the in-flight slabs to land early;
-//   * the epilogue stages fp16 results in the ring stage that was consumed last (free until
-//     the next refill), index arithmetic is 32-bit and tile-relative, full tiles take a
-//     branch-free path.
-// Ring discipline: barrier B(g) sits before the MFMAs of the LAST k-step of slab g-1, after the
-// fragments of that k-step have arrived in registers.  Passing it means (a) every wavefront's
-// copies of slab g have landed (each waited on its own vmcnt first) and (b) nobody will read slab
-// g-1's stage again, so that stage is refilled at once with slab g-1+STAGES (after a tile's last
-// slab the refill waits until the epilogue, which borrows the stage, has finished).
+// (wave tile 128 token rows x 64 channels), LDS ring of two 128-byte slabs fed by direct global -> LDS copies.
+// Compared with the one-tile-per-workgroup kernels of gemm_tile.hpp the stream of slabs never drains: the copies of the
+// next tile's first two slabs are issued at the ends of this tile's last two and land under its epilogue, whose patches
+// have LDS of their own.  As there
+//   * the MFMA is v_mfma_i32_16x16x64_i8 (v_mfma_f32_16x16x32_f16 on the fp16 path): with random operand bytes it sustains ~18 % more
+//     than the 32x32x32 form on this part (the matrix pipes are clock/power limited once operands toggle);
+//   * both operands' fragments are double buffered in registers, fetched ahead of the MFMAs of the step before theirs, and the
+//     waits for them are known to the compiler;
+//   * a slab's end is one barrier: every wavefront holds its last fragments and its copies of the next slab have landed.
+// Loads and stores of a wavefront retire in the order of their issue, so a wait that leaves the youngest operations in flight leaves the
+// epilogue's stores alone: at the end of a tile's first slab, whose successor was requested before them, they may all still be on
+// their way (kStores).  They are buffer stores whose range check drops rows and channels beyond the matrix, so that every wavefront
+// issues the same number whatever its tile.
+// The per-tile scale vectors (s_w, bias, s_tok[r mod L]) are copied into LDS at the start of a tile (double buffered).
 // Requirements (host-checked): 16-byte aligned bases and pitches, 256 * pitch below 2^31, k_bytes % SLAB == 0,
 // k_bytes >= 2 SLAB, N % 8 == 0, 16-byte aligned y pitch, 4-byte aligned bias, 256 * ldy * 2 < 2^31, L < 2^31.
 // ------------------------------------------------------------------------------------------
-// The tiles `first`, `first + stride`, ... (n_my of them) of the grid of (32 FR)-row x BO-channel
+constexpr int kTileCols = 256, kSlab = 128, kPatchPitch = 160;  // (16 rows of 64 fp16; 2 mod 4 pieces of 16 bytes: no bank conflicts)
+template <class Path>
+constexpr int persistent_scale_bytes() {
+    return kTileCols * 4 + 256 * 4 + kTileCols * 2 + (Path::kOffset ? kTileCols * 4 + 256 * 4 : 0);
+}
+template <class Path>
+constexpr int persistent_lds_bytes() {
+    return 2 * (256 + kTileCols) * kSlab + 2 * persistent_scale_bytes<Path>() + 8 * 16 * kPatchPitch;
+}
+
+// The tiles `first`, `first + stride`, ... (n_my of them) of the grid of (32 FR)-row x 256-channel
 // tiles, channel tiles fastest, processed by the whole workgroup.  FR = 8: 256-row tiles; FR = 4:
 // 128-row half tiles (used to spread a last, partial round of tiles over idle workgroups).
-template <class Path, int BO, int SLAB, int STAGES, bool HAS_BIAS, bool DUMP_ACC, int FR>
-__device__ __forceinline__ void persistent_tiles(const LinearArgs &p, const int first, const int stride,
-                                                 const int n_my) {
-    // (32 FR) x 256 tile on 8 wavefronts (one workgroup per CU) or (32 FR) x 128 on 4 (two per CU)
-    constexpr int BR = 32 * FR, WO = BO / 64, NW = 2 * WO;
-    constexpr int WAVE_R = 16 * FR, WAVE_O = 64;
-    constexpr int FO = WAVE_O / 16;  // 16 x 16 MFMA blocks of the wave tile: FO x FR
-    static_assert(FR == 8 || FR == 4, "wave tile height");
-    static_assert(BO == 256 || BO == 128, "tile width");
-    constexpr int KS = SLAB / 64;             // MFMA k-steps (64 bytes of K each) per slab
-    constexpr int CHUNKS = SLAB / 16;         // 16-byte chunks per LDS row
-    constexpr int ROWS_PER_COPY = 64 / CHUNKS;  // rows in one wavefront-wide 1 KiB copy
+template <class Path, bool HAS_BIAS, bool DUMP_ACC, int FR>
+__device__ __forceinline__ void persistent_tiles(const LinearArgs &p, const int first, const int stride, const int n_my) {
+    constexpr int BR = 32 * FR, BO = kTileCols, SLAB = kSlab, NW = 8, WO = 4, WAVE_R = 16 * FR, WAVE_O = 64, FO = WAVE_O / 16;
+    constexpr int CHUNKS = SLAB / 16, ROWS_PER_COPY = 64 / CHUNKS;  // rows in one wavefront-wide 1 KiB copy
     constexpr int X_COPIES = BR / ROWS_PER_COPY / NW, W_COPIES = BO / ROWS_PER_COPY / NW;
-    constexpr int LOADS_PER_SLAB = X_COPIES + W_COPIES;
-    constexpr int STAGE_BYTES = (BR + BO) * SLAB;
-    constexpr int KEEP = (STAGES - 2) * LOADS_PER_SLAB;  // copies allowed in flight when a slab is needed
-    static_assert(SLAB == 64 || SLAB == 128, "LDS rows hold 64 or 128 bytes of K");
-    static_assert(NW * 32 * WAVE_O * 2 <= STAGE_BYTES, "epilogue patches must fit one stage");
+    constexpr int STAGE_BYTES = (BR + BO) * SLAB, SCALE_BYTES = persistent_scale_bytes<Path>();
+    constexpr int kStores = 2 * FR;  // of a wavefront and tile
     constexpr bool kInt8 = Path::kElemBytes == 1;
     using Acc = typename Path::Acc16;
 
     char *const ring = lds_dyn;
-    // per-tile scale vectors, double buffered by tile parity
-    constexpr int SCALE_BYTES = BO * 4 + BR * 4 + BO * 2 + (Path::kOffset ? BO * 4 + BR * 4 : 0);
-    char *const scales = lds_dyn + STAGES * STAGE_BYTES;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    char *const scales = lds_dyn + 2 * (256 + BO) * SLAB;  // per-tile scale vectors, double buffered by tile parity
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char *const patch = scales + 2 * SCALE_BYTES + wave * (16 * kPatchPitch);
     const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
     const int l16 = lane & 15, lq = lane >> 4;
-    auto lds_chunk = [&](int row, int chunk) {  // byte offset of a 16-byte chunk inside a stage half
-        return row * SLAB + ((chunk ^ (SLAB == 64 ? swizzle(row) : (row & 7))) << 4);
-    };
 
-    const int wgs_per_xcd = stride, last = first + n_my * stride;
+    const int last = first + n_my * stride;
     const int n_slabs = (int)(p.k_bytes / SLAB);
     const int total_slabs = n_my * n_slabs;
     if (total_slabs == 0) return;
+    // The lane by way of a zero that the compiler cannot see through: addresses built on it are computed where they are used instead
+    // of being hoisted out of the tile loop into scratch memory, whose loads would wait for every copy and store in flight.
+    auto lane_now = [&]() {
+        uint32_t zero;
+        asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+        return (int)((threadIdx.x + zero) & 63);
+    };
 
     // ---- producer: the next slab to copy, possibly of a later tile than the one being computed
-    int pf_tile = first, pf_slab = 0, pf_stage = 0, issued = 0;
+    int pf_tile = first, pf_slab = 0, issued = 0;
     const char *pf_x = nullptr, *pf_w = nullptr;
-    uint32_t x_off[X_COPIES], w_off[W_COPIES];
+    int pf_rows = 0, pf_cols = 0;
     auto pf_setup = [&]() {
-        const int to = pf_tile % p.tiles_o, tr = pf_tile / p.tiles_o;
+        const int tr = pf_tile / p.tiles_o, to = pf_tile - tr * p.tiles_o;
         const int64_t r0 = (int64_t)tr * BR, o0 = (int64_t)to * BO;
         pf_x = p.x + r0 * p.ldx_bytes;
         pf_w = p.w + o0 * p.ldw_bytes;
-        const int rows_x = (int)min((int64_t)BR, p.M - r0), rows_w = (int)min((int64_t)BO, p.N - o0);
+        pf_rows = (int)min((int64_t)BR, p.M - r0), pf_cols = (int)min((int64_t)BO, p.N - o0);
+    };
+    const int copy_row = wave * ROWS_PER_COPY + lane / CHUNKS;  // (rows of later copies differ by multiples of 64: same swizzle, same order)
+    const int copy_channel = channel_of_row(copy_row);
+    const uint32_t copy_chunk = (uint32_t)((lane % CHUNKS) ^ (copy_row & 7)) * 16;
+    auto issue = [&](int stage) {  // copy the producer's slab into a ring stage, then advance
+        char *const sx = ring + stage * STAGE_BYTES, *const sw = sx + BR * SLAB;
+        const char *const gx = pf_x + (int64_t)pf_slab * SLAB, *const gw = pf_w + (int64_t)pf_slab * SLAB;
 #pragma unroll
-        for (int i = 0; i < X_COPIES; i++) {
-            const int row = (wave + NW * i) * ROWS_PER_COPY + lane / CHUNKS;
-            const int chunk = (lane % CHUNKS) ^ (SLAB == 64 ? swizzle(row) : (row & 7));
-            x_off[i] = (uint32_t)min(row, rows_x - 1) * (uint32_t)p.ldx_bytes + chunk * 16;
+        for (int i = 0; i < X_COPIES; i++) {  // (pitches are below 2^23)
+            const uint32_t off = __umul24((uint32_t)min(copy_row + NW * ROWS_PER_COPY * i, pf_rows - 1), (uint32_t)p.ldx_bytes) + copy_chunk;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gx + off),
+                                             (__attribute__((address_space(3))) void *)(sx + (wave + NW * i) * 1024), 16, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < W_COPIES; i++) {
-            const int row = (wave + NW * i) * ROWS_PER_COPY + lane / CHUNKS;
-            const int chunk = (lane % CHUNKS) ^ (SLAB == 64 ? swizzle(row) : (row & 7));
-            w_off[i] = (uint32_t)min(row, rows_w - 1) * (uint32_t)p.ldw_bytes + chunk * 16;
+            const uint32_t off = __umul24((uint32_t)min(copy_channel + NW * ROWS_PER_COPY * i, pf_cols - 1), (uint32_t)p.ldw_bytes) + copy_chunk;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gw + off),
+                                             (__attribute__((address_space(3))) void *)(sw + (wave + NW * i) * 1024), 16, 0, 0);
         }
-    };
-    auto issue = [&]() {  // copy the producer's slab into ring stage pf_stage, then advance
-        char *sx = ring + pf_stage * STAGE_BYTES;
-        char *sw = sx + BR * SLAB;
-        const char *gx = pf_x + (int64_t)pf_slab * SLAB;
-        const char *gw = pf_w + (int64_t)pf_slab * SLAB;
-#pragma unroll
-        for (int i = 0; i < X_COPIES; i++)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gx + x_off[i]),
-                                             (__attribute__((address_space(3))) void *)(sx + (wave + NW * i) * 1024),
-                                             16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < W_COPIES; i++)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gw + w_off[i]),
-                                             (__attribute__((address_space(3))) void *)(sw + (wave + NW * i) * 1024),
-                                             16, 0, 0);
         issued++;
-        if (++pf_stage == STAGES) pf_stage = 0;
         if (++pf_slab == n_slabs) {
             pf_slab = 0;
-            pf_tile += wgs_per_xcd;
+            pf_tile += stride;
             if (pf_tile < last) pf_setup();
         }
     };
-    // Slab g has landed for this wavefront once at most `younger` of its copies are outstanding.
-    auto wait_slab = [&](int g) {
-        if (g + STAGES - 2 < total_slabs)
-            wait_vmcnt_at_most<KEEP>();
-        else
-            wait_vmcnt_at_most<0>();
+
+    Acc acc[FO][FR];
+    // The activations' fragments are doubled in half tiles only: beside 128 result registers each is fetched again as soon as its MFMAs have
+    // been issued.
+    constexpr bool TIGHT = FR == 8;
+    v4i fw[2][FO], fx[TIGHT ? 1 : 2][FR];
+    uint32_t frag[2];  // where row l16 of a block has the lane's operand
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) frag[ks] = (uint32_t)l16 * SLAB + (((4 * ks + lq) ^ (l16 & 7)) << 4);
+    auto load_fw = [&](int buf, int stage, int ks) {
+        const char *const sw = ring + stage * STAGE_BYTES + (BR + wave_o) * SLAB + frag[ks];
+#pragma unroll
+        for (int i = 0; i < FO; i++) fw[buf][i] = *reinterpret_cast<const v4i *>(sw + i * 16 * SLAB);
+    };
+    auto load_fx = [&](int buf, int j, int stage, int ks) {
+        fx[TIGHT ? 0 : buf][j] = *reinterpret_cast<const v4i *>(ring + stage * STAGE_BYTES + wave_r * SLAB + frag[ks] + j * 16 * SLAB);
+    };
+    auto load_fragments = [&](int buf, int stage, int ks) {
+        load_fw(buf, stage, ks);
+#pragma unroll
+        for (int j = 0; j < FR; j++) load_fx(buf, j, stage, ks);
+    };
+    auto products = [&](int buf, bool fresh, auto fetch) {  // fresh: the tile's first step; fetch(j) behind the MFMAs of row block j
+        const Acc zero = {0, 0, 0, 0};
+        v4i we[FO], wo[FO];
+#pragma unroll
+        for (int i = 0; i < FO; i++) {
+            // a packed 16-byte fragment is two MFMA operands: even and odd reduction indices
+            if constexpr (Path::kPacked4)
+                we[i] = Path::even_codes(fw[buf][i]), wo[i] = Path::odd_codes(fw[buf][i]);
+            else
+                we[i] = fw[buf][i];
+        }
+#pragma unroll
+        for (int j = 0; j < FR; j++) {
+            const v4i x = fx[TIGHT ? 0 : buf][j];
+            if constexpr (Path::kPacked4) {
+                const v4i xe = Path::even_codes(x), xo = Path::odd_codes(x);
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(we[i], xe, fresh ? zero : acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(wo[i], xo, acc[i][j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(we[i], x, fresh ? zero : acc[i][j]);
+            }
+            fetch(j);
+        }
+    };
+    // The products of buffer `buf` while the fragments of step `ks` of ring stage `stg` arrive for buffer buf ^ 1
+    auto products_and_fetch = [&](int buf, bool fresh, int stg, int ks) {
+        if constexpr (TIGHT) {
+            load_fw(buf ^ 1, stg, ks);
+            products(buf, fresh, [&](int j) {
+                load_fx(0, j, stg, ks);
+                __builtin_amdgcn_sched_barrier(0);  // keep a fetch behind the MFMAs that free its registers
+            });
+        } else {
+            load_fragments(buf ^ 1, stg, ks);
+            __builtin_amdgcn_sched_barrier(0);  // fetch first, then multiply
+            products(buf, fresh, [](int) {});
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
 
     pf_setup();
-    while (issued < STAGES - 1 && issued < total_slabs) issue();
-    wait_slab(0);
-    __builtin_amdgcn_s_barrier();  // B(0)
-    if (issued < total_slabs) issue();
+    issue(0);
+    issue(1);  // (a tile has two slabs at least)
+    wait_vmcnt_at_most<X_COPIES + W_COPIES>();
+    __builtin_amdgcn_s_barrier();
+    wait_lgkmcnt_0();
+    load_fragments(0, 0, 0);
 
-    int stage = 0, g = 0, parity = 0;  // consumer: ring stage, running slab number, scale buffer
-    for (int tile = first; tile < last; tile += wgs_per_xcd, parity ^= 1) {
-        const int tile_o = tile % p.tiles_o, tile_r = tile / p.tiles_o;
+    int stage = 0, parity = 0;  // consumer: ring stage, scale buffer
+    for (int tile = first; tile < last; tile += stride, parity ^= 1) {
+        const int tile_r = tile / p.tiles_o, tile_o = tile - tile_r * p.tiles_o;
         const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
         const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
         float *const cs_lds = reinterpret_cast<float *>(scales + parity * SCALE_BYTES);  // s_w of the tile's channels
         float *const rs_lds = cs_lds + BO;                                              // s_tok of the tile's rows
-        uint32_t *const cb_lds = reinterpret_cast<uint32_t *>(rs_lds + BR);             // bias, two fp16 per word
+        uint32_t *const cb_lds = reinterpret_cast<uint32_t *>(rs_lds + 256);            // bias, two fp16 per word
         int *const cz_lds = reinterpret_cast<int *>(cb_lds + BO / 2);                   // rowsum of the tile's channels
         int *const rz_lds = cz_lds + BO;                                                // z_tok of the tile's rows
 
-        // Scale vectors of this tile, one 4-byte element per lane, straight into LDS.  Indices
-        // beyond the matrix are clamped; those rows / channels are never stored.
-        constexpr int kScaleTasks = BO / 64 + BR / 64 + BO / 128;
-        constexpr int kOffsetTasks = Path::kOffset ? BO / 64 + BR / 64 : 0;
+        // Scale vectors of this tile, 64 elements of 4 bytes a task, straight into LDS.  Indices beyond the matrix are clamped; those
+        // rows / channels are never stored.  The tasks are dealt round-robin to the wavefronts.
+        constexpr int kColTasks = BO / 64, kRowTasks = BR / 64, kBiasTasks = BO / 128;
+        constexpr int kScaleTasks = kColTasks + kRowTasks + kBiasTasks, kOffsetTasks = Path::kOffset ? kColTasks + kRowTasks : 0;
+        auto copy_element = [&](const void *src, void *dst) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
+        };
+        const int ln = lane_now();
+        auto token = [&](int block) {
+            const uint32_t t0 = p.M <= 0x7fffffffLL ? (uint32_t)r0 % (uint32_t)p.L : (uint32_t)(r0 % p.L);
+            return (t0 + (uint32_t)min(block * 64 + ln, rows_valid - 1)) % (uint32_t)p.L;
+        };
 #pragma unroll
-        for (int task = kScaleTasks; task < kScaleTasks + kOffsetTasks; task++) {
+        for (int task = 0; task < kScaleTasks + kOffsetTasks; task++) {
             if (task % NW != wave) continue;
-            if constexpr (Path::kOffset) {
+            if (task < kColTasks) {
+                if constexpr (kInt8) copy_element(p.s_w + o0 + min(task * 64 + ln, cols_valid - 1), cs_lds + task * 64);
+            } else if (task < kColTasks + kRowTasks) {
+                if constexpr (kInt8) copy_element(p.s_tok + token(task - kColTasks), rs_lds + (task - kColTasks) * 64);
+            } else if (task < kScaleTasks) {
+                const int blk = task - kColTasks - kRowTasks;
+                if constexpr (HAS_BIAS) copy_element(reinterpret_cast<const uint32_t *>(p.bias + o0) + min(blk * 64 + ln, cols_valid / 2 - 1), cb_lds + blk * 64);
+            } else if constexpr (Path::kOffset) {
                 const int blk = task - kScaleTasks;
-                if (blk < BO / 64) {  // rowsum of 64 channels
-                    const int c = min(blk * 64 + lane, cols_valid - 1);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p.rowsum + o0 + c),
-                                                     (__attribute__((address_space(3))) void *)(cz_lds + blk * 64), 4, 0, 0);
-                } else {  // z_tok of 64 rows
-                    const int rblk = blk - BO / 64;
-                    const int r = min(rblk * 64 + lane, rows_valid - 1);
-                    const uint32_t t = ((uint32_t)(r0 % p.L) + (uint32_t)r) % (uint32_t)p.L;
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p.z_tok + t),
-                                                     (__attribute__((address_space(3))) void *)(rz_lds + rblk * 64), 4, 0, 0);
-                }
+                if (blk < kColTasks)
+                    copy_element(p.rowsum + o0 + min(blk * 64 + ln, cols_valid - 1), cz_lds + blk * 64);
+                else
+                    copy_element(p.z_tok + token(blk - kColTasks), rz_lds + (blk - kColTasks) * 64);
             }
         }
-#pragma unroll
-        for (int task = 0; task < kScaleTasks; task++) {
-            if (task % NW != wave) continue;  // the copies are dealt round-robin to the wavefronts
-            if (task < BO / 64) {             // s_w of 64 channels
-                if constexpr (kInt8) {
-                    const int c = min(task * 64 + lane, cols_valid - 1);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p.s_w + o0 + c),
-                                                     (__attribute__((address_space(3))) void *)(cs_lds + task * 64), 4, 0, 0);
-                }
-            } else if (task < BO / 64 + BR / 64) {  // s_tok of 64 rows
-                if constexpr (kInt8) {
-                    const int blk = task - BO / 64;
-                    const int r = min(blk * 64 + lane, rows_valid - 1);
-                    const uint32_t t = ((uint32_t)(r0 % p.L) + (uint32_t)r) % (uint32_t)p.L;
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(p.s_tok + t),
-                                                     (__attribute__((address_space(3))) void *)(rs_lds + blk * 64), 4, 0, 0);
-                }
-            } else {  // bias of 128 channels, two fp16 per lane
-                if constexpr (HAS_BIAS) {
-                    const int blk = task - BO / 64 - BR / 64;
-                    const int c2 = min(blk * 64 + lane, cols_valid / 2 - 1);
-                    __builtin_amdgcn_global_load_lds(
-                        (const __attribute__((address_space(1))) void *)(reinterpret_cast<const uint32_t *>(p.bias + o0) + c2),
-                        (__attribute__((address_space(3))) void *)(cb_lds + blk * 64), 4, 0, 0);
-                }
-            }
-        }
-        int loads_after_scales = 0;
 
-        Acc acc[FO][FR];
-#pragma unroll
-        for (int i = 0; i < FO; i++)
-#pragma unroll
-            for (int j = 0; j < FR; j++)
-#pragma unroll
-                for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
-
-        // Weight fragments are double buffered; an activation fragment is dead after its FO MFMAs
-        // of a k-step, so the next k-step's fragment is fetched into the same registers right then.
-        v4i fw[2][FO], fx[FR];
-        auto load_fw = [&](int buf, int stg, int ks) {
-            const char *sw = ring + stg * STAGE_BYTES + (BR + wave_o) * SLAB;
-#pragma unroll
-            for (int i = 0; i < FO; i++) fw[buf][i] = *reinterpret_cast<const v4i *>(sw + lds_chunk(i * 16 + l16, 4 * ks + lq));
+        // One step inside a slab, one at its end (s: its number in the tile), where everyone holds the slab's last fragments
+        auto step_inside = [&](bool fresh) {
+            wait_lgkmcnt_0();
+            products_and_fetch(0, fresh, stage, 1);
         };
-        auto load_fx = [&](int j, int stg, int ks) {
-            const char *sx = ring + stg * STAGE_BYTES + wave_r * SLAB;
-            fx[j] = *reinterpret_cast<const v4i *>(sx + lds_chunk(j * 16 + l16, 4 * ks + lq));
+        auto slab_end = [&](bool stores_younger) {  // the next slab landed and everyone here: it is visible, this one's stage is free
+            wait_lgkmcnt_0();
+            if (stores_younger)
+                wait_vmcnt_at_most<kStores>();
+            else
+                wait_vmcnt_at_most<0>();
+            __builtin_amdgcn_s_barrier();
+            if (issued < total_slabs) issue(stage);
+            stage ^= 1;
         };
-
-        load_fw(0, stage, 0);  // B(g) for the tile's first slab was passed during the previous tile
-#pragma unroll
-        for (int j = 0; j < FR; j++) load_fx(j, stage, 0);
-        // U slabs per trip of the loop, so that the register buffer of the weight fragments, which
-        // alternates per k-step, starts every trip (and every tile) at buffer 0.
-        constexpr int U = (KS % 2 == 0) ? 1 : 2;
-        for (int s0 = 0; s0 < n_slabs; s0 += U)
-#pragma unroll
-        for (int h = 0; h < U; h++, g++) {
-            const int s = s0 + h;
-            int next_stage = stage + 1;
-            if (next_stage == STAGES) next_stage = 0;
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                const int cur = (h * KS + ks) & 1;
-                bool has_next = false;
-                int nstg = stage, nks = ks + 1;
-                if (ks + 1 < KS) {
-                    has_next = true;
-                } else if (g + 1 < total_slabs) {
-                    // B(g+1): this wavefront holds the last fragments of slab g in registers and its
-                    // copies of slab g+1 have landed.
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    wait_slab(g + 1);
-                    __builtin_amdgcn_s_barrier();
-                    if (s + 1 < n_slabs) {
-                        if (issued < total_slabs) {
-                            issue();  // refills the stage of slab g
-                            loads_after_scales += LOADS_PER_SLAB;
-                        }
-                        has_next = true, nstg = next_stage, nks = 0;
-                    }  // after the tile's last slab that stage first serves the epilogue
-                }
-                if constexpr (Path::kPacked4) {
-                    // a packed 16-byte fragment is two MFMA operands: even and odd reduction indices
-                    v4i we[FO], wo[FO];
-#pragma unroll
-                    for (int i = 0; i < FO; i++) we[i] = Path::even_codes(fw[cur][i]), wo[i] = Path::odd_codes(fw[cur][i]);
-                    if (has_next) load_fw(cur ^ 1, nstg, nks);
-#pragma unroll
-                    for (int j = 0; j < FR; j++) {
-                        const v4i xe = Path::even_codes(fx[j]), xo = Path::odd_codes(fx[j]);
-                        if (has_next) load_fx(j, nstg, nks);
-#pragma unroll
-                        for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(we[i], xe, acc[i][j]);
-#pragma unroll
-                        for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(wo[i], xo, acc[i][j]);
-                    }
-                } else {
-                    if (has_next) load_fw(cur ^ 1, nstg, nks);
-#pragma unroll
-                    for (int j = 0; j < FR; j++) {
-#pragma unroll
-                        for (int i = 0; i < FO; i++) acc[i][j] = Path::mfma16(fw[cur][i], fx[j], acc[i][j]);
-                        if (has_next) load_fx(j, nstg, nks);
-                    }
-                }
-            }
-            stage = next_stage;
+        auto step_over = [&](bool stores_younger) {
+            slab_end(stores_younger);
+            products_and_fetch(1, false, stage, 0);
+        };
+        step_inside(true);
+        step_over(tile != first && !DUMP_ACC);
+#pragma unroll 1
+        for (int s = 1; s + 1 < n_slabs; s++) {
+            step_inside(false);
+            step_over(false);
         }
+        step_inside(false);
+        slab_end(false);  // (also: the tile's scale vectors are visible)
+        products(1, false, [](int) {});
+        __builtin_amdgcn_sched_barrier(0);
 
-        // ---- epilogue of this tile.  The ring stage of the tile's last slab is free: B(g) was passed
-        // with that slab's fragments in registers and its refill has been held back; it holds the
-        // wavefronts' fp16 patches until the barrier that ends the epilogue.
-        if (loads_after_scales >= KEEP && KEEP > 0)
-            wait_vmcnt_at_most<KEEP>();
-        else
-            wait_vmcnt_at_most<0>();
-        __builtin_amdgcn_s_barrier();  // scale vectors are visible to every wavefront
-        const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;  // stage of the tile's last slab
-        char *patch = ring + free_stage * STAGE_BYTES + wave * (32 * WAVE_O * 2);
-        char *y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
+        // ---- epilogue.  Accumulator register v of block (i, j): token row 16 j + l16, channel 32 (i / 2) + 8 lq + 4 (i mod 2) + v.
+        // Each 16-row block crosses the wavefront's patch into stores of eight whole 128-byte row segments; a block's stores are issued
+        // behind the conversion of the next one, so that its way through LDS costs no wait.
+        const int le = lane_now(), e16 = le & 15, eq = le >> 4;
+        v4f cs[FO / 2][2], cb[FO / 2];
+        v4i cz[FO / 2][2];
+#pragma unroll
+        for (int g = 0; g < FO / 2; g++) {
+            const int col = wave_o + 32 * g + 8 * eq;
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                cs[g][h] = *reinterpret_cast<const v4f *>(cs_lds + col + 4 * h);
+                cz[g][h] = Path::kOffset ? *reinterpret_cast<const v4i *>(cz_lds + col + 4 * h) : v4i{0, 0, 0, 0};
+            }
+            cb[g] = HAS_BIAS ? *reinterpret_cast<const v4f *>(cb_lds + col / 2) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
         const uint32_t ldy_bytes = (uint32_t)p.ldy * 2;
-        auto patch_chunk = [&](int row, int chunk) { return row * (WAVE_O * 2) + ((chunk ^ (row & 7)) << 4); };
-        const bool full_tile = rows_valid == BR && cols_valid == BO;
-
-        // Accumulator register v of block (i, j):  token row 16 j + (lane mod 16),
-        // channel 16 i + 4 (lane / 16) + v.  Column scales / biases of this lane's 16 channels
-        // (cb_raw[i] holds the eight fp16 biases around them), row scales of its 8 rows.
-        v4f cs_raw[4], cb_raw[4];
-        float rs_raw[8];
-        if constexpr (kInt8) lds_read_4x_b128<64>(lds_addr(cs_lds + wave_o + lq * 4), cs_raw);
-        if constexpr (HAS_BIAS) lds_read_4x_b128<32>(lds_addr(cb_lds + (wave_o + (lq >> 1) * 8) / 2), cb_raw);
-        if constexpr (kInt8) {
-            if constexpr (FR == 8) {
-                lds_read_8x_b32<64>(lds_addr(rs_lds + wave_r + l16), rs_raw);
-            } else {
-                float half_rs[4];
-                lds_read_4x_b32<64>(lds_addr(rs_lds + wave_r + l16), half_rs);
+        const int srow = le >> 3, scol = wave_o + (le & 7) * 8;
+        const uint32_t beyond = 0x80000000u;  // past every tile's span
+        const uint32_t y_off = scol < cols_valid ? (uint32_t)(wave_r + srow) * ldy_bytes + (uint32_t)scol * 2 : beyond;
+        const __amdgpu_buffer_rsrc_t y_rows =
+            __builtin_amdgcn_make_buffer_rsrc(p.y + r0 * p.ldy + o0, 0, (int)(((int64_t)(rows_valid - 1) * p.ldy + cols_valid) * 2), 0x00020000);
+        v4f data[2];
+        auto store_block = [&](int j) {
+            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
-                for (int j = 0; j < 4; j++) rs_raw[j] = half_rs[j];
-            }
-        }
-        v4f cz_raw[4];   // rowsum of the lane's channels and z_tok of its rows (zero-offset path), as raw bits
-        float rz_raw[8];
-        if constexpr (Path::kOffset) {
-            lds_read_4x_b128<64>(lds_addr(cz_lds + wave_o + lq * 4), cz_raw);
-            if constexpr (FR == 8) {
-                lds_read_8x_b32<64>(lds_addr(rz_lds + wave_r + l16), rz_raw);
-            } else {
-                float half_rz[4];
-                lds_read_4x_b32<64>(lds_addr(rz_lds + wave_r + l16), half_rz);
+            for (int h = 0; h < 2; h++)  // non-temporal: measured 4-8 % faster than write-back stores here
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, (int)(y_off + (uint32_t)(j * 16 + h * 8) * ldy_bytes), 0, 2);
+        };
 #pragma unroll
-                for (int j = 0; j < 4; j++) rz_raw[j] = half_rz[j];
-            }
-        }
-        float bias4[FO][4];
+        for (int j = 0; j < FR; j++) {
+            const float rs = kInt8 ? rs_lds[wave_r + j * 16 + e16] : 1.0f;
+            const int rz = Path::kOffset ? rz_lds[wave_r + j * 16 + e16] : 0;
+            v4f out[FO / 2];
 #pragma unroll
-        for (int i = 0; i < FO; i++) {
+            for (int g = 0; g < FO / 2; g++) {
+                const v2f lo = finish_four<Path>(acc[2 * g][j], rs, rz, cs[g][0], cz[g][0], v2f{cb[g].x, cb[g].y});
+                const v2f hi = finish_four<Path>(acc[2 * g + 1][j], rs, rz, cs[g][1], cz[g][1], v2f{cb[g].z, cb[g].w});
+                out[g] = v4f{lo.x, lo.y, hi.x, hi.y};
+                if constexpr (DUMP_ACC) {
 #pragma unroll
-            for (int c = 0; c < 4; c++) bias4[i][c] = 0.0f;
-            if constexpr (HAS_BIAS) {
-                const float w01 = (lq & 1) ? cb_raw[i].z : cb_raw[i].x, w23 = (lq & 1) ? cb_raw[i].w : cb_raw[i].y;
-                const __half2 b01 = __builtin_bit_cast(__half2, w01), b23 = __builtin_bit_cast(__half2, w23);
-                bias4[i][0] = __low2float(b01), bias4[i][1] = __high2float(b01);
-                bias4[i][2] = __low2float(b23), bias4[i][3] = __high2float(b23);
-            }
-        }
-
-#pragma unroll
-        for (int jp = 0; jp < FR / 2; jp++) {  // 32 rows per round through the patch
-#pragma unroll
-            for (int jj = 0; jj < 2; jj++) {
-                const int j = 2 * jp + jj;
-#pragma unroll
-                for (int i = 0; i < FO; i++) {
-                    float out[4];
-#pragma unroll
-                    for (int c = 0; c < 4; c++) {
-                        if constexpr (kInt8) {
-                            int a = acc[i][j][c];
-                            if constexpr (Path::kPacked4) a >>= 8;  // operands were codes times 16: exact
-                            if constexpr (DUMP_ACC) {
-                                const int64_t r = r0 + wave_r + j * 16 + l16;
-                                const int64_t o = o0 + wave_o + i * 16 + lq * 4 + c;
-                                if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = a;
-                            }
-                            if constexpr (Path::kOffset) {
-                                const float zf = rz_raw[j], sf = cz_raw[i][c];  // scalars first: bit casts of vector elements misread
-                                a -= __mul24(__builtin_bit_cast(int, zf), __builtin_bit_cast(int, sf));  // |z| < 2^8, |rowsum| < 2^23
-                            }
-                            out[c] = (float)a * (rs_raw[j] * cs_raw[i][c]) + bias4[i][c];
-                        } else {
-                            out[c] = acc[i][j][c] + bias4[i][c];
-                        }
+                    for (int c = 0; c < 8; c++) {
+                        const int64_t r = r0 + wave_r + j * 16 + e16, o = o0 + wave_o + 32 * g + 8 * eq + c;
+                        const int a = (int)acc[2 * g + (c >> 2)][j][c & 3];
+                        if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = Path::kPacked4 ? a >> 8 : a;
                     }
-                    __half2 lo = __floats2half2_rn(out[0], out[1]);
-                    __half2 hi = __floats2half2_rn(out[2], out[3]);
-                    u32x2 packed = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                    lds_write_b64(lds_addr(patch + patch_chunk(jj * 16 + l16, 2 * i + (lq >> 1)) + (lq & 1) * 8), packed);
                 }
             }
-            v4f data[4];
-            uint32_t src[4];
+            if (j > 0) store_block(j - 1);
+            asm volatile("" ::: "memory");  // wavefront-private patch: LDS runs a wavefront's accesses in order
 #pragma unroll
-            for (int q = 0; q < 4; q++)  // 8 rows x 128 bytes per store instruction
-                src[q] = lds_addr(patch + patch_chunk(q * 8 + (lane >> 3), lane & 7));
-            lds_read_4_b128(src, data);
-            const uint32_t base = (uint32_t)(wave_r + jp * 32 + (lane >> 3)) * ldy_bytes + (uint32_t)(wave_o + (lane & 7) * 8) * 2;
-            if (full_tile) {
+            for (int g = 0; g < FO / 2; g++) *reinterpret_cast<v4f *>(patch + e16 * kPatchPitch + (4 * g + eq) * 16) = out[g];
+            asm volatile("" ::: "memory");
 #pragma unroll
-                for (int q = 0; q < 4; q++)
-                    // non-temporal: measured 4-8 % faster than write-back stores here
-                    __builtin_nontemporal_store(data[q], reinterpret_cast<v4f *>(y_tile + base + (uint32_t)(q * 8) * ldy_bytes));
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const int rr = wave_r + jp * 32 + q * 8 + (lane >> 3), cc = wave_o + (lane & 7) * 8;
-                    if (rr < rows_valid && cc < cols_valid)
-                        *reinterpret_cast<v4f *>(y_tile + base + (uint32_t)(q * 8) * ldy_bytes) = data[q];
-                }
-            }
+            for (int h = 0; h < 2; h++) data[h] = *reinterpret_cast<const v4f *>(patch + (h * 8 + srow) * kPatchPitch + (le & 7) * 16);
         }
-        __builtin_amdgcn_s_barrier();  // every wavefront has read its patch back: the stage can be refilled
-        if (issued < total_slabs) issue();
+        store_block(FR - 1);
+        load_fragments(0, stage, 0);  // the next tile's first (behind the last tile: what is left in the ring, unused)
     }
 }
 
@@ -435,8 +338,8 @@ __device__ __forceinline__ void persistent_tiles(const LinearArgs &p, const int 
 // workgroups' epilogues out of step with the others' (in_proj, 9.23 rounds: 149.4 -> 146.9 us; with
 // the halves last it gained nothing there).  FRM = 4: every tile has 128 rows (packed 4-bit operands,
 // whose expanded fragments would not fit the register file next to a 256-row tile's accumulators).
-template <class Path, int BO, int SLAB, int STAGES, bool HAS_BIAS, bool DUMP_ACC, int FRM>
-__global__ __launch_bounds__(BO * 2, 2) void linear_mfma_persistent(const LinearArgs p) {
+template <class Path, bool HAS_BIAS, bool DUMP_ACC, int FRM>
+__global__ __launch_bounds__(512, 2) void linear_mfma_persistent(const LinearArgs p) {
     const int total_tiles = p.tiles_o * p.tiles_r;
     const int per_xcd = (total_tiles + kXcds - 1) / kXcds;
     const int wpx = (int)gridDim.x / kXcds, xcd = (int)(blockIdx.x % kXcds), j = (int)(blockIdx.x / kXcds);
@@ -450,13 +353,13 @@ __global__ __launch_bounds__(BO * 2, 2) void linear_mfma_persistent(const Linear
             const int tile = lo + rounds * wpx + (j >> 1);
             const int half_tile = ((tile / p.tiles_o) * 2 + (j & 1)) * p.tiles_o + tile % p.tiles_o;  // in the 128-row grid
             if ((int64_t)(half_tile / p.tiles_o) * 128 < p.M) {
-                persistent_tiles<Path, BO, SLAB, STAGES, HAS_BIAS, DUMP_ACC, 4>(p, half_tile, 1, 1);
+                persistent_tiles<Path, HAS_BIAS, DUMP_ACC, 4>(p, half_tile, 1, 1);
                 __syncthreads();  // the ring and the scale buffers change layout
             }
         }
-        persistent_tiles<Path, BO, SLAB, STAGES, HAS_BIAS, DUMP_ACC, 8>(p, lo + j, wpx, n_full);
+        persistent_tiles<Path, HAS_BIAS, DUMP_ACC, 8>(p, lo + j, wpx, n_full);
     } else {
-        persistent_tiles<Path, BO, SLAB, STAGES, HAS_BIAS, DUMP_ACC, 4>(p, lo + j, wpx, rounds + (j < tail ? 1 : 0));
+        persistent_tiles<Path, HAS_BIAS, DUMP_ACC, 4>(p, lo + j, wpx, rounds + (j < tail ? 1 : 0));
     }
 }
 
@@ -596,29 +499,28 @@ __global__ __launch_bounds__(kThreads) void linear_mfma_smallk(const LinearArgs 
 // ------------------------------------------------------------------------------------------
 // Host side
 // ------------------------------------------------------------------------------------------
-template <class Path, int BO, int SLAB, int STAGES>
+template <class Path>
 int launch_persistent(LinearArgs a, hipStream_t stream) {
     constexpr int FRM = Path::kPacked4 ? 4 : 8;  // tile rows / 32
     dim3 grid;
-    if (!set_grid<32 * FRM, BO>(a, grid)) return PTQ4VM_ERR_SHAPE;
-    // One 8-wavefront or two 4-wavefront workgroups per CU (all that LDS allows), a multiple of the XCD count.
+    if (!set_grid<32 * FRM, kTileCols>(a, grid)) return PTQ4VM_ERR_SHAPE;
+    // One 8-wavefront workgroup per CU (all that LDS allows), a multiple of the XCD count.
     int device = 0, cus = 0;
     hipError_t err = hipGetDevice(&device);
     if (err == hipSuccess) err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (err != hipSuccess) return ptq4vm::record_hip_error(err, "hipDeviceGetAttribute(multiprocessor count)");
-    unsigned wgs = (unsigned)(cus / kXcds * kXcds) * (BO == 256 ? 1 : 2);
+    unsigned wgs = (unsigned)(cus / kXcds * kXcds);
     if (wgs == 0) wgs = kXcds;
     if (wgs > grid.x) wgs = grid.x;  // grid.x is the tile count rounded up to a multiple of kXcds
-    constexpr int lds_bytes = STAGES * (256 + BO) * SLAB + 2 * (BO * 4 + 256 * 4 + BO * 2 + (Path::kOffset ? BO * 4 + 256 * 4 : 0));
+    constexpr int lds_bytes = persistent_lds_bytes<Path>();
+    static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");
     using Kernel = void (*)(const LinearArgs);
     // [has bias][also write the int32 accumulators]
-    static const Kernel kernels[2][2] = {{linear_mfma_persistent<Path, BO, SLAB, STAGES, false, false, FRM>,
-                                          linear_mfma_persistent<Path, BO, SLAB, STAGES, false, true, FRM>},
-                                         {linear_mfma_persistent<Path, BO, SLAB, STAGES, true, false, FRM>,
-                                          linear_mfma_persistent<Path, BO, SLAB, STAGES, true, true, FRM>}};
+    static const Kernel kernels[2][2] = {{linear_mfma_persistent<Path, false, false, FRM>, linear_mfma_persistent<Path, false, true, FRM>},
+                                         {linear_mfma_persistent<Path, true, false, FRM>, linear_mfma_persistent<Path, true, true, FRM>}};
     const Kernel kernel = kernels[a.bias ? 1 : 0][a.acc_out ? 1 : 0];
     if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_mfma_persistent)")) return rc;
-    kernel<<<dim3(wgs), dim3(BO * 2), lds_bytes, stream>>>(a);
+    kernel<<<dim3(wgs), dim3(512), lds_bytes, stream>>>(a);
     return ptq4vm::check_launch("linear_mfma_persistent");
 }
 
@@ -695,9 +597,9 @@ int dispatch(LinearArgs a, hipStream_t stream) {
                                a.N % 8 == 0 && a.y_vec == 8 && ptq4vm::aligned_to(a.bias, 4) &&
                                a.ldy * 512 < (1LL << 31) && a.L < (1LL << 31) && a.N >= 256 &&
                                ptq4vm::ceil_div(a.N, 256) * 256 * 4 <= a.N * 5 &&
-                               a.k_bytes % PTQ4VM_PERSISTENT_SLAB == 0 && a.k_bytes >= 2 * PTQ4VM_PERSISTENT_SLAB &&
+                               a.k_bytes % kSlab == 0 && a.k_bytes >= 2 * kSlab &&
                                ptq4vm::ceil_div(a.M, 256) * ptq4vm::ceil_div(a.N, 256) >= 256;
-    if (persistent_ok) return launch_persistent<Path, PTQ4VM_PERSISTENT_BO, PTQ4VM_PERSISTENT_PHYS_SLAB, PTQ4VM_PERSISTENT_STAGES>(a, stream);
+    if (persistent_ok) return launch_persistent<Path>(a, stream);
     return launch_tiles<Path>(a, stream);
 }
 

@@ -23,9 +23,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int kSlabBytes = 64;  // K bytes per LDS stage per row: two MFMA k-steps of 32 bytes
 constexpr int kXcds = 8;
-#ifndef PTQ4VM_PERSISTENT_SLAB
-#define PTQ4VM_PERSISTENT_SLAB 128   // K bytes per LDS row that the 256 x 256 persistent kernel needs K to divide by
-#endif
 
 struct Int8Path {
     static constexpr int kElemBytes = 1;
