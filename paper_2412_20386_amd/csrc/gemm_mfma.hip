@@ -284,6 +284,7 @@ __device__ __forceinline__ void persistent_tiles(const LinearArgs &p, const int 
             cb[g] = HAS_BIAS ? *reinterpret_cast<const v4f *>(cb_lds + col / 2) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
         const uint32_t ldy_bytes = (uint32_t)p.ldy * 2;
+        const bool whole_lines = p.ldy % 64 == 0;
         const int srow = le >> 3, scol = wave_o + (le & 7) * 8;
         const uint32_t beyond = 0x80000000u;  // past every tile's span
         const uint32_t y_off = scol < cols_valid ? (uint32_t)(wave_r + srow) * ldy_bytes + (uint32_t)scol * 2 : beyond;
@@ -293,8 +294,13 @@ __device__ __forceinline__ void persistent_tiles(const LinearArgs &p, const int 
         auto store_block = [&](int j) {
             typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int h = 0; h < 2; h++)  // non-temporal: measured 4-8 % faster than write-back stores here
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, (int)(y_off + (uint32_t)(j * 16 + h * 8) * ldy_bytes), 0, 2);
+            for (int h = 0; h < 2; h++) {
+                const int off = (int)(y_off + (uint32_t)(j * 16 + h * 8) * ldy_bytes);
+                if (whole_lines)  // non-temporal: measured 4-8 % faster than ordinary stores here
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, off, 0, 2);
+                else  // lines shared between tiles meet in the L2
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, off, 0, 0);
+            }
         };
 #pragma unroll
         for (int j = 0; j < FR; j++) {

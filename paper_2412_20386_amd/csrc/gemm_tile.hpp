@@ -87,26 +87,35 @@ __device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid) {
             reinterpret_cast<uint16_t *>(dst)[e] = (uint16_t)(__builtin_bit_cast(uint32_t, w[e >> 1]) >> (16 * (e & 1)));
 }
 
-// 16 bytes of a row at byte kb, bytes at or beyond k_bytes read as 0; `end` is the end of the matrix.
-__device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_bytes, const char *end) {
+// 16 bytes of a row at byte kb, bytes at or beyond k_bytes read as 0; `base` and `end` bound the matrix.  Where the 16 bytes would pass the
+// end, the last 16 of the matrix are loaded and moved down.  Short code on purpose: a workgroup runs through it once, and loads byte by
+// byte for that case, 64 of them per call skipped by branches, cost the instructions' way through the cache.
+__device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_bytes, const char *base, const char *end) {
     v4i out = {0, 0, 0, 0};
-    const int64_t valid = k_bytes - kb;
+    const int valid = (int)min((int64_t)16, k_bytes - kb);
     if (valid <= 0) return out;
-    if (row + kb + 16 <= end) {
-        out = *reinterpret_cast<const v4i_unaligned *>(row + kb);
-        if (valid < 16) {
-#pragma unroll
-            for (int j = 0; j < 4; j++) out[j] = (int)keep_low_bytes((uint32_t)out[j], (int)valid - 4 * j);
+    const char *at = row + kb;
+    const int over = (int)max((int64_t)0, (int64_t)(at + 16 - end));
+    if (at - over >= base) {
+        out = *reinterpret_cast<const v4i_unaligned *>(at - over);
+        if (over > 0) {  // move down by `over` bytes; what enters from above lies beyond K
+            if (over & 8) out = v4i{out[2], out[3], 0, 0};
+            if (over & 4) out = v4i{out[1], out[2], out[3], 0};
+            const int b = over & 3;
+            out = v4i{(int)__builtin_amdgcn_alignbyte(out[1], out[0], b), (int)__builtin_amdgcn_alignbyte(out[2], out[1], b),
+                      (int)__builtin_amdgcn_alignbyte(out[3], out[2], b), (int)__builtin_amdgcn_alignbyte(0, out[3], b)};
         }
-        return out;
+    } else {  // a matrix of fewer than 16 bytes
+#pragma unroll 1
+        for (int i = 0; i < valid; i++) {
+            const int byte = (int)*reinterpret_cast<const uint8_t *>(at + i) << (8 * (i & 3));
+#pragma unroll
+            for (int j = 0; j < 4; j++) out[j] |= (i >> 2) == j ? byte : 0;
+        }
     }
+    if (valid < 16) {
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-        uint32_t v = 0;
-#pragma unroll
-        for (int b = 0; b < 4; b++)
-            if (4 * j + b < valid) v |= (uint32_t) * reinterpret_cast<const uint8_t *>(row + kb + 4 * j + b) << (8 * b);
-        out[j] = (int)v;
+        for (int j = 0; j < 4; j++) out[j] = (int)keep_low_bytes((uint32_t)out[j], valid - 4 * j);
     }
     return out;
 }
@@ -141,12 +150,14 @@ struct TileArgs {
     int32_t *acc_out;
 };
 // How results leave: kAny any address and channel count; the others whole 16-byte pieces at 16-byte aligned addresses (y, its
-// pitch and N multiples of 8 elements), kThrough at device scope, kPast non-temporal.
-enum Stores : uint32_t { kAny = 0, kThrough = 1, kPast = 2 };
+// pitch and N multiples of 8 elements): kThrough at device scope, kPast non-temporal, kCached ordinary ones.
+enum Stores : uint32_t { kAny = 0, kThrough = 1, kPast = 2, kCached = 3 };
 // Device-scope stores leave no dirty lines in the L2 for the end of the launch to write back, but push the operands of this and the
 // next launches out of the memory-side cache (us, kThrough / kPast / ordinary stores: 12608 x 384 -> 384 6.1 / 6.8 / 7.8, 6304 x 384 -> 1536
 // 9.4 / 10.1 / 11.0, 25216 x 768 -> 384 13.4 / 13.7 / 14.5, 50240 x 768 -> 384 30.0 / 24.7 / 32.4; whole Vim-S blocks over 128 x 197 rows, results of
-// 9.7 M elements, 88.2 / 86.9, and over 64 x 785 rows 155.5 / 152.3).
+// 9.7 M elements, 88.2 / 86.9, and over 64 x 785 rows 155.5 / 152.3).  Rows that are no whole 128-byte lines share lines between tiles; in large
+// results these have to meet in the L2 (12608 x 384 -> 1000 16.7 / 18.5 / 14.2, 24104 x 830 -> 760 43 kPast, 38 ordinary; small ones gain all
+// the same: 12608 x 384 -> 328 6.5 / 7.0 / 7.2).
 constexpr int64_t kThroughElements = 6LL << 20;  // results up to this many are stored kThrough
 
 // Tiles of BR x BO for `a`; false if there are too many.  Neighbouring workgroups of an XCD walk the dimension with the
@@ -164,7 +175,8 @@ inline bool tile_args(const LinearArgs &a, TileArgs &t, dim3 &grid) {
     t.inner = fast_div((uint32_t)(t.rows_first ? tiles_r : tiles_o));
     t.tok = fast_div((uint32_t)a.L);
     const bool wide = a.N % 8 == 0 && a.ldy % 8 == 0 && ptq4vm::aligned_to(a.y, 16) && a.ldy * 2 * BR < (1LL << 31);
-    t.stores = !wide ? kAny : (a.M * a.N > kThroughElements ? kPast : kThrough);
+    const bool whole_lines = a.ldy % 64 == 0 && ptq4vm::aligned_to(a.y, 128);
+    t.stores = !wide ? kAny : a.M * a.N <= kThroughElements ? kThrough : whole_lines ? kPast : kCached;
     grid = grid_of_tiles(tiles_r * tiles_o);
     return true;
 }
@@ -321,22 +333,25 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
             }
         } else if (col < cols_valid) {
             typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+            auto store = [&](auto policy) {
+#pragma unroll
+                for (int s = 0; s < S; s++)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[s]), y_rows, (int)(y_off + (uint32_t)(jb * 16 + s * RPS) * ldy_bytes), 0,
+                                                           decltype(policy)::value);
+            };
             // cache policy of the store: 16 is sc1 (device scope), 2 is nt
-            if (p.stores == kThrough) {
-#pragma unroll
-                for (int s = 0; s < S; s++)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[s]), y_rows, (int)(y_off + (uint32_t)(jb * 16 + s * RPS) * ldy_bytes), 0, 16);
-            } else {
-#pragma unroll
-                for (int s = 0; s < S; s++)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[s]), y_rows, (int)(y_off + (uint32_t)(jb * 16 + s * RPS) * ldy_bytes), 0, 2);
-            }
+            if (p.stores == kThrough)
+                store(std::integral_constant<int, 16>{});
+            else if (p.stores == kPast)
+                store(std::integral_constant<int, 2>{});
+            else
+                store(std::integral_constant<int, 0>{});
         }
         asm volatile("" ::: "memory");
     }
 }
 
-// How linear_mfma_tile brings its slabs to LDS: copied directly, through registers, through registers with a reduction of one slab.
+// How linear_mfma_tile gets its operands: copied to LDS directly, to LDS through registers, as fragments (reductions of one slab).
 enum class Copy { kDirect, kRegisters, kOneSlab };
 
 template <int BR, int BO, int SLAB, int STAGES>
@@ -538,12 +553,13 @@ __device__ __forceinline__ void direct_tile(const TileArgs &p) {
     store_tile<Path, BR, BO, WR, WO, STAGES * STAGE_BYTES, DUMP>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
 }
 
-// The same tile for any pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).
+// The same tile for any pitch, alignment and K: slabs pass through registers, bytes beyond K zeroed (two stages).  Small tiles, of which a
+// CU has few, keep two slabs in flight (3184 x 1000 -> 500 10.1 / 9.5 us); the larger ones one, which leaves room for more workgroups
+// (24104 x 830 -> 760 43 / 49).
 // Only the last slab reaches beyond K; the loads of the others carry no tests (16236 x 1584 -> 760 fp16 106.7 -> 62.8 us, 24104 x 830 -> 760
-// 45.7 -> 36.1, 3184 x 1000 -> 500 12.3 -> 10.3, each with the larger tiles that this pays for; 69.1, 43.4 and 12.3 with the
-// tiles alone).  A reduction of one slab keeps the tested loads alone (ONE): the second form costs it 2 %.
+// 45.7 -> 36.1).
 // Requirements (host-checked): L < 2^31, BR * ldx_bytes and BO * ldw_bytes below 2^31.
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, bool DUMP, bool ONE>
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, bool DUMP>
 __device__ __forceinline__ void staged_tile(const TileArgs &p) {
     constexpr int NW = WR * WO, THREADS = 64 * NW;
     constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
@@ -574,25 +590,28 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
     }
     const char *gx = p.x + r0 * p.ldx_bytes, *gw = p.w + o0 * p.ldw_bytes;
     const int64_t k_bytes = p.k_bytes;
-    v4i staged[COPIES];
-    auto fetch = [&](int slab) {
+    constexpr int DEPTH = BR * BO <= 64 * 64 ? 2 : 1;
+    v4i staged[DEPTH][COPIES];
+    auto fetch = [&](int buf, int slab) {
+        const bool inside = (int64_t)(slab + 1) * SLAB <= k_bytes;  // uniform
 #pragma unroll
         for (int i = 0; i < COPIES; i++) {
             const int c = wave + NW * i;  // scalar
-            const char *src = c * ROWS_PER_COPY < BR ? gx : gw;
+            const bool is_x = c * ROWS_PER_COPY < BR;
+            const char *src = is_x ? gx : gw;
             const int chunk = chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS);  // (BR is a multiple of 16: a weight row swizzles like row - BR)
-            if (!ONE && (int64_t)(slab + 1) * SLAB <= k_bytes) {  // a slab inside the rows
-                staged[i] = *reinterpret_cast<const v4i_unaligned *>(src + off[i] + (int64_t)slab * SLAB + chunk * 16);
-                continue;
+            if (inside) {
+                staged[buf % DEPTH][i] = *reinterpret_cast<const v4i_unaligned *>(src + (int64_t)slab * SLAB + (off[i] + chunk * 16));
+            } else {
+                const char *end = is_x ? p.x + ((p.M - 1) * p.ldx_bytes + k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
+                staged[buf % DEPTH][i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, k_bytes, is_x ? p.x : p.w, end);
             }
-            const char *end = c * ROWS_PER_COPY < BR ? p.x + ((p.M - 1) * p.ldx_bytes + k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
-            staged[i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, k_bytes, end);
         }
     };
-    auto commit = [&](int stage) {
+    auto commit = [&](int buf, int stage) {
 #pragma unroll
         for (int i = 0; i < COPIES; i++)
-            *reinterpret_cast<v4i *>(ring + stage * STAGE_BYTES + (wave + NW * i) * 1024 + lane * 16) = staged[i];
+            *reinterpret_cast<v4i *>(ring + stage * STAGE_BYTES + (wave + NW * i) * 1024 + lane * 16) = staged[buf % DEPTH][i];
     };
 
     Acc acc[FO][FR];
@@ -604,14 +623,15 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
 
     const int n_slabs = (int)((k_bytes + SLAB - 1) / SLAB);
-    fetch(0);
+    fetch(0, 0);
     TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * STAGE_BYTES);
     vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
-    commit(0);
-    for (int it = 0; it < n_slabs; it++) {
+    if (DEPTH == 2 && n_slabs > 1) fetch(1, 1);
+    commit(0, 0);
+    auto slab = [&](int it, int buf) {  // the slab lies in stage buf; the next one is on its way or (DEPTH 1) requested now
         __syncthreads();
-        if (it + 1 < n_slabs) fetch(it + 1);
-        const char *sx = ring + (it & 1) * STAGE_BYTES + wave_r * SLAB, *sw = ring + (it & 1) * STAGE_BYTES + (BR + wave_o) * SLAB;
+        if (it + DEPTH < n_slabs) fetch(DEPTH == 2 ? buf : 0, it + DEPTH);
+        const char *sx = ring + buf * STAGE_BYTES + wave_r * SLAB, *sw = ring + buf * STAGE_BYTES + (BR + wave_o) * SLAB;
 #pragma unroll
         for (int ks = 0; ks < SLAB / 64; ks++) {
             if (ks > 0 && (int64_t)it * SLAB + ks * 64 >= k_bytes) break;
@@ -628,11 +648,71 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             }
             mfma_step<Path, FO, FR>(acc, fw, fx);
         }
-        if (it + 1 < n_slabs) commit((it + 1) & 1);
+        if (it + 1 < n_slabs) commit(buf ^ 1, buf ^ 1);
+    };
+    if constexpr (DEPTH == 2) {
+#pragma unroll 1
+        for (int it = 0; it < n_slabs; it += 2) {
+            slab(it, 0);
+            if (it + 1 < n_slabs) slab(it + 1, 1);
+        }
+    } else {
+#pragma unroll 1
+        for (int it = 0; it < n_slabs; it++) slab(it, it & 1);
     }
     vec.park(p, tid);
     __syncthreads();  // the vectors are visible, the ring becomes the wavefronts' transposition patches
     store_tile<Path, BR, BO, WR, WO, 2 * STAGE_BYTES, DUMP>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
+}
+
+// The same tile for a reduction of one slab at any pitch and alignment: every wavefront loads its operands as MFMA fragments, 16 rows x 64
+// bytes at a time; nothing is shared but through the caches, and nothing waits for anybody before the epilogue.  What bounds it is
+// that chain of latencies and the output stream (12608 x 12 -> 384 7.1 us through LDS, 5.6 now; 6304 x 24 -> 768 6.7 / 5.7).
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, bool DUMP>
+__device__ __forceinline__ void one_slab_tile(const TileArgs &p) {
+    constexpr int NW = WR * WO, THREADS = 64 * NW;
+    constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16, KS = SLAB / 64;
+    using Acc = typename Path::Acc16;
+
+    uint32_t tile_r, tile_o;
+    if (!locate_tile(p, tile_r, tile_o)) return;
+    const int64_t r0 = (int64_t)tile_r * BR, o0 = (int64_t)tile_o * BO;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_r = (wave / WO) * WAVE_R, wave_o = (wave % WO) * WAVE_O;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int rows_valid = (int)min((int64_t)BR, p.M - r0), cols_valid = (int)min((int64_t)BO, p.N - o0);
+    const char *const gx = p.x + r0 * p.ldx_bytes, *const gw = p.w + o0 * p.ldw_bytes;
+    const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + p.k_bytes), *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + p.k_bytes);
+    v4i fw[KS][FO], fx[KS][FR];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+        if (ks > 0 && ks * 64 >= p.k_bytes) break;  // (uniform)
+#pragma unroll
+        for (int i = 0; i < FO; i++) {
+            const int row = min(wave_o + channel_of_row(i * 16 + l16), cols_valid - 1);
+            fw[ks][i] = load_any(gw + (uint32_t)row * (uint32_t)p.ldw_bytes, ks * 64 + lq * 16, p.k_bytes, p.w, w_end);
+        }
+#pragma unroll
+        for (int j = 0; j < FR; j++) {
+            const int row = min(wave_r + j * 16 + l16, rows_valid - 1);
+            fx[ks][j] = load_any(gx + (uint32_t)row * (uint32_t)p.ldx_bytes, ks * 64 + lq * 16, p.k_bytes, p.x, x_end);
+        }
+    }
+    TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * (BR + BO) * SLAB);
+    vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
+    Acc acc[FO][FR];
+#pragma unroll
+    for (int i = 0; i < FO; i++)
+#pragma unroll
+        for (int j = 0; j < FR; j++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++)
+        if (ks == 0 || ks * 64 < p.k_bytes) mfma_step<Path, FO, FR>(acc, fw[ks], fx[ks]);
+    vec.park(p, tid);
+    __syncthreads();
+    store_tile<Path, BR, BO, WR, WO, 2 * (BR + BO) * SLAB, DUMP>(acc, p, lds_dyn, vec, r0, o0, rows_valid, cols_valid);
 }
 
 // Registers of a direct tile: results, the fragments of two steps (TIGHT: those of the activations once), some for everything else.
@@ -656,12 +736,14 @@ constexpr bool tile_is_tight() {
 }
 
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, Copy COPY>
-__global__ __launch_bounds__(64 * WR * WO, (COPY == Copy::kDirect ? tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() : 4)) void linear_mfma_tile(const TileArgs p) {
+__global__ __launch_bounds__(64 * WR * WO, (COPY == Copy::kDirect ? tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() : WR * WO == 8 && SLAB == 64 && !Path::kPacked4 ? 6 : 4)) void linear_mfma_tile(const TileArgs p) {
     static_assert(COPY == Copy::kDirect || STAGES == 2, "the register-staged form is double buffered");
     if constexpr (COPY == Copy::kDirect)
         direct_tile<Path, BR, BO, WR, WO, SLAB, STAGES, DUMP, tile_is_tight<Path, BR, BO, WR, WO, SLAB, STAGES>()>(p);
+    else if constexpr (COPY == Copy::kRegisters)
+        staged_tile<Path, BR, BO, WR, WO, SLAB, DUMP>(p);
     else
-        staged_tile<Path, BR, BO, WR, WO, SLAB, DUMP, COPY == Copy::kOneSlab>(p);
+        one_slab_tile<Path, BR, BO, WR, WO, SLAB, DUMP>(p);
 }
 
 // The partial sums of a workgroup's SK wavefronts meet in LDS (SK FR FO KiB) and wavefront b finishes block b.
@@ -768,11 +850,11 @@ __global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p
 #pragma unroll
                 for (int i = 0; i < FO; i++)
                     fw[u][i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + (int64_t)s * 64)
-                                       : load_any(wrow[i] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, w_end);
+                                       : load_any(wrow[i] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, p.w, w_end);
 #pragma unroll
                 for (int j = 0; j < FR; j++)
                     fx[u][j] = ALIGNED ? *reinterpret_cast<const v4i *>(xrow[j] + (int64_t)s * 64)
-                                       : load_any(xrow[j] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, x_end);
+                                       : load_any(xrow[j] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, p.x, x_end);
             }
         }
 #pragma unroll

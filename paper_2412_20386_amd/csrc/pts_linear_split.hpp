@@ -152,7 +152,7 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
 #pragma unroll
         for (int i = 0; i < NL; i++)
             f.x[i] = ALIGNED ? __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + k0 * 2 + pc * 16))
-                             : load_any(xrow[i], k0 * 2 + pc * 16, K * 2, x_end);
+                             : load_any(xrow[i], k0 * 2 + pc * 16, K * 2, p.x, x_end);
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             f.im[h] = v4f{1.0f, 1.0f, 1.0f, 1.0f};
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
                 f.w4[i] = *reinterpret_cast<const u32x2 *>(wrow[i] + k0 / 2 + lq * 8);
             } else {
                 f.w[i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + k0 + lq * 16)
-                                 : load_any(wrow[i], k0 + lq * 16, K, w_end);
+                                 : load_any(wrow[i], k0 + lq * 16, K, p.w, w_end);
             }
         }
     };
