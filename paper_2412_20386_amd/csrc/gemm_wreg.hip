@@ -261,9 +261,8 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
         if (pf_in_unit == 0 && gw < 2) {  // the unit's per-row steps s_tok[r mod L], 64 rows per wavefront
             const int r = min((int)(gw * 64 + ln), pf_rows_valid - 1);
             const uint32_t t = ((uint32_t)(pf_r0 % p.L) + (uint32_t)r) % (uint32_t)p.L;
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(p.s_tok + t),
-                (__attribute__((address_space(3))) void *)(rs_lds + (pf_unit & (kRowScaleBufs - 1)) * kUnitRows + gw * 64), 4, 0, 0);
+            // (t * 4 fits: 2^30 rows of 384 codes would be more than the card holds)
+            copy_to_lds<4>(p.s_tok, t * 4, rs_lds + (pf_unit & (kRowScaleBufs - 1)) * kUnitRows + gw * 64);
         }
         const char *gx = pf_x + (int64_t)pf_in_unit * SLAB;
         char *dst = ring + pf_slot * SLOT_BYTES;
@@ -273,8 +272,7 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
             const int chunk = (int)(ln % CHUNKS) ^ (SLAB == 64 ? swizzle(row) : (row & 7));
             // rows beyond M are clamped to row M - 1: their results are copies of that row's (see `drain`)
             const uint32_t off = (uint32_t)min(row, pf_rows_valid - 1) * (uint32_t)p.ldx_bytes + chunk * 16;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gx + off),
-                                             (__attribute__((address_space(3))) void *)(dst + (gw + 4 * c) * 1024), 16, 0, 0);
+            copy_to_lds<16>(gx, off, dst + (gw + 4 * c) * 1024);
         }
         pf_step++;
         if (++pf_slot == kSlots) pf_slot = 0;
@@ -292,19 +290,25 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
     // of its channels.  Rows beyond M hold copies of row M - 1's results (their codes and steps were
     // clamped to that row when they were copied), so they are written onto row M - 1 again: same bytes,
     // same address.
-    auto drain = [&](int part, int64_t r0, int64_t o0) {
+    //
+    // The reads go out behind a step's barrier and the stores behind its MFMAs: read and stored one by one after
+    // them, each store waited a whole LDS latency while the other wavefronts stood at the next barrier.
+    auto drain_read = [&](int part, v4f (&data)[4]) {
+        const uint32_t ln = (threadIdx.x + opaque_zero()) & 63;
+        const char *src = stage + (gw * 32 + part * 8 + (ln >> 5)) * kStagePitch + (ln & 31) * 16;
+#pragma unroll
+        for (int q = 0; q < 4; q++) data[q] = *reinterpret_cast<const v4f *>(src + q * 2 * kStagePitch);
+    };
+    auto drain_store = [&](int part, const v4f (&data)[4], int64_t r0, int64_t o0) {
         const uint32_t ln = (threadIdx.x + opaque_zero()) & 63;
         const int row0 = gw * 32 + part * 8 + (int)(ln >> 5), chunk = (int)(ln & 31);
         const int rows_valid = (int)min((int64_t)kUnitRows, p.M - r0);
         char *dst = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0) + chunk * 16;
-        const uint32_t src = lds_addr(stage) + row0 * kStagePitch + chunk * 16;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            v4f data;
-            lds_read_1x_b128(src + q * 2 * kStagePitch, data);
             const int row = min(row0 + q * 2, rows_valid - 1);
             if (!(PTQ4VM_WREG_SKIP & 1))
-                __builtin_nontemporal_store(data, reinterpret_cast<v4f *>(dst + (uint32_t)row * ldy_bytes));
+                __builtin_nontemporal_store(data[q], reinterpret_cast<v4f *>(dst + (uint32_t)row * ldy_bytes));
         }
     };
 
@@ -326,8 +330,7 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
             const int idx = min(gw * PER_WAVE + c2 * 64 + (int)ln, LINES - 1);
             const int row = idx / LINES_PER_ROW, line = idx - row * LINES_PER_ROW;
             const uint32_t off = (uint32_t)min(row, rows_valid - 1) * (uint32_t)p.ldx_bytes + line * 128;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + off),
-                                             (__attribute__((address_space(3))) void *)(pf_sink + gw * 256), 4, 0, 0);
+            copy_to_lds<4>(base, off, pf_sink + gw * 256);
         }
     };
 
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
                     LastStep ls;
                     if (s < kSteps - 1) {
                         if constexpr (KPS == 2) k_step(fw[0][2 * s], fw[1][2 * s], s == 0, true, slot, 1);
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this slot's operands are all in registers
+                        wait_lgkmcnt_0();  // this slot's operands are all in registers (known to the compiler: no MFMA waits for a refetch)
                     } else {
                         last_step_prefetch(ls, slot, u & (kRowScaleBufs - 1));
                         lds_wait_all(ls.rs, ls.csb);
@@ -392,16 +395,21 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
                         }
                     }
                     if constexpr (!(PTQ4VM_WREG_SKIP & 16)) __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");  // nothing below is read ahead of the barrier
                     WREG_TRACE();
                     if constexpr (COPIER) {
                         if (pf_step < total_steps) issue();  // slot g + 4 into the ring place of slot g - 1
+                    }
+                    v4f drained[4];  // the previous unit's staged tile, a quarter per step
+                    if constexpr (!COPIER) {
+                        if (s < 4) drain_read(s, drained);
                     }
                     if (s < kSteps - 1)
                         k_step(fw[0][KPS * s + KPS - 1], fw[1][KPS * s + KPS - 1], KPS == 1 && s == 0, s + 2 < kSteps, next_slot, 0);
                     else
                         last_step_run(ls, slot, r0, o0);
-                    if constexpr (!COPIER) {  // the previous unit's staged tile, a quarter per step
-                        if (s < 4 && u > 0) drain(s, prev_r0, prev_o0);
+                    if constexpr (!COPIER) {
+                        if (s < 4 && u > 0) drain_store(s, drained, prev_r0, prev_o0);
                     }
                     slot = next_slot;
                 }
@@ -411,11 +419,15 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
                 u++;
             } while (u < wr.count && cc.strip == strip);
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the last unit's staged results are in LDS before the barrier
+        wait_lgkmcnt_0();  // the last unit's staged results are in LDS before the barrier
         __builtin_amdgcn_s_barrier();
         if constexpr (!COPIER) {
 #pragma unroll 1
-            for (int part = 0; part < 4; part++) drain(part, prev_r0, prev_o0);
+            for (int part = 0; part < 4; part++) {
+                v4f drained[4];
+                drain_read(part, drained);
+                drain_store(part, drained, prev_r0, prev_o0);
+            }
         }
     };
     if (wave < 4)

@@ -371,6 +371,17 @@ __device__ __forceinline__ void wait_vmcnt_at_most() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (KEEP & 15) | ((KEEP >> 4) << 14));
 }
 
+// Copies BYTES of every lane from base + off (off below 2^32 - 16; the base in scalar registers) to dst + lane * BYTES of
+// LDS (dst scalar).  As a buffer load: after a `global_load_lds`, a flat instruction to the compiler, it makes every wait
+// for an LDS read a wait for all of them, up to the next full wait.
+template <int BYTES>
+__device__ __forceinline__ void copy_to_lds(const void *base, uint32_t off, void *dst) {
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
+    static_assert(BYTES == 4 || BYTES == 16);
+    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)dst, 16, off, 0, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)dst, 4, off, 0, 0, 0);
+}
+
 // Every LDS read and scalar load has returned (a wait that the compiler takes into account, unlike one inside inline asm).
 __device__ __forceinline__ void wait_lgkmcnt_0() {
     __builtin_amdgcn_s_waitcnt(0xC07F);
