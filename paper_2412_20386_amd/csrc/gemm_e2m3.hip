@@ -17,12 +17,6 @@
 //   linear_e2m3_splitk      a few hundred blocks of 16 x 16 or fewer: the wavefronts of a workgroup split the reduction
 #include "gemm_tile.hpp"
 
-// Timing experiments only (results are wrong when any bit is set): 1 no output stores, 2 no epilogue at all,
-// 4 no global -> LDS copies of the operands, 8 no MFMAs.
-#ifndef PTQ4VM_E2M3_SKIP
-#define PTQ4VM_E2M3_SKIP 0
-#endif
-
 namespace ptq4vm {
 namespace mfma {
 namespace {
@@ -112,36 +106,35 @@ __global__ __launch_bounds__(64 * SK) void linear_e2m3_splitk(const LinearArgs p
 
 // ------------------------------------------------------------------------------------------
 // Persistent kernel.  LDS: ring of kStages stages, each (256 token rows + 256 channels) x 96 bytes, then two
-// buffers of per-tile scale vectors.  The containers are block-major, so what a stage receives is two contiguous
+// buffers of per-tile scale vectors and the wavefronts' patches.  The containers are block-major, so what a stage receives is two contiguous
 // 24 KiB spans of memory.  A stage row is the 96-byte block as in memory, except that rows with bit 3 set keep
 // their last two 16-byte chunks (the groups' 8-byte high parts) swapped.  Measured with a stand-alone read loop
 // (bytes per clock and CU, 16-byte low-part reads / 8-byte high-part reads / both): rows as in memory 228 / 118 /
 // 168, high chunks swapped by row bit 3: 245 / 174 / 203, all chunk pairs swapped by row bit 3: 127 / 170 / 141.
+// Weight rows sit in the order of channel_of_row, so that a lane's results are 16-byte pieces of its row.
 // Ring discipline: barrier B(g) sits before the MFMAs of block g - 1, after its fragments have arrived in
 // registers.  Passing it means every wavefront's copies of block g have landed and nobody reads block g - 1's
-// stage again, so that stage is refilled at once with block g + 2 (after a tile's last block the refill waits
-// until the epilogue, which borrows the stage, has finished).
+// stage again, so that stage is refilled at once with block g + 2, after a tile's last block too: the results cross
+// patches of their own, and the stores queue behind the copies of the next tile's first two blocks, so that only
+// the third of them waits for the stores.  With the results crossing the ring, that refill came behind the stores and
+// the next tile's first block waited for them all (us, before -> now: 50432 x 768 -> 3072 116.8 -> 108.4,
+// 50432 x 1536 -> 768 54.0 -> 51.6, 25216 x 384 -> 1536 28.1 -> 26.0; rows that are not whole lines, stored past the L2
+// before, 50240 x 384 -> 1000 44.9 -> 34.8).
 // Requirements (host-checked): K a multiple of 128 and at least 256 codes, 16-byte aligned operand rows,
 // N a multiple of 8, y rows 16-byte aligned, 4-byte aligned bias, 256 row pitches below 2^31, L < 2^31.
 // ------------------------------------------------------------------------------------------
-// Tile geometry: BR token rows x 256 channels; 4 wavefronts side by side along the channels per 128 rows.
-#ifndef PTQ4VM_E2M3_BR
-#define PTQ4VM_E2M3_BR 256
-#endif
-#ifndef PTQ4VM_E2M3_STAGES
-#define PTQ4VM_E2M3_STAGES 3
-#endif
+// Tile geometry: 256 token rows x 256 channels; 4 wavefronts side by side along the channels per 128 rows.
 // Which 16-byte chunk of a row's block goes to chunk position c of its stage row.
 __device__ __forceinline__ int stage_chunk_source(int row, int c) { return c < 4 ? c : 4 + ((c - 4) ^ ((row >> 3) & 1)); }
 
 constexpr int kTile = 256;                 // channels per tile
-constexpr int kTileRows = PTQ4VM_E2M3_BR;  // token rows per tile: 256 (one workgroup of 8 wavefronts per CU) or 128 (two of 4)
-constexpr int kStages = PTQ4VM_E2M3_STAGES;
+constexpr int kTileRows = 256;             // token rows per tile: one workgroup of 8 wavefronts per CU
+constexpr int kStages = 3;
 constexpr int kWavesPerWg = 4 * kTileRows / 128;
 constexpr int kStageBytes = (kTileRows + kTile) * kBlockBytes;
 constexpr int kScaleBytes = kTile * 4 + kTileRows * 4 + kTile * 2;
-constexpr int kPersistentLds = kStages * kStageBytes + 2 * kScaleBytes;
-static_assert(kTileRows == 256 || kTileRows == 128, "tile height");
+constexpr int kPatchPitch = 160, kPatchBytes = 8 * kPatchPitch;  // a wavefront's patch: 8 rows of 64 fp16 (2 mod 4 pieces of 16 bytes: no bank conflicts)
+constexpr int kPersistentLds = kStages * kStageBytes + 2 * kScaleBytes + kWavesPerWg * kPatchBytes;
 
 template <bool HAS_BIAS, bool DUMP_ACC>
 __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(const LinearArgs p) {
@@ -150,9 +143,11 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
     constexpr int W_COPIES = kTile * 6 / 64 / NW;      // 3 or 6 of weight rows
     constexpr int LOADS_PER_BLOCK = X_COPIES + W_COPIES;
     constexpr int KEEP = (kStages - 2) * LOADS_PER_BLOCK;  // copies allowed in flight when a block is needed
+    constexpr int TILE_STORES = 2 * FR;                    // a wavefront's store instructions per tile
 
     char *const ring = lds_dyn;
     char *const scales = lds_dyn + kStages * kStageBytes;
+    char *const patch = scales + 2 * kScaleBytes + (threadIdx.x >> 6) * kPatchBytes;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wave_r = (wave >> 2) * WAVE_R, wave_o = (wave & 3) * WAVE_O;
@@ -197,7 +192,7 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
         for (int i = 0; i < W_COPIES; i++) {
             const int q = (wave + NW * i) * 64 + lane;
             const int row = q / 6, c = q - row * 6;
-            w_off[i] = (uint32_t)min(row, rows_w - 1) * kBlockBytes + stage_chunk_source(row, c) * 16;
+            w_off[i] = (uint32_t)min(channel_of_row(row), rows_w - 1) * kBlockBytes + stage_chunk_source(row, c) * 16;
         }
     };
     auto issue = [&]() {  // copy the producer's block into ring stage pf_stage, then advance
@@ -206,12 +201,12 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
         const char *gx = pf_x + (int64_t)pf_block * p.ldx_bytes;
         const char *gw = pf_w + (int64_t)pf_block * p.ldw_bytes;
 #pragma unroll
-        for (int i = 0; i < ((PTQ4VM_E2M3_SKIP & 4) ? 0 : X_COPIES); i++)
+        for (int i = 0; i < X_COPIES; i++)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gx + x_off[i]),
                                              (__attribute__((address_space(3))) void *)(sx + (wave + NW * i) * 1024),
                                              16, 0, 0);
 #pragma unroll
-        for (int i = 0; i < ((PTQ4VM_E2M3_SKIP & 4) ? 0 : W_COPIES); i++)
+        for (int i = 0; i < W_COPIES; i++)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gw + w_off[i]),
                                              (__attribute__((address_space(3))) void *)(sw + (wave + NW * i) * 1024),
                                              16, 0, 0);
@@ -223,16 +218,20 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
             if (pf_tile < last) pf_setup();
         }
     };
-    auto wait_block = [&](int g) {  // block g has landed for this wavefront
-        if (g + kStages - 2 < total_blocks)
-            wait_vmcnt_at_most<KEEP>();
-        else
+    // Block g has landed for this wavefront.  after_tile: one of the two blocks that were copied ahead of the last tile's
+    // stores, which may stay in flight (loads and stores retire in the order of their issue).
+    auto wait_block = [&](int g, bool after_tile) {
+        if (g + kStages - 2 >= total_blocks)
             wait_vmcnt_at_most<0>();
+        else if (after_tile)
+            wait_vmcnt_at_most<KEEP + TILE_STORES>();
+        else
+            wait_vmcnt_at_most<KEEP>();
     };
 
     pf_setup();
     while (issued < kStages - 1 && issued < total_blocks) issue();
-    wait_block(0);
+    wait_block(0, false);
     __builtin_amdgcn_s_barrier();  // B(0)
     if (issued < total_blocks) issue();
 
@@ -300,23 +299,20 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
             bool has_next = false;
             if (g + 1 < total_blocks) {
                 // B(g+1): this wavefront holds the fragments of block g in registers and its copies of block g+1 have landed
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                wait_block(g + 1);
+                wait_lgkmcnt_0();
+                wait_block(g + 1, s < kStages - 1 && tile != first);
                 __builtin_amdgcn_s_barrier();
-                if (s + 1 < n_blocks) {
-                    if (issued < total_blocks) {
-                        issue();  // refills the stage of block g
-                        loads_after_scales += LOADS_PER_BLOCK;
-                    }
-                    has_next = true;
-                }  // after the tile's last block that stage first serves the epilogue
+                if (issued < total_blocks) {
+                    issue();  // refills the stage of block g
+                    loads_after_scales += LOADS_PER_BLOCK;
+                }
+                has_next = s + 1 < n_blocks;
             }
 #pragma unroll
             for (int j = 0; j < FR; j++) {
 #pragma unroll
                 for (int i = 0; i < FO; i++) {
-                    if constexpr (!(PTQ4VM_E2M3_SKIP & 8)) acc[i][j] = mfma_e2m3(fw[i], fx[j], acc[i][j]);
-                    else acc[i][j][0] += __builtin_bit_cast(float, fw[i][0] ^ fx[j][5]);
+                    acc[i][j] = mfma_e2m3(fw[i], fx[j], acc[i][j]);
                     if (j == FR - 1 && has_next) load_fw(i, next_stage);
                 }
                 if (has_next) load_fx(j, next_stage);
@@ -324,89 +320,81 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(co
             stage = next_stage;
         }
 
-        // ---- epilogue of this tile.  The ring stage of the tile's last block is free: B(g) was passed with that
-        // block's fragments in registers and its refill has been held back; it holds the wavefronts' fp16
-        // patches until the barrier that ends the epilogue.
-        if (loads_after_scales >= KEEP && KEEP > 0)
-            wait_vmcnt_at_most<KEEP>();
+        // ---- epilogue, under the copies of the next tile's first two blocks.  The scale vectors were copied ahead of the
+        // blocks counted in loads_after_scales.
+        if (loads_after_scales >= 2 * KEEP)
+            wait_vmcnt_at_most<2 * KEEP>();
         else
             wait_vmcnt_at_most<0>();
         __builtin_amdgcn_s_barrier();  // scale vectors are visible to every wavefront
-        const int free_stage = stage == 0 ? kStages - 1 : stage - 1;  // stage of the tile's last block
-        char *patch = ring + free_stage * kStageBytes + wave * (32 * WAVE_O * 2);
-        char *y_tile = reinterpret_cast<char *>(p.y + r0 * p.ldy + o0);
+        asm volatile("" ::: "memory");
+
+        // Accumulator register v of block (i, j): token row 16 j + l16, channel 32 (i / 2) + 8 lq + 4 (i mod 2) + v: two pieces of 16
+        // bytes per lane and 16-row block.  The lanes of rows 0..7 hand their second piece to those of rows 8..15 for their
+        // first, so that each half of the block crosses the wavefront's patch by itself, into stores of eight whole 128-byte
+        // row segments; a block's stores are issued behind the conversion of the next one.
+        v4f cs[FO], cb[FO / 2];
+#pragma unroll
+        for (int h = 0; h < FO / 2; h++) {
+            const int col = wave_o + 32 * h + 8 * lq;
+            cs[2 * h] = *reinterpret_cast<const v4f *>(cs_lds + col), cs[2 * h + 1] = *reinterpret_cast<const v4f *>(cs_lds + col + 4);
+            cb[h] = HAS_BIAS ? *reinterpret_cast<const v4f *>(cb_lds + col / 2) : v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        }
         const uint32_t ldy_bytes = (uint32_t)p.ldy * 2;
-        auto patch_chunk = [&](int row, int chunk) { return row * (WAVE_O * 2) + ((chunk ^ (row & 7)) << 4); };
-        const bool full_tile = rows_valid == kTileRows && cols_valid == kTile;
-
-        // Accumulator register v of block (i, j): token row 16 j + (lane mod 16), channel 16 i + 4 (lane / 16) + v.
-        // cs_raw[i]: steps of this lane's four channels of block i; cb_raw[i]: the eight fp16 biases around them.
-        v4f cs_raw[4], cb_raw[4];
-        float rs_raw[8];
-        lds_read_4x_b128<64>(lds_addr(cs_lds + wave_o + lq * 4), cs_raw);
-        if constexpr (HAS_BIAS) lds_read_4x_b128<32>(lds_addr(cb_lds + (wave_o + (lq >> 1) * 8) / 2), cb_raw);
-        lds_read_8x_b32<64>(lds_addr(rs_lds + wave_r + l16), rs_raw);
-
-        if constexpr (PTQ4VM_E2M3_SKIP & 2) {
-            float sum = 0.0f;
+        const bool whole_lines = p.ldy % 64 == 0;
+        const int srow = lane >> 3, scol = wave_o + (lane & 7) * 8;
+        const uint32_t beyond = 0x80000000u;  // past every tile's span
+        const uint32_t y_off = scol < cols_valid ? (uint32_t)(wave_r + srow) * ldy_bytes + (uint32_t)scol * 2 : beyond;
+        const __amdgpu_buffer_rsrc_t y_rows =
+            __builtin_amdgcn_make_buffer_rsrc(p.y + r0 * p.ldy + o0, 0, (int)(((int64_t)(rows_valid - 1) * p.ldy + cols_valid) * 2), 0x00020000);
+        v4f data[2];
+        auto store_block = [&](int j) {
+            typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int i = 0; i < FO; i++)
-#pragma unroll
-                for (int j = 0; j < FR; j++) sum += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
-            if (sum == 1.2345e-30f) p.y[0] = __float2half(sum);
-        } else
-#pragma unroll
-        for (int jp = 0; jp < FR / 2; jp++) {  // 32 rows per round through the patch
-#pragma unroll
-            for (int jj = 0; jj < 2; jj++) {
-                const int j = 2 * jp + jj;
-#pragma unroll
-                for (int i = 0; i < FO; i++) {
-                    float b01 = 0.0f, b23 = 0.0f;  // two fp16 biases each, raw
-                    if constexpr (HAS_BIAS) {
-                        b01 = (lq & 1) ? cb_raw[i].z : cb_raw[i].x;
-                        b23 = (lq & 1) ? cb_raw[i].w : cb_raw[i].y;
-                    }
-                    if constexpr (DUMP_ACC) {
-                        const int64_t r = r0 + wave_r + j * 16 + l16;
-#pragma unroll
-                        for (int c = 0; c < 4; c++) {
-                            const int64_t o = o0 + wave_o + i * 16 + lq * 4 + c;
-                            if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = (int)acc[i][j][c];
-                        }
-                    }
-                    const float lo = dequantize_pair_f16(acc[i][j][0], rs_raw[j] * cs_raw[i][0], acc[i][j][1],
-                                                         rs_raw[j] * cs_raw[i][1], b01);
-                    const float hi = dequantize_pair_f16(acc[i][j][2], rs_raw[j] * cs_raw[i][2], acc[i][j][3],
-                                                         rs_raw[j] * cs_raw[i][3], b23);
-                    const u32x2 packed = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                    lds_write_b64(lds_addr(patch + patch_chunk(jj * 16 + l16, 2 * i + (lq >> 1)) + (lq & 1) * 8), packed);
-                }
+            for (int h = 0; h < 2; h++) {
+                const int off = (int)(y_off + (uint32_t)(j * 16 + h * 8) * ldy_bytes);
+                if (whole_lines)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, off, 0, 2);  // non-temporal
+                else  // lines shared between tiles meet in the L2
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, data[h]), y_rows, off, 0, 0);
             }
-            v4f data[4];
-            uint32_t src[4];
+        };
+        constexpr int kRowRotate8 = 0x128;  // DPP: every 16 lanes rotated by 8; bank masks 0xc, 0x3: lanes 8..15, 0..7 are written
 #pragma unroll
-            for (int q = 0; q < 4; q++)  // 8 rows x 128 bytes per store instruction
-                src[q] = lds_addr(patch + patch_chunk(q * 8 + (lane >> 3), lane & 7));
-            lds_read_4_b128(src, data);
-            const uint32_t base = (uint32_t)(wave_r + jp * 32 + (lane >> 3)) * ldy_bytes + (uint32_t)(wave_o + (lane & 7) * 8) * 2;
-            if constexpr (PTQ4VM_E2M3_SKIP & 1) {
-                if (data[0][0] == 1.2345e-30f) p.y[0] = __float2half(data[1][1]);
-            } else if (full_tile) {
+        for (int j = 0; j < FR; j++) {
+            const float rs = rs_lds[wave_r + j * 16 + l16];
+            v4f piece[2];
 #pragma unroll
-                for (int q = 0; q < 4; q++)
-                    __builtin_nontemporal_store(data[q], reinterpret_cast<v4f *>(y_tile + base + (uint32_t)(q * 8) * ldy_bytes));
-            } else {
+            for (int i = 0; i < FO; i++) {
+                if constexpr (DUMP_ACC) {
+                    const int64_t r = r0 + wave_r + j * 16 + l16;
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const int rr = wave_r + jp * 32 + q * 8 + (lane >> 3), cc = wave_o + (lane & 7) * 8;
-                    if (rr < rows_valid && cc < cols_valid)
-                        *reinterpret_cast<v4f *>(y_tile + base + (uint32_t)(q * 8) * ldy_bytes) = data[q];
+                    for (int c = 0; c < 4; c++) {
+                        const int64_t o = o0 + wave_o + 32 * (i >> 1) + 8 * lq + 4 * (i & 1) + c;
+                        if (r < p.M && o < p.N) p.acc_out[r * p.N + o] = (int)acc[i][j][c];
+                    }
                 }
+                const int e = 2 * (i & 1);  // two fp16 biases a word
+                piece[i >> 1][e] = dequantize_pair_f16(acc[i][j][0], rs * cs[i][0], acc[i][j][1], rs * cs[i][1], cb[i >> 1][e]);
+                piece[i >> 1][e + 1] = dequantize_pair_f16(acc[i][j][2], rs * cs[i][2], acc[i][j][3], rs * cs[i][3], cb[i >> 1][e + 1]);
+            }
+            const v4i near = __builtin_bit_cast(v4i, piece[0]), far = __builtin_bit_cast(v4i, piece[1]);
+            v4i half[2];
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                half[0][c] = __builtin_amdgcn_update_dpp(near[c], far[c], kRowRotate8, 0xf, 0xc, false);
+                half[1][c] = __builtin_amdgcn_update_dpp(far[c], near[c], kRowRotate8, 0xf, 0x3, false);
+            }
+            if (j > 0) store_block(j - 1);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                asm volatile("" ::: "memory");  // wavefront-private patch: LDS runs a wavefront's accesses in order
+                *reinterpret_cast<v4i *>(patch + (l16 & 7) * kPatchPitch + ((l16 >> 3) * 4 + lq) * 16) = half[h];
+                asm volatile("" ::: "memory");
+                data[h] = *reinterpret_cast<const v4f *>(patch + srow * kPatchPitch + (lane & 7) * 16);
             }
         }
-        __builtin_amdgcn_s_barrier();  // every wavefront has read its patch back: the stage can be refilled
-        if (issued < total_blocks) issue();
+        store_block(FR - 1);
     }
 }
 

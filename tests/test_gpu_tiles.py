@@ -119,6 +119,16 @@ def test_tiles_of_whole_rounds(M, K, N, pad):
     test_tile_kernels_all_operand_types(M, K, N, pad)
 
 
+@pytest.mark.parametrize("M,K,N,pad", [
+    (33013, 256, 1016, 0),   # two blocks a tile, rows that are not whole lines, the last tile partly empty both ways
+    (33013, 256, 1016, 8),   # the same with rows of whole lines
+    (43777, 384, 768, 0),    # three blocks, a last tile of one row
+])
+def test_persistent_tiles_with_stores_in_flight(M, K, N, pad):
+    """Few blocks a tile: the copies of the next tile's first blocks, its scale vectors and this tile's stores in one queue."""
+    test_tile_kernels_all_operand_types(M, K, N, pad)
+
+
 @pytest.mark.parametrize("K,N,B,L", [(384, 3072, 124, 199), (768, 3072, 128, 197), (768, 1536, 190, 260)])
 def test_weights_in_registers_against_smaller_launches(K, N, B, L):
     """Around nine 128 x 256 units a CU the weight-in-registers kernel takes over: the same bits as two launches of half the
