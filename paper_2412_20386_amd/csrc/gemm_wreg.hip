@@ -24,9 +24,9 @@
 // The staged 128 x 256 fp16 tile leaves for memory during the first four steps of the next unit, in
 // whole 512-byte row segments, so the store stream is spread over the unit instead of bursting.
 // Roles: wavefronts 0-3 issue every global -> LDS copy and never store; wavefronts 4-7 issue every
-// output store and never wait for a copy.  Loads and stores share one counter (vmcnt) and complete
-// out of order with each other, so a wavefront that did both could only wait for a copy by draining
-// its stores.
+// output store and never wait for a copy.  Loads and stores share one counter (vmcnt) and
+// retire in the order of their issue, so in a wavefront that did both, a wait for a copy would also wait for
+// every store issued before it.
 //
 // Output channel order inside a wavefront: MFMA block i (0, 1), A-operand row a (0..15) carries
 // strip channel 32 w + 8 (a / 4) + 4 i + (a mod 4).  A lane's eight results of a token row are then
@@ -38,33 +38,6 @@
 
 #include "mfma_linear.hpp"
 #include "unit_order.hpp"
-
-// Timing experiments only (results are wrong when any bit is set): 1 no output stores, 2 no conversion,
-// 4 no global -> LDS copies, 8 no operand refetch from LDS, 16 no step barriers, 32 no MFMAs.
-#ifndef PTQ4VM_WREG_SKIP
-#define PTQ4VM_WREG_SKIP 0
-#endif
-
-#ifndef PTQ4VM_WREG_TRACE
-#define PTQ4VM_WREG_TRACE 0
-#endif
-#if PTQ4VM_WREG_TRACE
-// Debug build only: wall-clock ticks (100 MHz) of workgroups 0 and 77, per wavefront.
-__device__ unsigned long long ptq4vm_wreg_trace[2][8][256];
-extern "C" int ptq4vm_debug_wreg_trace(void *host_dst) {
-    return (int)hipMemcpyFromSymbol(host_dst, HIP_SYMBOL(ptq4vm_wreg_trace), sizeof(ptq4vm_wreg_trace));
-}
-#define WREG_TRACE()                                                                                     \
-    do {                                                                                                 \
-        if (tr_wg >= 0 && tr_n < 256) {                                                                  \
-            const unsigned long long now = __builtin_amdgcn_s_memrealtime();                             \
-            if (lane == 0) ptq4vm_wreg_trace[tr_wg][wave][tr_n] = now;                                   \
-            tr_n++;                                                                                      \
-        }                                                                                                \
-    } while (0)
-#else
-#define WREG_TRACE() do {} while (0)
-#endif
 
 namespace ptq4vm {
 namespace mfma {
@@ -78,10 +51,7 @@ constexpr int kAhead = kSlots - 1;  // slots copied ahead of the one being consu
 constexpr int kStagePitch = 528;  // bytes per staged row: 256 channels of fp16 + 16 (bank spread)
 constexpr int kStageBytes = kUnitRows * kStagePitch;
 constexpr int kRowScaleBufs = 4;  // per-row step vectors of the units in flight
-#ifndef PTQ4VM_WREG_PREFETCH
-#define PTQ4VM_WREG_PREFETCH 3
-#endif
-constexpr int kPrefetchAhead = PTQ4VM_WREG_PREFETCH;  // units between a row tile's L2 prefetch and its first copy (0: none)
+constexpr int kPrefetchAhead = 3;  // units between a row tile's L2 prefetch and its first copy (0: none)
 constexpr int kPrefetchSinkBytes = 4 * 256;           // where the prefetch loads land: 256 bytes per storing wavefront
 
 template <int KSTEPS, bool HAS_BIAS, bool DUMP_ACC>
@@ -107,11 +77,6 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
     const int gw = wave & 3;  // wavefront inside its group of four
     const int l16 = lane & 15, lq = lane >> 4;
 
-#if PTQ4VM_WREG_TRACE
-    const int tr_wg = blockIdx.x == 0 ? 0 : (blockIdx.x == 77 ? 1 : -1);
-    int tr_n = 0;
-#endif
-    WREG_TRACE();
     const WorkRange wr = work_range(p);
     if (wr.count == 0) return;  // the whole workgroup: no barrier has been executed yet
     const int total_steps = wr.count * kSteps;
@@ -160,13 +125,9 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             const Acc zero = {0, 0, 0, 0};
-            if constexpr (!(PTQ4VM_WREG_SKIP & 32)) {
-                acc[0][j] = Int8Path::mfma16(w0, fx[j], fresh ? zero : acc[0][j]);
-                acc[1][j] = Int8Path::mfma16(w1, fx[j], fresh ? zero : acc[1][j]);
-            } else if (fresh) {
-                acc[0][j] = fx[j], acc[1][j] = fx[j] + w0 + w1;
-            }
-            if (refetch && !(PTQ4VM_WREG_SKIP & 8)) fx[j] = operand(j, slot, k2);
+            acc[0][j] = Int8Path::mfma16(w0, fx[j], fresh ? zero : acc[0][j]);
+            acc[1][j] = Int8Path::mfma16(w1, fx[j], fresh ? zero : acc[1][j]);
+            if (refetch) fx[j] = operand(j, slot, k2);
             __builtin_amdgcn_sched_barrier(0);  // keep the refetch behind its MFMAs: hoisted, it would need a second register set
         }
     };
@@ -200,10 +161,6 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
             for (int k2 = 0; k2 < KPS; k2++) fx[j * KPS + k2] = operand(j, slot, k2);
     };
     auto convert_block = [&](const LastStep &ls, int j, int64_t r0, int64_t o0) {
-        if constexpr (PTQ4VM_WREG_SKIP & 2) {
-            if (acc[0][j][0] == 0x12345678 && acc[1][j][3] == 0x7654321) p.y[0] = __float2half(1.0f);
-            return;
-        }
         v4f packed;
 #pragma unroll
         for (int i = 0; i < 2; i++) {  // four results at a time: keeps the temporaries few
@@ -231,11 +188,9 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
 #pragma unroll
             for (int k2 = 0; k2 < KPS; k2++) {
                 const int f = (j % LOOKAHEAD) * KPS + k2, ks = (kSteps - 1) * KPS + k2;
-                if constexpr (!(PTQ4VM_WREG_SKIP & 32)) {
-                    acc[0][j] = Int8Path::mfma16(fw[0][ks], fx[f], acc[0][j]);
-                    acc[1][j] = Int8Path::mfma16(fw[1][ks], fx[f], acc[1][j]);
-                }
-                if (j + LOOKAHEAD < 8 && !(PTQ4VM_WREG_SKIP & 8)) fx[f] = operand(j + LOOKAHEAD, slot, k2);
+                acc[0][j] = Int8Path::mfma16(fw[0][ks], fx[f], acc[0][j]);
+                acc[1][j] = Int8Path::mfma16(fw[1][ks], fx[f], acc[1][j]);
+                if (j + LOOKAHEAD < 8) fx[f] = operand(j + LOOKAHEAD, slot, k2);
             }
             if (j > 0) convert_block(ls, j - 1, r0, o0);
             __builtin_amdgcn_sched_barrier(0);
@@ -267,7 +222,7 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
         const char *gx = pf_x + (int64_t)pf_in_unit * SLAB;
         char *dst = ring + pf_slot * SLOT_BYTES;
 #pragma unroll
-        for (int c = 0; c < ((PTQ4VM_WREG_SKIP & 4) ? 0 : COPIES); c++) {
+        for (int c = 0; c < COPIES; c++) {
             const int row = (gw + 4 * c) * ROWS_PER_COPY + (int)(ln / CHUNKS);
             const int chunk = (int)(ln % CHUNKS) ^ (SLAB == 64 ? swizzle(row) : (row & 7));
             // rows beyond M are clamped to row M - 1: their results are copies of that row's (see `drain`)
@@ -307,8 +262,7 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int row = min(row0 + q * 2, rows_valid - 1);
-            if (!(PTQ4VM_WREG_SKIP & 1))
-                __builtin_nontemporal_store(data[q], reinterpret_cast<v4f *>(dst + (uint32_t)row * ldy_bytes));
+            __builtin_nontemporal_store(data[q], reinterpret_cast<v4f *>(dst + (uint32_t)row * ldy_bytes));
         }
     };
 
@@ -363,7 +317,6 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
             wait_vmcnt_at_most<0>();  // also lands every copy in flight; happens once or twice per launch
             if (first_run) __builtin_amdgcn_s_barrier();  // slot 0 is visible to everyone
             first_run = false;
-            WREG_TRACE();
             const int64_t o0 = (int64_t)strip * kStripCols;
 #pragma unroll 1
             do {
@@ -394,9 +347,8 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
                                 wait_vmcnt_at_most<0>();
                         }
                     }
-                    if constexpr (!(PTQ4VM_WREG_SKIP & 16)) __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");  // nothing below is read ahead of the barrier
-                    WREG_TRACE();
                     if constexpr (COPIER) {
                         if (pf_step < total_steps) issue();  // slot g + 4 into the ring place of slot g - 1
                     }
@@ -413,7 +365,6 @@ __global__ __launch_bounds__(512, 1) void linear_mfma_wreg(const LinearArgs p) {
                     }
                     slot = next_slot;
                 }
-                WREG_TRACE();
                 prev_r0 = r0, prev_o0 = o0;
                 advance(cc, wr);
                 u++;
