@@ -279,13 +279,6 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
         const int64_t r_end = min(p.M, unit_r0 + unit_rows);  // rows at or beyond it are not this unit's
         const int unit_groups = groups;                        // (`groups` moves on to the next unit before the epilogue)
 
-        // Steps of the lane's result rows, fetched ahead of the reduction: behind it their latency was exposed.  (Nor does a unit
-        // end with a wait for its stores: loads and stores retire in the order of their issue, so the waits for the next
-        // unit's lines do not cover them.  us, before -> now: 25216 x 768 -> 44 13.0 -> 12.3, 12608 x 768 -> 44 8.66 -> 8.49.)
-        float rs[RB];
-#pragma unroll
-        for (int j = 0; j < RB; j++) rs[j] = p.s_tok[(uint32_t)min(r_unit + j * 16 + l16, p.M - 1) % (uint32_t)L];
-
         auto k_loop = [&](auto g_tag, auto depth_tag) {
             constexpr int G = decltype(g_tag)::value, DEPTH = decltype(depth_tag)::value;
             auto load_g = [&](int d, int ks) {
@@ -357,8 +350,9 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
             k_loop(std::integral_constant<int, NL / 2>{}, std::integral_constant<int, D>{});
 
         // Accumulator register v of block (j, i): token row 16 j + (lane mod 16), channel 16 i + 4 (lane / 16) + v.
+        float rs[RB];
 #pragma unroll
-        for (int j = 0; j < RB; j++) asm volatile("" : "+v"(rs[j]));  // in registers before the next unit's loads are issued
+        for (int j = 0; j < RB; j++) rs[j] = p.s_tok[(uint32_t)min(r_unit + j * 16 + l16, p.M - 1) % (uint32_t)L];
         int rz[RB];  // zero offset of the lane's result row
 #pragma unroll
         for (int j = 0; j < RB; j++) rz[j] = OFFSET ? z_lds[(uint32_t)min(r_unit + j * 16 + l16, p.M - 1) % (uint32_t)L] : 0;
@@ -429,6 +423,10 @@ __global__ __launch_bounds__(kFusedWaves * 64) void pts_linear_wres(const Linear
             }
             asm volatile("" ::: "memory");
         }
+        // Stores and loads share the vmcnt counter and complete out of order with each other, so with
+        // stores possibly outstanding every wait on a fetched line would have to be a full drain.
+        // Drain once here instead: the next unit's first lines were fetched during the epilogue.
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     }
 }
 
