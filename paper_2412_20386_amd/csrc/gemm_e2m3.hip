@@ -477,9 +477,9 @@ extern "C" int ptq4vm_w4a4_linear_e2m3(const uint8_t *xq6, const uint8_t *wq6, c
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     auto tiles = [&](int br, int bo) { return ptq4vm::ceil_div(M, br) * ptq4vm::ceil_div(N, bo); };
     // 256 x 256 tiles from two rounds of them (50432 x 384 -> 1536 [1182 tiles] 43.8 us against 54.0 on 128 x 256 tiles,
-    // 50432 x 1536 -> 768 [591] 56.2 / 60.0, 12608 x 768 -> 3072 [600] 35.4 / 34.8, but 25216 x 1536 -> 768 [297] 35.0 / 28.6),
+    // 50432 x 1536 -> 768 [591] 51.5 / 60.0, 12608 x 768 -> 3072 [600] 33.6 / 34.8, but 25216 x 1536 -> 768 [297] 35.0 / 28.6),
     // unless they pad the channels by more than a quarter (40000 x 768 -> 520: 29.3 / 24.3).  Also within one round, where the
-    // 128 x 128 tiles, three to a CU, would need a second one (14148 x 1152 -> 832 [224] 15.9 / 19.7, 9030 x 1280 -> 1344 [216]
+    // 128 x 128 tiles, three to a CU, would need a second one (14148 x 1152 -> 832 [224] 16.0 / 19.7, 9030 x 1280 -> 1344 [216]
     // 16.7 / 20.9, 20860 x 1920 -> 576 [246] 22.6 / 28.2; with at most 768 of the smaller tiles they are 4 to 12 % slower), for
     // shorter reductions just beyond that line only (K <= 1024 from 832 small tiles on, 116 shapes: 0.83 to 1.10 of the time).
     const int64_t big_tiles = tiles(256, kTile), small_tiles = tiles(128, 128);

@@ -1,4 +1,4 @@
-// Tile kernels of the MFMA linears for problems that do not fill the chip with 256 x 256 tiles
+// Tile kernels of the MFMA linears for problems that fill the chip with 256 x 256 tiles once or not at all
 // (small and medium row counts, narrow outputs): included by gemm_tile.hip, which holds their dispatch.
 //
 //   linear_mfma_tile    BR x BO tiles, one workgroup each, both operands copied global -> LDS directly
