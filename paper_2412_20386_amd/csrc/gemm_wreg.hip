@@ -406,12 +406,13 @@ int launch_wreg(const LinearArgs &a_in, hipStream_t stream) {
     if (err == hipSuccess) err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     if (err != hipSuccess) return ptq4vm::record_hip_error(err, "hipDeviceGetAttribute(multiprocessor count)");
     const unsigned wgs = (unsigned)max(1, cus / kXcds) * kXcds;  // one workgroup per CU, a multiple of the XCD count
-    // From nine units a workgroup.  With fewer, loading the weight rows, the first slots and the last, uneven unit weigh more
-    // than what the resident weight saves (us, this kernel / persistent or tile kernels; units per workgroup in brackets:
-    // 12608 x 768 -> 1536 [2.3] 34.6 / 24.3, 12608 x 768 -> 3072 [4.6] 46.3 / 40.2, 33096 x 768 -> 1536 [6.1] 56.3 / 52.6,
-    // 20488 x 768 -> 3072 [7.5] 63.7 / 60.8, 25216 x 768 -> 3072 [9.2] 74.4 / 75.0, 50240 x 384 -> 1536 [9.2] 51.7 / 52.6,
-    // 50240 x 768 -> 3072 [18.4] 135 / 148).
-    if (tiles_r * tiles_o < 9 * (int64_t)wgs) return 1;
+    // From nine units a workgroup, and whole rounds of units only.  The persistent kernel, whose next tile arrives under the epilogue
+    // of the last, has overtaken this one (us, this kernel / persistent; units per workgroup in brackets): 25216 x 768 -> 3072
+    // [9.2] 77.8 / 70.5, 50240 x 384 -> 1536 [9.2] 51.5 / 47.0, 50432 x 768 -> 3072 [18.5] 147.4 / 137.7, 50432 x 384 -> 3072
+    // [18.5] 99 / 88, 100864 x 768 -> 1536 [18.5] 147 / 134.  It comes closest where no workgroup has an uneven last unit, and keeps
+    // those shapes as they were: 294789 x 384 -> 256 [9] 65.0 / 62.6, 73601 x 768 -> 1024 [9] 73.9 / 70.5, 98276 x 768 -> 768 [9]
+    // 74.0 / 68.0, 24525 x 384 -> 3072 [9] 56.4 / 52.5.
+    if (tiles_r * tiles_o < 9 * (int64_t)wgs || tiles_r * tiles_o % wgs != 0) return 1;
     using Kernel = void (*)(const LinearArgs);
     // [K = 768][has bias][also write the int32 accumulators]
     static const Kernel kernels[2][2][2] = {
