@@ -16,7 +16,7 @@
 //
 // Kernels: linear_mfma_persistent here (many 256 x 256 tiles), linear_mfma_smallk here (fp16, reductions of at most 128
 // bytes), the row-streaming kernel of pts_linear_fused.hip (very short reductions over many rows), the
-// weights-in-registers kernel of gemm_wreg.hip (wide outputs, short reductions), and the tile kernels of
+// weights-in-registers kernel of gemm_wreg.hip (short reductions, whole rounds of its units), and the tile kernels of
 // gemm_tile.hip for everything else.
 #include "gemm_tile.hpp"
 
@@ -593,7 +593,7 @@ int dispatch(LinearArgs a, hipStream_t stream) {
             return la == 16 ? launch_smallk_ksteps<16>(a, stream) : launch_smallk_ksteps<4>(a, stream);
     }
     if constexpr (Path::kElemBytes == 1 && !Path::kOffset && !Path::kPacked4) {
-        // wide output, short reduction (in_proj of the Vim-S / Vim-B stacks): weight rows held in registers
+        // short reduction, whole rounds of units: weight rows held in registers (both sides measured there)
         const int rc = launch_wreg(a, stream);
         if (rc <= 0) return rc;
     }
