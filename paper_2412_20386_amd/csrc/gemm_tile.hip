@@ -30,11 +30,11 @@ int launch_staged(const LinearArgs &a, hipStream_t stream) {
     return a.k_bytes <= SLAB ? launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kOneSlab>(a, stream) : launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kRegisters>(a, stream);
 }
 
-template <class Path, int FR, int FO, int SK, int U, bool ALIGNED>
+template <class Path, int FR, int FO, int SK, int U, Rows ROWS>
 int launch_splitk(LinearArgs a, hipStream_t stream) {
     dim3 grid;
     if (!set_grid<16 * FR, 16 * FO>(a, grid)) return PTQ4VM_ERR_SHAPE;
-    linear_mfma_splitk<Path, FR, FO, SK, U, ALIGNED><<<grid, dim3(64 * SK), 0, stream>>>(a);
+    linear_mfma_splitk<Path, FR, FO, SK, U, ROWS><<<grid, dim3(64 * SK), 0, stream>>>(a);
     return ptq4vm::check_launch("linear_mfma_splitk");
 }
 
@@ -63,7 +63,7 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
     // 32-bit offsets inside a tile and token positions; the split-reduction kernel takes any size
     const bool small = a.ldx_bytes * 256 < (1LL << 31) && a.ldw_bytes * 256 < (1LL << 31) && a.L < (1LL << 31);
     if (aligned && small) {
-        if (tiles(a, 16, 16) <= 256) return launch_splitk<Path, 1, 1, 4, 4, true>(a, stream);
+        if (tiles(a, 16, 16) <= 256) return launch_splitk<Path, 1, 1, 4, 4, Rows::kAligned>(a, stream);
         auto padded = [&](int br, int bo) { return tiles(a, br, bo) * br * bo; };
         const int64_t most = padded(32, 64) * 4 / 3;
         auto fills = [&](int br, int bo, int percent) {  // whole rounds of 256 workgroups, the last one to `percent`
@@ -89,8 +89,9 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
     // 64 x 64 ones (against 64 x 128 tiles, over 300 shapes: 0.7 .. 0.85 of the time from 1024 bytes of K, there with 128-byte
     // slabs, 0.85 .. 0.95 below; half-padded ones, 46670 x 1968 -> 61, 1.4 times); with one or two slabs their larger epilogue
     // counts more (11938 x 32 -> 745 [564 tiles] 10.4 / 9.0) and they start at 1600.
-    if (tiles(a, 16, 16) <= 600) return launch_splitk<Path, 1, 1, 4, 4, false>(a, stream);
-    if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= 1000)) return launch_splitk<Path, 2, 2, 4, 3, false>(a, stream);
+    if (is_tiny(a.M, a.ldx_bytes, a.k_bytes) || is_tiny(a.N, a.ldw_bytes, a.k_bytes)) return launch_splitk<Path, 1, 1, 1, 1, Rows::kTiny>(a, stream);
+    if (tiles(a, 16, 16) <= 600) return launch_splitk<Path, 1, 1, 4, 4, Rows::kAny>(a, stream);
+    if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= 1000)) return launch_splitk<Path, 2, 2, 4, 3, Rows::kAny>(a, stream);
     if (tiles(a, 128, 128) >= (a.k_bytes > 128 ? 300 : 1600) && 3 * tiles(a, 128, 128) * 128 * 128 <= 4 * tiles(a, 64, 64) * 64 * 64)
         return a.k_bytes < 1024 ? launch_staged<Path, 128, 128, 2, 4, 64>(a, stream) : launch_staged<Path, 128, 128, 2, 4, 128>(a, stream);
     if (tiles(a, 64, 128) >= 800) return launch_staged<Path, 64, 128, 2, 2, 64>(a, stream);

@@ -87,37 +87,58 @@ __device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid) {
             reinterpret_cast<uint16_t *>(dst)[e] = (uint16_t)(__builtin_bit_cast(uint32_t, w[e >> 1]) >> (16 * (e & 1)));
 }
 
-// 16 bytes of a row at byte kb, bytes at or beyond k_bytes read as 0; `base` and `end` bound the matrix.  Where the 16 bytes would pass the
-// end, the last 16 of the matrix are loaded and moved down.  Short code on purpose: a workgroup runs through it once, and loads byte by
-// byte for that case, 64 of them per call skipped by branches, cost the instructions' way through the cache.
-__device__ __forceinline__ v4i load_any(const char *row, int64_t kb, int64_t k_bytes, const char *base, const char *end) {
-    v4i out = {0, 0, 0, 0};
-    const int valid = (int)min((int64_t)16, k_bytes - kb);
-    if (valid <= 0) return out;
-    const char *at = row + kb;
-    const int over = (int)max((int64_t)0, (int64_t)(at + 16 - end));
-    if (at - over >= base) {
-        out = *reinterpret_cast<const v4i_unaligned *>(at - over);
-        if (over > 0) {  // move down by `over` bytes; what enters from above lies beyond K
-            if (over & 8) out = v4i{out[2], out[3], 0, 0};
-            if (over & 4) out = v4i{out[1], out[2], out[3], 0};
-            const int b = over & 3;
-            out = v4i{(int)__builtin_amdgcn_alignbyte(out[1], out[0], b), (int)__builtin_amdgcn_alignbyte(out[2], out[1], b),
-                      (int)__builtin_amdgcn_alignbyte(out[3], out[2], b), (int)__builtin_amdgcn_alignbyte(0, out[3], b)};
-        }
-    } else {  // a matrix of fewer than 16 bytes
-#pragma unroll 1
-        for (int i = 0; i < valid; i++) {
-            const int byte = (int)*reinterpret_cast<const uint8_t *>(at + i) << (8 * (i & 3));
-#pragma unroll
-            for (int j = 0; j < 4; j++) out[j] |= (i >> 2) == j ? byte : 0;
-        }
+// Operands of any pitch, alignment and K.  Only the last MFMA step (or slab) of a reduction reaches beyond K; every other one loads its 16-byte
+// pieces without tests.  The last one's are requested by load_within and put right by place_within where they are used, so that
+// nothing between a request and the next one depends on loaded data: with the correction behind each load (and its branches, whose joins wait
+// for the load) the requests ran one after another (us, so / as now: 33 x 1648 -> 49 5.3 / 3.5, fp16 76 x 1818 -> 2020 13.9 / 9.7, fused
+// 362 x 288 -> 893 6.9 / 6.1).
+//
+// kTiny, a matrix of fewer than 16 bytes, is loaded byte by byte (host-checked: the other forms never meet one).
+enum class Rows { kAligned, kAny, kTiny };
+inline bool is_tiny(int64_t rows, int64_t pitch_bytes, int64_t k_bytes) {
+    return k_bytes < 16 && (rows == 1 || (rows < 16 && pitch_bytes < 16 && (rows - 1) * pitch_bytes + k_bytes < 16));
+}
+
+// The 16 bytes at `at`; where these would pass the end of the matrix, its last 16.
+__device__ __forceinline__ v4i load_within(const char *at, const char *end) {
+    const char *const last = end - 16;
+    return *reinterpret_cast<const v4i_unaligned *>(at < last ? at : last);
+}
+// What load_within returned, moved to where it would lie in the 16 bytes at `at`; what enters from above lies beyond K.  (Where K is a multiple of
+// 16 bytes, no piece of a row passes the end.)
+__device__ __forceinline__ v4i place_within(v4i v, const char *at, const char *end) {
+    const int over = (int)min((int64_t)16, (int64_t)(at + 16 - end));
+    if (over > 0) {
+        if (over & 8) v = v4i{v[2], v[3], 0, 0};
+        if (over & 4) v = v4i{v[1], v[2], v[3], 0};
+        const int b = over & 3;
+        v = v4i{(int)__builtin_amdgcn_alignbyte(v[1], v[0], b), (int)__builtin_amdgcn_alignbyte(v[2], v[1], b),
+                (int)__builtin_amdgcn_alignbyte(v[3], v[2], b), (int)__builtin_amdgcn_alignbyte(0, v[3], b)};
     }
-    if (valid < 16) {
+    return v;
+}
+// The 16 bytes at `at`, those from `end` on repeating the last one before it (no branches: all 16 in flight).
+__device__ __forceinline__ v4i load_bytes(const char *at, const char *end) {
+    v4i out;
 #pragma unroll
-        for (int j = 0; j < 4; j++) out[j] = (int)keep_low_bytes((uint32_t)out[j], valid - 4 * j);
+    for (int j = 0; j < 4; j++) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+            const char *const byte = at + 4 * j + b;
+            word |= (uint32_t) * reinterpret_cast<const uint8_t *>(byte < end ? byte : end - 1) << (8 * b);
+        }
+        out[j] = (int)word;
     }
     return out;
+}
+// The bytes of a row's 16 at byte kb that lie before k_bytes, as a mask.  Integer products need it on one operand only.
+__device__ __forceinline__ v4i mask_within(int64_t kb, int64_t k_bytes) {
+    const int valid = (int)max((int64_t)0, min((int64_t)16, k_bytes - kb));
+    v4i m;
+#pragma unroll
+    for (int j = 0; j < 4; j++) m[j] = (int)keep_low_bytes(0xffffffffu, valid - 4 * j);
+    return m;
 }
 
 // n / d for n < 2^31 and a divisor known on the host, 1 <= d < 2^31: with 2^(shift-1) < d <= 2^shift and mul = floor(2^32 (2^shift -
@@ -590,6 +611,7 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
     }
     const char *gx = p.x + r0 * p.ldx_bytes, *gw = p.w + o0 * p.ldw_bytes;
     const int64_t k_bytes = p.k_bytes;
+    const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + k_bytes), *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
     constexpr int DEPTH = BR * BO <= 64 * 64 ? 2 : 1;
     v4i staged[DEPTH][COPIES];
     auto fetch = [&](int buf, int slab) {
@@ -603,12 +625,21 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             if (inside) {
                 staged[buf % DEPTH][i] = *reinterpret_cast<const v4i_unaligned *>(src + (int64_t)slab * SLAB + (off[i] + chunk * 16));
             } else {
-                const char *end = is_x ? p.x + ((p.M - 1) * p.ldx_bytes + k_bytes) : p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
-                staged[buf % DEPTH][i] = load_any(src + off[i], (int64_t)slab * SLAB + chunk * 16, k_bytes, is_x ? p.x : p.w, end);
+                staged[buf % DEPTH][i] = load_within(src + (int64_t)slab * SLAB + (off[i] + chunk * 16), is_x ? x_end : w_end);
             }
         }
     };
-    auto commit = [&](int buf, int stage) {
+    auto commit = [&](int buf, int stage, int slab) {
+        if ((int64_t)(slab + 1) * SLAB > k_bytes) {  // uniform
+#pragma unroll
+            for (int i = 0; i < COPIES; i++) {
+                const int c = wave + NW * i;
+                const bool is_x = c * ROWS_PER_COPY < BR;
+                const int64_t kb = (int64_t)slab * SLAB + chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS) * 16;
+                if (k_bytes % 16 != 0) staged[buf % DEPTH][i] = place_within(staged[buf % DEPTH][i], (is_x ? gx : gw) + off[i] + kb, is_x ? x_end : w_end);
+                staged[buf % DEPTH][i] &= mask_within(kb, k_bytes);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < COPIES; i++)
             *reinterpret_cast<v4i *>(ring + stage * STAGE_BYTES + (wave + NW * i) * 1024 + lane * 16) = staged[buf % DEPTH][i];
@@ -627,7 +658,7 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
     TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * STAGE_BYTES);
     vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
     if (DEPTH == 2 && n_slabs > 1) fetch(1, 1);
-    commit(0, 0);
+    commit(0, 0, 0);
     auto slab = [&](int it, int buf) {  // the slab lies in stage buf; the next one is on its way or (DEPTH 1) requested now
         __syncthreads();
         if (it + DEPTH < n_slabs) fetch(DEPTH == 2 ? buf : 0, it + DEPTH);
@@ -648,7 +679,7 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             }
             mfma_step<Path, FO, FR>(acc, fw, fx);
         }
-        if (it + 1 < n_slabs) commit(buf ^ 1, buf ^ 1);
+        if (it + 1 < n_slabs) commit(buf ^ 1, buf ^ 1, it + 1);
     };
     if constexpr (DEPTH == 2) {
 #pragma unroll 1
@@ -690,12 +721,12 @@ __device__ __forceinline__ void one_slab_tile(const TileArgs &p) {
 #pragma unroll
         for (int i = 0; i < FO; i++) {
             const int row = min(wave_o + channel_of_row(i * 16 + l16), cols_valid - 1);
-            fw[ks][i] = load_any(gw + (uint32_t)row * (uint32_t)p.ldw_bytes, ks * 64 + lq * 16, p.k_bytes, p.w, w_end);
+            fw[ks][i] = load_within(gw + ((uint32_t)row * (uint32_t)p.ldw_bytes + ks * 64 + lq * 16), w_end);
         }
 #pragma unroll
         for (int j = 0; j < FR; j++) {
             const int row = min(wave_r + j * 16 + l16, rows_valid - 1);
-            fx[ks][j] = load_any(gx + (uint32_t)row * (uint32_t)p.ldx_bytes, ks * 64 + lq * 16, p.k_bytes, p.x, x_end);
+            fx[ks][j] = load_within(gx + ((uint32_t)row * (uint32_t)p.ldx_bytes + ks * 64 + lq * 16), x_end);
         }
     }
     TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * (BR + BO) * SLAB);
@@ -707,9 +738,35 @@ __device__ __forceinline__ void one_slab_tile(const TileArgs &p) {
         for (int j = 0; j < FR; j++)
 #pragma unroll
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
+    // uniform: a row of the tile whose 16-byte pieces may pass the end of the matrix
+    const bool pieces = p.k_bytes % 16 != 0;
+    const bool w_edge = pieces && gw + ((int64_t)(cols_valid - 1) * p.ldw_bytes + KS * 64) > w_end, x_edge = pieces && gx + ((int64_t)(rows_valid - 1) * p.ldx_bytes + KS * 64) > x_end;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-        if (ks == 0 || ks * 64 < p.k_bytes) mfma_step<Path, FO, FR>(acc, fw[ks], fx[ks]);
+    for (int ks = 0; ks < KS; ks++) {
+        if (ks > 0 && ks * 64 >= p.k_bytes) break;
+        if (w_edge) {
+#pragma unroll
+            for (int i = 0; i < FO; i++) {
+                const int row = min(wave_o + channel_of_row(i * 16 + l16), cols_valid - 1);
+                fw[ks][i] = place_within(fw[ks][i], gw + ((uint32_t)row * (uint32_t)p.ldw_bytes + ks * 64 + lq * 16), w_end);
+            }
+        }
+        if (x_edge) {
+#pragma unroll
+            for (int j = 0; j < FR; j++) {
+                const int row = min(wave_r + j * 16 + l16, rows_valid - 1);
+                fx[ks][j] = place_within(fx[ks][j], gx + ((uint32_t)row * (uint32_t)p.ldx_bytes + ks * 64 + lq * 16), x_end);
+            }
+        }
+        const v4i mask = mask_within(ks * 64 + lq * 16, p.k_bytes);
+#pragma unroll
+        for (int i = 0; i < FO; i++) fw[ks][i] &= mask;
+        if constexpr (Path::kElemBytes == 2) {  // (infinities and NaN beyond K)
+#pragma unroll
+            for (int j = 0; j < FR; j++) fx[ks][j] &= mask;
+        }
+        mfma_step<Path, FO, FR>(acc, fw[ks], fx[ks]);
+    }
     vec.park(p, tid);
     __syncthreads();
     store_tile<Path, BR, BO, WR, WO, 2 * (BR + BO) * SLAB, DUMP>(acc, p, lds_dyn, vec, r0, o0, rows_valid, cols_valid);
@@ -811,11 +868,12 @@ __device__ __forceinline__ void finish_split(const typename Path::Acc16 (&acc)[F
 // of SK wavefronts owns one tile of 16 FR rows x 16 FO channels; wavefront w takes
 // the MFMA steps w, w + SK, ... (64 bytes of K each, so that neighbouring wavefronts read neighbouring bytes),
 // with U steps of operands in flight in registers, then the partial sums meet in LDS and wavefront b finishes
-// block b.  ALIGNED: 16-byte aligned bases and pitches and k_bytes a multiple of 64; otherwise any pitch,
-// alignment and K: loads of 16 bytes wherever they fall, bytes beyond K zeroed.
+// block b.  kAligned: 16-byte aligned bases and pitches and k_bytes a multiple of 64; otherwise any pitch,
+// alignment and K: loads of 16 bytes wherever they fall, bytes beyond K zeroed.  Four workgroups to a CU, or the up to 1000 tiles of
+// 32 x 32 become two rounds (packed 826 x 650 -> 1068 11.5 us at three, 9.1 at four).
 // ------------------------------------------------------------------------------------------
-template <class Path, int FR, int FO, int SK, int U, bool ALIGNED>
-__global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p) {
+template <class Path, int FR, int FO, int SK, int U, Rows ROWS>
+__global__ __launch_bounds__(64 * SK, 4) void linear_mfma_splitk(const LinearArgs p) {
     constexpr int BR = 16 * FR, BO = 16 * FO;
     using Acc = typename Path::Acc16;
     __shared__ __attribute__((aligned(16))) char partial[SK * FR * FO * 1024];
@@ -840,26 +898,54 @@ __global__ __launch_bounds__(64 * SK) void linear_mfma_splitk(const LinearArgs p
 #pragma unroll
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
 
-    const int n_steps = (int)((p.k_bytes + 63) / 64);
-    for (int s0 = wave; s0 < n_steps; s0 += SK * U) {
+    const int n_whole = (int)(p.k_bytes / 64);
+    // The step that reaches beyond K, requested first and used last
+    const bool last = ROWS != Rows::kAligned && p.k_bytes % 64 != 0 && wave == n_whole % SK;
+    auto load_last = [&](const char *at, const char *end) {
+        if constexpr (ROWS == Rows::kTiny)
+            return load_bytes(at, end);
+        else
+            return load_within(at, end);
+    };
+    v4i lw[FO], lx[FR];
+    if (last) {
+#pragma unroll
+        for (int i = 0; i < FO; i++) lw[i] = load_last(wrow[i] + (int64_t)n_whole * 64, w_end);
+#pragma unroll
+        for (int j = 0; j < FR; j++) lx[j] = load_last(xrow[j] + (int64_t)n_whole * 64, x_end);
+    }
+    using Load = std::conditional_t<ROWS == Rows::kAligned, v4i, v4i_unaligned>;
+    for (int s0 = wave; s0 < n_whole; s0 += SK * U) {
         v4i fw[U][FO], fx[U][FR];
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int s = s0 + u * SK;
-            if (s < n_steps) {
+            if (s < n_whole) {
 #pragma unroll
-                for (int i = 0; i < FO; i++)
-                    fw[u][i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + (int64_t)s * 64)
-                                       : load_any(wrow[i] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, p.w, w_end);
+                for (int i = 0; i < FO; i++) fw[u][i] = *reinterpret_cast<const Load *>(wrow[i] + (int64_t)s * 64);
 #pragma unroll
-                for (int j = 0; j < FR; j++)
-                    fx[u][j] = ALIGNED ? *reinterpret_cast<const v4i *>(xrow[j] + (int64_t)s * 64)
-                                       : load_any(xrow[j] - lq * 16, (int64_t)s * 64 + lq * 16, p.k_bytes, p.x, x_end);
+                for (int j = 0; j < FR; j++) fx[u][j] = *reinterpret_cast<const Load *>(xrow[j] + (int64_t)s * 64);
             }
         }
 #pragma unroll
         for (int u = 0; u < U; u++)
-            if (s0 + u * SK < n_steps) mfma_step<Path, FO, FR>(acc, fw[u], fx[u]);
+            if (s0 + u * SK < n_whole) mfma_step<Path, FO, FR>(acc, fw[u], fx[u]);
+    }
+    if (last) {
+        if (ROWS == Rows::kAny && p.k_bytes % 16 != 0) {
+#pragma unroll
+            for (int i = 0; i < FO; i++) lw[i] = place_within(lw[i], wrow[i] + (int64_t)n_whole * 64, w_end);
+#pragma unroll
+            for (int j = 0; j < FR; j++) lx[j] = place_within(lx[j], xrow[j] + (int64_t)n_whole * 64, x_end);
+        }
+        const v4i mask = mask_within((int64_t)n_whole * 64 + lq * 16, p.k_bytes);
+#pragma unroll
+        for (int i = 0; i < FO; i++) lw[i] &= mask;
+        if constexpr (Path::kElemBytes == 2) {  // (infinities and NaN beyond K)
+#pragma unroll
+            for (int j = 0; j < FR; j++) lx[j] &= mask;
+        }
+        mfma_step<Path, FO, FR>(acc, lw, lx);
     }
 
     finish_split<Path, FR, FO, SK>(acc, p, partial, r0, o0);

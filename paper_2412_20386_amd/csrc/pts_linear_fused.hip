@@ -848,34 +848,42 @@ int launch_stream_aligned(const LinearArgs &a, int xa, int wa, const StreamLayou
     return ptq4vm::check_launch("linear_stream_smallk");
 }
 
-template <Form FORM, int RB, int W, bool ALIGNED>
-int launch_split(LinearArgs a, hipStream_t stream) {
-    using Kernel = void (*)(const LinearArgs);
-    static const Kernel kernels[8] = {  // by the number of 16-channel blocks of a tile
-        pts_linear_split<FORM, 1, RB, W, ALIGNED>, pts_linear_split<FORM, 2, RB, W, ALIGNED>, pts_linear_split<FORM, 3, RB, W, ALIGNED>,
-        pts_linear_split<FORM, 4, RB, W, ALIGNED>, pts_linear_split<FORM, 5, RB, W, ALIGNED>, pts_linear_split<FORM, 6, RB, W, ALIGNED>,
-        pts_linear_split<FORM, 7, RB, W, ALIGNED>, pts_linear_split<FORM, 8, RB, W, ALIGNED>};
-    const int64_t nb = a.N >= 128 ? 8 : ptq4vm::ceil_div(a.N, 16);
-    const int64_t tiles_r = ptq4vm::ceil_div(a.M, 16 * RB), tiles_o = ptq4vm::ceil_div(a.N, 16 * nb);
+// NB: 16-channel blocks of a tile
+template <Form FORM, int NB, int RB, int W, Rows ROWS>
+int launch_split_blocks(LinearArgs a, hipStream_t stream) {
+    const int64_t tiles_r = ptq4vm::ceil_div(a.M, 16 * RB), tiles_o = ptq4vm::ceil_div(a.N, 16 * NB);
     if (tiles_r * tiles_o > 0x3fffffffLL) return PTQ4VM_ERR_SHAPE;
     a.tiles_r = (int)tiles_r;
     a.tiles_o = (int)tiles_o;
-    kernels[nb - 1]<<<grid_of_tiles(tiles_r * tiles_o), dim3(64 * W), 0, stream>>>(a);
+    pts_linear_split<FORM, NB, RB, W, ROWS><<<grid_of_tiles(tiles_r * tiles_o), dim3(64 * W), 0, stream>>>(a);
     return ptq4vm::check_launch("pts_linear_split");
+}
+template <Form FORM, int RB, int W, Rows ROWS>
+int launch_split(const LinearArgs &a, hipStream_t stream) {
+    switch (a.N >= 128 ? 8 : ptq4vm::ceil_div(a.N, 16)) {
+        case 1: return launch_split_blocks<FORM, 1, RB, W, ROWS>(a, stream);
+        case 2: return launch_split_blocks<FORM, 2, RB, W, ROWS>(a, stream);
+        case 3: return launch_split_blocks<FORM, 3, RB, W, ROWS>(a, stream);
+        case 4: return launch_split_blocks<FORM, 4, RB, W, ROWS>(a, stream);
+        case 5: return launch_split_blocks<FORM, 5, RB, W, ROWS>(a, stream);
+        case 6: return launch_split_blocks<FORM, 6, RB, W, ROWS>(a, stream);
+        case 7: return launch_split_blocks<FORM, 7, RB, W, ROWS>(a, stream);
+        default: return launch_split_blocks<FORM, 8, RB, W, ROWS>(a, stream);
+    }
 }
 // Eight wavefronts on 16 rows while that gives every CU at most one workgroup, four on 32 rows beyond (us, 8 x 16 / 4 x 32
 // rows: 2364 x 768 -> 56 5.6 / 8.3, 4137 x 1536 -> 80 13.3 / 12.9, 12608 x 768 -> 56 13.3 / 10.8).
-template <Form FORM, bool ALIGNED>
+template <Form FORM, Rows ROWS>
 int launch_split_rows(const LinearArgs &a, hipStream_t stream) {
-    return ptq4vm::ceil_div(a.M, 16) * ptq4vm::ceil_div(a.N, 128) <= 256 ? launch_split<FORM, 1, 8, ALIGNED>(a, stream)
-                                                                         : launch_split<FORM, 2, 4, ALIGNED>(a, stream);
+    return ptq4vm::ceil_div(a.M, 16) * ptq4vm::ceil_div(a.N, 128) <= 256 ? launch_split<FORM, 1, 8, ROWS>(a, stream)
+                                                                         : launch_split<FORM, 2, 4, ROWS>(a, stream);
 }
 // The shapes of the resident kernel below its rows (N <= 128, fewer than 4096 rows): 16 rows a workgroup always.
 int launch_split_form(const LinearArgs &a, hipStream_t stream, Form form) {
     switch (form) {
-        case Form::kInt8: return launch_split<Form::kInt8, 1, 8, true>(a, stream);
-        case Form::kBits4: return launch_split<Form::kBits4, 1, 8, true>(a, stream);
-        default: return launch_split<Form::kOffset, 1, 8, true>(a, stream);
+        case Form::kInt8: return launch_split<Form::kInt8, 1, 8, Rows::kAligned>(a, stream);
+        case Form::kBits4: return launch_split<Form::kBits4, 1, 8, Rows::kAligned>(a, stream);
+        default: return launch_split<Form::kOffset, 1, 8, Rows::kAligned>(a, stream);
     }
 }
 
@@ -976,9 +984,11 @@ int dispatch(LinearArgs a, hipStream_t stream, Form form = Form::kInt8) {
     if (form != Form::kInt8) return PTQ4VM_ERR_SHAPE;
     // Narrow outputs, or so few rows that the tiled kernel below has no more than a few workgroups a CU
     // (us, split / tiled: 19031 x 1000 -> 80 24 / 144, 4137 x 333 -> 128 14 / 123, 197 x 1536 -> 80 8 / 164).
-    if (a.N <= 128 || a.M <= 2048)
-        return small && xa == 16 && wa == 16 && a.k_bytes % 64 == 0 ? launch_split_rows<Form::kInt8, true>(a, stream)
-                                                           : launch_split_rows<Form::kInt8, false>(a, stream);
+    if (a.N <= 128 || a.M <= 2048) {
+        if (is_tiny(a.M, a.ldx_bytes, a.k_bytes * 2) || is_tiny(a.N, a.ldw_bytes, a.k_bytes)) return launch_split_blocks<Form::kInt8, 1, 1, 1, Rows::kTiny>(a, stream);
+        return small && xa == 16 && wa == 16 && a.k_bytes % 64 == 0 ? launch_split_rows<Form::kInt8, Rows::kAligned>(a, stream)
+                                                           : launch_split_rows<Form::kInt8, Rows::kAny>(a, stream);
+    }
     return launch_generic<256, 128, 2, 2>(a, xa, wa, stream);
 }
 

@@ -88,13 +88,15 @@ struct FusedPath<Form::kOffset> {
 // 16 RB rows (from L2, through the CU's one 64-byte-per-clock load path, which is what bounds long reductions) instead of
 // once per CU (us, this / weight-resident: 4137 x 1536 -> 80 14.1 / 10.3, 25216 x 768 -> 56 19.4 / 12.4), so it serves what
 // that kernel cannot: fewer rows than fill its CUs, any alignment, tables beyond the LDS.
-// ALIGNED: K % 64 == 0, 16-byte aligned rows of x and of the weight.  Otherwise any K and pitch: weight bytes beyond K
-// read as zero, so the codes there do not matter.
+// kAligned: K % 64 == 0, 16-byte aligned rows of x and of the weight.  Otherwise any K and pitch: weight bytes beyond K
+// read as zero, so the codes there do not matter.  (Six blocks of 32 rows: a third wavefront per SIMD is worth a small spill, 37575 x 136 -> 91
+// 22.4 / 19.9 us; at three, four and seven blocks a bound that spills loses.)
 // ------------------------------------------------------------------------------------------
-template <Form FORM, int NB, int RB, int W, bool ALIGNED>
-__global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
+template <Form FORM, int NB, int RB, int W, Rows ROWS>
+__global__ __launch_bounds__(64 * W, (ROWS == Rows::kAny && NB == 6 && RB == 2 ? 3 : 1)) void pts_linear_split(const LinearArgs p) {
     using Path = typename FusedPath<FORM>::Path;
     constexpr bool BITS4 = FORM == Form::kBits4, OFFSET = FORM == Form::kOffset;
+    constexpr bool ALIGNED = ROWS == Rows::kAligned;
     static_assert(ALIGNED || FORM == Form::kInt8, "the other forms exist for the shapes of the resident kernel only");
     constexpr int NL = 2 * RB;  // loads of 8 rows per step
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -147,23 +149,39 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
         v4i w[BITS4 ? 1 : NB];
         u32x2 w4[BITS4 ? NB : 1];
     };
+    auto whole = [&](int s) { return ALIGNED || (int64_t)(s + 1) * 64 <= K; };  // uniform
     auto fetch = [&](Step &f, int s) {
         const int64_t k0 = (int64_t)s * 64;
+        if (!whole(s)) {
+            auto load_last = [&](const char *at, const char *end) {
+                if constexpr (ROWS == Rows::kTiny)
+                    return load_bytes(at, end);
+                else
+                    return load_within(at, end);
+            };
+#pragma unroll
+            for (int i = 0; i < NL; i++) f.x[i] = load_last(xrow[i] + k0 * 2 + pc * 16, x_end);
+            f.im[0] = f.im[1] = v4f{1.0f, 1.0f, 1.0f, 1.0f};
+            if (p.inv_m) {
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) f.im[h][e] = p.inv_m[min(k0 + pc * 8 + 4 * h + e, K - 1)];
+            }
+            if constexpr (!BITS4) {
+#pragma unroll
+                for (int i = 0; i < NB; i++) f.w[i] = load_last(wrow[i] + k0 + lq * 16, w_end);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NL; i++)
             f.x[i] = ALIGNED ? __builtin_nontemporal_load(reinterpret_cast<const v4i *>(xrow[i] + k0 * 2 + pc * 16))
-                             : load_any(xrow[i], k0 * 2 + pc * 16, K * 2, p.x, x_end);
+                             : *reinterpret_cast<const v4i_unaligned *>(xrow[i] + k0 * 2 + pc * 16);
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             f.im[h] = v4f{1.0f, 1.0f, 1.0f, 1.0f};
-            if (p.inv_m) {
-                if constexpr (ALIGNED) {
-                    f.im[h] = *reinterpret_cast<const f32x4_any *>(p.inv_m + k0 + pc * 8 + 4 * h);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) f.im[h][e] = p.inv_m[min(k0 + pc * 8 + 4 * h + e, K - 1)];
-                }
-            }
+            if (p.inv_m) f.im[h] = *reinterpret_cast<const f32x4_any *>(p.inv_m + k0 + pc * 8 + 4 * h);
         }
 #pragma unroll
         for (int i = 0; i < NB; i++) {
@@ -171,12 +189,27 @@ __global__ __launch_bounds__(64 * W) void pts_linear_split(const LinearArgs p) {
                 f.w4[i] = *reinterpret_cast<const u32x2 *>(wrow[i] + k0 / 2 + lq * 8);
             } else {
                 f.w[i] = ALIGNED ? *reinterpret_cast<const v4i *>(wrow[i] + k0 + lq * 16)
-                                 : load_any(wrow[i], k0 + lq * 16, K, p.w, w_end);
+                                 : *reinterpret_cast<const v4i_unaligned *>(wrow[i] + k0 + lq * 16);
             }
         }
     };
-    auto compute = [&](const Step &f, int s) {
+    auto compute = [&](Step &f, int s) {
         const int64_t k0 = (int64_t)s * 64;
+        if (!whole(s)) {  // (codes beyond K meet weights of zero)
+            if (ROWS == Rows::kAny && K % 8 != 0) {
+#pragma unroll
+                for (int i = 0; i < NL; i++) f.x[i] = place_within(f.x[i], xrow[i] + k0 * 2 + pc * 16, x_end);
+            }
+            if constexpr (!BITS4) {
+                if (ROWS == Rows::kAny && K % 16 != 0) {
+#pragma unroll
+                    for (int i = 0; i < NB; i++) f.w[i] = place_within(f.w[i], wrow[i] + k0 + lq * 16, w_end);
+                }
+                const v4i mask = mask_within(k0 + lq * 16, K);
+#pragma unroll
+                for (int i = 0; i < NB; i++) f.w[i] &= mask;
+            }
+        }
         float im[8];
 #pragma unroll
         for (int e = 0; e < 8; e++) im[e] = f.im[e >> 2][e & 3];
