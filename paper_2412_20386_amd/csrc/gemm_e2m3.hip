@@ -52,7 +52,7 @@ struct E2m3Path {
 // ------------------------------------------------------------------------------------------
 template <int BR, int BO, int WR, int WO, int STAGES, bool DUMP>
 __global__ __launch_bounds__(64 * WR * WO, (tile_waves<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES>())) void linear_e2m3_tile(const TileArgs p) {
-    direct_tile<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES, DUMP, tile_is_tight<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES>()>(p);
+    direct_tile<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES, DUMP, tile_fragments<E2m3Path, BR, BO, WR, WO, kBlockBytes, STAGES>()>(p);
 }
 
 // Split reduction (see linear_mfma_splitk): wavefront w takes the 128-code blocks w, w + SK, ... with U blocks of operands

@@ -372,6 +372,8 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
     }
 }
 
+// How a direct tile holds its fragments: those of the next step too (kDoubled), the weight's only (kTight), one step's (kSingle).
+enum class Fragments { kDoubled, kTight, kSingle };
 // How linear_mfma_tile gets its operands: copied to LDS directly, to LDS through registers, as fragments (reductions of one slab).
 enum class Copy { kDirect, kRegisters, kOneSlab };
 
@@ -392,12 +394,13 @@ constexpr int tile_lds_bytes() {
 // Requirements (host-checked): 16-byte aligned bases and pitches, k_bytes a multiple of 64 (E2M3: of 96), L < 2^31, 256 pitches
 // below 2^31.
 // ------------------------------------------------------------------------------------------
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, bool TIGHT>
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, Fragments HELD>
 __device__ __forceinline__ void direct_tile(const TileArgs &p) {
     constexpr int NW = WR * WO, THREADS = 64 * NW;
     constexpr int WAVE_R = BR / WR, WAVE_O = BO / WO, FR = WAVE_R / 16, FO = WAVE_O / 16;
-    constexpr bool E2M3 = Path::kE2m3;
+    constexpr bool E2M3 = Path::kE2m3, TIGHT = HELD == Fragments::kTight;
     constexpr int KS = E2M3 ? 1 : SLAB / 64;  // MFMA steps per slab
+    static_assert(HELD != Fragments::kSingle || KS == 1, "one step per slab");
     constexpr int CHUNKS = SLAB / 16;
     constexpr int STAGE_BYTES = (BR + BO) * SLAB, X_COPIES = BR * SLAB / 1024, ALL_COPIES = STAGE_BYTES / 1024;
     constexpr int COPIES = (ALL_COPIES + NW - 1) / NW;     // 1 KiB each; those beyond the last repeat it
@@ -479,12 +482,13 @@ __device__ __forceinline__ void direct_tile(const TileArgs &p) {
     };
     // Both operands' fragments are doubled; in a TIGHT kernel the activations' are not: each is fetched again as soon as its MFMAs
     // have been issued, and the other wavefronts of the SIMD hide what is left of that latency.
-    Frag fw[2][FO], fx[TIGHT ? 1 : 2][FR];
+    constexpr int BUFFERS = HELD == Fragments::kSingle ? 1 : 2;
+    Frag fw[BUFFERS][FO], fx[HELD == Fragments::kDoubled ? 2 : 1][FR];
     auto load_fw = [&](int buf, const char *st, int ks) {
 #pragma unroll
         for (int i = 0; i < FO; i++) fw[buf][i] = fragment(st + (BR + wave_o + i * 16) * SLAB, ks);
     };
-    auto load_fx = [&](int buf, int j, const char *st, int ks) { fx[TIGHT ? 0 : buf][j] = fragment(st + (wave_r + j * 16) * SLAB, ks); };
+    auto load_fx = [&](int buf, int j, const char *st, int ks) { fx[HELD == Fragments::kDoubled ? buf : 0][j] = fragment(st + (wave_r + j * 16) * SLAB, ks); };
     // The products of buffer `buf`, `fetch(j)` behind those of row block j
     auto products = [&](int buf, auto fetch) {
         Frag we[FO], wo[FO];
@@ -497,7 +501,7 @@ __device__ __forceinline__ void direct_tile(const TileArgs &p) {
         }
 #pragma unroll
         for (int j = 0; j < FR; j++) {
-            const Frag x = fx[TIGHT ? 0 : buf][j];
+            const Frag x = fx[HELD == Fragments::kDoubled ? buf : 0][j];
             if constexpr (Path::kPacked4) {
                 const v4i xe = Path::even_codes(x), xo = Path::odd_codes(x);
 #pragma unroll
@@ -517,57 +521,73 @@ __device__ __forceinline__ void direct_tile(const TileArgs &p) {
         else
             wait_vmcnt_at_most<KEEP>();
     };
-    wait_slab(0);
-    __builtin_amdgcn_s_barrier();
-    if (STAGES - 1 < n_slabs) issue(STAGES - 1, STAGES - 1);
-    load_fw(0, ring, 0);
-#pragma unroll
-    for (int j = 0; j < FR; j++) load_fx(0, j, ring, 0);
-
-    // One MFMA step on the fragments of buffer `cur`; the next step's, step `nks` of its slab, are fetched meanwhile.  Where a slab
-    // ends (over) every wavefront holds its last fragments, so one barrier makes the next slab visible and frees this one's stage.
-    // What the very last step fetches nobody uses.
     int stage = 0;
-    auto step = [&](int cur, int nks, bool over, int slab) {
-        wait_lgkmcnt_0();  // (known to the compiler, so that no MFMA waits for the fetches that follow)
-        if (over) {
-            if (slab + 1 < n_slabs) {
-                wait_slab(slab + 1);
-                __builtin_amdgcn_s_barrier();
-                if (slab + STAGES < n_slabs) issue(slab + STAGES, stage);
-            }
+    if constexpr (HELD == Fragments::kSingle) {  // the other workgroups of the CU hide the latency of the fragments
+#pragma unroll 1
+        for (int it = 0; it < n_slabs; it++) {
+            wait_slab(it);
+            wait_lgkmcnt_0();
+            __builtin_amdgcn_s_barrier();  // everyone's copies of slab `it` are visible; slab it - 1 is in registers and used
+            if (it + STAGES - 1 < n_slabs) issue(it + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+            const char *const now = ring + stage * STAGE_BYTES;
+            load_fw(0, now, 0);
+#pragma unroll
+            for (int j = 0; j < FR; j++) load_fx(0, j, now, 0);
+            products(0, [](int) {});
             if (++stage == STAGES) stage = 0;
         }
-        const char *const next = ring + stage * STAGE_BYTES;
-        load_fw(cur ^ 1, next, nks);
-        if constexpr (TIGHT) {
-            products(cur, [&](int j) {
-                load_fx(0, j, next, nks);
-                __builtin_amdgcn_sched_barrier(0);  // keep a fetch behind the MFMAs that free its registers
-            });
-        } else {
-#pragma unroll
-            for (int j = 0; j < FR; j++) load_fx(cur ^ 1, j, next, nks);
-            __builtin_amdgcn_sched_barrier(0);  // fetch first, then multiply
-            products(cur, [](int) {});
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    if constexpr (KS == 2) {
-        const int whole = (int)(k_bytes / SLAB);
-#pragma unroll 1
-        for (int it = 0; it < whole; it++) {
-            step(0, 1, false, it);
-            step(1, 0, true, it);
-        }
-        if (whole < n_slabs) step(0, 0, false, whole);
     } else {
+        wait_slab(0);
+        __builtin_amdgcn_s_barrier();
+        if (STAGES - 1 < n_slabs) issue(STAGES - 1, STAGES - 1);
+        load_fw(0, ring, 0);
+#pragma unroll
+        for (int j = 0; j < FR; j++) load_fx(0, j, ring, 0);
+
+        // One MFMA step on the fragments of buffer `cur`; the next step's, step `nks` of its slab, are fetched meanwhile.  Where a slab
+        // ends (over) every wavefront holds its last fragments, so one barrier makes the next slab visible and frees this one's stage.
+        // What the very last step fetches nobody uses.
+        auto step = [&](int cur, int nks, bool over, int slab) {
+            wait_lgkmcnt_0();  // (known to the compiler, so that no MFMA waits for the fetches that follow)
+            if (over) {
+                if (slab + 1 < n_slabs) {
+                    wait_slab(slab + 1);
+                    __builtin_amdgcn_s_barrier();
+                    if (slab + STAGES < n_slabs) issue(slab + STAGES, stage);
+                }
+                if (++stage == STAGES) stage = 0;
+            }
+            const char *const next = ring + stage * STAGE_BYTES;
+            load_fw(cur ^ 1, next, nks);
+            if constexpr (TIGHT) {
+                products(cur, [&](int j) {
+                    load_fx(0, j, next, nks);
+                    __builtin_amdgcn_sched_barrier(0);  // keep a fetch behind the MFMAs that free its registers
+                });
+            } else {
+#pragma unroll
+                for (int j = 0; j < FR; j++) load_fx(cur ^ 1, j, next, nks);
+                __builtin_amdgcn_sched_barrier(0);  // fetch first, then multiply
+                products(cur, [](int) {});
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if constexpr (KS == 2) {
+            const int whole = (int)(k_bytes / SLAB);
 #pragma unroll 1
-        for (int it = 0; it + 2 <= n_slabs; it += 2) {
-            step(0, 0, true, it);
-            step(1, 0, true, it + 1);
+            for (int it = 0; it < whole; it++) {
+                step(0, 1, false, it);
+                step(1, 0, true, it);
+            }
+            if (whole < n_slabs) step(0, 0, false, whole);
+        } else {
+#pragma unroll 1
+            for (int it = 0; it + 2 <= n_slabs; it += 2) {
+                step(0, 0, true, it);
+                step(1, 0, true, it + 1);
+            }
+            if (n_slabs & 1) step(0, 0, true, n_slabs - 1);
         }
-        if (n_slabs & 1) step(0, 0, true, n_slabs - 1);
     }
     vec.park(p, tid);
     __syncthreads();  // the vectors are visible, the ring becomes the wavefronts' transposition patches
@@ -772,31 +792,45 @@ __device__ __forceinline__ void one_slab_tile(const TileArgs &p) {
     store_tile<Path, BR, BO, WR, WO, 2 * (BR + BO) * SLAB, DUMP>(acc, p, lds_dyn, vec, r0, o0, rows_valid, cols_valid);
 }
 
-// Registers of a direct tile: results, the fragments of two steps (TIGHT: those of the activations once), some for everything else.
+// Registers of a direct tile: results, the fragments that it holds, some for everything else.
 template <class Path, int FR, int FO>
-constexpr int tile_registers(bool tight) {
+constexpr int tile_registers(Fragments held) {
     constexpr int frag = sizeof(typename Path::Frag) / 4;
-    return FR * FO * 4 + (2 * FO + (tight ? FR : 2 * FR)) * frag + (Path::kPacked4 ? (FO + 2) * frag : 0) + (Path::kE2m3 ? 24 : 16);
+    const int frags = held == Fragments::kDoubled ? 2 * FO + 2 * FR : held == Fragments::kTight ? 2 * FO + FR : FO + 1;
+    return FR * FO * 4 + frags * frag + (Path::kPacked4 ? (FO + 2) * frag : 0) + (Path::kE2m3 ? 24 : 16);
 }
 // Wavefronts per SIMD that a direct tile is compiled for: those of as many workgroups as the LDS of a CU holds, as far as the registers
 // go round.  (A bound also keeps results in plain registers; moving them from accumulation registers costs an instruction each.)
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES>
-constexpr int tile_waves() {
-    constexpr int by_lds = 160 * 1024 / tile_lds_bytes<BR, BO, SLAB, STAGES>() * WR * WO / 4;
-    constexpr int by_registers = 512 / tile_registers<Path, BR / WR / 16, BO / WO / 16>(true);
-    constexpr int waves = by_lds < by_registers ? by_lds : by_registers;
+constexpr int tile_waves_by_lds() {
+    constexpr int waves = 160 * 1024 / tile_lds_bytes<BR, BO, SLAB, STAGES>() * WR * WO / 4;
     return waves < 1 ? 1 : (waves > 8 ? 8 : waves);
 }
+// E2M3 fragments are twice as large: where holding those of two steps would cost a quarter of the CU's workgroups or more, whose epilogues
+// run under the others' products, one step's do (us, kTight / kSingle: 22663 x 1024 -> 1972 in 128 x 256 tiles 81.5 / 53.5, 42321 x 128
+// -> 861 29.7 / 23.6; over 500 shapes 128 x 256 0.86 of the time, 128 x 128 0.92, 64 x 128 0.96).  64 x 64 tiles, five workgroups for six,
+// keep two steps (reductions from 640 codes on 0.96 of the time).
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES>
-constexpr bool tile_is_tight() {
-    return tile_registers<Path, BR / WR / 16, BO / WO / 16>(false) > 512 / tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() / 8 * 8;
+constexpr Fragments tile_fragments() {
+    constexpr int by_lds = tile_waves_by_lds<Path, BR, BO, WR, WO, SLAB, STAGES>(), FR = BR / WR / 16, FO = BO / WO / 16;
+    constexpr int by_registers = 512 / tile_registers<Path, FR, FO>(Fragments::kTight), waves = by_lds < by_registers ? by_lds : by_registers;
+    if (Path::kE2m3 && waves * 4 <= by_lds * 3) return Fragments::kSingle;
+    return tile_registers<Path, FR, FO>(Fragments::kDoubled) > 512 / waves / 8 * 8 ? Fragments::kTight : Fragments::kDoubled;
+}
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES>
+constexpr int tile_waves() {
+    constexpr int by_lds = tile_waves_by_lds<Path, BR, BO, WR, WO, SLAB, STAGES>();
+    constexpr Fragments held = tile_fragments<Path, BR, BO, WR, WO, SLAB, STAGES>();
+    constexpr int by_registers = 512 / tile_registers<Path, BR / WR / 16, BO / WO / 16>(held == Fragments::kSingle ? held : Fragments::kTight);
+    constexpr int waves = by_lds < by_registers ? by_lds : by_registers;
+    return waves < 1 ? 1 : waves;
 }
 
 template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, Copy COPY>
 __global__ __launch_bounds__(64 * WR * WO, (COPY == Copy::kDirect ? tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() : WR * WO == 8 && SLAB == 64 && !Path::kPacked4 ? 6 : 4)) void linear_mfma_tile(const TileArgs p) {
     static_assert(COPY == Copy::kDirect || STAGES == 2, "the register-staged form is double buffered");
     if constexpr (COPY == Copy::kDirect)
-        direct_tile<Path, BR, BO, WR, WO, SLAB, STAGES, DUMP, tile_is_tight<Path, BR, BO, WR, WO, SLAB, STAGES>()>(p);
+        direct_tile<Path, BR, BO, WR, WO, SLAB, STAGES, DUMP, tile_fragments<Path, BR, BO, WR, WO, SLAB, STAGES>()>(p);
     else if constexpr (COPY == Copy::kRegisters)
         staged_tile<Path, BR, BO, WR, WO, SLAB, DUMP>(p);
     else
