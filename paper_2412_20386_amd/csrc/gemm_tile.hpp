@@ -594,9 +594,9 @@ __device__ __forceinline__ void direct_tile(const TileArgs &p) {
     store_tile<Path, BR, BO, WR, WO, STAGES * STAGE_BYTES, DUMP>(acc, p, ring, vec, r0, o0, rows_valid, cols_valid);
 }
 
-// The same tile for any pitch, alignment and K: slabs pass through registers, bytes beyond K zeroed (two stages).  Small tiles, of which a
-// CU has few, keep two slabs in flight (3184 x 1000 -> 500 10.1 / 9.5 us); the larger ones one, which leaves room for more workgroups
-// (24104 x 830 -> 760 43 / 49).
+// The same tile for any pitch, alignment and K: slabs pass through registers, one in flight, bytes beyond K zeroed (two stages).  (Two in
+// flight cost a quarter to a half more registers, which packed operands in 64 x 64 tiles spilled: 6854 x 704 -> 512 9.8 us with one,
+// 11.7 with two; over 1500 shapes one is 1 % faster, 3 % with 128-byte slabs.)
 // Only the last slab reaches beyond K; the loads of the others carry no tests (16236 x 1584 -> 760 fp16 106.7 -> 62.8 us, 24104 x 830 -> 760
 // 45.7 -> 36.1).
 // Requirements (host-checked): L < 2^31, BR * ldx_bytes and BO * ldw_bytes below 2^31.
@@ -632,9 +632,8 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
     const char *gx = p.x + r0 * p.ldx_bytes, *gw = p.w + o0 * p.ldw_bytes;
     const int64_t k_bytes = p.k_bytes;
     const char *const x_end = p.x + ((p.M - 1) * p.ldx_bytes + k_bytes), *const w_end = p.w + ((p.N - 1) * p.ldw_bytes + k_bytes);
-    constexpr int DEPTH = BR * BO <= 64 * 64 ? 2 : 1;
-    v4i staged[DEPTH][COPIES];
-    auto fetch = [&](int buf, int slab) {
+    v4i staged[COPIES];
+    auto fetch = [&](int slab) {
         const bool inside = (int64_t)(slab + 1) * SLAB <= k_bytes;  // uniform
 #pragma unroll
         for (int i = 0; i < COPIES; i++) {
@@ -643,26 +642,26 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             const char *src = is_x ? gx : gw;
             const int chunk = chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS);  // (BR is a multiple of 16: a weight row swizzles like row - BR)
             if (inside) {
-                staged[buf % DEPTH][i] = *reinterpret_cast<const v4i_unaligned *>(src + (int64_t)slab * SLAB + (off[i] + chunk * 16));
+                staged[i] = *reinterpret_cast<const v4i_unaligned *>(src + (int64_t)slab * SLAB + (off[i] + chunk * 16));
             } else {
-                staged[buf % DEPTH][i] = load_within(src + (int64_t)slab * SLAB + (off[i] + chunk * 16), is_x ? x_end : w_end);
+                staged[i] = load_within(src + (int64_t)slab * SLAB + (off[i] + chunk * 16), is_x ? x_end : w_end);
             }
         }
     };
-    auto commit = [&](int buf, int stage, int slab) {
+    auto commit = [&](int slab, int stage) {
         if ((int64_t)(slab + 1) * SLAB > k_bytes) {  // uniform
 #pragma unroll
             for (int i = 0; i < COPIES; i++) {
                 const int c = wave + NW * i;
                 const bool is_x = c * ROWS_PER_COPY < BR;
                 const int64_t kb = (int64_t)slab * SLAB + chunk_of(c * ROWS_PER_COPY + lane / CHUNKS, lane % CHUNKS) * 16;
-                if (k_bytes % 16 != 0) staged[buf % DEPTH][i] = place_within(staged[buf % DEPTH][i], (is_x ? gx : gw) + off[i] + kb, is_x ? x_end : w_end);
-                staged[buf % DEPTH][i] &= mask_within(kb, k_bytes);
+                if (k_bytes % 16 != 0) staged[i] = place_within(staged[i], (is_x ? gx : gw) + off[i] + kb, is_x ? x_end : w_end);
+                staged[i] &= mask_within(kb, k_bytes);
             }
         }
 #pragma unroll
         for (int i = 0; i < COPIES; i++)
-            *reinterpret_cast<v4i *>(ring + stage * STAGE_BYTES + (wave + NW * i) * 1024 + lane * 16) = staged[buf % DEPTH][i];
+            *reinterpret_cast<v4i *>(ring + stage * STAGE_BYTES + (wave + NW * i) * 1024 + lane * 16) = staged[i];
     };
 
     Acc acc[FO][FR];
@@ -674,15 +673,16 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             for (int v = 0; v < 4; v++) acc[i][j][v] = 0;
 
     const int n_slabs = (int)((k_bytes + SLAB - 1) / SLAB);
-    fetch(0, 0);
+    fetch(0);
     TileVectors<Path, BR, BO, THREADS> vec(lds_dyn + 2 * STAGE_BYTES);
     vec.fetch(p, tid, r0, o0, rows_valid, cols_valid);
-    if (DEPTH == 2 && n_slabs > 1) fetch(1, 1);
-    commit(0, 0, 0);
-    auto slab = [&](int it, int buf) {  // the slab lies in stage buf; the next one is on its way or (DEPTH 1) requested now
+    commit(0, 0);
+#pragma unroll 1
+    for (int it = 0; it < n_slabs; it++) {
+        const int stage = it & 1;
         __syncthreads();
-        if (it + DEPTH < n_slabs) fetch(DEPTH == 2 ? buf : 0, it + DEPTH);
-        const char *sx = ring + buf * STAGE_BYTES + wave_r * SLAB, *sw = ring + buf * STAGE_BYTES + (BR + wave_o) * SLAB;
+        if (it + 1 < n_slabs) fetch(it + 1);
+        const char *sx = ring + stage * STAGE_BYTES + wave_r * SLAB, *sw = ring + stage * STAGE_BYTES + (BR + wave_o) * SLAB;
 #pragma unroll
         for (int ks = 0; ks < SLAB / 64; ks++) {
             if (ks > 0 && (int64_t)it * SLAB + ks * 64 >= k_bytes) break;
@@ -699,17 +699,7 @@ __device__ __forceinline__ void staged_tile(const TileArgs &p) {
             }
             mfma_step<Path, FO, FR>(acc, fw, fx);
         }
-        if (it + 1 < n_slabs) commit(buf ^ 1, buf ^ 1, it + 1);
-    };
-    if constexpr (DEPTH == 2) {
-#pragma unroll 1
-        for (int it = 0; it < n_slabs; it += 2) {
-            slab(it, 0);
-            if (it + 1 < n_slabs) slab(it + 1, 1);
-        }
-    } else {
-#pragma unroll 1
-        for (int it = 0; it < n_slabs; it++) slab(it, it & 1);
+        if (it + 1 < n_slabs) commit(it + 1, stage ^ 1);
     }
     vec.park(p, tid);
     __syncthreads();  // the vectors are visible, the ring becomes the wavefronts' transposition patches

@@ -73,3 +73,10 @@ def test_e2m3_tiles_share_a_compute_unit(kernels, tile, workgroups):
     assert len(found) == 2  # without and with the accumulators
     for name, k in found.items():
         assert waves_per_simd(k) * 4 // (wave_rows * wave_cols) >= workgroups, name
+
+
+def test_tiles_of_any_alignment_spill_nothing(kernels):
+    found = {n: k for n, k in kernels.items() if "linear_mfma_tile<" in n and "Copy)0>" not in n}
+    assert len(found) >= 40
+    for name, k in found.items():
+        assert k[".private_segment_fixed_size"] == 0, name
