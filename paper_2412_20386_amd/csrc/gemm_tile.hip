@@ -45,8 +45,11 @@ int launch_splitk(LinearArgs a, hipStream_t stream) {
 // another's MFMAs; and tiles that take a CU each, where they fill their rounds of 256.  The lines were read off sweeps over 170 random and
 // model shapes (M 49 .. 50 240, K 64 .. 2048, N 16 .. 3072, int8 and fp16).  Around the lines (us, int8; tiles in brackets):
 //   256 x 256, one round:                    9456 x 384 -> 1536 [222] 11.6 / 13.0 (64 x 128); 18912 x 1536 -> 768 [222] 25.6 / 29.9; 18912 x 192 -> 768 [222] 9.6 / 10.6
-//   256 x 192, rounds filled to 70 %:        25216 x 768 -> 384 [198] 12.7 / 14.8 (64 x 128); 6304 x 384 -> 1536 [200] 9.4 / 10.1; 12608 x 1536 -> 768 [200] 19.9 / 22.8;
-//                                            50240 x 768 -> 384 [394] 25.3 / 26.2 (128 x 128), but short K 12608 x 192 -> 768 [200] 7.9 / 7.2, half-filled 18912 x 768 -> 384 [148] 12.0 / 11.7
+//   256 x 192, a round filled to 70 % or two to 75 %: 25216 x 768 -> 384 [198] 12.7 / 14.8 (64 x 128); 6304 x 384 -> 1536 [200] 9.4 / 10.1; 12608 x 1536 -> 768 [200] 19.9 / 22.8;
+//                                            50240 x 768 -> 384 [394] 25.3 / 26.2 (128 x 128), but short K 12608 x 192 -> 768 [200] 7.9 / 7.2, half-filled 18912 x 768 -> 384 [148] 12.0 / 11.7;
+//                                            over 900 shapes the other tiles take 1.08 of the time at 70 .. 75 % of one round and 1.14 .. 1.18 beyond, of two rounds
+//                                            0.96 below 75 % and 1.03 .. 1.12 above, and of three and more 0.88 .. 0.99, most 128 x 256 (offset 49220 x 768 ->
+//                                            3072, odd rows of y 242 / 201, 23274 x 832 -> 1024 42.4 / 34.5)
 //   128 x 256 against 128 x 128, 800 tiles:  25216 x 384 -> 1536 [1182] 28.1 / 29.8; 13057 x 192 -> 2048 [824] 16.8 / 16.2, but 12608 x 192 -> 768 [297] 7.7 / 7.2
 //   128 x 128 against 64 x 128, 384 tiles:   4728 x 384 -> 1536 [444] 7.4 / 7.6;         9456 x 384 -> 192 [148] 5.3 / 5.1, 6304 x 768 -> 384 [150] 6.6 / 6.5
 //   64 x 128 against 64 x 64, 384 tiles:     3152 x 384 -> 1536 [600] 6.1 / 7.2;         6304 x 768 -> 384 [297] 6.5 / 6.3
@@ -72,7 +75,8 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         };
         if constexpr (!Path::kPacked4) {  // (packed operands are expanded into more registers than these leave)
             if (tiles(a, 256, 256) <= 256 && fills(256, 256, 80) && padded(256, 256) <= most) return launch<Path, 256, 256, 2, 4, 128, 2, Copy::kDirect>(a, stream);
-            if (a.k_bytes >= 384 && fills(256, 192, 70) && padded(256, 192) <= most) return launch<Path, 256, 192, 4, 3, 128, 2, Copy::kDirect>(a, stream);
+            const int rounds = tiles(a, 256, 192) <= 256 ? 1 : tiles(a, 256, 192) <= 512 ? 2 : 3;
+            if (a.k_bytes >= 384 && rounds < 3 && fills(256, 192, rounds == 1 ? 70 : 75) && padded(256, 192) <= most) return launch<Path, 256, 192, 4, 3, 128, 2, Copy::kDirect>(a, stream);
         }
         if (tiles(a, 128, 256) >= 800 && padded(128, 256) <= most) return launch<Path, 128, 256, 2, 4, 64, 3, Copy::kDirect>(a, stream);
         if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most)

@@ -174,6 +174,16 @@ def test_int8_tiles_of_whole_rounds(M, K, N, parts):
     test_int8_tiles(M, K, N, parts)
 
 
+@pytest.mark.parametrize("M,K,N,parts", [
+    (49153, 448, 384, (TILE, "256, 192", DIRECT)), (48897, 448, 384, (TILE, "256, 192", DIRECT)), (48896, 448, 384, (TILE, "128, 128", DIRECT)),  # 386, 384 and 382 of 512
+    (65536, 448, 384, (TILE, "256, 192", DIRECT)), (65537, 448, 384, (TILE, "128, 128", DIRECT)),  # 512 and 514 of 768
+    (23274, 832, 1024, (TILE, "128, 128", DIRECT)), (24577, 448, 1500, (TILE, "128, 256", DIRECT)),  # 546 and 776
+])
+def test_int8_tiles_of_a_few_rounds(M, K, N, parts):
+    """256 x 192 tiles: one round filled to 70 %, two to 75 %, never three."""
+    test_int8_tiles(M, K, N, parts)
+
+
 @pytest.mark.parametrize("M,K,N", [(12345, 31, 2179), (12345, 33, 2179), (5121, 520, 900), (6401, 32, 1028), (6401, 33, 1029), (401, 66, 899), (2049, 200, 643)])
 def test_f16_tiles_any_alignment(M, K, N):
     """fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|, and one fp16 rounding.  Infinities beyond K (the
