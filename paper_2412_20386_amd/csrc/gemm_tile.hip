@@ -56,8 +56,10 @@ int launch_splitk(LinearArgs a, hipStream_t stream) {
 //   64 x 64 against 32 x 64, 200 tiles:      3152 x 768 -> 384 [300] 4.8 / 5.0;          197 x 768 -> 3072 [192] 4.6 / 4.3
 //   split reduction, 256 blocks of 16 x 16:  788 x 1536 -> 80 [250] 4.3 / 5.1 (32 x 64); 1576 x 1536 -> 80 [495] 5.6 / 5.1
 // 128 x 128 tiles: three 64-byte stages on four wavefronts let three workgroups share a CU and waste no half slab (25216 x 192 -> 1536 21.6 / 25.3);
-// over a long reduction twice the barriers cost more (12608 x 1536 -> 768 25.6 / 23.3).  64 x 64 tiles: three stages, but two from 768 tiles on, which
-// leave room for a fourth workgroup per CU (6304 x 1536 -> 80 [198] 6.4 / 8.2, 12608 x 384 -> 192 [591] 4.6 / 4.8; 37824 x 768 -> 56 [591] 8.9 / 8.2).
+// over a long reduction twice the barriers cost more (12608 x 1536 -> 768 25.6 / 23.3).  64 x 64 tiles: three stages hold more of a long reduction in flight where few
+// tiles are resident (6304 x 1536 -> 80 [198] 6.4 / 8.2 with two), two leave room for a fourth workgroup per CU: from 513 tiles, and from 769 with less
+// than 256 bytes of K, which take one or two slabs anyway (over 900 shapes of 513 .. 768 tiles two take 1.02 of the time at 64 bytes, 0.99 up to 383,
+// 0.95 up to 1023, 0.93 beyond; 35992 x 1920 -> 64 [563] 16.6 / 15.1).
 // A tile that pads the matrix by a third more than the best one is passed over.
 template <class Path>
 int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
@@ -82,7 +84,7 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         if (tiles(a, 128, 128) >= 384 && padded(128, 128) <= most)
             return a.k_bytes <= 768 ? launch<Path, 128, 128, 2, 2, 64, 3, Copy::kDirect>(a, stream) : launch<Path, 128, 128, 2, 4, 128, 2, Copy::kDirect>(a, stream);
         if (tiles(a, 64, 128) >= 384 && padded(64, 128) <= most) return launch<Path, 64, 128, 2, 2, 128, 2, Copy::kDirect>(a, stream);
-        if (tiles(a, 64, 64) > 768) return launch<Path, 64, 64, 2, 2, 128, 2, Copy::kDirect>(a, stream);
+        if (tiles(a, 64, 64) > (a.k_bytes < 256 ? 768 : 512)) return launch<Path, 64, 64, 2, 2, 128, 2, Copy::kDirect>(a, stream);
         if (tiles(a, 64, 64) >= 200) return launch<Path, 64, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
         return launch<Path, 32, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
     }

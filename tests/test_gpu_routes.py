@@ -184,6 +184,15 @@ def test_int8_tiles_of_a_few_rounds(M, K, N, parts):
     test_int8_tiles(M, K, N, parts)
 
 
+@pytest.mark.parametrize("M,K,N,parts", [
+    (32769, 256, 56, (TILE, "64, 64", "128, 2,", DIRECT)), (32768, 256, 56, (TILE, "64, 64", "128, 3,", DIRECT)),  # 513 and 512 tiles
+    (49152, 192, 56, (TILE, "64, 64", "128, 3,", DIRECT)), (49153, 192, 56, (TILE, "64, 64", "128, 2,", DIRECT)),  # 768 and 769
+])
+def test_stages_of_the_64_x_64_tiles(M, K, N, parts):
+    """Two ring stages instead of three from 513 tiles on, from 769 where K is shorter than 256 bytes."""
+    test_int8_tiles(M, K, N, parts)
+
+
 @pytest.mark.parametrize("M,K,N", [(12345, 31, 2179), (12345, 33, 2179), (5121, 520, 900), (6401, 32, 1028), (6401, 33, 1029), (401, 66, 899), (2049, 200, 643)])
 def test_f16_tiles_any_alignment(M, K, N):
     """fp32 accumulation in any order, |error| <= (K + 2) 2^-24 sum |terms|, and one fp16 rounding.  Infinities beyond K (the
