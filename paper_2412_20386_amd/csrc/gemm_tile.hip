@@ -7,15 +7,15 @@ using namespace ptq4vm::mfma;
 
 int64_t tiles(const LinearArgs &a, int br, int bo) { return ptq4vm::ceil_div(a.M, br) * ptq4vm::ceil_div(a.N, bo); }
 
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY>
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, Copy COPY, bool VIA_LDS = false>
 int launch(const LinearArgs &a, hipStream_t stream) {
     TileArgs t;
     dim3 grid;
     if (!tile_args<BR, BO>(a, t, grid)) return PTQ4VM_ERR_SHAPE;
     constexpr int lds_bytes = tile_lds_bytes<BR, BO, SLAB, STAGES>();
-    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, false, COPY>;
+    auto kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, false, VIA_LDS, COPY>;
     if constexpr (Path::kElemBytes == 1) {
-        if (a.acc_out) kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, true, COPY>;
+        if (a.acc_out) kernel = linear_mfma_tile<Path, BR, BO, WR, WO, SLAB, STAGES, true, VIA_LDS, COPY>;
     }
     if constexpr (lds_bytes > 64 * 1024) {
         if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), lds_bytes, "hipFuncSetAttribute(linear_mfma_tile)")) return rc;
@@ -24,10 +24,15 @@ int launch(const LinearArgs &a, hipStream_t stream) {
     return ptq4vm::check_launch("linear_mfma_tile");
 }
 
-// Slabs through registers (any pitch, alignment and K).
+// Slabs through registers (any pitch, alignment and K).  A reduction of one slab: as fragments, which every wavefront loads for itself, where rows
+// start at multiples of 4 bytes (over 900 shapes the way through LDS takes 1.09 to 1.15 of the time).  The loads of other rows take the
+// memory path longer and are better made once for the workgroup (64 x 128 and 128 x 128 tiles 0.66 .. 0.93 of the time, 12748 x 41 -> 2056 25.5 /
+// 17.1 us; 64 x 64 0.96 .. 1.01; 32 x 64 0.64 .. 0.95 above 64 bytes), but in 32 x 64 tiles up to 64 bytes latency is all (1.11 .. 1.13).
 template <class Path, int BR, int BO, int WR, int WO, int SLAB>
 int launch_staged(const LinearArgs &a, hipStream_t stream) {
-    return a.k_bytes <= SLAB ? launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kOneSlab>(a, stream) : launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kRegisters>(a, stream);
+    if (a.k_bytes > SLAB) return launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kRegisters>(a, stream);
+    const bool fragments = (a.ldx_bytes % 4 == 0 && a.ldw_bytes % 4 == 0) || (BR * BO <= 32 * 64 && a.k_bytes <= 64);
+    return fragments ? launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kOneSlab>(a, stream) : launch<Path, BR, BO, WR, WO, SLAB, 2, Copy::kOneSlab, true>(a, stream);
 }
 
 template <class Path, int FR, int FO, int SK, int U, Rows ROWS>

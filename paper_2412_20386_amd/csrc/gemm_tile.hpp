@@ -374,7 +374,8 @@ __device__ __forceinline__ void store_tile(const typename Path::Acc16 (&acc)[FO]
 
 // How a direct tile holds its fragments: those of the next step too (kDoubled), the weight's only (kTight), one step's (kSingle).
 enum class Fragments { kDoubled, kTight, kSingle };
-// How linear_mfma_tile gets its operands: copied to LDS directly, to LDS through registers, as fragments (reductions of one slab).
+// How linear_mfma_tile gets its operands: copied to LDS directly, to LDS through registers, or (reductions of one slab) as fragments or, VIA_LDS,
+// through registers too.
 enum class Copy { kDirect, kRegisters, kOneSlab };
 
 template <int BR, int BO, int SLAB, int STAGES>
@@ -816,12 +817,12 @@ constexpr int tile_waves() {
     return waves < 1 ? 1 : waves;
 }
 
-template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, Copy COPY>
+template <class Path, int BR, int BO, int WR, int WO, int SLAB, int STAGES, bool DUMP, bool VIA_LDS, Copy COPY>
 __global__ __launch_bounds__(64 * WR * WO, (COPY == Copy::kDirect ? tile_waves<Path, BR, BO, WR, WO, SLAB, STAGES>() : WR * WO == 8 && SLAB == 64 && !Path::kPacked4 ? 6 : 4)) void linear_mfma_tile(const TileArgs p) {
     static_assert(COPY == Copy::kDirect || STAGES == 2, "the register-staged form is double buffered");
     if constexpr (COPY == Copy::kDirect)
         direct_tile<Path, BR, BO, WR, WO, SLAB, STAGES, DUMP, tile_fragments<Path, BR, BO, WR, WO, SLAB, STAGES>()>(p);
-    else if constexpr (COPY == Copy::kRegisters)
+    else if constexpr (COPY == Copy::kRegisters || VIA_LDS)
         staged_tile<Path, BR, BO, WR, WO, SLAB, DUMP>(p);
     else
         one_slab_tile<Path, BR, BO, WR, WO, SLAB, DUMP>(p);

@@ -184,6 +184,29 @@ def test_int8_tiles_of_a_few_rounds(M, K, N, parts):
     test_int8_tiles(M, K, N, parts)
 
 
+FRAGMENTS, VIA_LDS = "false, (ptq4vm::mfma::Copy)2>", "true, (ptq4vm::mfma::Copy)2>"
+
+
+@pytest.mark.parametrize("M,K,N,more,parts", [
+    (12345, 60, 2179, 0, (TILE, "128, 128", FRAGMENTS)), (12345, 61, 2179, 0, (TILE, "128, 128", VIA_LDS)), (12345, 64, 2179, 2, (TILE, "128, 128", VIA_LDS)),
+    (6401, 63, 1029, 1, (TILE, "64, 128", FRAGMENTS)), (6401, 64, 1029, 1, (TILE, "64, 128", VIA_LDS)),
+    (1279, 12, 645, 0, (TILE, "64, 64", FRAGMENTS)), (1279, 12, 645, 3, (TILE, "64, 64", VIA_LDS)),
+    (401, 64, 899, 1, (TILE, "32, 64", FRAGMENTS)), (401, 65, 899, 0, (TILE, "32, 64", VIA_LDS)), (401, 128, 899, 4, (TILE, "32, 64", FRAGMENTS)),
+])
+def test_one_slab_by_the_rows(M, K, N, more, parts):
+    """Rows at multiples of 4 bytes (and the smallest tiles up to 64 bytes) as fragments, others through LDS; the operands' rows are part
+    of wider ones."""
+    print(f"one slab M={M} K={K} N={N} more={more}", flush=True)
+    p = Problem(M, K, N)
+    wide = lambda t: torch.nn.functional.pad(t, (0, more), value=127)[:, :K]
+    x, w = wide(p.x), wide(p.w)
+    run = lambda **kw: ptq.w8a8_linear(x, w, p.s_tok, p.s_w, p.bias, p.B, p.L, **kw)
+    check_kernel(run, *parts)
+    y = run(acc_out=p.acc)
+    assert close(y, p.acc64, p.scale, p.bias) and torch.equal(p.acc.double(), p.acc64)
+    assert torch.equal(run().view(torch.int16), y.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,K,N,parts", [
     (32769, 256, 56, (TILE, "64, 64", "128, 2,", DIRECT)), (32768, 256, 56, (TILE, "64, 64", "128, 3,", DIRECT)),  # 513 and 512 tiles
     (49152, 192, 56, (TILE, "64, 64", "128, 3,", DIRECT)), (49153, 192, 56, (TILE, "64, 64", "128, 2,", DIRECT)),  # 768 and 769
