@@ -15,8 +15,7 @@
 // per-token step s_tok[r mod L] is one scalar per lane.
 //
 // Kernels: linear_mfma_persistent here (many 256 x 256 tiles), linear_mfma_smallk here (fp16, reductions of at most 128
-// bytes), the row-streaming kernel of pts_linear_fused.hip (very short reductions over many rows), the
-// weights-in-registers kernel of gemm_wreg.hip (short reductions, whole rounds of its units), and the tile kernels of
+// bytes), the row-streaming kernel of pts_linear_fused.hip (very short reductions over many rows), and the tile kernels of
 // gemm_tile.hip for everything else.
 #include "gemm_tile.hpp"
 
@@ -591,11 +590,6 @@ int dispatch(LinearArgs a, hipStream_t stream) {
         // kernels copy directly: 25216 x 64 -> 768 20.6 / 12.6.)
         if (a.k_bytes <= 128 && la >= 4 && !(la == 16 && a.k_bytes % 64 == 0))
             return la == 16 ? launch_smallk_ksteps<16>(a, stream) : launch_smallk_ksteps<4>(a, stream);
-    }
-    if constexpr (Path::kElemBytes == 1 && !Path::kOffset && !Path::kPacked4) {
-        // short reduction, whole rounds of units: weight rows held in registers (both sides measured there)
-        const int rc = launch_wreg(a, stream);
-        if (rc <= 0) return rc;
     }
     // 256 x 256 tiles on one 8-wavefront workgroup per CU, unless they pad the channels by more than a quarter
     // (50240 x 768 -> 384: 29.4 us against 26.1 us on 128 x 128 tiles).

@@ -312,58 +312,6 @@ inline bool set_grid(LinearArgs &a, dim3 &grid) {
 }
 
 
-// LDS accesses of the epilogue are written as inline asm: the compiler does not see them, so it
-// cannot tie them to the outstanding global -> LDS copies (for which it would insert a full
-// vmcnt(0) drain).  Every read block ends with its own s_waitcnt inside the same asm statement,
-// so the outputs are valid as soon as the compiler may touch them.  Outputs are float vectors:
-// this compiler reads every element of an integer-vector asm output from its first register.
-__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)p; }
-
-// four 16-byte reads at base + STEP n
-template <int STEP>
-__device__ __forceinline__ void lds_read_4x_b128(uint32_t base, v4f (&v)[4]) {
-    asm volatile(
-        "ds_read_b128 %0, %4 offset:%5\n ds_read_b128 %1, %4 offset:%6\n ds_read_b128 %2, %4 offset:%7\n"
-        "ds_read_b128 %3, %4 offset:%8\n s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-        : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP)
-        : "memory");
-}
-// eight 4-byte reads at base + STEP n
-template <int STEP>
-__device__ __forceinline__ void lds_read_8x_b32(uint32_t base, float (&v)[8]) {
-    asm volatile(
-        "ds_read_b32 %0, %8 offset:%9\n ds_read_b32 %1, %8 offset:%10\n ds_read_b32 %2, %8 offset:%11\n"
-        "ds_read_b32 %3, %8 offset:%12\n ds_read_b32 %4, %8 offset:%13\n ds_read_b32 %5, %8 offset:%14\n"
-        "ds_read_b32 %6, %8 offset:%15\n ds_read_b32 %7, %8 offset:%16\n s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP), "n"(6 * STEP),
-          "n"(7 * STEP)
-        : "memory");
-}
-// four 4-byte reads at base + STEP n
-template <int STEP>
-__device__ __forceinline__ void lds_read_4x_b32(uint32_t base, float (&v)[4]) {
-    asm volatile(
-        "ds_read_b32 %0, %4 offset:%5\n ds_read_b32 %1, %4 offset:%6\n ds_read_b32 %2, %4 offset:%7\n"
-        "ds_read_b32 %3, %4 offset:%8\n s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-        : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP)
-        : "memory");
-}
-// four 16-byte reads at arbitrary addresses
-__device__ __forceinline__ void lds_read_4_b128(const uint32_t (&addr)[4], v4f (&v)[4]) {
-    asm volatile(
-        "ds_read_b128 %0, %4\n ds_read_b128 %1, %5\n ds_read_b128 %2, %6\n ds_read_b128 %3, %7\n"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-        : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3])
-        : "memory");
-}
-__device__ __forceinline__ void lds_write_b64(uint32_t addr, u32x2 v) {
-    asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory");
-}
-
 template <int KEEP>
 __device__ __forceinline__ void wait_vmcnt_at_most() {
     // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14
@@ -371,56 +319,10 @@ __device__ __forceinline__ void wait_vmcnt_at_most() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (KEEP & 15) | ((KEEP >> 4) << 14));
 }
 
-// Copies BYTES of every lane from base + off (off below 2^32 - 16; the base in scalar registers) to dst + lane * BYTES of
-// LDS (dst scalar).  As a buffer load: after a `global_load_lds`, a flat instruction to the compiler, it makes every wait
-// for an LDS read a wait for all of them, up to the next full wait.
-template <int BYTES>
-__device__ __forceinline__ void copy_to_lds(const void *base, uint32_t off, void *dst) {
-    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
-    static_assert(BYTES == 4 || BYTES == 16);
-    if constexpr (BYTES == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)dst, 16, off, 0, 0, 0);
-    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rows, (__attribute__((address_space(3))) void *)dst, 4, off, 0, 0, 0);
-}
-
 // Every LDS read and scalar load has returned (a wait that the compiler takes into account, unlike one inside inline asm).
 __device__ __forceinline__ void wait_lgkmcnt_0() {
     __builtin_amdgcn_s_waitcnt(0xC07F);
     asm volatile("" ::: "memory");
-}
-
-__device__ __forceinline__ void lds_read_1x_b128(uint32_t addr, v4f &v) {
-    asm volatile("ds_read_b128 %0, %1\n s_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(addr) : "memory");
-}
-// Reads that are only ISSUED here (eight 4-byte reads at base + STEP n; three 16-byte reads at base +
-// STEP n): the caller must pass every destination through lds_wait_all before using it.
-template <int STEP>
-__device__ __forceinline__ void lds_issue_8x_b32(uint32_t base, float (&v)[8]) {
-    asm volatile(
-        "ds_read_b32 %0, %8 offset:%9\n ds_read_b32 %1, %8 offset:%10\n ds_read_b32 %2, %8 offset:%11\n"
-        "ds_read_b32 %3, %8 offset:%12\n ds_read_b32 %4, %8 offset:%13\n ds_read_b32 %5, %8 offset:%14\n"
-        "ds_read_b32 %6, %8 offset:%15\n ds_read_b32 %7, %8 offset:%16"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP), "n"(6 * STEP),
-          "n"(7 * STEP)
-        : "memory");
-}
-template <int STEP>
-__device__ __forceinline__ void lds_issue_3x_b128(uint32_t base, v4f (&v)[3]) {
-    asm volatile("ds_read_b128 %0, %3 offset:%4\n ds_read_b128 %1, %3 offset:%5\n ds_read_b128 %2, %3 offset:%6"
-                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2])
-                 : "v"(base), "n"(0), "n"(STEP), "n"(2 * STEP)
-                 : "memory");
-}
-// s_waitcnt lgkmcnt(0) that the given registers depend on: no use of them can be scheduled ahead of it.
-__device__ __forceinline__ void lds_wait_all(float (&a)[8], v4f (&b)[3]) {
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]),
-                   "+v"(b[0]), "+v"(b[1]), "+v"(b[2])
-                 :
-                 : "memory");
-}
-__device__ __forceinline__ void lds_write_b128(uint32_t addr, v4f v) {
-    asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
 
 // Row-streaming kernel for short reductions (K <= 128), defined next to the fused kernels.
@@ -431,10 +333,6 @@ __device__ __forceinline__ void lds_write_b128(uint32_t addr, v4f v) {
 // 4-bit form) x holds fp16 activations, only w is packed and k_bytes = K.
 // offset: z_tok / rowsum are honoured (per-token zero offset; with `quantize` the codes carry the offset); not with `packed4`.
 int launch_stream_smallk(const LinearArgs &a, bool quantize, hipStream_t stream, bool packed4 = false, bool offset = false);
-
-// Weights-in-registers kernel for wide int8 linears with a short reduction (K = 384 or 768, e.g. the
-// in_proj of the Vim-S / Vim-B stacks), defined in gemm_wreg.hip.  Same return convention.
-int launch_wreg(const LinearArgs &a, hipStream_t stream);
 
 // Tile kernels (gemm_tile.hip): any shape, pitch and alignment.
 template <class Path>

@@ -5,7 +5,7 @@ Usage (from the repository root, after the rocprofv3 runs named in the summary's
 
   python3 -m paper_2412_20386_amd.profile_summary --kernel-trace out/prof/kt --fetch out/prof/fetch \
       --write out/prof/write --bench-json out/prof/bench_kt.json --config 3 \
-      --dominant linear_mfma_wreg --out profiles/bench_vim_b_stack_kernel_trace_and_traffic.txt
+      --dominant "linear_mfma_persistent<int8>" --out profiles/bench_vim_b_stack_kernel_trace_and_traffic.txt
 
 Every input is optional; what is missing is left out of the summary.  HBM traffic of a kernel = the counter's
 median over its dispatches (KiB) times the factor that makes the same counter read 262144 KiB for the 256 MiB
@@ -25,7 +25,7 @@ import sys
 
 OURS = ("linear_", "pts_linear", "quantize_", "fold_smoothing", "weight_rowsum", "count_bad_scales", "sum_bad_scales")
 BASES = ("linear_e2m3_persistent", "linear_e2m3_tile", "linear_e2m3_splitk", "quantize_pts_a4_e2m3_blocks", "quantize_pts_a4_e2m3_stream",
-         "quantize_pts_a4_e2m3_generic", "fold_smoothing_w4_e2m3_rows", "linear_mfma_wreg", "linear_mfma_persistent", "linear_mfma_smallk",
+         "quantize_pts_a4_e2m3_generic", "fold_smoothing_w4_e2m3_rows", "linear_mfma_persistent", "linear_mfma_smallk",
          "linear_mfma_tile", "linear_mfma_splitk", "linear_stream_smallk", "pts_linear_wres", "pts_linear_split", "pts_linear_generic",
          "quantize_pts_stream", "quantize_pts_any", "quantize_dynamic_rows", "quantize_dynamic_generic", "fold_smoothing_w4_rows",
          "fold_smoothing_rows", "weight_rowsum_rows", "count_bad_scales", "sum_bad_scales")
@@ -68,8 +68,6 @@ def short(name: str) -> str:
         if m:
             rows, cols = m.group(1) or m.group(3), m.group(2) or m.group(4)
             tag = f"{tag[:-1]} {rows}x{cols}>" if tag else f"<{rows}x{cols}>"
-    if base == "linear_mfma_wreg":
-        tag = "<K=768>" if ("ILi12E" in name or "<12," in name) else "<K=384>"
     return base + tag
 
 

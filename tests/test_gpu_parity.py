@@ -433,11 +433,10 @@ def test_skinny_output_shapes_sampled(B, L, K, N, ldy, bias):
 
 
 @pytest.mark.parametrize("B,L,K,N,bias", [(43, 197, 768, 512, True), (65, 131, 384, 256, False)])
-def test_weights_in_registers_kernel_whole_result(B, L, K, N, bias):
-    """Every code, accumulator and output at the reductions of the weights-in-registers kernel (K = 768 / 384), ragged in rows,
-    below the nine units a CU from which it takes over (test_gpu_routes.py has those)."""
+def test_short_reduction_whole_result(B, L, K, N, bias):
+    """Every code, accumulator and output at the reductions of the Vim-B and Vim-S in_proj (K = 768 / 384), ragged in rows."""
     c = synth.random_problem(4100 + K + N, B, L, K, N, device=DEV)
-    _run_w8a8_case(c, use_bias=bias, what="wreg-whole")
+    _run_w8a8_case(c, use_bias=bias, what="short-whole")
 
 
 def test_skinny_output_whole_result():

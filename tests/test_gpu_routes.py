@@ -10,7 +10,7 @@ import paper_2412_20386_amd as ptq
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-WREG, PERSISTENT, STREAM, SMALLK = "linear_mfma_wreg<", "linear_mfma_persistent<", "linear_stream_smallk<", "linear_mfma_smallk<"
+PERSISTENT, STREAM, SMALLK = "linear_mfma_persistent<", "linear_stream_smallk<", "linear_mfma_smallk<"
 TILE, SPLITK, WRES, SPLIT, FUSED_TILE = "linear_mfma_tile<", "linear_mfma_splitk<", "pts_linear_wres<", "pts_linear_split<", "pts_linear_generic<"
 E_PERSISTENT, E_TILE, E_SPLITK = "linear_e2m3_persistent<", "linear_e2m3_tile<", "linear_e2m3_splitk<"
 DIRECT, STAGED, ONE_SLAB = "Copy)0>", "Copy)1>", "Copy)2>"  # how linear_mfma_tile brings its slabs
@@ -64,21 +64,21 @@ class Problem:
 @pytest.mark.parametrize("M,K,N", [
     (128 * 2303 + 5, 384, 256), (128 * 191 + 77, 384, 3072), (128 * 575 + 1, 768, 1024), (128 * 767 + 100, 768, 768),
 ])
-def test_weights_in_registers_kernel(M, K, N):
-    """From nine units of 128 rows x 256 channels a CU; ragged last units; one strip and several, an uneven band; with and
-    without bias; with the accumulators.  One row unit less runs on the persistent kernel."""
-    print(f"wreg M={M} K={K} N={N}", flush=True)
+def test_persistent_kernel_over_many_tiles(M, K, N):
+    """Short reductions over whole rounds of 128 x 256 units; ragged last tiles; one column of tiles and several, full and
+    half tiles; with and without bias; with the accumulators; and one row unit less."""
+    print(f"persistent M={M} K={K} N={N}", flush=True)
     p = Problem(M, K, N)
     for bias in (p.bias, None):
         run = lambda **kw: ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, bias, p.B, p.L, **kw)
-        check_kernel(run, WREG, f"<{K // 64},")
+        check_kernel(run, PERSISTENT, "Int8Path")
         y = run()
         assert close(y, p.acc64, p.scale, bias)
-        check_kernel(lambda: run(acc_out=p.acc), WREG)
+        check_kernel(lambda: run(acc_out=p.acc), PERSISTENT)
         p.acc.fill_(-1)
         y_dump = run(acc_out=p.acc)
         assert torch.equal(p.acc.double(), p.acc64) and torch.equal(y_dump.view(torch.int16), y.view(torch.int16))
-    M = (M // 128) * 128 - M // 128 // 100  # fewer than nine units a CU
+    M = (M // 128) * 128 - M // 128 // 100
     x = p.x[:M]
     check_kernel(lambda: ptq.w8a8_linear(x, p.w, p.s_tok[:1], p.s_w, p.bias, M, 1), PERSISTENT)
 

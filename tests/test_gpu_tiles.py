@@ -130,10 +130,10 @@ def test_persistent_tiles_with_stores_in_flight(M, K, N, pad):
 
 
 @pytest.mark.parametrize("K,N,B,L", [(384, 3072, 124, 199), (768, 3072, 128, 197), (768, 1536, 190, 260)])
-def test_weights_in_registers_against_smaller_launches(K, N, B, L):
-    """Around nine 128 x 256 units a CU the weight-in-registers kernel takes over: the same bits as two launches of half the
-    images, which stay on the persistent or tile kernels (ragged and whole units)."""
-    print(f"wreg line B={B} L={L} K={K} N={N}", flush=True)
+def test_persistent_kernel_against_smaller_launches(K, N, B, L):
+    """Many rounds of tiles, with a part round in half tiles: the same bits as two launches of half the images, whose rounds and half
+    tiles fall elsewhere."""
+    print(f"persistent B={B} L={L} K={K} N={N}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(77 + K + N)
     M = B * L
     x = torch.randint(-127, 128, (M, K), dtype=torch.int8, device=DEV, generator=g)
