@@ -184,6 +184,40 @@ def test_int8_tiles_of_a_few_rounds(M, K, N, parts):
     test_int8_tiles(M, K, N, parts)
 
 
+@pytest.mark.parametrize("kind,M,K,N,parts", [
+    ("packed", 13057, 384, 2048, ("Int4Path", "128, 256, 2, 4, 64, 3", DIRECT)), ("f16", 13057, 96, 2048, ("Half16Path", "128, 256, 2, 4, 64, 3", DIRECT)),
+    ("offset", 13057, 192, 2048, ("Int8OffsetPath", "128, 256, 2, 4, 64, 3", DIRECT)), ("packed", 13057, 384, 2045, ("Int4Path", "128, 256", DIRECT)),
+    ("packed", 49153, 384, 56, ("Int4Path", "64, 64, 2, 2, 128, 2", DIRECT)), ("f16", 49153, 96, 56, ("Half16Path", "64, 64, 2, 2, 128, 2", DIRECT)),
+    ("offset", 49153, 192, 56, ("Int8OffsetPath", "64, 64, 2, 2, 128, 2", DIRECT)), ("offset", 32769, 320, 50, ("Int8OffsetPath", "64, 64, 2, 2, 128, 2", DIRECT)),
+    ("offset", 25009, 448, 380, ("Int8OffsetPath", "256, 192", DIRECT)), ("f16", 25009, 224, 380, ("Half16Path", "256, 192", DIRECT)),
+    ("packed", 25009, 896, 380, ("Int4Path", "128, 128", DIRECT)),  # (never on 256-row tiles)
+    ("offset", 8705, 320, 1536, ("Int8OffsetPath", "256, 256", DIRECT)), ("f16", 8705, 160, 1536, ("Half16Path", "256, 256", DIRECT)),
+])
+def test_direct_tiles_of_the_other_operands(kind, M, K, N, parts):
+    """The largest tiles, the tiles of whole rounds and the two-stage 64 x 64 tiles on each of the other operand types."""
+    print(f"{kind} tiles M={M} K={K} N={N}", flush=True)
+    p = Problem(M, K, N, limit=7 if kind == "packed" else 127)
+    if kind == "f16":
+        x, w = p.x.half() / 64, p.w.half() / 64  # (exact; products sum without rounding)
+        run = lambda **kw: ptq.f16_linear(x, w, p.bias)
+        check_kernel(run, TILE, *parts)
+        assert close(run(), p.acc64 / 4096, torch.ones((), dtype=torch.float64, device=DEV), p.bias)
+        return
+    if kind == "packed":
+        pack = lambda c: ((c[:, 0::2] & 15) | ((c[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous()
+        x, w = pack(p.x), pack(p.w)
+        run = lambda **kw: ptq.w4a4_linear(x, w, p.s_tok, p.s_w, p.bias, p.B, p.L, **kw)
+        want = p.acc64
+    else:
+        run = lambda **kw: ptq.w8a8_linear_offset(p.x, p.w, p.s_tok, p.z, p.rowsum, p.s_w, p.bias, p.B, p.L, **kw)
+        want = p.acc64 - p.z.double()[rows_of(p.L, M)][:, None] * p.rowsum.double()[None, :]
+    check_kernel(run, TILE, *parts)
+    y = run()
+    assert close(y, want, p.scale, p.bias)
+    p.acc.fill_(-1)
+    assert torch.equal(run(acc_out=p.acc).view(torch.int16), y.view(torch.int16)) and torch.equal(p.acc.double(), p.acc64)
+
+
 FRAGMENTS, VIA_LDS = "false, (ptq4vm::mfma::Copy)2>", "true, (ptq4vm::mfma::Copy)2>"
 
 

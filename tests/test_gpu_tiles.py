@@ -1,5 +1,6 @@
-"""The tile kernels of the linears (csrc/gemm_tile.hpp, csrc/gemm_e2m3.hip) at the edges of their tiles, on every operand type, against a
-64-bit product (exact for the integer paths)."""
+"""The linears' kernels at the edges of their tiles (csrc/gemm_tile.hpp, csrc/gemm_e2m3.hip), on every operand type, against a 64-bit
+product (exact for the integer paths).  A shape's comment names the tiles of the 8-bit linear unless it says otherwise; which kernel a
+shape runs on is asserted in test_gpu_routes.py."""
 import pytest
 import torch
 
@@ -12,10 +13,10 @@ SHAPES = [  # M, K, N (int8 reductions; every operand type picks its own tile fr
     (1, 64, 1, 0), (33, 192, 17, 1), (255, 1536, 80, 0),           # split reduction over 16 x 16 blocks: one element, ragged, long
     (65, 128, 2049, 0), (197, 1088, 769, 3),                       # 32 x 64 tiles; K ends in half a slab; odd rows of y
     (785, 192, 1601, 0), (1001, 960, 832, 8),                      # 64 x 64 tiles, three ring stages
-    (1999, 320, 1216, 0),                                          # 64 x 64 tiles, two ring stages
+    (1999, 320, 1216, 0),                                          # 64 x 64 tiles, two ring stages (packed: three)
     (3137, 448, 1153, 0),                                          # 64 x 128 tiles
     (6209, 192, 1025, 5), (49217, 1536, 80, 0),                    # 128 x 128 tiles, and with a column tile mostly padding
-    (13057, 192, 2048, 0),                                         # 128 x 256 tiles
+    (13057, 192, 2048, 0),                                         # 128 x 256 tiles (fp16: persistent; packed: any alignment)
     (50, 13, 7, 0), (301, 100, 130, 0), (17, 1001, 333, 1),        # any alignment: 16 x 16 blocks
     (1111, 514, 402, 0),                                           # 32 x 32 blocks
     (401, 72, 899, 2), (1279, 200, 645, 0), (2049, 722, 643, 0),   # 32 x 64, 64 x 64 with short and long slabs
@@ -110,7 +111,9 @@ def test_tile_kernels_all_operand_types(M, K, N, pad):
     (25009, 448, 380, 3),    # 256 x 192 tiles, K ends in half a slab, odd rows of y
     (25201, 1152, 376, 8),   # the same, whole slabs and 16-byte stores, the last tile partly empty both ways
     (9433, 320, 1531, 0),    # 256 x 256 tiles
-    (40009, 128, 640, 0),    # 128 x 256 tiles, results past the caches
+    (40009, 128, 640, 0),    # E2M3: 128 x 256 tiles, results past the caches; integers: streamed; fp16: persistent
+    (13057, 384, 2045, 3),   # packed: 128 x 256 tiles, the last 253 channels wide
+    (13057, 96, 2048, 0),    # fp16: 128 x 256 tiles, results past the caches
     (12301, 64, 776, 0),     # 128 x 128 tiles of one step
     (97, 320, 2048, 0),      # more channels than rows: rows walked first
 ])
