@@ -13,7 +13,7 @@
 //   linear_e2m3_persistent  one workgroup of 8 wavefronts per CU walks 256 x 256 tiles (wave tile 128 token rows x
 //                           64 channels); a ring of 3 stages, each one 128-code block of the tile's 256 + 256
 //                           rows, is filled by direct global -> LDS copies that run two stages ahead.
-//   linear_e2m3_tile        one tile of 32 x 64 .. 128 x 128 per workgroup, every other shape and any alignment of y
+//   linear_e2m3_tile        one tile of 32 x 64 .. 128 x 256 per workgroup, every other shape and any alignment of y
 //   linear_e2m3_splitk      a few hundred blocks of 16 x 16 or fewer: the wavefronts of a workgroup split the reduction
 #include "gemm_tile.hpp"
 
@@ -128,9 +128,9 @@ __global__ __launch_bounds__(64 * SK) void linear_e2m3_splitk(const LinearArgs p
 __device__ __forceinline__ int stage_chunk_source(int row, int c) { return c < 4 ? c : 4 + ((c - 4) ^ ((row >> 3) & 1)); }
 
 constexpr int kTile = 256;                 // channels per tile
-constexpr int kTileRows = 256;             // token rows per tile: one workgroup of 8 wavefronts per CU
+constexpr int kTileRows = 256;             // token rows per tile
 constexpr int kStages = 3;
-constexpr int kWavesPerWg = 4 * kTileRows / 128;
+constexpr int kWavesPerWg = 8;             // one workgroup per CU
 constexpr int kStageBytes = (kTileRows + kTile) * kBlockBytes;
 constexpr int kScaleBytes = kTile * 4 + kTileRows * 4 + kTile * 2;
 constexpr int kPatchPitch = 160, kPatchBytes = 8 * kPatchPitch;  // a wavefront's patch: 8 rows of 64 fp16 (2 mod 4 pieces of 16 bytes: no bank conflicts)
@@ -140,7 +140,7 @@ template <bool HAS_BIAS, bool DUMP_ACC>
 __global__ __launch_bounds__(kWavesPerWg * 64, 2) void linear_e2m3_persistent(const LinearArgs p) {
     constexpr int NW = kWavesPerWg, FR = 8, FO = 4, WAVE_R = 128, WAVE_O = 64;
     constexpr int X_COPIES = kTileRows * 6 / 64 / NW;  // 1 KiB copies per wavefront and stage: 3 of token rows,
-    constexpr int W_COPIES = kTile * 6 / 64 / NW;      // 3 or 6 of weight rows
+    constexpr int W_COPIES = kTile * 6 / 64 / NW;      // 3 of weight rows
     constexpr int LOADS_PER_BLOCK = X_COPIES + W_COPIES;
     constexpr int KEEP = (kStages - 2) * LOADS_PER_BLOCK;  // copies allowed in flight when a block is needed
     constexpr int TILE_STORES = 2 * FR;                    // a wavefront's store instructions per tile
@@ -406,8 +406,7 @@ int launch_persistent(LinearArgs a, hipStream_t stream) {
     const int64_t tiles_r = ptq4vm::ceil_div(a.M, kTileRows), tiles_o = ptq4vm::ceil_div(a.N, kTile);
     a.tiles_r = (int)tiles_r;
     a.tiles_o = (int)tiles_o;
-    // 8 wavefronts per CU (one workgroup, or two of 4), a multiple of the XCD count
-    const unsigned wgs = (unsigned)max(1, cus / kXcds) * kXcds * (8 / kWavesPerWg);
+    const unsigned wgs = (unsigned)max(1, cus / kXcds) * kXcds;  // one workgroup per CU, a multiple of the XCD count
     using Kernel = void (*)(const LinearArgs);
     static const Kernel kernels[2][2] = {{linear_e2m3_persistent<false, false>, linear_e2m3_persistent<false, true>},
                                          {linear_e2m3_persistent<true, false>, linear_e2m3_persistent<true, true>}};
