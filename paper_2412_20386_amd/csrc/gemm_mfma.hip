@@ -569,19 +569,16 @@ int dispatch(LinearArgs a, hipStream_t stream) {
     a.y_vec = (a.ldy % 8 == 0 && ptq4vm::aligned_to(a.y, 16)) ? 8
               : ((a.ldy % 4 == 0 && ptq4vm::aligned_to(a.y, 8)) ? 4 : 1);
     if constexpr (Path::kElemBytes == 1) {
-        // Very short reductions over many rows: whole rows of y streamed out by one wavefront each.  (us, streamed / tiles:
-        // 50432 x 48 -> 1536 36.3 / 44.7, 25216 x 24 -> 768 11.6 / 13.5, but 12608 x 48 -> 1536 18.0 / 12.4.)
-        // Two MFMA steps of K (65 .. 128 codes): where the streamed segments of 64 channels leave whole half lines of y (45408 x
-        // 68 -> 192 9.3 / 13.9, 29120 x 112 -> 512 10.0 / 13.3, 46726 x 96 -> 896 21.6 / 27.1, 47424 x 128 -> 832 19.8 / 30.2; at 128
-        // codes, which the tiles copy directly, from 30 000 rows: 29376 x 128 -> 128 6.2 / 5.6), or where 128-channel tiles
-        // would be half padding (47736 x 108 -> 176 11.4 / 14.7, 44040 x 96 -> 96 6.3 / 7.8, but 21111 x 112 -> 160 7.1 / 6.4).  Other
-        // channel counts merge their segments in the L2, which tiles do better (46648 x 80 -> 664: 1.4 times slower streamed), and
-        // operands of any alignment would be loaded byte by byte (2 to 3 times slower).
+        // One MFMA step of K and results of 24 M elements and more in whole lines: whole rows of y streamed out by one wavefront each.  (us,
+        // streamed / tiles: 39246 x 24 -> 768 [30 M] 14.0 / 18.2, 50432 x 48 -> 1536 [77 M] 34.0 / 43.0, over 160 such shapes tiles take 1.15
+        // of the time, packed and offset alike, but 25216 x 24 -> 768 [19 M] 10.3 / 9.2, 29083 x 12 -> 512 [15 M] 10.3 / 9.0.  Rows of y that are
+        // not whole lines, 46384 x 32 -> 712 37.6 / 16.9, 49570 x 48 -> 171 21.4 / 11.2; operands at any alignment 0.36 .. 0.7 for the
+        // tiles; operands that the tiles copy directly, K a multiple of 64 bytes, 0.86 .. 0.97; two steps of K 0.82 of the time below 24 M
+        // elements and as long above.)
         const int64_t codes = Path::kPacked4 ? 2 * a.k_bytes : a.k_bytes;
-        const bool direct = a.k_bytes % 64 == 0;
-        const bool half_lines = a.N % 32 == 0 && a.N >= 96 && (a.N > 128 || a.M >= (a.N == 128 ? 28000 : 40000)) && (!direct || a.M >= 30000 || a.N >= 448);
-        const bool half_padding = a.N > 128 && a.N <= 192 && a.N % 4 == 0 && a.M >= 36000 && !direct;
-        if (codes <= 64 || (codes <= 128 && la >= 4 && (half_lines || half_padding))) {
+        const bool direct = la == 16 && a.k_bytes % 64 == 0;
+        const bool whole_lines = a.N % 64 == 0 && a.ldy % 64 == 0 && ptq4vm::aligned_to(a.y, 128);
+        if (codes <= 64 && la >= 4 && !direct && whole_lines && a.M * a.N >= (24LL << 20)) {
             const int rc = launch_stream_smallk(a, false, stream, Path::kPacked4, Path::kOffset);
             if (rc <= 0) return rc;
         }

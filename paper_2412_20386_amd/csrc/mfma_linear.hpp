@@ -325,7 +325,7 @@ __device__ __forceinline__ void wait_lgkmcnt_0() {
     asm volatile("" ::: "memory");
 }
 
-// Row-streaming kernel for short reductions (K <= 128), defined next to the fused kernels.
+// Row-streaming kernel for short reductions (K <= 128 with `quantize`, <= 64 without), defined next to the fused kernels.
 // quantize: x holds fp16 activations and inv_m / xq_out are honoured; otherwise x holds int8 codes.
 // Returns PTQ4VM_OK after a launch, a negative status on error, or 1 if the shape does not fit
 // this kernel (nothing was launched; the caller picks another one).

@@ -477,8 +477,8 @@ __device__ __forceinline__ v4i load_quantized_chunk(const char *row_ptr, int64_t
 // whole 128-byte lines.  A unit's output is one contiguous 16-row span of y written by at most four
 // wavefronts (the channel groups of a unit are dealt in up to four parts) within a few microseconds.  No barrier
 // after the set-up.
-// QUANT: activations are fp16 and pass through the PTS quantizer; otherwise they are int8 codes.
-// Any pitch and alignment (X_ALIGN / W_ALIGN: 16, 4 or 0 = element-wise loads).
+// QUANT: activations are fp16 and pass through the PTS quantizer; otherwise they are int8 codes (one MFMA step of K, rows at
+// multiples of 4 bytes).  Fused, any pitch and alignment (X_ALIGN / W_ALIGN: 16, 4 or 0 = element-wise loads).
 // ------------------------------------------------------------------------------------------
 #ifndef PTQ4VM_STREAM_RB
 #define PTQ4VM_STREAM_RB 1
@@ -487,7 +487,7 @@ constexpr int kStreamRB = PTQ4VM_STREAM_RB;       // 16-row MFMA blocks per unit
 constexpr int kStreamWaves = 16 / kStreamRB;      // wavefronts per workgroup
 constexpr int kStreamPatch = 2048 * kStreamRB;    // bytes of the per-wavefront transposition patch
 // A unit (16 rows x all channels) is one serial chain per wavefront and costs ~1 us per 64 channels however
-// few rows there are; the channel-strip kernel is faster below ~20 k rows (N = 384 ... 1536).  The fused form
+// few rows there are; the tile kernels are faster below ~20 k rows.  The fused form
 // has only the tiled fused kernel as an alternative and takes over much earlier.
 constexpr int64_t kStreamMinRows = 20480, kStreamMinRowsFused = 1024;
 
@@ -814,16 +814,24 @@ __global__ __launch_bounds__(kThreads, 2) void pts_linear_generic(const LinearAr
 template <int KSTEPS, bool QUANT, bool PACKED4 = false, bool OFFSET = false>
 int launch_stream_aligned(const LinearArgs &a, int xa, int wa, const StreamLayout &lay, unsigned wgs, hipStream_t stream) {
     using Kernel = void (*)(const LinearArgs);
-    // [activation alignment 16 / 4 / 0][weight alignment 16 / 4 / 0]
-    static const Kernel kernels[3][3] = {
-        {linear_stream_smallk<KSTEPS, QUANT, 16, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, QUANT, 16, 4, PACKED4, OFFSET>,
-         linear_stream_smallk<KSTEPS, QUANT, 16, 0, PACKED4, OFFSET>},
-        {linear_stream_smallk<KSTEPS, QUANT, 4, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, QUANT, 4, 4, PACKED4, OFFSET>,
-         linear_stream_smallk<KSTEPS, QUANT, 4, 0, PACKED4, OFFSET>},
-        {linear_stream_smallk<KSTEPS, QUANT, 0, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, QUANT, 0, 4, PACKED4, OFFSET>,
-         linear_stream_smallk<KSTEPS, QUANT, 0, 0, PACKED4, OFFSET>}};
-    auto idx = [](int al) { return al == 16 ? 0 : (al == 4 ? 1 : 2); };
-    const Kernel kernel = kernels[idx(xa)][idx(wa)];
+    Kernel kernel;
+    if constexpr (QUANT) {
+        // [activation alignment 16 / 4 / 0][weight alignment 16 / 4 / 0]
+        static const Kernel kernels[3][3] = {
+            {linear_stream_smallk<KSTEPS, true, 16, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, true, 16, 4, PACKED4, OFFSET>,
+             linear_stream_smallk<KSTEPS, true, 16, 0, PACKED4, OFFSET>},
+            {linear_stream_smallk<KSTEPS, true, 4, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, true, 4, 4, PACKED4, OFFSET>,
+             linear_stream_smallk<KSTEPS, true, 4, 0, PACKED4, OFFSET>},
+            {linear_stream_smallk<KSTEPS, true, 0, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, true, 0, 4, PACKED4, OFFSET>,
+             linear_stream_smallk<KSTEPS, true, 0, 0, PACKED4, OFFSET>}};
+        auto idx = [](int al) { return al == 16 ? 0 : (al == 4 ? 1 : 2); };
+        kernel = kernels[idx(xa)][idx(wa)];
+    } else {  // (codes: rows at multiples of 4 bytes at least)
+        static const Kernel kernels[2][2] = {
+            {linear_stream_smallk<KSTEPS, false, 16, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, false, 16, 4, PACKED4, OFFSET>},
+            {linear_stream_smallk<KSTEPS, false, 4, 16, PACKED4, OFFSET>, linear_stream_smallk<KSTEPS, false, 4, 4, PACKED4, OFFSET>}};
+        kernel = kernels[xa == 16 ? 0 : 1][wa == 16 ? 0 : 1];
+    }
     if (int rc = ptq4vm::set_lds_limit(reinterpret_cast<const void *>(kernel), kLdsBytes, "hipFuncSetAttribute(linear_stream_smallk)")) return rc;
     kernel<<<dim3(wgs), dim3(kStreamWaves * 64), lay.total, stream>>>(a);
     return ptq4vm::check_launch("linear_stream_smallk");
@@ -984,7 +992,7 @@ int ptq4vm::mfma::launch_stream_smallk(const LinearArgs &a, bool quantize, hipSt
     const int xa = align_of(a.x, a.ldx_bytes), wa = align_of(a.w, a.ldw_bytes);
     // bytes of K per row once the operands are int8 (two-launch 4-bit form: k_bytes counts packed bytes; fused 4-bit form: codes)
     const int64_t k_codes = (packed4 && !quantize) ? 2 * a.k_bytes : a.k_bytes;
-    if (k_codes > 128 || (offset && packed4) || a.M < (quantize ? kStreamMinRowsFused : kStreamMinRows) || a.M >= (1LL << 31) || a.L >= (1LL << 31) || a.N > 8192) return 1;
+    if (k_codes > (quantize ? 128 : 64) || (!quantize && (xa == 0 || wa == 0)) || (offset && packed4) || a.M < (quantize ? kStreamMinRowsFused : kStreamMinRows) || a.M >= (1LL << 31) || a.L >= (1LL << 31) || a.N > 8192) return 1;
     const int ksteps = k_codes <= 64 ? 1 : 2;
     const StreamLayout lay = stream_layout((int)a.N, ksteps);
     if (lay.total > kLdsBytes) return 1;
@@ -1005,14 +1013,9 @@ int ptq4vm::mfma::launch_stream_smallk(const LinearArgs &a, bool quantize, hipSt
     if (quantize)
         return ksteps == 1 ? launch_stream_aligned<1, true>(a, xa, wa, lay, (unsigned)wgs, stream)
                            : launch_stream_aligned<2, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    if (offset)
-        return ksteps == 1 ? launch_stream_aligned<1, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream)
-                           : launch_stream_aligned<2, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    if (packed4)
-        return ksteps == 1 ? launch_stream_aligned<1, false, true>(a, xa, wa, lay, (unsigned)wgs, stream)
-                           : launch_stream_aligned<2, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
-    return ksteps == 1 ? launch_stream_aligned<1, false>(a, xa, wa, lay, (unsigned)wgs, stream)
-                       : launch_stream_aligned<2, false>(a, xa, wa, lay, (unsigned)wgs, stream);
+    if (offset) return launch_stream_aligned<1, false, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
+    if (packed4) return launch_stream_aligned<1, false, true>(a, xa, wa, lay, (unsigned)wgs, stream);
+    return launch_stream_aligned<1, false>(a, xa, wa, lay, (unsigned)wgs, stream);
 }
 
 extern "C" int ptq4vm_w4a4_linear_fused(const void *x_f16, const float *inv_m, const float *s_tok, const uint8_t *wq4,

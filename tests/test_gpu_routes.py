@@ -117,13 +117,15 @@ def test_e2m3_kernels(M, K, N, kernel):
 
 
 @pytest.mark.parametrize("M,K,N,kernel", [
-    (20480, 66, 160, TILE), (20483, 68, 160, STREAM), (20479, 68, 160, TILE), (20501, 100, 416, STREAM), (20501, 100, 424, TILE),
-    (27999, 72, 128, TILE), (28001, 72, 128, STREAM), (39999, 72, 96, TILE), (40003, 72, 96, STREAM),
-    (36001, 76, 132, STREAM), (36001, 76, 130, TILE), (35999, 76, 132, TILE), (36001, 76, 196, TILE),
-    (29999, 128, 416, TILE), (30001, 128, 416, STREAM), (20483, 128, 448, STREAM), (20483, 128, 2080, TILE),
+    (20480, 66, 160, TILE), (20483, 68, 160, TILE), (20479, 68, 160, TILE), (20501, 100, 416, TILE), (20501, 100, 424, TILE),
+    (27999, 72, 128, TILE), (28001, 72, 128, TILE), (39999, 72, 96, TILE), (40003, 72, 96, TILE),
+    (36001, 76, 132, TILE), (36001, 76, 130, TILE), (35999, 76, 132, TILE), (36001, 76, 196, TILE),
+    (29999, 128, 416, TILE), (30001, 128, 416, TILE), (20483, 128, 448, TILE), (20483, 128, 2080, TILE),  # 65 to 128 codes
+    (32768, 24, 768, STREAM), (32767, 24, 768, TILE), (32768, 24, 776, TILE), (32768, 26, 768, TILE), (32768, 64, 768, TILE),  # 24 M results in whole lines
+    (98304, 12, 256, STREAM), (20479, 48, 1536, TILE), (20483, 48, 1536, STREAM), (20483, 16, 1600, STREAM), (20483, 16, 1728, TILE),  # (no more channels fit the LDS)
 ])
-def test_streaming_kernel_two_steps_of_k(M, K, N, kernel):
-    """65 to 128 codes, in the three forms (packed 4-bit: the same number of codes, so half the bytes and half the alignment)."""
+def test_short_reductions_over_many_rows(M, K, N, kernel):
+    """In the three forms (packed 4-bit: the same number of codes, so half the bytes and half the alignment)."""
     print(f"stream M={M} K={K} N={N}", flush=True)
     p = Problem(M, K, N)
     check_kernel(lambda: ptq.w8a8_linear(p.x, p.w, p.s_tok, p.s_w, p.bias, p.B, p.L), kernel)
@@ -137,7 +139,7 @@ def test_streaming_kernel_two_steps_of_k(M, K, N, kernel):
     pack = lambda c: ((c[:, 0::2] & 15) | ((c[:, 1::2] & 15) << 4)).to(torch.uint8).contiguous()
     xp, wp = pack(x4), pack(w4)
     packed = lambda: ptq.w4a4_linear(xp, wp, p.s_tok, p.s_w, p.bias, p.B, p.L, acc_out=p.acc)
-    check_kernel(packed, TILE if K // 2 % 4 else kernel)
+    check_kernel(packed, TILE if K // 2 % 4 else STREAM if K == 64 else kernel)  # (64 packed codes are no whole step of bytes)
     acc4 = x4.double() @ w4.double().t()
     assert close(packed(), acc4, p.scale, p.bias) and torch.equal(p.acc.double(), acc4)
 
