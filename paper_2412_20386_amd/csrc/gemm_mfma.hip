@@ -369,13 +369,14 @@ __global__ __launch_bounds__(512, 2) void linear_mfma_persistent(const LinearArg
 }
 
 // ------------------------------------------------------------------------------------------
-// Small-K fp16 path (K bytes <= 128, e.g. dt_proj with K = dt_rank): the whole reduction is 1-4 MFMA
+// Small-K fp16 path (K bytes < 128, large results in whole lines, e.g. dt_proj with K = dt_rank): the whole reduction is 1-4 MFMA
 // k-steps, so the kernel is a stream of output rows bound by the fp16 stores.  A wavefront owns
 // 64 output channels for its whole life and keeps their weight fragments and biases in
 // registers; it walks over 32-row blocks, fetching the activation fragments straight from
 // global memory (no LDS staging of operands), and transposes results through a private LDS
 // patch so that every store instruction writes eight whole 128-byte row segments.
-// LOAD_ALIGN 16: pitches and bases are multiples of 16 bytes; 4: multiples of 4 bytes.
+// LOAD_ALIGN 16: pitches and bases are multiples of 16 bytes; 4: multiples of 4 bytes.  N and the pitch of y are multiples of 64,
+// y is 128-byte aligned.
 // ------------------------------------------------------------------------------------------
 template <int LOAD_ALIGN>
 __device__ __forceinline__ v4i load_fragment_chunk(const char *row_ptr, int kb, int k_bytes) {
@@ -410,14 +411,12 @@ __global__ __launch_bounds__(kThreads) void linear_mfma_smallk(const LinearArgs 
     const int k_bytes = (int)p.k_bytes;
     const int64_t o_base = ((int64_t)blockIdx.y * kWaves + wave) * 64;
     if (o_base >= p.N) return;  // whole wavefront out of range; no barriers are used below
-    const int cols_valid = (int)min((int64_t)64, p.N - o_base);
 
     // weight fragments of the strip's 64 channels: block i covers channels 32 i .. 32 i + 31
     v4i fw[2][KSTEPS];
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-        const int row = min(i * 32 + l32, cols_valid - 1);  // clamped rows are never stored
-        const char *wrow = p.w + (o_base + row) * p.ldw_bytes;
+        const char *wrow = p.w + (o_base + i * 32 + l32) * p.ldw_bytes;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ks++) fw[i][ks] = load_fragment_chunk<LOAD_ALIGN>(wrow, (2 * ks + lhalf) * 16, k_bytes);
     }
@@ -429,9 +428,8 @@ __global__ __launch_bounds__(kThreads) void linear_mfma_smallk(const LinearArgs 
         for (int g = 0; g < 4; g++)
 #pragma unroll
             for (int c = 0; c < 4; c++) {
-                const int col = min(i * 32 + g * 8 + lhalf * 4 + c, cols_valid - 1);
                 cb[i][g][c] = 0.0f;
-                if constexpr (HAS_BIAS) cb[i][g][c] = __half2float(p.bias[o_base + col]);
+                if constexpr (HAS_BIAS) cb[i][g][c] = __half2float(p.bias[o_base + i * 32 + g * 8 + lhalf * 4 + c]);
             }
 
     const int64_t n_blocks = (p.M + 31) / 32;
@@ -444,7 +442,6 @@ __global__ __launch_bounds__(kThreads) void linear_mfma_smallk(const LinearArgs 
     };
     char *patch = patches[wave];
     auto patch_chunk = [&](int row, int chunk) { return row * 128 + ((chunk ^ (row & 7)) << 4); };
-    const bool y_fast = p.y_vec == 8 && cols_valid == 64;
 
     v4i fx[KSTEPS], fx_next[KSTEPS];
     if (rb < n_blocks) load_x(rb, fx);
@@ -479,21 +476,7 @@ __global__ __launch_bounds__(kThreads) void linear_mfma_smallk(const LinearArgs 
             const int row = q * 8 + (lane >> 3), chunk = lane & 7;
             const v4i data = *reinterpret_cast<const v4i *>(patch + patch_chunk(row, chunk));
             const int64_t rr = rb * 32 + row;
-            if (rr < p.M) {
-                __half *dst = p.y + rr * p.ldy + o_base + chunk * 8;
-                if (y_fast) {
-                    __builtin_nontemporal_store(data, reinterpret_cast<v4i *>(dst));
-                } else if (p.y_vec >= 4 && chunk * 8 + 8 <= cols_valid) {
-                    u32x2 a = {(uint32_t)data[0], (uint32_t)data[1]}, b = {(uint32_t)data[2], (uint32_t)data[3]};
-                    *reinterpret_cast<u32x2 *>(dst) = a;
-                    *reinterpret_cast<u32x2 *>(dst + 4) = b;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        if (chunk * 8 + e < cols_valid)
-                            reinterpret_cast<uint16_t *>(dst)[e] = (uint16_t)((uint32_t)data[e >> 1] >> (16 * (e & 1)));
-                }
-            }
+            if (rr < p.M) __builtin_nontemporal_store(data, reinterpret_cast<v4i *>(p.y + rr * p.ldy + o_base + chunk * 8));
         }
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -546,12 +529,13 @@ int launch_smallk(const LinearArgs &a, hipStream_t stream) {
 
 template <int LOAD_ALIGN>
 int launch_smallk_ksteps(const LinearArgs &a, hipStream_t stream) {
-    switch ((int)ptq4vm::ceil_div(a.k_bytes, 32)) {
-        case 1: return launch_smallk<1, LOAD_ALIGN>(a, stream);
-        case 2: return launch_smallk<2, LOAD_ALIGN>(a, stream);
-        case 3: return launch_smallk<3, LOAD_ALIGN>(a, stream);
-        default: return launch_smallk<4, LOAD_ALIGN>(a, stream);
+    const int ksteps = (int)ptq4vm::ceil_div(a.k_bytes, 32);
+    if (ksteps == 1) return launch_smallk<1, LOAD_ALIGN>(a, stream);
+    if constexpr (LOAD_ALIGN == 16) {
+        if (ksteps == 3) return launch_smallk<3, LOAD_ALIGN>(a, stream);
+        if (ksteps == 4) return launch_smallk<4, LOAD_ALIGN>(a, stream);
     }
+    return launch_smallk<2, LOAD_ALIGN>(a, stream);
 }
 
 // Widest load granularity that base pointers and pitches allow for both operands.
@@ -583,10 +567,16 @@ int dispatch(LinearArgs a, hipStream_t stream) {
             if (rc <= 0) return rc;
         }
     } else {
-        // (us, this / tiles: 12608 x 12 -> 384 5.6 / 6.3, 50432 x 48 -> 1536 39 / 45; whole MFMA steps of K, where the tile
-        // kernels copy directly: 25216 x 64 -> 768 20.6 / 12.6.)
-        if (a.k_bytes <= 128 && la >= 4 && !(la == 16 && a.k_bytes % 64 == 0))
-            return la == 16 ? launch_smallk_ksteps<16>(a, stream) : launch_smallk_ksteps<4>(a, stream);
+        // Results of 24 M elements and more in whole lines.  (us, channel strips / tiles: 39238 x 24 -> 768 [30 M] 15.0 / 17.8, 27273 x 14 ->
+        // 1024 [28 M] 11.5 / 16.5, 39184 x 48 -> 1536 [60 M] 26.4 / 34.1, over 90 such shapes tiles take 1.19 of the time, but 25146 x 24 -> 768
+        // [19 M] 11.1 / 9.5, 5852 x 12 -> 384 4.3 / 3.4, over 130 of 8 .. 24 M 0.78.  Other rows of y, 28912 x 12 -> 300 9.5 / 7.9, 13647 x 22 -> 1288
+        // 20.3 / 11.3; rows of operands that start between 16-byte boundaries up to 48 bytes of K only, 39130 x 12 -> 1472 alike 1.2, but 34005 x 60
+        // -> 2880 89.6 / 51.4; whole MFMA steps of K, which the tiles copy directly, 25216 x 64 -> 768 20.6 / 12.6.)
+        const bool whole_lines = a.N % 64 == 0 && a.ldy % 64 == 0 && ptq4vm::aligned_to(a.y, 128);
+        if (a.k_bytes <= 128 && a.k_bytes % 64 != 0 && whole_lines && a.M * a.N >= (24LL << 20)) {
+            if (la == 16) return launch_smallk_ksteps<16>(a, stream);
+            if (la == 4 && a.k_bytes <= 48) return launch_smallk_ksteps<4>(a, stream);
+        }
     }
     // 256 x 256 tiles on one 8-wavefront workgroup per CU, unless they pad the channels by more than a quarter
     // (50240 x 768 -> 384: 29.4 us against 26.1 us on 128 x 128 tiles).

@@ -144,6 +144,26 @@ def test_short_reductions_over_many_rows(M, K, N, kernel):
     assert close(packed(), acc4, p.scale, p.bias) and torch.equal(p.acc.double(), acc4)
 
 
+@pytest.mark.parametrize("M,K,N,more,kernel", [
+    (32768, 24, 768, 0, SMALLK), (32767, 24, 768, 0, TILE), (32771, 24, 776, 0, TILE), (32771, 24, 768, 2, SMALLK), (32771, 26, 768, 0, TILE),
+    (32771, 24, 768, 1, TILE), (32771, 32, 768, 0, TILE), (32771, 8, 768, 0, SMALLK), (16391, 48, 1536, 0, SMALLK), (16391, 56, 1600, 0, SMALLK),
+    (16391, 40, 1536, 8, SMALLK), (200003, 17, 128, 3, SMALLK), (200003, 64, 128, 8, TILE),
+])
+def test_f16_short_reductions(M, K, N, more, kernel):
+    """Channel strips from 24 M results in whole lines, if rows start at 16-byte boundaries (up to 24 elements at 4-byte ones).  Infinities
+    beyond K stay out; without and with bias."""
+    print(f"f16 short M={M} K={K} N={N} more={more}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    x, w = (torch.full((r, K + more), float("inf"), dtype=torch.float16, device=DEV)[:, :K] for r in (M, N))
+    x.copy_(torch.randn(M, K, generator=g, device=DEV))
+    w.copy_(torch.randn(N, K, generator=g, device=DEV))
+    y64, mag = x.double() @ w.double().t(), x.double().abs() @ w.double().abs().t()
+    for bias in (None, torch.randn(N, generator=g, device=DEV).half()):
+        check_kernel(lambda: ptq.f16_linear(x, w, bias), kernel)
+        want = y64 if bias is None else y64 + bias.double()
+        assert bool(((ptq.f16_linear(x, w, bias).double() - want).abs() <= (K + 2) * 2.0 ** -24 * (mag + 4.0) + 2.0 ** -10 * want.abs() + 2.0 ** -24).all())
+
+
 @pytest.mark.parametrize("M,K,N,parts", [
     (16 * 16, 1536, 16 * 16, (SPLITK,)), (16 * 16 + 1, 64, 16 * 16, (TILE, "32, 64", DIRECT)),
     (1001, 960, 832, (TILE, "64, 64", DIRECT)), (3137, 448, 1153, (TILE, "64, 128", DIRECT)), (6209, 192, 1025, (TILE, "128, 128", DIRECT)),
