@@ -94,15 +94,18 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
         return launch<Path, 32, 64, 2, 2, 128, 3, Copy::kDirect>(a, stream);
     }
     // Any pitch, alignment and K.  Loads go through registers, so the small tiles hide less of their latency and the
-    // split reduction, with all of its loads in flight, holds out longer (1707 x 1528 -> 424 [756 blocks of 32 x 32] 9.6 us
-    // against 12.5); the element-wise loads and stores used before took 86 us there, 396 us for 24104 x 830 -> 760 (now 36)
-    // and 79 us for 3184 x 1000 -> 500 (10.3).  128 x 128 tiles from 300 of them unless they pad the matrix by a third more than
-    // 64 x 64 ones (against 64 x 128 tiles, over 300 shapes: 0.7 .. 0.85 of the time from 1024 bytes of K, there with 128-byte
-    // slabs, 0.85 .. 0.95 below; half-padded ones, 46670 x 1968 -> 61, 1.4 times); with one or two slabs their larger epilogue
-    // counts more (11938 x 32 -> 745 [564 tiles] 10.4 / 9.0) and they start at 1600.
+    // split reduction, with all of its loads in flight, holds out longer: to 1000 blocks of 32 x 32 where rows start at multiples of 4 bytes
+    // (1707 x 1528 -> 424 [756] 9.1 us, staged tiles 9.7; staged tiles take 1.33 of the time at 151 .. 250 blocks, 1.06 to 600, 0.94 beyond, but up to
+    // 1.27 of it for single shapes), to 250 where they start at any byte, whose loads take the memory path longer and which the tiles make
+    // fewer of (6399 x 993 -> 138 [1000] 17.4 / 10.1, 281 x 581 -> 2543 [720] 10.7 / 6.3, 2436 x 530 -> 127 [308] 7.2 / 5.0; 0.92 of the time at 151 ..
+    // 250 blocks, 0.64 to 500, 0.5 beyond).  128 x 128 tiles from 300 of them (to 600 the smaller ones take 1.02 of the time up to 320 bytes of K,
+    // 1.12 up to 1023, 1.27 beyond), there with 128-byte slabs from 1024 bytes of K, unless they pad the matrix by a third more than 64 x 64 ones
+    // (half-padded ones, 46670 x 1968 -> 61, 1.4 times); with one or two slabs their larger epilogue counts more (11938 x 32 -> 745 [564 tiles]
+    // 10.4 / 9.0) and they start at 1600.
     if (is_tiny(a.M, a.ldx_bytes, a.k_bytes) || is_tiny(a.N, a.ldw_bytes, a.k_bytes)) return launch_splitk<Path, 1, 1, 1, 1, Rows::kTiny>(a, stream);
     if (tiles(a, 16, 16) <= 600) return launch_splitk<Path, 1, 1, 4, 4, Rows::kAny>(a, stream);
-    if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= 1000)) return launch_splitk<Path, 2, 2, 4, 3, Rows::kAny>(a, stream);
+    const bool words = a.ldx_bytes % 4 == 0 && a.ldw_bytes % 4 == 0;
+    if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= (words ? 1000 : 250))) return launch_splitk<Path, 2, 2, 4, 3, Rows::kAny>(a, stream);
     if (tiles(a, 128, 128) >= (a.k_bytes > 128 ? 300 : 1600) && 3 * tiles(a, 128, 128) * 128 * 128 <= 4 * tiles(a, 64, 64) * 64 * 64)
         return a.k_bytes < 1024 ? launch_staged<Path, 128, 128, 2, 4, 64>(a, stream) : launch_staged<Path, 128, 128, 2, 4, 128>(a, stream);
     if (tiles(a, 64, 128) >= 800) return launch_staged<Path, 64, 128, 2, 2, 64>(a, stream);

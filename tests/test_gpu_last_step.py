@@ -26,7 +26,7 @@ SHAPES = [  # M, K, N, elements that a row's pitch exceeds K by
     (1, 16, 5, 0), (2, 8, 9, 0), (4, 5, 33, 1), (16, 1, 16, 0), (2, 9, 2, 7),                                   # 16 bytes and little more
     (1, 17, 3, 0), (33, 31, 49, 0), (65, 47, 130, 3), (7, 63, 20, 1), (40, 65, 24, 0), (17, 79, 33, 2),          # 16 x 16 blocks
     (90, 130, 300, 5), (33, 1648, 49, 0), (200, 257, 180, 0),
-    (700, 300, 401, 1), (1200, 515, 390, 0),                                                                      # 32 x 32 blocks
+    (700, 300, 401, 0), (600, 515, 390, 0),                                                                       # 32 x 32 blocks
     (3000, 29, 700, 0), (3000, 63, 700, 1), (3000, 64, 700, 1), (401, 127, 899, 0), (401, 130, 899, 1),            # tiles, one slab and more
     (9000, 33, 1600, 0), (9000, 64, 1600, 2), (12345, 61, 2179, 0), (12345, 334, 2179, 1),
 ]

@@ -240,6 +240,15 @@ def test_direct_tiles_of_the_other_operands(kind, M, K, N, parts):
     assert torch.equal(run(acc_out=p.acc).view(torch.int16), y.view(torch.int16)) and torch.equal(p.acc.double(), p.acc64)
 
 
+@pytest.mark.parametrize("M,K,N,more,parts", [
+    (800, 513, 320, 0, (SPLITK, "2, 2")), (801, 513, 320, 0, (TILE, "32, 64", STAGED)),  # 250 and 260 blocks
+    (800, 512, 320, 2, (SPLITK, "2, 2")), (801, 514, 320, 0, (TILE, "32, 64", STAGED)),
+    (3200, 516, 320, 0, (SPLITK, "2, 2")), (3201, 516, 320, 0, (TILE, "64, 64", STAGED)), (3200, 512, 320, 4, (SPLITK, "2, 2")),  # 1000 and 1010
+])
+def test_split_and_staged_by_the_rows(M, K, N, more, parts):
+    test_one_slab_by_the_rows(M, K, N, more, parts)
+
+
 FRAGMENTS, VIA_LDS = "false, (ptq4vm::mfma::Copy)2>", "true, (ptq4vm::mfma::Copy)2>"
 
 

@@ -18,7 +18,7 @@ SHAPES = [  # M, K, N (int8 reductions; every operand type picks its own tile fr
     (6209, 192, 1025, 5), (49217, 1536, 80, 0),                    # 128 x 128 tiles, and with a column tile mostly padding
     (13057, 192, 2048, 0),                                         # 128 x 256 tiles (fp16: persistent; packed: any alignment)
     (50, 13, 7, 0), (301, 100, 130, 0), (17, 1001, 333, 1),        # any alignment: 16 x 16 blocks
-    (1111, 514, 402, 0),                                           # 32 x 32 blocks
+    (1111, 514, 402, 0), (1111, 516, 402, 0), (600, 514, 402, 0),  # 32 x 64 tiles; 32 x 32 blocks
     (401, 72, 899, 2), (1279, 200, 645, 0), (2049, 722, 643, 0),   # 32 x 64, 64 x 64 with short and long slabs
     (6401, 30, 1029, 0), (12345, 334, 2179, 1),                    # 64 x 128, 128 x 128
 ]
