@@ -190,7 +190,7 @@ int ptq4vm_w4a4_linear(const uint8_t *xq4, const uint8_t *wq4, const float *s_to
  * xq6 / wq6 are 16-byte aligned; any K >= 1 (odd K too).  Errors as for the 4-bit entry points, with
  * K > PTQ4VM_MAX_K_E2M3 -> PTQ4VM_ERR_SHAPE and a plane pitch below 96 R or not a multiple of 16 -> PTQ4VM_ERR_STRIDE.
  * The linear runs on a persistent 256 x 256-tile kernel (K a multiple of 128 and >= 256, N a multiple of 8,
- * 16-byte aligned y rows, tiles that fill nearly one round of the device or two and more) or on smaller tiles (every
+ * 16-byte aligned y rows, tiles that fill nearly one round of the device or most of two and more) or on smaller tiles (every
  * other shape).
  */
 #define PTQ4VM_E2M3_BLOCKS(K) ((((int64_t)(K)) + 127) / 128)

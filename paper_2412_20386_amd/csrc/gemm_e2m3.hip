@@ -475,18 +475,19 @@ extern "C" int ptq4vm_w4a4_linear_e2m3(const uint8_t *xq6, const uint8_t *wq6, c
     a.L = L;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     auto tiles = [&](int br, int bo) { return ptq4vm::ceil_div(M, br) * ptq4vm::ceil_div(N, bo); };
-    // 256 x 256 tiles from two rounds of them (50432 x 384 -> 1536 [1182 tiles] 43.8 us against 54.0 on 128 x 256 tiles,
-    // 50432 x 1536 -> 768 [591] 51.5 / 60.0, 12608 x 768 -> 3072 [600] 33.6 / 34.8, but 25216 x 1536 -> 768 [297] 35.0 / 28.6),
-    // unless they pad the channels by more than a quarter (40000 x 768 -> 520: 29.3 / 24.3).  Also within one round, where the
-    // 128 x 128 tiles, three to a CU, would need a second one (14148 x 1152 -> 832 [224] 16.0 / 19.7, 9030 x 1280 -> 1344 [216]
-    // 16.7 / 20.9, 20860 x 1920 -> 576 [246] 22.6 / 28.2; with at most 768 of the smaller tiles they are 4 to 12 % slower), for
-    // shorter reductions just beyond that line only (K <= 1024 from 832 small tiles on, 116 shapes: 0.83 to 1.10 of the time).
+    // 256 x 256 tiles from two rounds of them that are filled to 80 % (us, persistent / tiles: 50432 x 384 -> 1536 [1182 tiles] 43.9 / 46.6,
+    // 36906 x 256 -> 1120 [725] 23.1 / 30.0, 21704 x 1280 -> 2072 [765] 50.4 / 62.3, but 50432 x 1536 -> 768 [591] 52.3 / 47.5, 12608 x 768 -> 3072 [600]
+    // 33.9 / 29.1, 25216 x 1536 -> 768 [297] 34.7 / 27.1; over 600 shapes tiles take 0.90 .. 0.96 of the time below 80 %, 0.98 .. 1.01 to 90 % and
+    // 1.04 .. 1.08 beyond), unless they pad the channels by more than a quarter.  Also within one round, where the
+    // 128 x 128 tiles, three to a CU, would need a second one (14148 x 1152 -> 832 [224] 15.3 / 17.4, 9030 x 1280 -> 1344 [216]
+    // 16.0 / 18.7, 20860 x 1920 -> 576 [246] 20.9 / 25.8), for shorter reductions just beyond that line only (K <= 1024 from 832 small tiles on).
     const int64_t big_tiles = tiles(256, kTile), small_tiles = tiles(128, 128);
     const bool one_round = big_tiles <= 256 && small_tiles > 768 && (K > 1024 || small_tiles < 832);
+    const bool full_rounds = big_tiles >= 512 && big_tiles * 100 >= ptq4vm::ceil_div(big_tiles, 256) * 256 * 80;
     const bool little_padding = ptq4vm::ceil_div(N, kTile) * kTile * 4 <= N * 5;
     const bool persistent_ok = K % 128 == 0 && K >= 256 && N % 8 == 0 && ptq4vm::aligned_to(y_f16, 16) && ldy % 8 == 0 &&
                                ptq4vm::aligned_to(bias_f16, 4) &&
-                               ldy * 2 * kTile < (1LL << 31) && L < (1LL << 31) && ((big_tiles >= 512 && little_padding) || one_round) && big_tiles <= 0x3fffffffLL;
+                               ldy * 2 * kTile < (1LL << 31) && L < (1LL << 31) && ((full_rounds && little_padding) || one_round) && big_tiles <= 0x3fffffffLL;
     if (persistent_ok) return launch_persistent(a, stream);
     // The largest tile that leaves the CUs a few workgroups each, as in gemm_tile.hip; measured (us, tiles in brackets):
     //   split reduction / 32 x 64:  197 x 1536 -> 80 [65 blocks] 3.2 / 4.9, 392 x 1152 -> 200 [325] 3.5 / 4.5, 60 x 384 -> 2281 [572] 3.4 / 3.2

@@ -93,8 +93,8 @@ def _e2m3(p):
 
 
 @pytest.mark.parametrize("M,K,N,kernel", [
-    (26373, 256, 1032, E_PERSISTENT), (14807, 384, 2056, E_PERSISTENT),      # 520 and 522 tiles, 8 channels in the last; 2 and 3 blocks
-    (26112, 256, 1032, E_TILE),                                               # 510 tiles
+    (31301, 256, 1032, E_PERSISTENT), (17451, 384, 2056, E_PERSISTENT),      # 615 and 621 tiles, 8 channels in the last; 2 and 3 blocks
+    (31232, 256, 1032, E_TILE), (26373, 256, 1032, E_TILE), (14807, 384, 2056, E_TILE), (26112, 256, 1032, E_TILE),  # 610, 520, 522 and 510 tiles
     (12301, 256, 1024, E_PERSISTENT), (12288, 256, 1024, E_TILE),             # 776 and 768 tiles of 128 x 128
     (13312, 384, 1024, E_TILE), (13312, 1152, 1024, E_PERSISTENT),            # 832: from there long reductions only
     (17000, 1152, 1032, E_TILE), (26900, 384, 520, E_TILE),                   # more than one round; padding

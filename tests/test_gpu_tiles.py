@@ -126,6 +126,7 @@ def test_tiles_of_whole_rounds(M, K, N, pad):
     (33013, 256, 1016, 0),   # two blocks a tile, rows that are not whole lines, the last tile partly empty both ways
     (33013, 256, 1016, 8),   # the same with rows of whole lines
     (43777, 384, 768, 0),    # three blocks, a last tile of one row
+    (39433, 256, 1016, 0), (39433, 256, 1016, 8), (52481, 384, 768, 0),  # the same for E2M3, whose rounds have to be filled
 ])
 def test_persistent_tiles_with_stores_in_flight(M, K, N, pad):
     """Few blocks a tile: the copies of the next tile's first blocks, its scale vectors and this tile's stores in one queue."""
