@@ -490,11 +490,12 @@ extern "C" int ptq4vm_w4a4_linear_e2m3(const uint8_t *xq6, const uint8_t *wq6, c
                                ldy * 2 * kTile < (1LL << 31) && L < (1LL << 31) && ((full_rounds && little_padding) || one_round) && big_tiles <= 0x3fffffffLL;
     if (persistent_ok) return launch_persistent(a, stream);
     // The largest tile that leaves the CUs a few workgroups each, as in gemm_tile.hip; measured (us, tiles in brackets):
-    //   split reduction / 32 x 64:  197 x 1536 -> 80 [65 blocks] 3.2 / 4.9, 392 x 1152 -> 200 [325] 3.5 / 4.5, 60 x 384 -> 2281 [572] 3.4 / 3.2
-    //   32 x 64 / 64 x 64:          788 x 1536 -> 768 [156] 5.9 / 6.3, 197 x 768 -> 3072 [192] 5.0 / 4.3
-    //   64 x 64 / 64 x 128:         6304 x 768 -> 384 [297] 6.1 / 6.4, 3192 x 896 -> 1047 [450] 8.1 / 7.6
-    //   64 x 128 / 128 x 128:       3152 x 384 -> 1536 [300] 6.1 / 6.4, 6304 x 384 -> 1536 [600] 9.5 / 8.1
-    //   128 x 128 / 128 x 256:      25216 x 768 -> 384 [394] 11.6 / 12.3, 12608 x 768 -> 3072 [1188] 36.3 / 32.9
+    //   split reduction / 32 x 64:  197 x 1536 -> 80 [65 blocks] 3.3 / 4.6, 392 x 1152 -> 200 [325] 3.6 / 4.1, 60 x 384 -> 2281 [572] 3.6 / 3.0
+    //   32 x 64 / 64 x 64:          788 x 1536 -> 768 [156] 5.4 / 5.8, 197 x 768 -> 3072 [192] 4.1 / 4.1
+    //   64 x 64 / 64 x 128:         6304 x 768 -> 384 [297] 5.4 / 5.9, 3192 x 896 -> 1047 [450] 7.6 / 7.6
+    //   64 x 128 / 128 x 128:       3152 x 384 -> 1536 [300] 5.7 / 6.5, 6304 x 384 -> 1536 [600] 8.5 / 8.1
+    //   128 x 128 / 128 x 256:      25216 x 768 -> 384 [394] 11.5 / 12.8, 12608 x 768 -> 3072 [1188] 34.4 / 30.5
+    // (over 500 shapes the best of these forms takes 0.99 of the time of the rule's)
     if (L >= (1LL << 31) || tiles(16, 16) <= (K >= 896 ? 600 : 256)) return launch_splitk<1, 1, 4, 3>(a, stream);
     const int64_t most = tiles(32, 64) * 32 * 64 * 4 / 3;  // padded size that a tile may have
     if (tiles(128, 256) >= 800 && tiles(128, 256) * 128 * 256 <= most) return launch_tile<128, 256, 2, 4, 2>(a, stream);

@@ -578,8 +578,9 @@ int dispatch(LinearArgs a, hipStream_t stream) {
             if (la == 4 && a.k_bytes <= 48) return launch_smallk_ksteps<4>(a, stream);
         }
     }
-    // 256 x 256 tiles on one 8-wavefront workgroup per CU, unless they pad the channels by more than a quarter
-    // (50240 x 768 -> 384: 29.4 us against 26.1 us on 128 x 128 tiles).
+    // 256 x 256 tiles on one 8-wavefront workgroup per CU from a round of them on (over 400 shapes the tile kernels take 1.05 of the time of one to
+    // two rounds, 1.08 .. 1.17 beyond), unless they pad the channels by more than a quarter (50240 x 768 -> 384 26.1 us against 25.0 on 256 x
+    // 192 tiles; over 300 shapes 1.07 .. 1.22 of the time).
     const bool persistent_ok = la == 16 && a.ldx_bytes * 256 < (1LL << 31) && a.ldw_bytes * 256 < (1LL << 31) &&
                                a.N % 8 == 0 && a.y_vec == 8 && ptq4vm::aligned_to(a.bias, 4) &&
                                a.ldy * 512 < (1LL << 31) && a.L < (1LL << 31) && a.N >= 256 &&
