@@ -40,18 +40,44 @@ PEAK_HBM_GBS = 8000.0     # HBM3E
 
 # HBM traffic of the dominant kernel per launch: written by `python -m paper_2412_20386_amd.profile_summary`
 # from two rocprofv3 --pmc runs of this script (FETCH_SIZE, WRITE_SIZE, each scaled by the 256 MiB copy that
-# this script also issues).  Absent or for another workload: "traffic" is null.
+# this script also issues).  Absent, for another workload or of another kernel than the one launched: "traffic" is null.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dominant_kernel_traffic.json")
 GRAPH_HEADLINE_CONFIGS = (0, 1)  # launch-bound: a step is tens of microseconds of kernels
 
 
-def dominant_traffic(config: int):
+def dominant_traffic(config: int, cfg, dominant):
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
-        return float(rec["traffic_bytes"]) if int(rec["config"]) == config else None
+        if int(rec["config"]) != config or rec["kernel"] != dominant_kernel_name(config, cfg, dominant):
+            return None
+        return float(rec["traffic_bytes"])
     except (OSError, ValueError, KeyError):
         return None
+
+
+def dominant_kernel_name(config: int, cfg, dominant):
+    """The kernel that the dominant linear launches, from torch's profiler (None under rocprofv3, which two profilers
+    would share).  Called after everything is timed."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    import paper_2412_20386_amd as ptq
+    from paper_2412_20386_amd import profile_summary, synth
+
+    if any(v.startswith("ROCP") for v in os.environ):
+        return None
+    c = synth.make_linear_case(config, 0, cfg.linears.index(dominant), device="cuda:0")
+    wq, s_w, inv_m = ptq.fold_smoothing(c.w, c.m)
+    xq = ptq.quantize_pts(c.x, inv_m, c.s_tok, c.B, c.L)
+    call = lambda: ptq.w8a8_linear(xq, wq, c.s_tok, s_w, c.bias, c.B, c.L)
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as record:
+        call()
+        torch.cuda.synchronize()
+    names = [profile_summary.short(e.key) for e in record.key_averages() if "linear_" in e.key and "<" in e.key]
+    return names[0] if len(names) == 1 else None
 
 
 def measure_config(args, config: int, full: bool):
@@ -467,7 +493,7 @@ def main() -> int:
                     frac=round(achieved / PEAK_INT8_TOPS, 4), avg_launch_us=round(dom_us, 2),
                     median_launch_us=round(dom_all[len(dom_all) // 2], 2), min_launch_us=round(dom_all[0], 2),
                     p90_launch_us=round(dom_all[min(len(dom_all) - 1, int(0.9 * len(dom_all)))], 2),
-                    launches_timed=r["launches_timed"], traffic=dominant_traffic(args.config),
+                    launches_timed=r["launches_timed"], traffic=None,
                     algorithmic_bytes=1.0 * M * dK + dN * dK + 2.0 * M * dN)
 
     configs = [config_record(r, args.fused)]
@@ -476,6 +502,8 @@ def main() -> int:
             if other != args.config:
                 configs.append(config_record(measure_config(args, other, full=False), args.fused))
         configs.sort(key=lambda c: c["config"])
+
+    roofline["traffic"] = dominant_traffic(args.config, r["cfg"], r["dominant"])
 
     tokens_per_s = M / (ms_per_step * 1e-3)
     # W4A4 (the precision of the paper's latency table, Sec. 6.4): sums of the kernel times measured above, per layer

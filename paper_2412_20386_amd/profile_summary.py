@@ -143,13 +143,25 @@ def counter_lines(name: str, agg, out: list):
     return copy_reading
 
 
-def dominant_median(agg, substr: str):
-    """Median counter reading over the dispatches of the dominant kernel (its long cluster, if it has two)."""
-    values = [x for k, v in agg.items() if substr in k[0] for x in v]
-    if not values:
-        return None
-    parts = split_bimodal(values)
-    return statistics.median(parts[-1][1])
+def dominant_values(directory: str, substr: str):
+    """Counter readings of the dominant kernel's dispatches in the order of their launch."""
+    f = first(os.path.join(directory, "**", "*counter_collection.csv")) or first(os.path.join(directory, "*counter_collection.csv"))
+    values = collections.defaultdict(float)
+    if f:
+        for r in csv.DictReader(open(f)):
+            if substr in short(r["Kernel_Name"]):
+                values[int(r["Dispatch_Id"])] += float(r["Counter_Value"])
+    return [v for _, v in sorted(values.items())]
+
+
+def dominant_readings(fetch: str, write: str, substr: str):
+    """Readings of the two counters over the launches of the dominant problem.  Where the kernel serves two problems, the dominant
+    one is that with the larger result; the two runs launch alike, so a launch's place among them tells which problem it is."""
+    reads, writes = dominant_values(fetch, substr), dominant_values(write, substr)
+    if not writes or len(reads) != len(writes):
+        return [], []
+    keep = set(split_bimodal(writes)[-1][1])
+    return [r for r, w in zip(reads, writes) if w in keep], [w for w in writes if w in keep]
 
 
 def counter_table(directories, kernels, out: list) -> None:
@@ -170,15 +182,14 @@ def counter_table(directories, kernels, out: list) -> None:
             rows = [c for d, c in per_dispatch.items() if want == names[d]]
             if not rows:
                 continue
-            # a kernel used for two problem shapes: keep the cluster with the larger first counter
+            # a kernel used for two problem shapes: one block each, told apart by the first counter
             key = sorted(rows[0])[0]
-            vals = [r[key] for r in rows]
-            if len(vals) > 8 and max(vals) > 1.5 * min(vals):
-                cut = (max(vals) * min(vals)) ** 0.5
-                rows = [r for r in rows if r[key] >= cut]
-            out.append(f"  {want}: {len(rows)} dispatches")
-            for k in sorted(rows[0]):
-                out.append(f"     {k:34s} {statistics.median(r[k] for r in rows):18.0f}")
+            for suffix, vals in split_bimodal([r[key] for r in rows]):
+                part = [r for r in rows if r[key] in set(vals)]
+                if part:
+                    out.append(f"  {want}{suffix}: {len(part)} dispatches")
+                    for k in sorted(part[0]):
+                        out.append(f"     {k:34s} {statistics.median(r[k] for r in part):18.0f}")
 
 
 def main() -> int:
@@ -188,9 +199,9 @@ def main() -> int:
     ap.add_argument("--write", help="output directory of the rocprofv3 --pmc WRITE_SIZE run")
     ap.add_argument("--bench-json", help="stdout of bench.py under the kernel-trace run")
     ap.add_argument("--config", type=int, default=3)
-    ap.add_argument("--dominant", default="linear_mfma_wreg<K=768>", help="short name (substring) of the dominant kernel")
+    ap.add_argument("--dominant", default="linear_mfma_persistent<int8>", help="short name (substring) of the dominant kernel")
     ap.add_argument("--counters", nargs="*", default=[], help="output directories of further rocprofv3 --pmc runs (SQ_* ...)")
-    ap.add_argument("--kernels", default="linear_mfma_wreg<K=768>,linear_mfma_persistent<int8>,pts_linear_wres,linear_stream_smallk<fused>,quantize_pts_stream",
+    ap.add_argument("--kernels", default="linear_mfma_persistent<int8>,pts_linear_wres,linear_stream_smallk<fused>,quantize_pts_stream",
                     help="comma-separated short-name substrings for the --counters table")
     ap.add_argument("--header", help="text file whose content is put in front of the summary (workload, commands)")
     ap.add_argument("--out", help="summary text file to write (default: stdout only)")
@@ -209,13 +220,14 @@ def main() -> int:
     if args.counters:
         counter_table(args.counters, [k for k in args.kernels.split(",") if k], out)
     traffic = {}
-    for name, directory in (("FETCH_SIZE", args.fetch), ("WRITE_SIZE", args.write)):
+    readings = dominant_readings(args.fetch, args.write, args.dominant) if args.fetch and args.write else ([], [])
+    for (name, directory), values in zip((("FETCH_SIZE", args.fetch), ("WRITE_SIZE", args.write)), readings):
         if not directory:
             continue
         agg = counter_groups(directory)
         copy_reading = counter_lines(name, agg, out)
-        dom = dominant_median(agg, args.dominant)
-        if copy_reading and dom is not None:
+        if copy_reading and values:
+            dom = statistics.median(values)
             factor = COPY_KIB / copy_reading
             traffic[name] = dict(median_kib=dom, copy_reading_kib=copy_reading, factor=round(factor, 4),
                                  bytes=dom * factor * 1024.0)
