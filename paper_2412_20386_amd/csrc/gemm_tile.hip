@@ -102,7 +102,8 @@ int ptq4vm::mfma::launch_tiles(const LinearArgs &a, hipStream_t stream) {
     // 1.12 up to 1023, 1.27 beyond), there with 128-byte slabs from 1024 bytes of K, unless they pad the matrix by a third more than 64 x 64 ones
     // (half-padded ones, 46670 x 1968 -> 61, 1.4 times); with one or two slabs their larger epilogue counts more (11938 x 32 -> 745 [564 tiles]
     // 10.4 / 9.0) and they start at 1600.
-    if (is_tiny(a.M, a.ldx_bytes, a.k_bytes) || is_tiny(a.N, a.ldw_bytes, a.k_bytes)) return launch_splitk<Path, 1, 1, 1, 1, Rows::kTiny>(a, stream);
+    if (is_tiny(a.M, a.ldx_bytes, a.k_bytes)) return launch_splitk<Path, 1, 1, 1, 1, Rows::kTiny>(a, stream);
+    if (is_tiny(a.N, a.ldw_bytes, a.k_bytes)) return launch_splitk<Path, 1, 1, 1, 1, Rows::kTinyWeight>(a, stream);
     if (tiles(a, 16, 16) <= 600) return launch_splitk<Path, 1, 1, 4, 4, Rows::kAny>(a, stream);
     const bool words = a.ldx_bytes % 4 == 0 && a.ldw_bytes % 4 == 0;
     if (!small || (a.k_bytes > 256 && tiles(a, 32, 32) <= (words ? 1000 : 250))) return launch_splitk<Path, 2, 2, 4, 3, Rows::kAny>(a, stream);

@@ -93,8 +93,9 @@ __device__ __forceinline__ void store_eight(char *dst, v4f data, int n_valid) {
 // for the load) the requests ran one after another (us, so / as now: 33 x 1648 -> 49 5.3 / 3.5, fp16 76 x 1818 -> 2020 13.9 / 9.7, fused
 // 362 x 288 -> 893 6.9 / 6.1).
 //
-// kTiny, a matrix of fewer than 16 bytes, is loaded byte by byte (host-checked: the other forms never meet one).
-enum class Rows { kAligned, kAny, kTiny };
+// A matrix of fewer than 16 bytes is loaded byte by byte (host-checked: the other forms never meet one): kTiny both, kTinyWeight the
+// weight alone, whose activations may be many rows (50432 x 4 -> 3 5.2 us with both, 4.4 so, 4.8 before these forms came in).
+enum class Rows { kAligned, kAny, kTiny, kTinyWeight };
 inline bool is_tiny(int64_t rows, int64_t pitch_bytes, int64_t k_bytes) {
     return k_bytes < 16 && (rows == 1 || (rows < 16 && pitch_bytes < 16 && (rows - 1) * pitch_bytes + k_bytes < 16));
 }
@@ -926,18 +927,19 @@ __global__ __launch_bounds__(64 * SK, 4) void linear_mfma_splitk(const LinearArg
     const int n_whole = (int)(p.k_bytes / 64);
     // The step that reaches beyond K, requested first and used last
     const bool last = ROWS != Rows::kAligned && p.k_bytes % 64 != 0 && wave == n_whole % SK;
-    auto load_last = [&](const char *at, const char *end) {
-        if constexpr (ROWS == Rows::kTiny)
-            return load_bytes(at, end);
-        else
-            return load_within(at, end);
-    };
+    constexpr bool W_BYTES = ROWS == Rows::kTiny || ROWS == Rows::kTinyWeight, X_BYTES = ROWS == Rows::kTiny;
     v4i lw[FO], lx[FR];
     if (last) {
 #pragma unroll
-        for (int i = 0; i < FO; i++) lw[i] = load_last(wrow[i] + (int64_t)n_whole * 64, w_end);
+        for (int i = 0; i < FO; i++) {
+            const char *const at = wrow[i] + (int64_t)n_whole * 64;
+            lw[i] = W_BYTES ? load_bytes(at, w_end) : load_within(at, w_end);
+        }
 #pragma unroll
-        for (int j = 0; j < FR; j++) lx[j] = load_last(xrow[j] + (int64_t)n_whole * 64, x_end);
+        for (int j = 0; j < FR; j++) {
+            const char *const at = xrow[j] + (int64_t)n_whole * 64;
+            lx[j] = X_BYTES ? load_bytes(at, x_end) : load_within(at, x_end);
+        }
     }
     using Load = std::conditional_t<ROWS == Rows::kAligned, v4i, v4i_unaligned>;
     for (int s0 = wave; s0 < n_whole; s0 += SK * U) {
@@ -957,11 +959,13 @@ __global__ __launch_bounds__(64 * SK, 4) void linear_mfma_splitk(const LinearArg
             if (s0 + u * SK < n_whole) mfma_step<Path, FO, FR>(acc, fw[u], fx[u]);
     }
     if (last) {
-        if (ROWS == Rows::kAny && p.k_bytes % 16 != 0) {
+        if (p.k_bytes % 16 != 0) {
 #pragma unroll
-            for (int i = 0; i < FO; i++) lw[i] = place_within(lw[i], wrow[i] + (int64_t)n_whole * 64, w_end);
+            for (int i = 0; i < FO; i++)
+                if (!W_BYTES) lw[i] = place_within(lw[i], wrow[i] + (int64_t)n_whole * 64, w_end);
 #pragma unroll
-            for (int j = 0; j < FR; j++) lx[j] = place_within(lx[j], xrow[j] + (int64_t)n_whole * 64, x_end);
+            for (int j = 0; j < FR; j++)
+                if (!X_BYTES) lx[j] = place_within(lx[j], xrow[j] + (int64_t)n_whole * 64, x_end);
         }
         const v4i mask = mask_within((int64_t)n_whole * 64 + lq * 16, p.k_bytes);
 #pragma unroll

@@ -23,6 +23,7 @@ def inside(values, pitch, fill):
 
 SHAPES = [  # M, K, N, elements that a row's pitch exceeds K by
     (1, 1, 1, 0), (1, 7, 3, 0), (1, 15, 200, 0), (3, 5, 40, 0), (15, 1, 17, 0), (700, 13, 1, 0), (5, 3, 1, 0),  # under 16 bytes
+    (5003, 4, 3, 0), (700, 5, 2, 3), (9001, 1, 15, 0),                                                            # the weight alone
     (1, 16, 5, 0), (2, 8, 9, 0), (4, 5, 33, 1), (16, 1, 16, 0), (2, 9, 2, 7),                                   # 16 bytes and little more
     (1, 17, 3, 0), (33, 31, 49, 0), (65, 47, 130, 3), (7, 63, 20, 1), (40, 65, 24, 0), (17, 79, 33, 2),          # 16 x 16 blocks
     (90, 130, 300, 5), (33, 1648, 49, 0), (200, 257, 180, 0),
