@@ -108,7 +108,7 @@ __device__ __forceinline__ v4i load_within(const char *at, const char *end) {
 // What load_within returned, moved to where it would lie in the 16 bytes at `at`; what enters from above lies beyond K.  (Where K is a multiple of
 // 16 bytes, no piece of a row passes the end.)
 __device__ __forceinline__ v4i place_within(v4i v, const char *at, const char *end) {
-    const int over = (int)min((int64_t)16, (int64_t)(at + 16 - end));
+    const int over = (int)max((int64_t)0, min((int64_t)16, (int64_t)(at + 16 - end)));  // (the end may lie gigabytes away)
     if (over > 0) {
         if (over & 8) v = v4i{v[2], v[3], 0, 0};
         if (over & 4) v = v4i{v[1], v[2], v[3], 0};
